@@ -1,9 +1,13 @@
-"""ctypes binding of libechoattn: same names as include/echoattn.h, include/echodropout.h and
+"""Binding of libechoattn: same names as include/echoattn.h, include/echodropout.h and
 include/echolstm.h, argument marshalling only.  Device buffers are passed as torch tensors (their
 data_ptr() is taken) or as integer addresses; nothing is computed here.
 
 The shared library must have been built (python -m paper_1805_08899_amd.build);
 loading fails loudly otherwise -- there is no fallback path.
+
+Loading the library (the first call of any function here does it) replaces the launching calls of this module by
+builtin functions of the same names, parameters and defaults (csrc/py_calls.cpp), because ctypes costs more host time
+per call than the kernel launches do.  The ctypes forms below remain what a process without PyTorch uses.
 """
 from __future__ import annotations
 
@@ -68,6 +72,8 @@ EXPORTS = {
     "echo_version": (c_char_p, []),
 }
 
+PY_CALLS_PATH = os.path.join(_HERE, "_py_calls.so")
+
 _lib = None
 
 
@@ -83,15 +89,29 @@ def lib() -> ctypes.CDLL:
             # The process must end up with ONE HIP runtime.  PyTorch ships its own copy; if this library is
             # loaded first it pulls in the system's copy and PyTorch then finds no device.  Loading PyTorch first
             # makes both use PyTorch's.
-            import torch  # noqa: F401
+            import torch
         except ImportError:
-            pass
+            torch = None
         L = ctypes.CDLL(LIB_PATH)
         for name, (res, args) in EXPORTS.items():
             fn = getattr(L, name)
             fn.restype, fn.argtypes = res, args
+        if torch is not None:
+            _install_native_calls(L)
         _lib = L
     return _lib
+
+
+def _install_native_calls(L) -> None:
+    """Puts the builtin forms of the launching calls (csrc/py_calls.cpp) in the place of this module's ctypes forms."""
+    if not os.path.exists(PY_CALLS_PATH):
+        raise FileNotFoundError(f"{PY_CALLS_PATH} is missing: build it with `python -m paper_1805_08899_amd.build`")
+    from . import _py_calls
+    _py_calls.bind(echo_attn_desc_t, {name: ctypes.cast(getattr(L, name), c_void_p).value for name in EXPORTS})
+    for name in EXPORTS:
+        native = getattr(_py_calls, name, None)
+        if native is not None:
+            globals()[name] = native
 
 
 def _ptr(x):

@@ -1,4 +1,5 @@
-"""Builds libechoattn.so from csrc/*.hip for gfx950 with hipcc (in-tree).
+"""Builds libechoattn.so from csrc/*.hip for gfx950 with hipcc, and _py_calls.so, the Python binding's argument
+marshalling, from csrc/py_calls.cpp with g++ (in-tree; the latter needs PyTorch's headers and is left out without them).
 
     python -m paper_1805_08899_amd.build [--sanitize] [extra hipcc flags]
 
@@ -14,12 +15,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libechoattn.so")
+PY_CALLS = os.path.join(HERE, "_py_calls.so")
 
 # Packed fp32 VALU forms are switched off for all device code.
 HIPCC_FLAGS = [
@@ -53,12 +56,35 @@ def _compile(src: str, extra, suffix: str = "") -> str:
     return obj
 
 
+def build_py_calls() -> None:
+    """_py_calls.so: host code only, against the headers of the PyTorch that will import it."""
+    try:
+        import torch
+        from torch.utils import cpp_extension
+    except ImportError:
+        return
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]
+    lib_dirs = cpp_extension.library_paths()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(a for d in inc for a in ("-isystem", d)),
+           os.path.join(CSRC, "py_calls.cpp"), "-o", PY_CALLS, *("-L" + d for d in lib_dirs),
+           "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for py_calls.cpp:\n" + r.stdout + r.stderr)
+    if (r.stdout + r.stderr).strip():
+        print(r.stdout + r.stderr, file=sys.stderr)
+
+
 def build_library(extra_flags=(), verbose=True, sanitize=False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
     flags = list(extra_flags) + (SAN_COMPILE if sanitize else [])
-    with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as ex:
+        py_calls = None if sanitize else ex.submit(build_py_calls)
         objs = list(ex.map(lambda s: _compile(s, flags, "_san" if sanitize else ""), srcs))
+        if py_calls:
+            py_calls.result()
     out = SAN_LIB if sanitize else LIB
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *(SAN_LINK if sanitize else []), "-o", out, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
