@@ -144,7 +144,7 @@ echo_status_t echo_attn_bwd(const echo_attn_desc_t *desc,
  *   - All calls on one GPU share that GPU's buffer, which keeps the last call's contents (nothing in it has to
  *     be cleared between calls): two calls that may overlap on one GPU (different streams without an event
  *     between them, several host threads) race, and so does a graph replayed concurrently with itself. */
-#define ECHO_ATTN_STATIC_SCRATCH_BYTES ((size_t)16 << 20)
+#define ECHO_ATTN_STATIC_SCRATCH_BYTES ((size_t)20 << 20)
 echo_status_t echo_attn_bwd_static(const echo_attn_desc_t *desc,
                                    const float *dContext, const float *P,
                                    const void *Qp, const void *Kp, const void *V, const void *v,

@@ -173,7 +173,7 @@ def echo_attn_bwd(desc, dContext, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv, wo
                                _ws_bytes(workspace, workspace_bytes), _stream(stream))
 
 
-ECHO_ATTN_STATIC_SCRATCH_BYTES = 16 << 20
+ECHO_ATTN_STATIC_SCRATCH_BYTES = 20 << 20
 
 
 def echo_attn_bwd_static(desc, dContext, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv, stream=None) -> int:

@@ -43,7 +43,7 @@ echo_status_t check_desc(const echo_attn_desc_t *d, AttnShape *s, int max_tk = k
 inline bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
 struct BwdWs {
-    size_t ds_off, rowsum_off, dvpart_off, order_off, dvflag_off, total;
+    size_t ds_off, rowsum_off, dvpart_off, order_off, dvflag_off, mail_off, mail_bytes, total;
 };
 BwdWs bwd_layout(const AttnShape &s) {
     BwdWs w;
@@ -52,7 +52,9 @@ BwdWs bwd_layout(const AttnShape &s) {
     w.dvpart_off = w.rowsum_off + align_up((size_t)s.B * s.Tq * sizeof(float));
     w.order_off = w.dvpart_off + align_up((size_t)s.B * s.H * sizeof(float));
     w.dvflag_off = w.order_off + align_up((size_t)s.B * sizeof(int));
-    w.total = w.dvflag_off + align_up((size_t)((s.H + 63) / 64) * s.B * sizeof(unsigned long long));
+    w.mail_off = w.dvflag_off + align_up((size_t)((s.H + 63) / 64) * s.B * sizeof(unsigned long long));
+    w.mail_bytes = echo::recompute_split_mail_bytes(s);
+    w.total = w.mail_off + align_up(w.mail_bytes);
     return w;
 }
 // scores S [B,Tq,Tk] of the unfused forward kernels; the fused kernel keeps them in LDS and needs nothing
@@ -169,6 +171,11 @@ echo_status_t bwd_impl(const echo_attn_desc_t *desc, const float *dContext, cons
     int *order = reinterpret_cast<int *>(ws + lay.order_off);
     unsigned long long *dv_flag = reinterpret_cast<unsigned long long *>(ws + lay.dvflag_off);
     ECHO_LAUNCH("bwd_pre", echo::launch_bwd_pre(s, dContext, V, P, key_len, dS, rowsum, order, dV, st));
+    if (!use_map && lay.mail_bytes > 0) {
+        ECHO_LAUNCH("recompute_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, dQp, dKp, ws + lay.mail_off,
+                                                                    next_launch_number(), dv, st));
+        return ECHO_OK;
+    }
     ECHO_LAUNCH(use_map ? "recompute_stash" : "recompute",
                 echo::launch_recompute(s, Qp, Kp, v, order, dS, rowsum, use_map ? tmap : nullptr, dQp, dKp, dv_part,
                                        dv_flag, next_launch_number(), dv, st));
@@ -372,6 +379,11 @@ echo_status_t echo_attn_steps_bwd_keys(const echo_attn_desc_t *desc, const float
     int *order = reinterpret_cast<int *>(ws + lay.order_off);
     unsigned long long *dv_flag = reinterpret_cast<unsigned long long *>(ws + lay.dvflag_off);
     ECHO_LAUNCH("bwd_pre_dv", echo::launch_bwd_pre(s, dContext, nullptr, P, key_len, dS, rowsum, order, dV, st, false));
+    if (lay.mail_bytes > 0) {
+        ECHO_LAUNCH("recompute_keys_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, nullptr, dKp, ws + lay.mail_off,
+                                                                         next_launch_number(), dv, st));
+        return ECHO_OK;
+    }
     ECHO_LAUNCH("recompute_keys", echo::launch_recompute(s, Qp, Kp, v, order, dS, rowsum, nullptr, nullptr, dKp, dv_part,
                                                          dv_flag, next_launch_number(), dv, st));
     return ECHO_OK;

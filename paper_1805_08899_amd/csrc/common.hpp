@@ -28,6 +28,22 @@ __device__ __forceinline__ float4 ld4(const bf16_t *p, size_t i) {
     return r;
 }
 
+// An element as loaded, and the number it stands for, as two steps: a load that sits in a guarded branch together
+// with the first operation on its value (for bf16 the shift that widens it) makes the compiler wait for the load
+// inside that branch, one trip to memory per load.  The raw form is what the load instruction delivers (bf16: the
+// 16 bits, zero-extended); zero stands for zero in both.
+template <typename T> struct RawElem;
+template <> struct RawElem<float> {
+    typedef float type;
+    static __device__ __forceinline__ type load(const float *p, size_t i) { return p[i]; }
+    static __device__ __forceinline__ float value(type r) { return r; }
+};
+template <> struct RawElem<bf16_t> {
+    typedef unsigned type;
+    static __device__ __forceinline__ type load(const bf16_t *p, size_t i) { return p[i].bits; }
+    static __device__ __forceinline__ float value(type r) { return __uint_as_float(r << 16); }
+};
+
 // Non-temporal loads, for inputs read once by the whole grid.  Measured: they help the LSTM block (nine input and
 // output streams at once, 180 -> 170 us) and hurt a single-stream copy (76 -> 93 us), so only the former uses them
 // (in the recompute kernel they cost 1 to 8 %).
@@ -187,6 +203,27 @@ __device__ __forceinline__ void wait_all_memory_ops() { asm volatile("s_waitcnt 
 // A wait on another block's flag gives up after this many ticks of the 100 MHz wall clock (2 s), so that every
 // wave ends whatever happens; the results of that launch are then marked invalid (NaN).
 constexpr long long kSpinLimitTicks = 200000000LL;
+
+// One float handed from one block of a launch to another without ordering between stores: two 64-bit words, each holding
+// the value next to one half of the launch's 64-bit number.  The receiver takes it once both halves and both copies of the
+// value agree, so the area may start in any state, and sets the slot back to zero, so that a captured launch, whose number
+// is fixed, can be replayed.
+constexpr unsigned long long kMailSalt = 0x9E3779B9ull;
+struct alignas(16) MailSlot {
+    unsigned long long w0, w1;
+};
+
+__device__ __forceinline__ void mail_put(MailSlot *s, float x, unsigned long long epoch) {
+    const unsigned long long bits = __float_as_uint(x);
+    store_agent(&s->w0, ((epoch & 0xffffffffull) << 32) | bits);
+    store_agent(&s->w1, ((((epoch >> 32) ^ kMailSalt) & 0xffffffffull) << 32) | bits);
+}
+__device__ __forceinline__ bool mail_try(const MailSlot *s, unsigned long long epoch, float &x) {
+    const unsigned long long a = load_agent(&s->w0), b = load_agent(&s->w1);
+    x = __uint_as_float((unsigned)a);
+    return (a >> 32) == (epoch & 0xffffffffull) && (b >> 32) == (((epoch >> 32) ^ kMailSalt) & 0xffffffffull) &&
+           (unsigned)a == (unsigned)b;
+}
 
 __device__ __forceinline__ int clamp_len(int len, int Tk) { return len < 0 ? 0 : (len > Tk ? Tk : len); }
 

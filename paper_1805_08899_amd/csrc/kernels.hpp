@@ -65,6 +65,12 @@ hipError_t launch_recompute(const AttnShape &s, const void *Qp, const void *Kp, 
                             const float *dS, const float *ds_rowsum, const float *tmap, float *dQp, float *dKp,
                             float *dv_part, unsigned long long *dv_flag, unsigned long long epoch, float *dv,
                             hipStream_t st);
+// The same for launches that recompute.hip would run in too few blocks: every tanh twice, in many independent blocks.
+// mail: recompute_split_mail_bytes(s) bytes of workspace in any state (0: the shape does not take this form)
+size_t recompute_split_mail_bytes(const AttnShape &s);
+hipError_t launch_recompute_split(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
+                                  const float *dS, float *dQp, float *dKp, void *mail, unsigned long long epoch, float *dv,
+                                  hipStream_t st);
 // B4  dv[h] = sum_b dv_part[b,h], fixed order
 hipError_t launch_dv_reduce(const AttnShape &s, const float *dv_part, float *dv, hipStream_t st);
 // One decoder step (Tq = 1) of the backward pass in one launch; dKp, dV and dv_part [B,H] are added to.

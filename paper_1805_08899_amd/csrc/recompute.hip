@@ -104,22 +104,6 @@ __device__ __forceinline__ void rc_tile_n(int ni, int live, const float (&fq)[RC
 #undef RC_CASE
 }
 
-// An element as loaded, and the number it stands for, as two steps: a load that sits in a guarded branch together
-// with the first operation on its value (for bf16 the shift that widens it) makes the compiler wait for the load
-// inside that branch, one trip to memory per load.  The raw form is what the load instruction delivers (bf16: the
-// 16 bits, zero-extended); zero stands for zero in both.
-template <typename T> struct RawElem;
-template <> struct RawElem<float> {
-    typedef float type;
-    static __device__ __forceinline__ type load(const float *p, size_t i) { return p[i]; }
-    static __device__ __forceinline__ float value(type r) { return r; }
-};
-template <> struct RawElem<bf16_t> {
-    typedef unsigned type;
-    static __device__ __forceinline__ type load(const bf16_t *p, size_t i) { return p[i].bits; }
-    static __device__ __forceinline__ float value(type r) { return __uint_as_float(r << 16); }
-};
-
 template <typename T, bool STASH>
 __global__ __launch_bounds__(RC_THREADS) void k_recompute(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ v,

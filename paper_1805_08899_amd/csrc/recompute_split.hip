@@ -1,0 +1,442 @@
+// The fused recomputation (recompute.hip) for launches that would leave most of the chip idle.
+//
+// k_recompute gives every sample and slice of h to one block, which evaluates each tanh once and spends it on
+// dQp, dKp and dv alike.  With B ceil(H / 16), its blocks at the narrowest, below the number of compute units a handful of
+// blocks walk a whole sample each while the rest of the chip waits.  Here the sums are split so
+// that no block needs another's partial result: blocks of one kind own query rows and sum over the keys (dQp), blocks of
+// the other kind own keys and sum over the query rows (dKp and the sample's part of dv).  Every tanh is evaluated twice
+// (15 issue slots per element instead of 9), but the work spreads over as many blocks and waves as wanted.
+//
+// A block owns up to XW * 8 * NS rows ("x": queries or keys) of one sample and a slice of HW columns of h, HW = 16, 32 or
+// 64: the 64 lanes are NS = 64 / HW groups of HW columns, so that a narrow H does not leave lanes idle.  Its eight waves
+// are XW groups of rows times YS shares of the other axis ("y"), XW YS = 8; a lane owns eight rows of its group and walks
+// its wave's share of y in chunks of four, the y values of the next chunk already requested.  The dS entries of the block's
+// rows are staged in LDS, one range of y at a time.  With YS > 1 the waves' sums meet in LDS at the end.  The order of all
+// additions is fixed.
+//
+// dv: every key-owning block hands its part (per column of h) to the last block of the slice through a mail slot; that
+// block, which starts last, adds the parts in order.
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace echo {
+
+constexpr int RS_W = 8;                    // waves per block
+constexpr int RS_THREADS = 64 * RS_W;
+constexpr int RS_R = 8;                    // rows a lane owns
+constexpr int RS_C = 4;                    // y per chunk
+constexpr int RS_TILE = 6144;              // floats of staged dS (24 KB)
+
+struct RsAxis {                            // how a kind of block cuts its axes (the same for the whole launch)
+    int groups;                            // blocks per sample and slice
+    int ys;                                // waves that share a row group (1, 2, 4, 8)
+    int y_tile;                            // y per staged range: a multiple of RS_C, rows * (y_tile + RS_C) <= RS_TILE
+};
+// rows of one block
+__host__ __device__ constexpr int rs_rows(int hw, int ys) { return RS_W / ys * RS_R * (64 / hw); }
+
+// One chunk: eight rows of a lane against four y.  EXACT: fx, fy hold 2 log2e x and the exponential of the sum is taken.
+template <bool EXACT, bool DV>
+__device__ __forceinline__ void rs_chunk(const float (&fx)[RS_R], const float (&fy)[RS_C], const float *__restrict__ d_row,
+                                         int d_step, float (&acc)[RS_R], float (&acc_v)[RS_C]) {
+#pragma unroll
+    for (int a0 = 0; a0 < RS_R; a0 += 2) {                 // two rows at a time: eight independent evaluations
+        float4 d4[2];
+        float r[2][RS_C], u[2][RS_C];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) d4[a] = *reinterpret_cast<const float4 *>(d_row + (a0 + a) * d_step);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int c = 0; c < RS_C; ++c)
+                r[a][c] = EXACT ? fast_exp2(fx[a0 + a] + fy[c]) + 1.0f : __builtin_fmaf(fx[a0 + a], fy[c], 1.0f);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int c = 0; c < RS_C; ++c) r[a][c] = fast_rcp(r[a][c]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int c = 0; c < RS_C; ++c) u[a][c] = __builtin_fmaf(-r[a][c], r[a][c], r[a][c]);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const float d[RS_C] = {d4[a].x, d4[a].y, d4[a].z, d4[a].w};
+            float p = d[0] * u[a][0], q = d[1] * u[a][1];
+            p = __builtin_fmaf(d[2], u[a][2], p);
+            q = __builtin_fmaf(d[3], u[a][3], q);
+            acc[a0 + a] += p + q;
+            if (DV) {
+#pragma unroll
+                for (int c = 0; c < RS_C; ++c) acc_v[c] = __builtin_fmaf(d[c], r[a][c], acc_v[c]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// X: rows of the owned axis [n_x valid rows, row stride H], Y: rows of the axis summed over [n_y rows].  out: rows of the
+// result.  KEYS: x = keys, y = queries (dKp, dv), else x = queries, y = keys (dQp).  ds: the sample's dS [query][key].
+template <typename T, int HW, bool KEYS>
+__device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__restrict__ Y, const T *__restrict__ v,
+                                         const float *__restrict__ ds, int pitch, float *__restrict__ out, bool add,
+                                         MailSlot *__restrict__ mail, unsigned long long epoch, int x_first, int n_x,
+                                         int n_out, int n_y, int H, int h0, int ys, int y_tile, float *__restrict__ s_d,
+                                         float *__restrict__ s_red) {
+    constexpr int NS = 64 / HW;
+    typedef RawElem<T> Raw;
+    const int lane = lane_id(), w = wave_id();
+    const int sub = lane / HW;
+    const int h = h0 + lane % HW;
+    const bool hv = h < H;
+    const int hc = hv ? h : H - 1;
+    const int yg = w & (ys - 1), xg = w / ys;
+    const int rows = rs_rows(HW, ys);                       // of this block
+    const int xl = xg * RS_R * NS + sub;                    // this lane's rows: x_first + xl + NS a
+    const bool wave_on = x_first + xg * RS_R * NS < n_x;    // the wave has valid rows
+
+    typename Raw::type v_raw = Raw::load(v, hc);
+    typename Raw::type x_raw[RS_R];
+#pragma unroll
+    for (int a = 0; a < RS_R; ++a) x_raw[a] = Raw::load(X, (size_t)min(x_first + xl + NS * a, n_x - 1) * H + hc);
+
+    float acc[RS_R], acc_v[RS_C] = {0.f, 0.f, 0.f, 0.f}, fx[RS_R], sx[RS_R];
+#pragma unroll
+    for (int a = 0; a < RS_R; ++a) acc[a] = 0.f;
+    bool x_big = false, first = true;
+    float d_sum = 0.f;
+    // an odd multiple of four floats: the lane groups of a narrow slice read four rows at once from different banks
+    const int d_pitch = RS_C * ((y_tile / RS_C) | 1);
+
+    for (int y0 = 0; y0 < n_y; y0 += y_tile) {
+        const int ny = min(y_tile, n_y - y0);
+        const int ny4 = (ny + RS_C - 1) & ~(RS_C - 1);
+        // the first chunk of this wave's share leaves together with the dS of the range
+        typename Raw::type y_raw[RS_C];
+        auto fetch = [&](int y) {
+#pragma unroll
+            for (int c = 0; c < RS_C; ++c) y_raw[c] = Raw::load(Y, (size_t)min(y0 + y + c, n_y - 1) * H + hc);
+        };
+        fetch(RS_C * yg);
+        if (!first) lds_barrier();                          // everybody is done with the previous range
+        // dS of (rows, range), four entries of a dS row per load, all loads of the range under way together; the pads of a
+        // dS row and its masked keys are stored zeros, rows past the end become zeros here: they add nothing
+        constexpr int U = (RS_TILE / 4 + RS_THREADS - 1) / RS_THREADS;
+        const int n_vec = rows * ny4 / 4, per_row = KEYS ? rows / 4 : ny4 / 4;
+        const float inv = fast_rcp((float)per_row);         // (e + 0.5) inv: exact quotient for e < 2^16
+        float4 d4[U];
+        int at[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = (int)threadIdx.x + u * RS_THREADS;
+            const int r = (int)(((float)e + 0.5f) * inv), c = 4 * (e - r * per_row);
+            const int xr = KEYS ? c : r, yr = KEYS ? r : c;
+            at[u] = e < n_vec ? xr * d_pitch + yr : -1;
+            d4[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (KEYS ? (e < n_vec && yr < ny && x_first + xr < pitch) : (e < n_vec && x_first + xr < n_x))
+                d4[u] = KEYS ? ld4(ds, (size_t)(y0 + yr) * pitch + x_first + xr) : ld4(ds, (size_t)(x_first + xr) * pitch + y0 + yr);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (at[u] < 0) continue;
+            if (KEYS) {
+                s_d[at[u]] = d4[u].x;
+                s_d[at[u] + d_pitch] = d4[u].y;
+                s_d[at[u] + 2 * d_pitch] = d4[u].z;
+                s_d[at[u] + 3 * d_pitch] = d4[u].w;
+                d_sum += (d4[u].x + d4[u].y) + (d4[u].z + d4[u].w);
+            } else {
+                *reinterpret_cast<float4 *>(s_d + at[u]) = d4[u];
+            }
+        }
+        if (first) {
+            asm volatile("" : "+v"(v_raw));
+#pragma unroll
+            for (int a = 0; a < RS_R; ++a) {
+                asm volatile("" : "+v"(x_raw[a]));
+                const float x = Raw::value(x_raw[a]);
+                x_big |= fabsf(x) > kFactorLimit;
+                sx[a] = kTwoLog2e * x;
+                fx[a] = fast_exp2(sx[a]);
+            }
+            first = false;
+        }
+        lds_barrier();
+        if (wave_on) {
+            for (int y = RS_C * yg; y < ny4; y += RS_C * ys) {
+                float sy[RS_C], fy[RS_C];
+                bool big = x_big;
+#pragma unroll
+                for (int c = 0; c < RS_C; ++c) asm volatile("" : "+v"(y_raw[c]));
+#pragma unroll
+                for (int c = 0; c < RS_C; ++c) {
+                    const float k = Raw::value(y_raw[c]);
+                    big |= fabsf(k) > kFactorLimit;
+                    sy[c] = kTwoLog2e * k;
+                    fy[c] = fast_exp2(sy[c]);
+                }
+                fetch(min(y + RS_C * ys, ny4 - RS_C));
+                const float *d_row = s_d + xl * d_pitch + y;
+                if (!__any(big)) rs_chunk<false, KEYS>(fx, fy, d_row, NS * d_pitch, acc, acc_v);
+                else rs_chunk<true, KEYS>(sx, sy, d_row, NS * d_pitch, acc, acc_v);
+            }
+        }
+    }
+
+    const float v4 = hv ? 4.f * Raw::value(v_raw) : 0.f;
+    auto store = [&](int x, float val) {
+        if (x >= n_out || !hv) return;
+        float *dst = out + (size_t)x * H + h;
+        if (x >= n_x) {
+            if (!add) *dst = 0.f;                           // masked key (adding: it holds a zero already)
+        } else if (add) {
+            *dst += val;
+        } else {
+            store_streaming(dst, val);
+        }
+    };
+    if (ys == 1) {
+#pragma unroll
+        for (int a = 0; a < RS_R; ++a) store(x_first + xl + NS * a, v4 * acc[a]);
+    } else {
+#pragma unroll
+        for (int a = 0; a < RS_R; ++a) s_red[(w * RS_R + a) * 64 + lane] = acc[a];
+    }
+    if (KEYS) {
+        float *s_v = s_red + RS_W * RS_R * 64;              // [RS_W][64], then RS_W sums of dS
+        s_v[w * 64 + lane] = (acc_v[0] + acc_v[1]) + (acc_v[2] + acc_v[3]);
+        d_sum = wave_sum(d_sum);
+        if (lane == 0) s_v[RS_W * 64 + w] = d_sum;
+    }
+    if (KEYS || ys > 1) lds_barrier();
+    if (ys > 1) {
+        // row a of group xg: its YS partial sums, added by the group's waves in turn
+        for (int a = yg; a < RS_R; a += ys) {
+            float tot = 0.f;
+            for (int k = 0; k < ys; ++k) tot += s_red[((xg * ys + k) * RS_R + a) * 64 + lane];
+            store(x_first + xl + NS * a, v4 * tot);
+        }
+    }
+    if (KEYS && w == 0) {
+        const float *s_v = s_red + RS_W * RS_R * 64;
+        float tot = 0.f, dtot = 0.f;
+#pragma unroll
+        for (int k = 0; k < RS_W; ++k) {
+            tot += s_v[k * 64 + lane];
+            dtot += s_v[RS_W * 64 + k];
+        }
+        if constexpr (NS >= 2) tot += __shfl_xor(tot, 32);
+        if constexpr (NS >= 4) tot += __shfl_xor(tot, 16);
+        if (sub == 0 && hv) mail_put(mail + h, __builtin_fmaf(-2.f, tot, dtot), epoch);   // sum dS t = sum dS - 2 sum dS r
+    }
+}
+
+// grid (slices of h, samples heaviest first, groups of keys then groups of queries)
+template <typename T, int HW>
+__global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
+    const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ v, const int *__restrict__ order,
+    const float *__restrict__ dS, float *__restrict__ dQp, float *__restrict__ dKp, MailSlot *__restrict__ mail,
+    unsigned long long epoch, float *__restrict__ dv, int Tq, int Tk, int H, int pitch, RsAxis ka, RsAxis qa, int acc) {
+    __shared__ __align__(16) float s_d[RS_TILE];
+    __shared__ __align__(16) float s_red[RS_W * RS_R * 64 + RS_W * 64 + RS_W];
+    __shared__ int s_seen[RS_W];
+    const int packed = order[blockIdx.y];
+    const int b = packed & 0xffff, L = packed >> 16;
+    const int h0 = blockIdx.x * HW;
+    const int n_slots = gridDim.y;
+    const int z = blockIdx.z;
+    const T *qb = Qp + (size_t)b * Tq * H, *kb = Kp + (size_t)b * Tk * H;
+    const float *dsb = dS + (size_t)b * Tq * pitch;
+    if (z < ka.groups) {
+        const int x0 = z * rs_rows(HW, ka.ys);
+        if (x0 < L) {
+            rs_block<T, HW, true>(kb, qb, v, dsb, pitch, dKp + (size_t)b * Tk * H, acc != 0,
+                                  mail + ((size_t)blockIdx.y * ka.groups + z) * H, epoch, x0, L, Tk, Tq, H, h0, ka.ys,
+                                  ka.y_tile, s_d, s_red);
+        } else if (!acc) {                                  // masked keys only: exact zeros
+            const int n = min(rs_rows(HW, ka.ys), Tk - x0), lh = threadIdx.x % HW;
+            for (int x = threadIdx.x / HW; x < n; x += RS_THREADS / HW)
+                if (h0 + lh < H) dKp[((size_t)b * Tk + x0 + x) * H + h0 + lh] = 0.f;
+        }
+    } else {
+        const int x0 = (z - ka.groups) * rs_rows(HW, qa.ys);
+        float *out = dQp + (size_t)b * Tq * H;
+        if (L > 0) {
+            rs_block<T, HW, false>(qb, kb, v, dsb, pitch, out, false, nullptr, 0, x0, Tq, Tq, L, H, h0, qa.ys, qa.y_tile,
+                                   s_d, s_red);
+        } else {
+            const int n = min(rs_rows(HW, qa.ys), Tq - x0), lh = threadIdx.x % HW;
+            for (int x = threadIdx.x / HW; x < n; x += RS_THREADS / HW)
+                if (h0 + lh < H) out[(size_t)(x0 + x) * H + h0 + lh] = 0.f;
+        }
+    }
+    if (z != (int)gridDim.z - 1 || (int)blockIdx.y != n_slots - 1) return;
+
+    // ---- the last block of the slice: dv = the parts of all samples and key groups, each wave every eighth in order,
+    // then the waves in order.  All blocks it waits for were dispatched before it.
+    lds_barrier();                                          // s_red is reused
+    const int lane = lane_id(), w = wave_id();
+    const int h = h0 + lane % HW;
+    const int key_rows = rs_rows(HW, ka.ys);
+    const int n_parts = n_slots * ka.groups;
+    constexpr int U = 4, STEP = RS_W * 64 / HW;             // parts in flight per lane; lanes past HW take parts of their own
+    const int p_first = w * (64 / HW) + lane / HW;
+    const long long t0 = wall_clock64();
+    float sum = 0.f;
+    bool ok = true;
+    if (h < H) {
+        for (int p0 = p_first; p0 < n_parts; p0 += U * STEP) {
+            float x[U];
+            bool there[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int p = p0 + u * STEP;
+                x[u] = 0.f;
+                // groups past the sample's last valid key send nothing
+                there[u] = p >= n_parts || (p % ka.groups) * key_rows >= (order[min(p, n_parts - 1) / ka.groups] >> 16);
+            }
+            for (;;) {
+                bool all = true;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (there[u]) continue;
+                    MailSlot *s = mail + (size_t)(p0 + u * STEP) * H + h;
+                    float y;
+                    if (mail_try(s, epoch, y)) {
+                        x[u] = y;
+                        there[u] = true;
+                        store_agent(&s->w0, 0ull);
+                        store_agent(&s->w1, 0ull);
+                    } else {
+                        all = false;
+                    }
+                }
+                if (all) break;
+                if (wall_clock64() - t0 > kSpinLimitTicks) {
+                    ok = false;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (!ok) break;
+#pragma unroll
+            for (int u = 0; u < U; ++u) sum += x[u];
+        }
+    }
+    s_red[w * 64 + lane] = sum;
+    const int all_ok = __all(ok) ? 1 : 0;
+    if (lane == 0) s_seen[w] = all_ok;
+    lds_barrier();
+    if (w == 0 && lane < HW && h < H) {
+        float tot = 0.f;
+        bool seen = true;
+        for (int k = 0; k < RS_W; ++k) {
+            for (int g = 0; g < 64 / HW; ++g) tot += s_red[k * 64 + g * HW + lane];
+            seen = seen && s_seen[k] != 0;
+        }
+        if (!seen) tot = __builtin_nanf("");                // a part never arrived: make the failure visible
+        dv[h] = acc ? dv[h] + tot : tot;
+    }
+}
+
+// ---- host side ------------------------------------------------------------------------------------------------------
+
+constexpr int RS_ROUND = 512;              // two blocks on every compute unit (128 registers per lane)
+constexpr float RS_BLOCK_US = 4.0f, RS_CHUNK_US = 1.1f;
+constexpr int RS_MOST_BLOCKS = 192;
+constexpr size_t RS_MOST_SLOTS = 1 << 18;  // 4 MB of mail
+
+// Blocks of one kind per sample and slice when n_x rows are owned and ys waves share a row group.
+static int rs_groups(int hw, int ys, int n_x) { return (n_x + rs_rows(hw, ys) - 1) / rs_rows(hw, ys); }
+
+static RsAxis rs_axis(int hw, int ys, int n_x, int n_y) {
+    RsAxis a;
+    a.ys = ys;
+    a.groups = rs_groups(hw, ys, n_x);
+    a.y_tile = (RS_TILE / rs_rows(hw, ys) - RS_C) / RS_C * RS_C;
+    const int n_y4 = (n_y + RS_C - 1) / RS_C * RS_C;
+    if (a.y_tile > n_y4) a.y_tile = n_y4;
+    return a;
+}
+
+// How a launch is cut, and what it is expected to take.
+struct RsPlan {
+    int hw;
+    RsAxis ka, qa;
+    float us;
+};
+
+// Expected time of a cut in microseconds: a block lives RS_BLOCK_US (launch, its trips to memory, its last reduction) plus
+// RS_CHUNK_US per chunk that its waves walk one after the other, RS_ROUND blocks run at a time (half of them: a chunk
+// takes half the time), and the launch takes as long as its longest block or as all blocks together.
+static RsPlan rs_plan(const AttnShape &s) {
+    RsPlan best{};
+    for (int hw = 64; hw >= 16; hw /= 2) {
+        const float per_group = (float)s.B * ((s.H + hw - 1) / hw);
+        for (int ys = 1; ys <= RS_W; ys *= 2) {
+            auto fit = [](int y, int n) {          // not more waves than chunks
+                while (y > 1 && y * RS_C > n + RS_C - 1) y /= 2;
+                return y;
+            };
+            RsPlan p;
+            p.hw = hw;
+            p.ka = rs_axis(hw, fit(ys, s.Tq), s.Tk, s.Tq);
+            p.qa = rs_axis(hw, fit(ys, s.Tk), s.Tq, s.Tk);
+            const float nk = per_group * p.ka.groups, nq = per_group * p.qa.groups;
+            const float chunk = nk + nq <= RS_ROUND / 2 ? RS_CHUNK_US / 2 : RS_CHUNK_US;
+            const float tk = RS_BLOCK_US + chunk * ((s.Tq + RS_C * p.ka.ys - 1) / (RS_C * p.ka.ys));
+            const float tq = RS_BLOCK_US + chunk * ((s.Tk + RS_C * p.qa.ys - 1) / (RS_C * p.qa.ys));
+            const float all = (nk * tk + nq * tq) / RS_ROUND, longest = tk > tq ? tk : tq;
+            p.us = all > longest ? all : longest;
+            if (best.hw == 0 || p.us < 0.95f * best.us) best = p;
+        }
+    }
+    return best;
+}
+
+// Taken while recompute.hip's narrowest slices would leave a quarter of the compute units without a block (measured: at 192
+// blocks the two forms meet, 10.7 against 11.6 us at B = 16, T = 40, H = 181; below it this one is ahead by up to 4 times,
+// 53 -> 13 us at B = 3, T = 200, H = 76; above it evaluating every tanh twice loses).
+size_t recompute_split_mail_bytes(const AttnShape &s) {
+    if ((long long)s.B * ((s.H + 15) / 16) > RS_MOST_BLOCKS) return 0;
+    const RsPlan p = rs_plan(s);
+    const size_t slots = (size_t)s.B * p.ka.groups * s.H;
+    return slots <= RS_MOST_SLOTS ? slots * sizeof(MailSlot) : 0;
+}
+
+template <typename T, int HW>
+static hipError_t launch_split_t(const AttnShape &s, const RsPlan &p, const void *Qp, const void *Kp, const void *v, const int *order,
+                                 const float *dS, float *dQp, float *dKp, MailSlot *mail, unsigned long long epoch, float *dv,
+                                 hipStream_t st) {
+    const RsAxis ka = p.ka;
+    RsAxis qa = p.qa;
+    if (!dQp) qa.groups = 0;
+    dim3 grid((s.H + HW - 1) / HW, s.B, ka.groups + qa.groups);
+    if (grid.z > 65535) return hipErrorInvalidValue;
+    k_recompute_split<T, HW><<<grid, RS_THREADS, 0, st>>>((const T *)Qp, (const T *)Kp, (const T *)v, order, dS, dQp, dKp, mail,
+                                                          epoch, dv, s.Tq, s.Tk, s.H, ds_pitch(s.Tk), ka, qa, s.acc ? 1 : 0);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_split_hw(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
+                                  const float *dS, float *dQp, float *dKp, void *mail, unsigned long long epoch, float *dv,
+                                  hipStream_t st) {
+    MailSlot *m = static_cast<MailSlot *>(mail);
+    const RsPlan p = rs_plan(s);
+    switch (p.hw) {
+        case 16: return launch_split_t<T, 16>(s, p, Qp, Kp, v, order, dS, dQp, dKp, m, epoch, dv, st);
+        case 32: return launch_split_t<T, 32>(s, p, Qp, Kp, v, order, dS, dQp, dKp, m, epoch, dv, st);
+        default: return launch_split_t<T, 64>(s, p, Qp, Kp, v, order, dS, dQp, dKp, m, epoch, dv, st);
+    }
+}
+
+hipError_t launch_recompute_split(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
+                                  const float *dS, float *dQp, float *dKp, void *mail, unsigned long long epoch, float *dv,
+                                  hipStream_t st) {
+    return s.bf16 ? launch_split_hw<bf16_t>(s, Qp, Kp, v, order, dS, dQp, dKp, mail, epoch, dv, st)
+                  : launch_split_hw<float>(s, Qp, Kp, v, order, dS, dQp, dKp, mail, epoch, dv, st);
+}
+
+}  // namespace echo

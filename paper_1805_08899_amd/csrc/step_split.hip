@@ -33,25 +33,8 @@ constexpr int SP_COLS = 128;                  // columns (h) per part after the 
 constexpr int SP_GROUPS = SP_THREADS / SP_COLS;    // row groups per block after the exchange (4): key g + 4 m
 constexpr int SP_ROWS = SP_KEYS / SP_GROUPS;  // rows per thread (16)
 constexpr int SP_MAX_WIDTH = 256 * SP_CH;     // H and Dv up to 512
-constexpr unsigned long long kMailSalt = 0x9E3779B9ull;
-
-struct alignas(16) MailSlot {
-    unsigned long long w0, w1;
-};
 
 __device__ __forceinline__ float comp4s(const float4 &x, int c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; }
-
-__device__ __forceinline__ void mail_put(MailSlot *s, float x, unsigned long long epoch) {
-    const unsigned long long bits = __float_as_uint(x);
-    store_agent(&s->w0, ((epoch & 0xffffffffull) << 32) | bits);
-    store_agent(&s->w1, ((((epoch >> 32) ^ kMailSalt) & 0xffffffffull) << 32) | bits);
-}
-__device__ __forceinline__ bool mail_try(const MailSlot *s, unsigned long long epoch, float &x) {
-    const unsigned long long a = load_agent(&s->w0), b = load_agent(&s->w1);
-    x = __uint_as_float((unsigned)a);
-    return (a >> 32) == (epoch & 0xffffffffull) && (b >> 32) == (((epoch >> 32) ^ kMailSalt) & 0xffffffffull) &&
-           (unsigned)a == (unsigned)b;
-}
 
 // On entry s_val holds this part's values at its keys (j < L, j % 4 == part); on return it holds the values of all
 // keys below L.  mail_b: the sample's boxes [SP_PARTS receivers][SP_KEYS].  Called by every thread of the block;

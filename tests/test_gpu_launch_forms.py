@@ -1,0 +1,53 @@
+"""The forms that the launchers choose by the size of the launch, at the edges where each begins or ends, against the
+float64 oracle and with guard zones around every output."""
+import numpy as np
+import pytest
+
+from paper_1805_08899_amd.workloads import Workload, make_inputs
+from parity import assert_parity, oracle_outputs
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name, B, Tq, Tk, H, Dv, dtype, big (entries beyond the range of the factorised exponential)
+    # recomputation, every tanh twice (few blocks): slices of 16, 32 and 64 columns, remainders on both axes, one row,
+    # more rows than one staged range of dS, entries that need the exponential of the sum
+    ("split_16_columns", 1, 33, 53, 12, 8, "f32", True),
+    ("split_32_columns_ragged_h", 3, 130, 70, 90, 8, "f32", False),
+    ("split_64_columns", 2, 61, 83, 256, 12, "f32", True),
+    ("split_one_query", 2, 1, 70, 64, 8, "f32", False),
+    ("split_one_key", 3, 70, 1, 40, 4, "f32", False),
+    ("split_many_ranges", 1, 700, 300, 20, 4, "f32", False),
+    ("split_bf16", 2, 37, 261, 100, 8, "bf16", False),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_launch_form(case):
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import harness
+    name, B, Tq, Tk, H, Dv, dt, big = case
+    print("launch form", case, flush=True)
+    wl = Workload(name, B, Tq, Tk, H, Dv, dt, 0.5, 1, Tk, dt == "bf16")
+    inputs = make_inputs(wl, seed=313 + len(name))
+    if B > 2:
+        inputs["key_len"][1] = 0                              # a sample without a valid key among the others
+    if big:
+        inputs["Qp"][0, Tq // 2, : H // 2] = 60.0
+        inputs["Kp"][0, 0, : H // 2] = -59.5
+        inputs["Kp"][B - 1, Tk - 1, H // 3] = 45.0
+        inputs["key_len"][B - 1] = Tk
+    db = harness.DeviceBatch(wl, inputs, guard_bytes=4096)
+    db.poison_outputs()
+    db.fwd()
+    db.bwd()
+    got = db.results()
+    assert db.check_guards() == []
+    assert_parity(got, oracle_outputs(inputs, workers=1), inputs, dt, name)
+    first = {k: v.copy() for k, v in got.items()}
+    db.fwd()
+    db.bwd()
+    again = db.results()
+    for k in first:
+        assert np.array_equal(first[k], again[k]), (name, k, "not reproducible")
