@@ -52,7 +52,7 @@ BwdWs bwd_layout(const AttnShape &s) {
     w.dvpart_off = w.rowsum_off + align_up((size_t)s.B * s.Tq * sizeof(float));
     w.order_off = w.dvpart_off + align_up((size_t)s.B * s.H * sizeof(float));
     w.dvflag_off = w.order_off + align_up((size_t)s.B * sizeof(int));
-    w.mail_off = w.dvflag_off + align_up((size_t)((s.H + 63) / 64) * s.B * sizeof(unsigned long long));
+    w.mail_off = w.dvflag_off + align_up((size_t)((s.H + 15) / 16) * s.B * sizeof(unsigned long long));
     w.mail_bytes = echo::recompute_split_mail_bytes(s);
     w.total = w.mail_off + align_up(w.mail_bytes);
     return w;

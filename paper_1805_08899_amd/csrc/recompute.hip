@@ -7,8 +7,9 @@
 //     dv[h]     += sum_{i,j} dS[b,i,j] t                  (Eq. 2: needs the tanh map as the input of the v projection)
 // without the B x Tq x Tk x H map ever existing in memory.
 //
-// A block owns one sample and one 64-wide slice of h; lanes run along h, so
-// dS[b,i,j] is uniform over a wave and dQp, dKp, dv are plain per-lane sums.
+// A block owns one sample and one slice of HW = 64, 32 or 16 columns of h; lanes run along h, and with a slice narrower
+// than the wave the 64 / HW lane groups own different query rows.  dS[b,i,j] is uniform over a lane group and dQp, dKp, dv
+// are plain per-lane sums.
 // With r = 1 / (exp(2(q+k)) + 1):  t = 1 - 2r  and  1 - t^2 = 4 r (1 - r).
 // Wave w owns query rows; all waves walk the keys together in tiles of RJ.
 // The key tile (exponentials) and the dS tile are fetched one tile ahead and
@@ -28,6 +29,7 @@ constexpr int RC_RI = 8;      // query rows per wave and pass
 constexpr int RC_RJ = 8;      // keys per tile (== kDsPad)
 constexpr int RC_W = 8;       // waves per block (== RC_RJ: wave jj finishes key jj of a tile)
 constexpr int RC_THREADS = 64 * RC_W;
+constexpr int RC_ROUND = 512; // blocks that run at a time: two on every compute unit
 static_assert(RC_RJ == kDsPad, "dS rows are padded to the key tile");
 static_assert(RC_W == RC_RJ, "one finishing wave per key of a tile");
 static_assert(RC_W == 8, "rows are dealt to eight waves");
@@ -104,8 +106,8 @@ __device__ __forceinline__ void rc_tile_n(int ni, int live, const float (&fq)[RC
 #undef RC_CASE
 }
 
-template <typename T, bool STASH>
-__global__ __launch_bounds__(RC_THREADS) void k_recompute(
+template <typename T, bool STASH, int HW>
+__global__ __launch_bounds__(RC_THREADS, 4) void k_recompute(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ v,
     const int *__restrict__ order, const float *__restrict__ dS, const float *__restrict__ ds_rowsum,
     const float *__restrict__ tmap, float *__restrict__ dQp, float *__restrict__ dKp, float *dv_part,
@@ -113,10 +115,12 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
     int Tq, int Tk, int H, int pitch, int rows_per_pass, int acc) {
     // Key tile staged once per block, double buffered: exp(2k) for the factor
     // path, 2 log2e k for the exact path, and per key a flag "beyond the factor limit".
-    __shared__ float s_fk[2][RC_RJ][64];
-    __shared__ float s_sk[2][RC_RJ][64];
+    __shared__ float s_fk[2][RC_RJ][HW];
+    __shared__ float s_sk[2][RC_RJ][HW];
     __shared__ int s_kbig[2][RC_RJ];
-    __shared__ __align__(16) float s_ds[2][RC_THREADS];     // dS of the pass rows x tile keys, [row][key]
+    constexpr int NS = 64 / HW;                             // lane groups
+    constexpr int ROWS = RC_W * RC_RI * NS;                 // rows of a pass at most
+    __shared__ __align__(16) float s_ds[2][ROWS * RC_RJ];   // dS of the pass rows x tile keys, [row][key]
     __shared__ float s_part[2][RC_W][RC_RJ][64];
     __shared__ float s_dv[RC_W][64];
     __shared__ float s_rowsum;
@@ -126,7 +130,8 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
     const int packed = order[blockIdx.y];
     const int b = packed & 0xffff, L = packed >> 16;
     const int lane = lane_id(), w = wave_id();
-    const int h = blockIdx.x * 64 + lane;
+    const int sub = lane / HW, hl = lane % HW;
+    const int h = blockIdx.x * HW + hl;
     const bool hv = h < H;
     const int hc = hv ? h : H - 1;
     // v of this lane's h: requested here, first touched behind the first loads of a pass (as a guarded load followed
@@ -138,10 +143,10 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
 
     // masked keys: exact zeros (when adding to earlier decoder steps they hold zeros already)
     if (!acc)
-        for (int j = L + w; j < Tk; j += RC_W)
+        for (int j = L + w * NS + sub; j < Tk; j += RC_W * NS)
             if (hv) dKb[(size_t)j * H + h] = 0.f;
     if (L == 0 && dQp) {                            // block-uniform
-        for (int i = w; i < Tq; i += RC_W)
+        for (int i = w * NS + sub; i < Tq; i += RC_W * NS)
             if (hv) dQb[(size_t)i * H + h] = 0.f;
     }
     // sum of this sample's dS (zero in exact arithmetic): the part of sum dS t that comes from t = 1 - 2r.  The last
@@ -162,27 +167,33 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
         const int n_jt = (L + RC_RJ - 1) / RC_RJ;
 
         // Tile staging, one tile ahead of the arithmetic.  Wave w fetches key w of the
-        // tile (RC_W == RC_RJ) and thread t the dS element (row t / 8, key t % 8) of
-        // the pass; the loads are issued before the current tile is evaluated and
+        // tile (RC_W == RC_RJ) and every thread an element of the pass's dS
+        // rows or four; the loads are issued before the current tile is evaluated and
         // committed to the other LDS buffer after it.
-        const int t_row = threadIdx.x / RC_RJ, t_col = threadIdx.x % RC_RJ;
+        // (one lane group: 64 rows, an element per thread; more: four elements of a row)
+        constexpr int DN = NS == 1 ? 1 : 4;
+        const int t_row = threadIdx.x / (RC_RJ / DN), t_col = DN * (threadIdx.x % (RC_RJ / DN));
+        const bool t_on = RC_THREADS / (RC_RJ / DN) <= ROWS || t_row < ROWS;
         typedef RawElem<T> Raw;
         typename Raw::type kx_raw = 0;
-        float dx = 0.f;
+        typedef float DVec __attribute__((ext_vector_type(DN)));
+        DVec dx = 0.f;
         auto fetch = [&](int jt, int i_pass0, int nrows) {
             const int j = jt * RC_RJ + w;
             kx_raw = 0;
             if (!STASH && j < L) kx_raw = Raw::load(kb, (size_t)j * H + hc);
-            dx = (t_row < nrows) ? dsb[(size_t)(i_pass0 + t_row) * pitch + jt * RC_RJ + t_col] : 0.f;
+            dx = 0.f;
+            if (t_row < nrows)
+                dx = *reinterpret_cast<const DVec *>(dsb + (size_t)(i_pass0 + t_row) * pitch + jt * RC_RJ + t_col);
         };
         auto commit = [&](int jt, int buf) {
             const int j = jt * RC_RJ + w;
-            s_ds[buf][threadIdx.x] = dx;
+            if (t_on) *reinterpret_cast<DVec *>(&s_ds[buf][t_row * RC_RJ + t_col]) = dx;
             if (STASH) return;
             asm volatile("" : "+v"(kx_raw));
             const float kx = Raw::value(kx_raw);
-            s_sk[buf][w][lane] = kTwoLog2e * kx;
-            s_fk[buf][w][lane] = (j < L) ? fast_exp2(kTwoLog2e * kx) : 0.f;
+            if (NS == 1 || sub == 0) s_sk[buf][w][hl] = kTwoLog2e * kx;
+            if (NS == 1 || sub == 0) s_fk[buf][w][hl] = (j < L) ? fast_exp2(kTwoLog2e * kx) : 0.f;
             const int big = __any(fabsf(kx) > kFactorLimit) ? 1 : 0;
             if (lane == 0) s_kbig[buf][w] = big;
         };
@@ -190,8 +201,10 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
         int pass = 0;
         for (int i_pass0 = 0; i_pass0 < Tq; i_pass0 += rows_per_pass, ++pass) {
             const int nrows = min(rows_per_pass, Tq - i_pass0);
-            const int r_lo = deal8_begin(nrows, w), r_hi = deal8_begin(nrows, w + 1);
-            const int ni = r_hi - r_lo;              // 0..RC_RI
+            // rows are dealt to the waves NS at a time, one to each lane group: this lane's rows are i0 + NS a
+            const int n_rg = (nrows + NS - 1) / NS;
+            const int g_lo = deal8_begin(n_rg, w), ni = deal8_begin(n_rg, w + 1) - g_lo;   // ni: 0..RC_RI
+            const int r_lo = g_lo * NS + sub;
             const int i0 = i_pass0 + r_lo;
 
             fetch(0, i_pass0, nrows);
@@ -202,7 +215,7 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
 #pragma unroll
                 for (int a = 0; a < RC_RI; ++a) {
                     xr[a] = 0;
-                    if (!STASH && a < ni) xr[a] = Raw::load(qb, (size_t)(i0 + a) * H + hc);
+                    if (!STASH && a < ni) xr[a] = Raw::load(qb, (size_t)(NS == 1 ? i0 + a : min(i0 + NS * a, Tq - 1)) * H + hc);
                 }
                 if (pass == 0 && w == RC_W - 1) sum_rows();
                 asm volatile("" : "+v"(v_raw));
@@ -246,7 +259,7 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
                     const float *t_tile = tmap + (((size_t)b * Tq + i0) * Tk) * H + hc;
 #pragma unroll
                     for (int c = 0; c < RC_RJ; ++c) fk[c] = 0.f;
-                    rc_tile_n<RC_STASH>(ni, live, fq, fk, ds_tile, RC_RJ, t_tile, (size_t)Tk * H, (size_t)H, kcol, accQ, accK,
+                    rc_tile_n<RC_STASH>(ni, live, fq, fk, ds_tile, NS * RC_RJ, t_tile, (size_t)Tk * H, (size_t)H, kcol, accQ, accK,
                                         accV);
                 } else {
                     int kbig = 0;
@@ -254,12 +267,12 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
                     for (int c = 0; c < RC_RJ; ++c) kbig |= s_kbig[buf][c];
                     if (!(wave_qbig || kbig)) {
 #pragma unroll
-                        for (int c = 0; c < RC_RJ; ++c) fk[c] = s_fk[buf][c][lane];
-                        rc_tile_n<RC_FACTOR>(ni, live, fq, fk, ds_tile, RC_RJ, nullptr, 0, 0, kcol, accQ, accK, accV);
+                        for (int c = 0; c < RC_RJ; ++c) fk[c] = s_fk[buf][c][hl];
+                        rc_tile_n<RC_FACTOR>(ni, live, fq, fk, ds_tile, NS * RC_RJ, nullptr, 0, 0, kcol, accQ, accK, accV);
                     } else {
 #pragma unroll
-                        for (int c = 0; c < RC_RJ; ++c) fk[c] = s_sk[buf][c][lane];
-                        rc_tile_n<RC_EXACT>(ni, live, sq, fk, ds_tile, RC_RJ, nullptr, 0, 0, kcol, accQ, accK, accV);
+                        for (int c = 0; c < RC_RJ; ++c) fk[c] = s_sk[buf][c][hl];
+                        rc_tile_n<RC_EXACT>(ni, live, sq, fk, ds_tile, NS * RC_RJ, nullptr, 0, 0, kcol, accQ, accK, accV);
                     }
                 }
                 if (more) commit(jt + 1, buf ^ 1);
@@ -271,7 +284,9 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
                 float tot = 0.f;
 #pragma unroll
                 for (int w2 = 0; w2 < RC_W; ++w2) tot += s_part[buf][w2][w][lane];
-                if (j < L && hv) {
+                if constexpr (NS >= 2) tot = transpose_pair<32>(tot, tot, lane);     // the lane groups
+                if constexpr (NS >= 4) tot = transpose_pair<16>(tot, tot, lane);
+                if (j < L && hv && (NS == 1 || sub == 0)) {
                     float *dst = dKb + (size_t)j * H + h;
                     const float val = v4 * tot;
                     if (pass == 0 && !acc) store_streaming(dst, val);
@@ -281,7 +296,8 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
             if (hv && dQp) {
 #pragma unroll
                 for (int a = 0; a < RC_RI; ++a)
-                    if (a < ni) store_streaming(&dQb[(size_t)(i0 + a) * H + h], v4 * accQ[a]);
+                    if (a < ni && (NS == 1 || i0 + NS * a < i_pass0 + nrows))
+                        store_streaming(&dQb[(size_t)(i0 + NS * a) * H + h], v4 * accQ[a]);
             }
             lds_barrier();   // the next pass restages buffer 0 and reuses s_part
         }
@@ -297,6 +313,8 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
             float tot = 0.f;
 #pragma unroll
             for (int w2 = 0; w2 < RC_W; ++w2) tot += s_dv[w2][lane];
+            if constexpr (NS >= 2) tot = transpose_pair<32>(tot, tot, lane);
+            if constexpr (NS >= 4) tot = transpose_pair<16>(tot, tot, lane);
             store_agent(&dv_part[(size_t)b * H + h], __builtin_fmaf(-2.f, tot, s_rowsum));
         }
         // B4 without a launch of its own: the part is published (written through, awaited, then flagged with
@@ -349,38 +367,61 @@ __global__ __launch_bounds__(RC_THREADS) void k_recompute(
 }
 
 
-template <typename T>
+template <typename T, bool STASH, int HW>
 static hipError_t launch_recompute_t(const AttnShape &s, const void *Qp, const void *Kp, const void *v,
                                      const int *order, const float *dS, const float *ds_rowsum, const float *tmap,
                                      float *dQp, float *dKp, float *dv_part, unsigned long long *dv_flag,
                                      unsigned long long epoch, float *dv, hipStream_t st) {
-    const int max_rows = RC_W * RC_RI;
-    const int n_pass = (s.Tq + max_rows - 1) / max_rows;
-    // full passes of 64 rows first, the remainder last: with the rows split evenly over the passes, waves of 7 and of 8
+    const int max_rows = RC_W * RC_RI * (64 / HW);
+    // full passes first, the remainder last: with the rows split evenly over the passes, waves of 7 and of 8
     // rows meet at every tile's barrier (100 rows: 64 + 36 instead of 50 + 50; backward 141.5 -> 139.8 us at B = 128)
     const int rows_per_pass = s.Tq > max_rows ? max_rows : s.Tq;
-    (void)n_pass;
-    dim3 grid((s.H + 63) / 64, s.B);
-    if (tmap)
-        k_recompute<T, true><<<grid, RC_THREADS, 0, st>>>((const T *)Qp, (const T *)Kp, (const T *)v, order, dS,
-                                                          ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag, epoch, dv,
-                                                          s.Tq, s.Tk, s.H, ds_pitch(s.Tk), rows_per_pass,
-                                                          s.acc ? 1 : 0);
-    else
-        k_recompute<T, false><<<grid, RC_THREADS, 0, st>>>((const T *)Qp, (const T *)Kp, (const T *)v, order, dS,
-                                                           ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag, epoch, dv,
-                                                           s.Tq, s.Tk, s.H, ds_pitch(s.Tk), rows_per_pass,
-                                                           s.acc ? 1 : 0);
+    dim3 grid((s.H + HW - 1) / HW, s.B);
+    k_recompute<T, STASH, HW><<<grid, RC_THREADS, 0, st>>>((const T *)Qp, (const T *)Kp, (const T *)v, order, dS, ds_rowsum,
+                                                           tmap, dQp, dKp, dv_part, dv_flag, epoch, dv, s.Tq, s.Tk, s.H,
+                                                           ds_pitch(s.Tk), rows_per_pass, s.acc ? 1 : 0);
     return hipGetLastError();
+}
+
+// Width of a block's slice of h: 64, 32 or 16.  A narrower slice means more blocks of less work each (lane groups share the
+// rows) and costs more per tanh (the staging and the sums of a key tile, about five rows' worth of time, are shared by fewer
+// rows of a wave), so it is taken only while the launch stays within one round of two blocks per compute unit: one block
+// per CU leaves half of the issue slots empty.  Measured (recompute launch): B = 32, T = 100, H = 512, 256 -> 512 blocks
+// 56 -> 33 us; B = 16, T = 300, H = 512, 128 -> 512 blocks 401 -> 145 us; with more than a round it loses (B = 64, T = 50,
+// H = 512, 512 -> 1024 blocks 20.7 -> 28.4 us), and with a wave's rows already down to three it gives nothing.  An H that
+// fits the narrower slice whole takes it in any case.
+static int recompute_width(const AttnShape &s) {
+    int hw = 64;
+    while (hw > 16) {
+        const int half = hw / 2;
+        const bool whole = s.H <= half;
+        const bool fits = (long long)s.B * ((s.H + half - 1) / half) <= RC_ROUND && s.Tq > 3 * RC_W;
+        if (!whole && !fits) break;
+        hw = half;
+    }
+    return hw;
+}
+
+template <typename T>
+static hipError_t launch_recompute_w(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
+                                     const float *dS, const float *ds_rowsum, const float *tmap, float *dQp, float *dKp,
+                                     float *dv_part, unsigned long long *dv_flag, unsigned long long epoch, float *dv,
+                                     hipStream_t st) {
+    if (tmap) return launch_recompute_t<T, true, 64>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag, epoch, dv, st);
+    switch (recompute_width(s)) {
+        case 16: return launch_recompute_t<T, false, 16>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag, epoch, dv, st);
+        case 32: return launch_recompute_t<T, false, 32>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag, epoch, dv, st);
+        default: return launch_recompute_t<T, false, 64>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag, epoch, dv, st);
+    }
 }
 
 hipError_t launch_recompute(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
                             const float *dS, const float *ds_rowsum, const float *tmap, float *dQp, float *dKp,
                             float *dv_part, unsigned long long *dv_flag, unsigned long long epoch, float *dv,
                             hipStream_t st) {
-    return s.bf16 ? launch_recompute_t<bf16_t>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag,
+    return s.bf16 ? launch_recompute_w<bf16_t>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag,
                                                epoch, dv, st)
-                  : launch_recompute_t<float>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag,
+                  : launch_recompute_w<float>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag,
                                               epoch, dv, st);
 }
 

@@ -19,6 +19,15 @@ CASES = [
     ("split_one_key", 3, 70, 1, 40, 4, "f32", False),
     ("split_many_ranges", 1, 700, 300, 20, 4, "f32", False),
     ("split_bf16", 2, 37, 261, 100, 8, "bf16", False),
+    # recomputation with slices of 16 columns (four lane groups): rows not a multiple of four, more than one pass of 256
+    # rows; 32 columns: fewer rows than lane groups would like, two passes; the whole of a narrow H in one slice
+    ("slices_of_16", 25, 50, 21, 130, 8, "f32", True),
+    ("slices_of_16_two_passes", 14, 259, 19, 240, 8, "f32", False),
+    ("slices_of_16_bf16", 30, 35, 30, 112, 8, "bf16", False),
+    ("slices_of_32", 34, 45, 9, 470, 8, "f32", True),
+    ("slices_of_32_two_passes", 20, 131, 9, 800, 4, "f32", False),
+    ("slice_of_16_is_the_whole_h", 200, 9, 11, 16, 4, "f32", False),
+    ("slice_of_32_is_the_whole_h", 200, 9, 11, 31, 4, "f32", False),
 ]
 
 
