@@ -78,7 +78,7 @@ typedef enum { ECHO_F32 = 0, ECHO_BF16 = 1 } echo_dtype_t; /* storage of Qp, Kp,
  *   - each per-sample tensor (Tq*H, Tk*H, Tk*Dv, Tq*Dv, Tq*(Tk+16) elements) stays below 2^31 elements and
  *     B*Tq*Tk*H below 2^62;
  *   - for the echo_attn_step_* calls, Tq == 1.
- * H may be any value >= 1: shapes whose H is not a multiple of 4, or whose tile of query rows does not fit
+ * H may be any value >= 1: shapes whose H is below 4, or whose tile of query rows does not fit
  * on-chip memory (H above about 4600), run through separate score / softmax / context kernels. */
 #define ECHO_ATTN_MAX_TK 2048
 #define ECHO_ATTN_STEP_MAX_TK 8192
@@ -97,9 +97,9 @@ typedef struct {
  * descriptor).  Workspace contents need not survive between calls and may start in any state: the only
  * state that persists from forward to backward is P (Section 5.1).
  * The forward pass needs none (0 is returned, and echo_attn_fwd then accepts workspace == NULL) whenever its
- * one-kernel form runs, which keeps the scores on chip: H a multiple of 4, a tile of eight query rows
+ * one-kernel form runs, which keeps the scores on chip, and H is a multiple of 4: a tile of eight query rows
  * within on-chip memory and a sample's V below 2 GiB, i.e. every shape of practical size; otherwise B*Tq*Tk
- * floats for the scores.
+ * floats for the scores (which an H that is no multiple of 4 asks for as well).
  * Exception, decoder steps: for Tq == 1, Tk <= 64, H and Dv multiples of 4 up to 512 and B <= 64 the forward call
  * asks for 4 KB per sample, through which the four blocks that share a sample pass the scores to one another (see
  * echo_attn_fwd). */

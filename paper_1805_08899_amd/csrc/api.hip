@@ -60,7 +60,7 @@ BwdWs bwd_layout(const AttnShape &s) {
 // scores S [B,Tq,Tk] of the unfused forward kernels; the fused kernel keeps them in LDS and needs nothing
 size_t fwd_bytes(const AttnShape &s, bool want_map) {
     if (!want_map && s.Tq == 1 && echo::step_split_mail_bytes(s) > 0) return align_up(echo::step_split_mail_bytes(s));
-    if (!want_map && echo::fwd_fused_supported(s)) return 0;
+    if (!want_map && s.H % 4 == 0 && echo::fwd_fused_supported(s)) return 0;   // (other H: asked for, not used)
     return align_up((size_t)s.B * s.Tq * s.Tk * sizeof(float));
 }
 

@@ -180,6 +180,14 @@ __device__ __forceinline__ float wave_transpose_sum(float (&a)[N]) {
     return a[0];
 }
 
+// The same within groups of G lanes: lane l of a group ends with the sums of values (N / G) l .. in a[0 .. N / G - 1], or, where
+// N < G, of value l / (G / N) in a[0].
+template <int N, int G>
+__device__ __forceinline__ void group_transpose_sum(float (&a)[N]) {
+    static_assert(N >= 1 && N <= 64 && (N & (N - 1)) == 0 && (G == 16 || G == 32 || G == 64), "powers of two");
+    TransposeSumStep<N, G / 2>::run(a, lane_id());
+}
+
 // Barrier for data exchanged through LDS only: waits for this wave's LDS operations, not for its global
 // loads and stores (__syncthreads() would also wait for every prefetch and store in flight).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

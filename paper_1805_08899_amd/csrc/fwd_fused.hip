@@ -3,8 +3,9 @@
 // (Section 2, attention steps 1-2; Section 4.1 scoring function; Section 6.1:
 // one fused kernel instead of many small ones, fewer launches and accesses).
 //
-// Block = (sample b, up to RT = 8 NG query rows), W waves: eight, or four in streaming mode at H <= 512 (four
-// such blocks share a CU and are in different phases of their lives, which keeps the vector units fed).
+// Block = (sample b, up to RT = 8 or 4 query rows), W waves: eight, or four in streaming mode at H <= 512 (four
+// such blocks share a CU and are in different phases of their lives, which keeps the vector units fed).  In streaming mode
+// the lanes may work as 64 / HL groups of HL = 32 or 16 that take different keys (a slice is then 4 HL columns of h).
 //   A  exp(2q) / v of the rows and 1 / v go to LDS (taken once per block).
 //   B  the valid keys are dealt to the waves in W contiguous shares that differ by at most one key;
 //      a wave walks its share in passes of up to four keys.  A lane owns four
@@ -49,14 +50,12 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 
 constexpr int FW_W = 8;          // waves per block in row mode (deal8_begin deals the keys to eight)
-constexpr int FW_W_STREAM = 4;   // waves per block in streaming mode when H <= 512: four blocks per CU instead of
-                                 // two, so that more blocks are in different phases at any time (placement, staging,
-                                 // softmax and context wait on memory; only the score loop fills the vector units)
 constexpr int FW_NJ = 4;         // keys per wave and pass (register tile columns)
-constexpr int FW_SS = 256;       // h per slice: four per lane
+constexpr int FW_ST = 256;       // columns of h staged by one wave-level load: four per lane
 constexpr int FW_XCD = 8;        // blockIdx.x mod 8 selects the XCD
 constexpr int FW_CU_PER_XCD = 32;
 constexpr int FW_KB = 16;        // value rows per batch in the context phase (two batches in flight per wave)
+constexpr int FW_SPREAD_B = 32;        // batches below this may be spread over the XCDs tile by tile
 constexpr int FW_MAX_RANKED_B = 128;   // the in-kernel ranking keeps two lengths per lane
 constexpr int FW_ROW_REGS = 16;  // row mode: 16-byte registers a wave spends on its keys (keys x slices)
 
@@ -70,18 +69,30 @@ __device__ __forceinline__ float comp(const float4 &x, int c) { return c == 0 ? 
 // keys); if the loaded value were taken apart or converted right away, the compiler would merge those pieces with
 // the other branch's zeros inside the branch and wait for every key in turn behind its load: one trip to memory per
 // key instead of one for all.  pin() marks the place from where the value may be used.
+// Loads need no more than the element's own alignment, so that rows of any H take this kernel.
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ float4 ld4_any(const float *p, size_t i) {
+    const f32x4 v = *reinterpret_cast<const f32x4_any *>(p + i);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 ld4_any(const bf16_t *p, size_t i) {
+    const u32x2 v = *reinterpret_cast<const u32x2_any *>(p + i);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
 template <typename T> struct RawKey;
 template <> struct RawKey<float> {
     f32x4 v;
-    __device__ __forceinline__ void load(const float *p, size_t i) { v = *reinterpret_cast<const f32x4 *>(p + i); }
+    __device__ __forceinline__ void load(const float *p, size_t i) { v = *reinterpret_cast<const f32x4_any *>(p + i); }
     __device__ __forceinline__ void zero() { v = f32x4{0.f, 0.f, 0.f, 0.f}; }
     __device__ __forceinline__ void pin() { asm("" : "+v"(v)); }
     __device__ __forceinline__ float4 get() const { return make_float4(v.x, v.y, v.z, v.w); }
 };
 template <> struct RawKey<bf16_t> {
     u32x2 v;
-    __device__ __forceinline__ void load(const bf16_t *p, size_t i) { v = *reinterpret_cast<const u32x2 *>(p + i); }
+    __device__ __forceinline__ void load(const bf16_t *p, size_t i) { v = *reinterpret_cast<const u32x2_any *>(p + i); }
     __device__ __forceinline__ void zero() { v = u32x2{0u, 0u}; }
     __device__ __forceinline__ void pin() { asm("" : "+v"(v)); }
     __device__ __forceinline__ float4 get() const {
@@ -131,13 +142,16 @@ __device__ __forceinline__ void fw_row_keys(const float4 &fq, const float4 &cv, 
 }
 
 // The keys of one wave as a stream of slices: pass p covers keys j0(p) .. j0(p+1), slice s the columns
-// 256 s + 4 lane .. + 3.  `cur` is the slice about to be consumed; once its values have been used advance()
-// issues the loads of the following slice into the same registers, a whole slice of arithmetic ahead of their
+// 4 HL s + 4 (l % HL) .. + 3 of lane l.  HL = 64: all lanes take the same four keys of a pass; HL = 32 or 16: the 64 / HL lane
+// groups take every (64 / HL)th key of the pass.  `cur` is the slice about to be consumed; once its values have been used
+// advance() issues the loads of the following slice into the same registers, a whole slice of arithmetic ahead of their
 // use.  Rows past a pass's last key repeat it.
-template <typename T>
+template <typename T, int HL>
 struct KeyStream {
+    static constexpr int KG = 64 / HL;  // lane groups
+    static constexpr int KP = FW_NJ * KG;   // keys per pass at most
     const T *kb;
-    int H, lane4, k_lo, npass, NS;
+    int H, lane4, grp, k_lo, npass, NS;
     int base, extra;                    // pass p has base + (p < extra) keys
     int p_f, s_f;                       // slice that the next fetch will load
     float4 cur[FW_NJ];
@@ -145,10 +159,11 @@ struct KeyStream {
     __device__ __forceinline__ void init(const T *kb_, int H_, int lane, int k_lo_, int nk, int NS_) {
         kb = kb_;
         H = H_;
-        lane4 = 4 * lane;
+        lane4 = 4 * (lane % HL);
+        grp = lane / HL;
         k_lo = nk > 0 ? k_lo_ : 0;        // a wave without keys loads key 0 (its own first key may be row L)
         NS = NS_;
-        npass = (nk + FW_NJ - 1) / FW_NJ;
+        npass = (nk + KP - 1) / KP;
         const int np = max(npass, 1);
         // the same in all lanes, but the division runs on the vector unit: back to scalar registers, so that
         // everything derived from it (pass bounds, row addresses) is scalar arithmetic
@@ -171,12 +186,16 @@ struct KeyStream {
         const int j0 = pass_begin(pc), j1 = max(pass_begin(pc + 1), j0 + 1);
         // columns past H: the load repeats the row's last four values; exp(2q)/v is 0 and 1/v is kHugeC
         // there, so they add nothing
-        const unsigned hc = (unsigned)min(s_f * FW_SS + lane4, H - 4);
+        const unsigned hc = (unsigned)min(s_f * 4 * HL + lane4, H - 4);
 #pragma unroll
         for (int c = 0; c < FW_NJ; ++c) {
-            // row address from scalars, column from the lane: the load takes them as base and offset
-            const T *row = kb + (size_t)(unsigned)(min(j0 + c, j1 - 1) * H);
-            cur[c] = ld4(row, (size_t)hc);
+            if constexpr (KG == 1) {
+                // row address from scalars, column from the lane: the load takes them as base and offset
+                const T *row = kb + (size_t)(unsigned)(min(j0 + c, j1 - 1) * H);
+                cur[c] = ld4_any(row, (size_t)hc);
+            } else {
+                cur[c] = ld4_any(kb, (size_t)((unsigned)(min(j0 + c * KG + grp, j1 - 1) * H) + hc));
+            }
         }
         const bool wrap = s_f + 1 == NS;
         s_f = wrap ? 0 : s_f + 1;
@@ -186,20 +205,20 @@ struct KeyStream {
     __device__ __forceinline__ void advance() { fetch(); }
 };
 
-// Streaming mode, one pass of one wave: NJ keys starting at column jcol0 of the score tile, all rows of the
-// block, all slices of h, factor path only.  s_e: LDS rows of exp(2q)/v, pitch Hp; s_c: 1/v.  NI > 0: exactly
+// Streaming mode, one pass of one wave: up to NJ keys per lane group, nj in all, starting at column jcol0 of the score tile,
+// all rows of the block, all slices of h, factor path only.  s_e: LDS rows of exp(2q)/v, pitch Hp; s_c: 1/v.  NI > 0: exactly
 // NI rows are live, known at compile time (no per-row branches, the next row's LDS read is issued a row ahead);
 // NI == 0: the first ni.  What is written is the score without its key-independent term: -2 sum_h v r.
 // qe_max, c_max: the block's largest |exp(2q)/v| and |1/v|.  Returns true if the operands may leave the
 // range of the factor path, in which case nothing was written and the caller must redo the pass exactly.
-template <typename T, int NG, int NJ, int NI>
-__device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const float *__restrict__ s_c, int Hp, int ni,
-                                        KeyStream<T> &ks, float qe_max, float c_max, float *__restrict__ s_S,
+template <typename T, int RT, int HL, int NJ, int NI>
+__device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const float *__restrict__ s_c, int Hp, int ni, int nj,
+                                        KeyStream<T, HL> &ks, float qe_max, float c_max, float *__restrict__ s_S,
                                         int spitch, int jcol0) {
-    constexpr int RT = 8 * NG;
     constexpr bool FULL = NI > 0;
     constexpr int NR = FULL ? NI : RT;       // rows the unrolled loops visit
-    const int lane = lane_id();
+    constexpr int SS = 4 * HL;               // columns per slice
+    const int lane = lane_id(), hl = lane % HL;
     float acc[RT][NJ];
 #pragma unroll
     for (int a = 0; a < RT; ++a)
@@ -216,8 +235,8 @@ __device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const flo
             kmax = fmaxf(fmaxf(kmax, fk[0][c]), fmaxf(fk[1][c], fmaxf(fk[2][c], fk[3][c])));
         }
         ks.advance();
-        const float4 cv = *reinterpret_cast<const float4 *>(s_c + s * FW_SS + 4 * lane);
-        const float *e_col = s_e + s * FW_SS + 4 * lane;
+        const float4 cv = *reinterpret_cast<const float4 *>(s_c + s * SS + 4 * hl);
+        const float *e_col = s_e + s * SS + 4 * hl;
         float4 fq_next = *reinterpret_cast<const float4 *>(e_col);
 #pragma unroll
         for (int a = 0; a < NR; ++a) {
@@ -235,20 +254,22 @@ __device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const flo
     }
     // the negation also sends a NaN bound (NaN or infinite operands) to the exact path
     if (__any(!(__builtin_fmaf(qe_max, kmax, c_max) < kPairLimit))) return true;
-    // per lane first, then one transposing reduction for the whole tile
+    // per lane first, then one transposing reduction for the whole tile, within each lane group
     constexpr int NP = RT * NJ;
     constexpr int NPOW = NP <= 8 ? 8 : NP <= 16 ? 16 : NP <= 32 ? 32 : 64;
+    constexpr int PER = NPOW > HL ? NPOW / HL : 1, SHARE = NPOW > HL ? 1 : HL / NPOW;   // sums per lane, lanes per sum
     float flat[NPOW];
 #pragma unroll
     for (int p = 0; p < NPOW; ++p) {
         const int a = p / NJ, c = p % NJ;
         flat[p] = p < NP ? acc[a < RT ? a : 0][c] : 0.f;
     }
-    const float tot = wave_transpose_sum<NPOW>(flat);
-    const int p = lane / (64 / NPOW);
-    if ((lane % (64 / NPOW)) == 0 && p < NP) {
-        const int a = p / NJ, c = p % NJ;
-        if (a < ni) s_S[a * spitch + jcol0 + c] = -2.f * tot;
+    group_transpose_sum<NPOW, HL>(flat);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int p = (hl / SHARE) * PER + k;
+        const int a = p / NJ, j = (p % NJ) * ks.KG + ks.grp;
+        if (hl % SHARE == 0 && p < NP && a < ni && (HL == 64 || j < nj)) s_S[a * spitch + jcol0 + j] = -2.f * flat[k];
     }
     return false;
 }
@@ -310,8 +331,8 @@ __device__ __forceinline__ bool fw_rows(const RawKey<T> (&raw)[NS][NKM], const f
             // operands of the next slice (of the next row after the last slice; the row past the last one
             // repeats it) are requested before this slice is evaluated
             const int a2 = s + 1 < NS ? a : min(a + 1, ni - 1), s2 = s + 1 < NS ? s + 1 : 0;
-            const float4 fq2 = *reinterpret_cast<const float4 *>(e_col + a2 * Hp + s2 * FW_SS);
-            const float4 cv2 = *reinterpret_cast<const float4 *>(c_col + s2 * FW_SS);
+            const float4 fq2 = *reinterpret_cast<const float4 *>(e_col + a2 * Hp + s2 * FW_ST);
+            const float4 cv2 = *reinterpret_cast<const float4 *>(c_col + s2 * FW_ST);
             if constexpr (NK <= 4) {
                 fw_row_keys<NK>(fq, cv, fk[s], acc);
             } else {                         // groups of two keys so that the temporaries stay few
@@ -744,18 +765,22 @@ __device__ __forceinline__ bool fw_pick_item(const int *__restrict__ key_len, in
         L = clamp_len(key_len[b], Tk);
         return true;
     }
-    // samples of this XCD: ranks 16 g + xcd and 16 g + 15 - xcd (snake over the XCDs), heaviest first
+    // samples of this XCD: ranks 16 g + xcd and 16 g + 15 - xcd (snake over the XCDs), heaviest first; spread over the
+    // whole chip (ranked == 2): all samples, and the block number is the position in the launch order
+    const bool spread = ranked == 2;
     const int rem = B % (2 * FW_XCD);
     const int M = 2 * (B / (2 * FW_XCD)) + (xcd < rem ? 1 : 0) + (2 * FW_XCD - 1 - xcd < rem ? 1 : 0);
-    const int n = M * tiles;               // tiles of this XCD
-    if (li >= n) return false;
+    const int pos = spread ? (int)blockIdx.x : li;
+    const int n = (spread ? B : M) * tiles;        // tiles of this XCD (of the launch)
+    const int cus = spread ? FW_XCD * FW_CU_PER_XCD : FW_CU_PER_XCD;
+    if (pos >= n) return false;
     // position in the launch order -> position in "heaviest first" order
-    int rho = li;
-    if (n > FW_CU_PER_XCD && n <= 2 * FW_CU_PER_XCD) {
-        const int singles = 2 * FW_CU_PER_XCD - n;             // CUs that get one block: the heaviest tiles
-        if (li >= FW_CU_PER_XCD) rho = n - 1 - (li - FW_CU_PER_XCD);
-        else if (li >= FW_CU_PER_XCD - singles) rho = li - (FW_CU_PER_XCD - singles);
-        else rho = singles + li;
+    int rho = pos;
+    if (n > cus && n <= 2 * cus) {
+        const int singles = 2 * cus - n;                       // CUs that get one block: the heaviest tiles
+        if (pos >= cus) rho = n - 1 - (pos - cus);
+        else if (pos >= cus - singles) rho = pos - (cus - singles);
+        else rho = singles + pos;
     }
     const int m = rho / tiles;             // the tiles of a sample weigh the same
     tile = rho % tiles;
@@ -769,7 +794,8 @@ __device__ __forceinline__ bool fw_pick_item(const int *__restrict__ key_len, in
         const unsigned key0 = c0 < B ? ((unsigned)clamp_len(len0, Tk) << 7) | (unsigned)(127 - c0) : 0u;
         const unsigned key1 = c1 < B ? ((unsigned)clamp_len(len1, Tk) << 7) | (unsigned)(127 - c1) : 0u;
         unsigned long long act0 = __ballot(c0 < B), act1 = __ballot(c1 < B);
-        int r = (m / 2) * (2 * FW_XCD) + ((m & 1) ? 2 * FW_XCD - 1 - xcd : xcd);   // keys larger than the wanted one
+        // keys larger than the wanted one
+        int r = spread ? m : (m / 2) * (2 * FW_XCD) + ((m & 1) ? 2 * FW_XCD - 1 - xcd : xcd);
         const int top = 7 + 32 - __builtin_clz((unsigned)Tk);                        // bits in use
         for (int bit = top - 1; bit >= 0; --bit) {
             const unsigned long long m0 = __ballot((key0 >> bit) & 1u) & act0;
@@ -803,14 +829,14 @@ template <int W> __device__ __forceinline__ int deal_begin(int n, int w) {
     else return (int)((unsigned)(n * w) / (unsigned)W);
 }
 
-template <typename T, int NG, int ROWNS, int W>
-__global__ __launch_bounds__(64 * W, NG == 1 ? 4 : 2) void k_fwd_fused(
+template <typename T, int RT, int HL, int ROWNS, int W>
+__global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ V, const T *__restrict__ v,
     const int *__restrict__ key_len, float *__restrict__ C, float *__restrict__ P,
     int B, int Tq, int Tk, int H, int Dv, int tiles, int rows_base, int Hp, int spitch, int ranked) {
-    constexpr int RT = 8 * NG;
     constexpr int FW_THREADS = 64 * W;
-    constexpr int NB = 32 / W;                                 // 16-byte pieces per thread and staging batch
+    static_assert(ROWNS == 0 || HL == 64, "row mode: all lanes along h");
+    constexpr int NB = ROWNS == 1 ? 1 : ROWNS == 2 ? 2 : 4;   // query rows per wave and staging batch
     constexpr bool ROWMODE = ROWNS > 0;                       // ROWNS: slices of h in row mode, 0 = streaming mode
     constexpr int NKM = fw_row_max_keys(ROWNS);
     extern __shared__ __align__(16) float smem[];
@@ -826,33 +852,28 @@ __global__ __launch_bounds__(64 * W, NG == 1 ? 4 : 2) void k_fwd_fused(
     // no issue slots while its neighbour is in the score loop.
     __builtin_amdgcn_s_setprio(3);
 
-    // v does not depend on the placement: the first batch of its loads leaves before the key counts are read
-    // (in wave 0, which reads the key counts and must not queue them behind anything, right after that)
-    // The row tile as pieces of 64 lanes x 16 bytes: piece m is slice m % ns of row m / ns; wave w takes pieces
-    // w, w + W, ...  The piece numbers are the same in all lanes, and m * ceil(2^16 / ns) >> 16 = m / ns as long as
-    // m ns < 2^16, so that rows and columns cost scalar multiplications (a division per piece, which is what
-    // `e / q4` on the thread's element number compiled to, was most of the instructions of this phase).
-    const int ns = Hp / FW_SS, n_pc = RT * ns;
-    const int ns_inv = __builtin_amdgcn_readfirstlane((65536 + ns - 1) / ns);
-    auto piece_row = [&](int m) { return (m * ns_inv) >> 16; };
-    auto piece_col = [&](int m, int a) { return (m - a * ns) * FW_SS + 4 * lane; };
-    // (v and the query rows stay as loaded until the staging loop: see RawKey)
-    RawKey<T> vv[NB];
-    auto load_v = [&]() {
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int m = w + u * W;
-            const int h = piece_col(m, piece_row(m));
-            if (m < n_pc && h < H) vv[u].load(v, (size_t)h);
-            else vv[u].zero();
-        }
+    // The row tile is staged in slices of 256 columns (64 lanes x 16 bytes).  Wave w takes slice w mod ns2 (and every ns2-th
+    // after it) of the rows w / ns2, + W / ns2, ..., where ns2 is the number of slices rounded up to a power of two, at most
+    // W: a wave then stays on its columns, so that v and 1 / v are loaded and formed once for all of its rows.
+    const int ns = ROWMODE ? ROWNS : (Hp + FW_ST - 1) / FW_ST;
+    constexpr int LG_W = W == 8 ? 3 : 2;
+    const int lg = ROWMODE ? (ROWNS == 4 ? 2 : ROWNS - 1) : min(ns <= 1 ? 0 : 32 - __builtin_clz((unsigned)(ns - 1)), LG_W);
+    const int ns2 = 1 << lg, w_row = w >> lg, row_step = W >> lg;
+    const int st_col = (w & (ns2 - 1)) * FW_ST + 4 * lane;    // first column of this lane's first slice
+    // v does not depend on the placement: its load leaves before the key counts are read (in wave 0, which reads the key
+    // counts and must not queue them behind anything, right after that).  Groups of four columns that reach past H are
+    // loaded as the row's last four; v and the query rows stay as loaded until the staging loop: see RawKey.
+    RawKey<T> vv;
+    auto load_v = [&](int h) {
+        if (h < H) vv.load(v, (size_t)min(h, H - 4));
+        else vv.zero();
     };
-    if (w != 0) load_v();
+    if (w != 0) load_v(st_col);
 
     __shared__ int s_pick[2];
     int b, tile, L;
     if (!fw_pick_item(key_len, B, Tk, tiles, ranked, s_pick, b, tile, L)) return;
-    if (w == 0) load_v();
+    if (w == 0) load_v(st_col);
     b = __builtin_amdgcn_readfirstlane(b);
     tile = __builtin_amdgcn_readfirstlane(tile);
     L = __builtin_amdgcn_readfirstlane(L);
@@ -876,16 +897,18 @@ __global__ __launch_bounds__(64 * W, NG == 1 ? 4 : 2) void k_fwd_fused(
     const T *qb = Qp + ((size_t)b * Tq + r0) * H;
     const T *kb = Kp + (size_t)b * Tk * H;
     RawKey<T> x[NB];
+    auto load_x = [&](int h, int u0) {
 #pragma unroll
-    for (int u = 0; u < NB; ++u) {
-        const int m = w + u * W;
-        const int a = piece_row(m), h = piece_col(m, a);
-        if (m < n_pc && h < H && a < ni) x[u].load(qb + (size_t)a * H, (size_t)h);
-        else x[u].zero();
-    }
+        for (int u = 0; u < NB; ++u) {
+            const int a = w_row + row_step * (u0 + u);
+            if (h < H && a < ni) x[u].load(qb + (size_t)a * H, (size_t)min(h, H - 4));
+            else x[u].zero();
+        }
+    };
+    load_x(st_col, 0);
     const int k_lo = deal_begin<W>(L, w);
     const int nk = deal_begin<W>(L, w + 1) - k_lo;
-    KeyStream<T> ks;
+    KeyStream<T, HL> ks;
     RawKey<T> raw[ROWMODE ? ROWNS : 1][NKM];
     if constexpr (ROWMODE) {
         // only the wave's own keys are requested (every load takes its turn in the CU's address unit whether
@@ -895,7 +918,7 @@ __global__ __launch_bounds__(64 * W, NG == 1 ? 4 : 2) void k_fwd_fused(
             if (c < nk) {
 #pragma unroll
                 for (int s = 0; s < ROWNS; ++s) {
-                    const int hc = min(s * FW_SS + 4 * lane, H - 4);   // columns past H: see KeyStream::fetch
+                    const int hc = min(s * FW_ST + 4 * lane, H - 4);   // columns past H: see KeyStream::fetch
                     raw[s][c].load(kb, (size_t)(unsigned)((k_lo + c) * H + hc));
                 }
             } else {
@@ -904,53 +927,58 @@ __global__ __launch_bounds__(64 * W, NG == 1 ? 4 : 2) void k_fwd_fused(
             }
         }
     } else {
-        ks.init(kb, H, lane, k_lo, nk, Hp / FW_SS);
+        ks.init(kb, H, lane, k_lo, nk, Hp / (4 * HL));
         ks.start();
     }
 
-    float qe_m = 0.f, c_m = 0.f;
-    for (int m0 = w; m0 < n_pc; m0 += NB * W) {
-        if (m0 != w) {                                         // later batches (H > 1024): loaded here
+    float c_m = 0.f;
+    unsigned qe_bits = 0;                                      // largest |exp(2q) / v|, as its bits (NaN above all numbers)
+    const bool tail = (H & 3) != 0;
+    for (int s = w & (ns2 - 1), h = st_col; s < ns; s += ns2, h += ns2 * FW_ST) {
+        if (s >= ns2) load_v(h);
+        float cc[4], cy[4];                                    // 1 / v, and the same with 0 where v counts as zero
+        vv.pin();
+        {
+            const float4 v4 = vv.get();
 #pragma unroll
-            for (int u = 0; u < NB; ++u) {
-                const int m = m0 + u * W;
-                const int a = piece_row(m), h = piece_col(m, a);
-                const bool in = m < n_pc && h < H;
-                if (in && a < ni) x[u].load(qb + (size_t)a * H, (size_t)h);
-                else x[u].zero();
-                if (in) vv[u].load(v, (size_t)h);
-                else vv[u].zero();
+            for (int q = 0; q < 4; ++q) {
+                float vq = comp(v4, q);
+                // a last group of fewer than four columns holds the row's last four: those of the group before it count
+                // here as zero
+                if (tail && min(h, H - 4) + q < h) vq = 0.f;
+                const bool v_on = fabsf(vq) >= kTinyV;         // false for columns past H (v read as 0)
+                cc[q] = v_on ? fast_rcp(vq) : kHugeC;
+                cy[q] = v_on ? cc[q] : 0.f;
+                // a |v| so large that products of two 1/v could underflow also goes to the exact path
+                c_m = fmaxf(c_m, !(fabsf(vq) <= 1e15f) ? INFINITY : fabsf(cc[q]));
             }
         }
+        const bool st_on = HL == 64 || h < Hp;                 // (a slice narrower than the load)
+        if (w_row == 0 && st_on) *reinterpret_cast<float4 *>(s_c + h) = make_float4(cc[0], cc[1], cc[2], cc[3]);
+        for (int u0 = 0; w_row + row_step * u0 < RT; u0 += NB) {
+            if (u0 > 0 || s >= ns2) load_x(h, u0);
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            x[u].pin();
-            vv[u].pin();
-        }
+            for (int u = 0; u < NB; ++u) x[u].pin();
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int m = m0 + u * W;
-            if (m < n_pc) {
-                const int a = piece_row(m), h = piece_col(m, a);
-                const bool row_on = a < ni;
-                const float4 x4 = x[u].get(), v4 = vv[u].get();
-                float y[4], cc[4];
+            for (int u = 0; u < NB; ++u) {
+                const int a = w_row + row_step * (u0 + u);
+                if (a < RT) {
+                    const float4 x4 = x[u].get();
+                    float y[4] = {0.f, 0.f, 0.f, 0.f};
+                    if (a < ni) {                              // rows past ni: zeros
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float vq = comp(v4, q);
-                    const bool v_on = fabsf(vq) >= kTinyV;         // false for columns past H (v read as 0)
-                    cc[q] = v_on ? fast_rcp(vq) : kHugeC;
-                    y[q] = (v_on && row_on) ? fast_exp2(kTwoLog2e * comp(x4, q)) * cc[q] : 0.f;
-                    qe_m = fmaxf(qe_m, fabsf(y[q]));
-                    // a |v| so large that products of two 1/v could underflow also goes to the exact path
-                    c_m = fmaxf(c_m, fabsf(vq) > 1e15f ? INFINITY : fabsf(cc[q]));
-                    if (y[q] != y[q]) qe_m = INFINITY;              // NaN input: exact path (fmaxf drops NaN)
+                        for (int q = 0; q < 4; ++q) {
+                            y[q] = fast_exp2(kTwoLog2e * comp(x4, q)) * cy[q];
+                            qe_bits = max(qe_bits, __float_as_uint(fabsf(y[q])));
+                        }
+                    }
+                    if (st_on) *reinterpret_cast<float4 *>(s_e + a * Hp + h) = make_float4(y[0], y[1], y[2], y[3]);
                 }
-                *reinterpret_cast<float4 *>(s_e + a * Hp + h) = make_float4(y[0], y[1], y[2], y[3]);
-                if (a == 0) *reinterpret_cast<float4 *>(s_c + h) = make_float4(cc[0], cc[1], cc[2], cc[3]);
             }
         }
     }
+    // a NaN (NaN input, or an infinite exponential times a zero) goes to the exact path, like infinity
+    float qe_m = __uint_as_float(min(qe_bits, 0x7f800000u));
     qe_m = wave_max(qe_m);
     c_m = wave_max(c_m);
     if (lane == 0) {
@@ -978,15 +1006,15 @@ __global__ __launch_bounds__(64 * W, NG == 1 ? 4 : 2) void k_fwd_fused(
     } else {
         for (int p = 0; p < ks.npass; ++p) {                   // passes of up to FW_NJ keys
             const int j0 = ks.pass_begin(p);
-            const int nj = ks.pass_begin(p + 1) - j0;          // 1..FW_NJ
+            const int nj = ks.pass_begin(p + 1) - j0;          // 1..ks.KP
             bool redo = true;
-#define FW_CASE(N)                                                                                          \
-    case N:                                                                                                 \
-        redo = (ni == RT)       ? fw_pass<T, NG, N, RT>(s_e, s_c, Hp, ni, ks, qe_max, c_max, s_S, spitch, j0)     \
-               : (ni == RT - 1) ? fw_pass<T, NG, N, RT - 1>(s_e, s_c, Hp, ni, ks, qe_max, c_max, s_S, spitch, j0) \
-                                : fw_pass<T, NG, N, 0>(s_e, s_c, Hp, ni, ks, qe_max, c_max, s_S, spitch, j0);     \
+#define FW_CASE(N)                                                                                                   \
+    case N:                                                                                                          \
+        redo = (ni == RT)       ? fw_pass<T, RT, HL, N, RT>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0)     \
+               : (ni == RT - 1) ? fw_pass<T, RT, HL, N, RT - 1>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0) \
+                                : fw_pass<T, RT, HL, N, 0>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0);     \
         break;
-            switch (nj) {
+            switch ((nj + ks.KG - 1) / ks.KG) {
                 FW_CASE(1) FW_CASE(2) FW_CASE(3) FW_CASE(4)
                 default: break;
             }
@@ -1057,75 +1085,95 @@ __global__ __launch_bounds__(64 * W, NG == 1 ? 4 : 2) void k_fwd_fused(
 }
 
 
-// Rows per block: 8.  (16 rows halve the exponentials of K per score, but need twice the accumulators; with
+// Rows per block: up to 8.  (16 rows halve the exponentials of K per score, but need twice the accumulators; with
 // two waves per SIMD instead of four that measured 20-25 % slower on the large workloads.)
 
-static size_t fwd_lds_bytes(const AttnShape &s, int ng) {
-    const int Hp = (s.H + FW_SS - 1) / FW_SS * FW_SS;
+static int fwd_h_pad(int H, int hl) { return (H + 4 * hl - 1) / (4 * hl) * (4 * hl); }
+static size_t fwd_lds_bytes(const AttnShape &s, int rt, int hl) {
+    const int Hp = fwd_h_pad(s.H, hl);
     const int spitch = ((s.Tk + 3) & ~3) + 4;
-    return ((size_t)(8 * ng) * (Hp + spitch) + Hp) * sizeof(float);
+    return ((size_t)rt * (Hp + spitch) + Hp) * sizeof(float);
 }
 
 bool fwd_fused_supported(const AttnShape &s) {
     // the context phase addresses a sample's value rows by 32-bit byte offsets (BufferRows)
     const bool v_in_range = (long long)s.Tk * s.Dv * (s.bf16 ? 2 : 4) < (1LL << 31);
-    return s.H % 4 == 0 && fwd_lds_bytes(s, 1) <= 150 * 1024 && v_in_range;
+    return s.H >= 4 && fwd_lds_bytes(s, 8, 64) <= 150 * 1024 && v_in_range;
 }
 
 // Row mode needs the longest key share of a wave, ceil(Tk / 8) keys, times the slices of h to fit the
 // registers set aside for it; it is built for 1, 2 and 4 slices (H up to 256, 512, 1024).
 static int fwd_row_mode_slices(const AttnShape &s) {
-    const int ns = (s.H + FW_SS - 1) / FW_SS;
+    const int ns = (s.H + FW_ST - 1) / FW_ST;
     if (ns != 1 && ns != 2 && ns != 4) return 0;
     return (s.Tk + FW_W - 1) / FW_W <= fw_row_max_keys(ns) ? ns : 0;
 }
 
-template <typename T, int NG, int ROWNS, int W>
+template <typename T, int RT, int HL, int ROWNS, int W>
 static hipError_t launch_fwd_fused_t(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,
                                      const int *key_len, float *C, float *P, hipStream_t st) {
-    constexpr int RT = 8 * NG;
-    const int Hp = (s.H + FW_SS - 1) / FW_SS * FW_SS;
+    const int Hp = fwd_h_pad(s.H, HL);
     const int spitch = ((s.Tk + 3) & ~3) + 4;
-    const size_t lds = fwd_lds_bytes(s, NG);
+    const size_t lds = fwd_lds_bytes(s, RT, HL);
     if (lds > 48 * 1024) {   // beyond the default dynamic LDS limit
         static LdsGrants granted;
-        hipError_t e = ensure_dynamic_lds((const void *)k_fwd_fused<T, NG, ROWNS, W>, lds, granted);
+        hipError_t e = ensure_dynamic_lds((const void *)k_fwd_fused<T, RT, HL, ROWNS, W>, lds, granted);
         if (e != hipSuccess) return e;
     }
-    int tiles = (s.Tq + RT - 1) / RT;
     const int samples_per_xcd = (s.B + FW_XCD - 1) / FW_XCD;
+    int tiles = (s.Tq + RT - 1) / RT;
     // Row mode with less than one round of blocks (two per CU): more, smaller row tiles while the grid still fits
     // the round, so that every CU holds a heavy and a light tile (with 448 blocks 64 CUs held a single heavy one and
     // the fullest CU 18 % more keys than the average; with 512 it is 5 %; the keys are exponentiated once more per sample).
     // At most twice the tiles (at least RT / 2 rows each).
     // (Streaming mode loses with smaller tiles: 74 -> 82 us at B = 128, T = 100, where whole rounds were filled that way.)
-    if (ROWNS > 0 && W == FW_W) {
+    if (ROWNS > 0) {
         const int most = min(s.Tq, 2 * tiles);
         while (tiles < most && (long long)FW_XCD * samples_per_xcd * (tiles + 1) <= 2 * FW_XCD * FW_CU_PER_XCD) ++tiles;
     }
-    const long long grid = (long long)FW_XCD * samples_per_xcd * tiles;
-    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     const int ranked = s.B <= FW_MAX_RANKED_B ? 1 : 0;
-    k_fwd_fused<T, NG, ROWNS, W><<<(unsigned)grid, 64 * W, lds, st>>>(
+    // A small batch spread over all XCDs, tile by tile, once an XCD would get more than a tile per CU: whole samples to XCDs
+    // leave XCDs idle or unequal (B = 8 of 100 to 300 keys: 88 -> 66 us; B = 20: 26 -> 23).  The price, every XCD reading
+    // every key and value row, grows with the batch; at B = 32 the two are level.
+    const int spread = ranked && s.B < FW_SPREAD_B && samples_per_xcd * tiles > FW_CU_PER_XCD ? 1 : 0;
+    const long long grid = spread ? (long long)s.B * tiles : (long long)FW_XCD * samples_per_xcd * tiles;
+    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    k_fwd_fused<T, RT, HL, ROWNS, W><<<(unsigned)grid, 64 * W, lds, st>>>(
         (const T *)Qp, (const T *)Kp, (const T *)V, (const T *)v, key_len, C, P, s.B, s.Tq, s.Tk, s.H, s.Dv, tiles,
-        s.Tq / tiles, Hp, spitch, ranked);
+        s.Tq / tiles, Hp, spitch, ranked + spread);
     return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, const void *Kp, const void *V,
                                         const void *v, const int *key_len, float *C, float *P, hipStream_t st) {
-    switch (fwd_row_mode_slices(s)) {
-        case 1: return launch_fwd_fused_t<T, 1, 1, FW_W>(s, Qp, Kp, V, v, key_len, C, P, st);
-        case 2: return launch_fwd_fused_t<T, 1, 2, FW_W>(s, Qp, Kp, V, v, key_len, C, P, st);
-        case 4: return launch_fwd_fused_t<T, 1, 4, FW_W>(s, Qp, Kp, V, v, key_len, C, P, st);
-        default: break;
+    const long long n8 = (long long)s.B * ((s.Tq + 7) / 8), n4 = (long long)s.B * ((s.Tq + 3) / 4);   // blocks of 8 and 4 rows
+    // Row mode: all lanes along h, so a last slice that H fills badly leaves lanes idle; on a small grid, where latency and
+    // not arithmetic decides, it is still the fastest (B = 128, T = 60, H = 64: 23.4 us against 14.6 in narrow slices;
+    // B = 1, T = 53, H = 48: 7.2 against 7.6).
+    const int row_ns = fwd_row_mode_slices(s);
+    if (row_ns > 0 && (5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
+        switch (row_ns) {
+            case 1: return launch_fwd_fused_t<T, 8, 64, 1, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+            case 2: return launch_fwd_fused_t<T, 8, 64, 2, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+            default: return launch_fwd_fused_t<T, 8, 64, 4, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+        }
     }
-    // Streaming mode.  Up to two slices of h (H <= 512): blocks of four waves, four of them on a CU (measured 9 %
-    // faster at B = 128, T = 100, H = 512); beyond that the row tile's LDS allows only three such blocks and the
-    // eight-wave block, two per CU, keeps more waves resident (four-wave blocks measured 2 % slower at H = 1024).
-    if (s.H <= 2 * FW_SS) return launch_fwd_fused_t<T, 1, 0, FW_W_STREAM>(s, Qp, Kp, V, v, key_len, C, P, st);
-    return launch_fwd_fused_t<T, 1, 0, FW_W>(s, Qp, Kp, V, v, key_len, C, P, st);
+    // Streaming mode on a grid that blocks of eight rows do not fill: blocks of four rows, of eight waves (two blocks on a CU)
+    // while there is hardly more than one for a CU, else of four waves (four blocks on a CU).
+    // B = 4, T = 300, H = 1024: 172 -> 71 us; B = 37, T = 61 / 83, H = 300: 28.8 -> 18.6; B = 16, T = 100, H = 512: 31 -> 21.
+    if (n4 <= 300) return launch_fwd_fused_t<T, 4, 16, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+    if (n4 <= (s.H > 512 ? 512 : 800)) return launch_fwd_fused_t<T, 4, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    // Full grids, up to H = 512: blocks of four waves, four of them on a CU (9 % faster than eight-wave blocks at B = 128,
+    // T = 100, H = 512); beyond that the row tile's LDS allows only three such blocks and the eight-wave block, two per CU,
+    // keeps more waves resident (four-wave blocks measured 2 % slower at H = 1024).  Slices of 128 columns, two lane groups:
+    // a pass takes eight keys, and its reduction and addressing are shared by twice as many (81 -> 77 us at that shape);
+    // slices of 64 where H fills them better (B = 23, T = 217 / 286, H = 40: 79 -> 35 us).
+    if (s.H <= 512) {
+        if (12 * fwd_h_pad(s.H, 16) <= 11 * fwd_h_pad(s.H, 32)) return launch_fwd_fused_t<T, 8, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+        return launch_fwd_fused_t<T, 8, 32, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    }
+    return launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
 }
 
 hipError_t launch_fwd_fused(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,

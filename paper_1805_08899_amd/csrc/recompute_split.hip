@@ -397,9 +397,11 @@ static RsPlan rs_plan(const AttnShape &s) {
 
 // Taken while recompute.hip's narrowest slices would leave a quarter of the compute units without a block (measured: at 192
 // blocks the two forms meet, 10.7 against 11.6 us at B = 16, T = 40, H = 181; below it this one is ahead by up to 4 times,
-// 53 -> 13 us at B = 3, T = 200, H = 76; above it evaluating every tanh twice loses).
+// 53 -> 13 us at B = 3, T = 200, H = 76; above it evaluating every tanh twice loses).  Samples of hardly more than a key tile
+// and a row per wave stay with the other form, which is then done before this one has exchanged its parts of dv (7.4
+// against 9.5 us at B = 50, T = 9 / 15).
 size_t recompute_split_mail_bytes(const AttnShape &s) {
-    if ((long long)s.B * ((s.H + 15) / 16) > RS_MOST_BLOCKS) return 0;
+    if ((long long)s.B * ((s.H + 15) / 16) > RS_MOST_BLOCKS || (long long)s.Tq * s.Tk <= 150) return 0;
     const RsPlan p = rs_plan(s);
     const size_t slots = (size_t)s.B * p.ka.groups * s.H;
     return slots <= RS_MOST_SLOTS ? slots * sizeof(MailSlot) : 0;

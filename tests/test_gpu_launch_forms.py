@@ -28,6 +28,22 @@ CASES = [
     ("slices_of_32_two_passes", 20, 131, 9, 800, 4, "f32", False),
     ("slice_of_16_is_the_whole_h", 200, 9, 11, 16, 4, "f32", False),
     ("slice_of_32_is_the_whole_h", 200, 9, 11, 31, 4, "f32", False),
+    # forward: blocks of four rows (eight waves, four waves), of eight rows with slices of 64 and 128 columns; a small batch
+    # spread over the XCDs; H that is no multiple of four (tails of one to three columns, in both storage types), H of a
+    # single group of four and just past it
+    ("forward_four_rows_eight_waves", 3, 45, 70, 90, 8, "f32", True),
+    ("forward_four_rows_four_waves", 41, 30, 66, 75, 4, "f32", True),
+    ("forward_four_rows_bf16", 41, 30, 66, 131, 4, "bf16", False),
+    ("forward_slices_of_64", 110, 30, 66, 41, 4, "f32", True),
+    ("forward_slices_of_128", 110, 29, 66, 102, 4, "f32", True),
+    ("forward_slices_of_128_bf16", 110, 31, 70, 103, 4, "bf16", False),
+    ("forward_spread_small_batch", 9, 150, 67, 36, 8, "f32", False),
+    ("forward_row_mode_odd_h", 3, 21, 20, 250, 8, "f32", True),
+    ("forward_row_mode_odd_h_bf16", 3, 21, 20, 511, 8, "bf16", False),
+    ("forward_eight_waves_odd_h", 70, 61, 66, 777, 4, "f32", False),
+    ("forward_h_4", 2, 9, 13, 4, 4, "f32", False),
+    ("forward_h_5", 2, 9, 13, 5, 4, "f32", False),
+    ("forward_h_7_bf16", 2, 9, 70, 7, 4, "bf16", False),
 ]
 
 
