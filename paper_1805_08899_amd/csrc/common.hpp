@@ -44,6 +44,52 @@ template <> struct RawElem<bf16_t> {
     static __device__ __forceinline__ float value(type r) { return __uint_as_float(r << 16); }
 };
 
+// Four consecutive elements of a row exactly as they were loaded: one 16- or 8-byte register group that stays
+// whole from the load to pin().  The forward's row mode, for one, loads its keys under uniform branches (a wave requests only its own
+// keys); if the loaded value were taken apart or converted right away, the compiler would merge those pieces with
+// the other branch's zeros inside the branch and wait for every key in turn behind its load: one trip to memory per
+// key instead of one for all.  pin() marks the place from where the value may be used.
+// Loads need no more than the element's own alignment, so that rows of any H take the same kernels.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ float4 ld4_any(const float *p, size_t i) {
+    const f32x4 v = *reinterpret_cast<const f32x4_any *>(p + i);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 ld4_any(const bf16_t *p, size_t i) {
+    const u32x2 v = *reinterpret_cast<const u32x2_any *>(p + i);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
+template <typename T> struct RawKey;
+template <> struct RawKey<float> {
+    f32x4 v;
+    __device__ __forceinline__ void load(const float *p, size_t i) { v = *reinterpret_cast<const f32x4_any *>(p + i); }
+    // the first n elements (any n), zeros behind them
+    __device__ __forceinline__ void load_some(const float *p, int n) {
+        v = f32x4{n > 0 ? p[0] : 0.f, n > 1 ? p[1] : 0.f, n > 2 ? p[2] : 0.f, n > 3 ? p[3] : 0.f};
+    }
+    __device__ __forceinline__ void zero() { v = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    __device__ __forceinline__ void pin() { asm("" : "+v"(v)); }
+    __device__ __forceinline__ float4 get() const { return make_float4(v.x, v.y, v.z, v.w); }
+};
+template <> struct RawKey<bf16_t> {
+    u32x2 v;
+    __device__ __forceinline__ void load(const bf16_t *p, size_t i) { v = *reinterpret_cast<const u32x2_any *>(p + i); }
+    __device__ __forceinline__ void load_some(const bf16_t *p, int n) {
+        v = u32x2{(n > 0 ? (unsigned)p[0].bits : 0u) | (n > 1 ? (unsigned)p[1].bits << 16 : 0u),
+                  (n > 2 ? (unsigned)p[2].bits : 0u) | (n > 3 ? (unsigned)p[3].bits << 16 : 0u)};
+    }
+    __device__ __forceinline__ void zero() { v = u32x2{0u, 0u}; }
+    __device__ __forceinline__ void pin() { asm("" : "+v"(v)); }
+    __device__ __forceinline__ float4 get() const {
+        return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
+                           __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+    }
+};
+
 // Non-temporal loads, for inputs read once by the whole grid.  Measured: they help the LSTM block (nine input and
 // output streams at once, 180 -> 170 us) and hurt a single-stream copy (76 -> 93 us), so only the former uses them
 // (in the recompute kernel they cost 1 to 8 %).

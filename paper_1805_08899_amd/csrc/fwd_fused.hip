@@ -46,9 +46,6 @@
 
 namespace echo {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-
 constexpr int FW_W = 8;          // waves per block in row mode (deal8_begin deals the keys to eight)
 constexpr int FW_NJ = 4;         // keys per wave and pass (register tile columns)
 constexpr int FW_ST = 256;       // columns of h staged by one wave-level load: four per lane
@@ -63,43 +60,6 @@ constexpr int FW_ROW_REGS = 16;  // row mode: 16-byte registers a wave spends on
 constexpr int fw_row_max_keys(int ns) { return ns <= 0 ? 1 : (FW_ROW_REGS / ns > 8 ? 8 : FW_ROW_REGS / ns); }
 
 __device__ __forceinline__ float comp(const float4 &x, int c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; }
-
-// Four consecutive elements of a key row exactly as they were loaded: one 16- or 8-byte register group that stays
-// whole from the load to pin().  Row mode loads its keys under uniform branches (a wave requests only its own
-// keys); if the loaded value were taken apart or converted right away, the compiler would merge those pieces with
-// the other branch's zeros inside the branch and wait for every key in turn behind its load: one trip to memory per
-// key instead of one for all.  pin() marks the place from where the value may be used.
-// Loads need no more than the element's own alignment, so that rows of any H take this kernel.
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef unsigned u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
-__device__ __forceinline__ float4 ld4_any(const float *p, size_t i) {
-    const f32x4 v = *reinterpret_cast<const f32x4_any *>(p + i);
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ float4 ld4_any(const bf16_t *p, size_t i) {
-    const u32x2 v = *reinterpret_cast<const u32x2_any *>(p + i);
-    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
-                       __uint_as_float(v.y & 0xffff0000u));
-}
-template <typename T> struct RawKey;
-template <> struct RawKey<float> {
-    f32x4 v;
-    __device__ __forceinline__ void load(const float *p, size_t i) { v = *reinterpret_cast<const f32x4_any *>(p + i); }
-    __device__ __forceinline__ void zero() { v = f32x4{0.f, 0.f, 0.f, 0.f}; }
-    __device__ __forceinline__ void pin() { asm("" : "+v"(v)); }
-    __device__ __forceinline__ float4 get() const { return make_float4(v.x, v.y, v.z, v.w); }
-};
-template <> struct RawKey<bf16_t> {
-    u32x2 v;
-    __device__ __forceinline__ void load(const bf16_t *p, size_t i) { v = *reinterpret_cast<const u32x2_any *>(p + i); }
-    __device__ __forceinline__ void zero() { v = u32x2{0u, 0u}; }
-    __device__ __forceinline__ void pin() { asm("" : "+v"(v)); }
-    __device__ __forceinline__ float4 get() const {
-        return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u),
-                           __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
-    }
-};
 
 // Pairs of reciprocals share one division (see B at the top): the product a0 a1 must stay finite.
 // |a| <= max|1/v| + max|exp(2q)/v| max exp(2k); a pass is evaluated by the factor path only while this

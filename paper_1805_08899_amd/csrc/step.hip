@@ -26,17 +26,11 @@ constexpr int ST_KB = 4;                  // keys per wave and batch: a batch of
 // keys 32 n + 4 w .. + 3 of every batch n; the first batch's K, old dKp and old dV are requested before dP is
 // formed.  dP is formed by every h slice of a sample for itself (a few ten thousand multiply-adds, V comes from
 // the L2 that the slices of a sample share).
-//
-// DEFER: the key-side sums are left to one batched call at the end of the sentence.  The step then only reads: it
-// writes dQp, and the block of the first h slice writes the step's row of dS (row `ds_row` of the sample's
-// `ds_rows` rows of `ds_pitch` floats, zeros at masked keys and pads) and its sum; dKp, dV and dv_part are not
-// touched.
-template <typename T, bool DEFER>
+template <typename T>
 __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
     const float *__restrict__ dC, const float *__restrict__ P, const T *__restrict__ Qp, const T *__restrict__ Kp,
     const T *__restrict__ V, const T *__restrict__ v, const int *__restrict__ key_len, float *__restrict__ dQp,
-    float *__restrict__ dKp, float *__restrict__ dV, float *__restrict__ dv_part, float *__restrict__ ds_out,
-    float *__restrict__ ds_sum_out, int ds_rows, int ds_row, int ds_pitch, int Tk, int H, int Dv, int cw) {
+    float *__restrict__ dKp, float *__restrict__ dV, float *__restrict__ dv_part, int Tk, int H, int Dv, int cw) {
     extern __shared__ float s_step[];     // [Tk] P, then [Tk] dP
     float *s_p = s_step, *s_dp = s_step + Tk;
     __shared__ float s_q[ST_W][64], s_r[ST_W][64];
@@ -46,11 +40,6 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
     const bool hv = h < H;
     const int hc = hv ? h : H - 1;
     const int L = clamp_len(key_len[b], Tk);
-    float *ds_dst = DEFER ? ds_out + ((size_t)b * ds_rows + ds_row) * ds_pitch : nullptr;
-    if (DEFER && hs == 0) {               // masked keys and pads of the stored dS row: zeros
-        for (int j = L + (int)threadIdx.x; j < ds_pitch; j += ST_THREADS) ds_dst[j] = 0.f;
-        if (L == 0 && threadIdx.x == 0) ds_sum_out[(size_t)b * ds_rows + ds_row] = 0.f;
-    }
     if (L == 0) {                         // no valid key: the query gets no gradient, the sums get nothing
         if (w == 0 && hv) dQp[(size_t)b * H + h] = 0.f;
         return;
@@ -71,8 +60,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
     for (int u = 0; u < ST_KB; ++u) {
         const int j = min(ST_KB * w + u, L - 1);
         k0[u] = ld(Kb, (size_t)j * H + hc);
-        oldk0[u] = DEFER ? 0.f : dKb[(size_t)j * H + hc];
-        oldv0[u] = DEFER ? 0.f : dVb[(size_t)j * Dv + c0];
+        oldk0[u] = dKb[(size_t)j * H + hc];
+        oldv0[u] = dVb[(size_t)j * Dv + c0];
     }
     const float sq = kTwoLog2e * ld(Qp, (size_t)b * H + hc);
     float v_raw = ld(v, (size_t)hc);     // scaled behind the barrier below: as a guarded load with its scaling it was
@@ -131,7 +120,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
             } else {
                 const size_t at = (size_t)min(j0 + u, L - 1) * H + hc;
                 k[u] = ld(Kb, at);
-                oldk[u] = DEFER ? 0.f : dKb[at];
+                oldk[u] = dKb[at];
             }
         }
 #pragma unroll
@@ -142,11 +131,10 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
                 const float g = ds * __builtin_fmaf(-rr, rr, rr);
                 accQ += g;
                 accR = __builtin_fmaf(ds, rr, accR);
-                if (!DEFER && hv) store_streaming(&dKb[(size_t)(j0 + u) * H + h], __builtin_fmaf(v4, g, oldk[u]));
-                if (DEFER && hs == 0 && lane == 0) ds_dst[j0 + u] = ds;
+                if (hv) store_streaming(&dKb[(size_t)(j0 + u) * H + h], __builtin_fmaf(v4, g, oldk[u]));
             }
         }
-        for (int c = c_lo + lane, m = 0; !DEFER && c < c_hi; c += 64, ++m) {
+        for (int c = c_lo + lane, m = 0; c < c_hi; c += 64, ++m) {
             const float dc = dCb[c];
 #pragma unroll
             for (int u = 0; u < ST_KB; ++u) {
@@ -169,74 +157,214 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
             tr += s_r[k2][lane];
         }
         store_streaming(&dQp[(size_t)b * H + h], v4 * tq);
-        if (!DEFER) {
-            float *dvp = dv_part + (size_t)b * H + h;
-            *dvp += __builtin_fmaf(-2.f, tr, dsum);
-        } else if (hs == 0 && lane == 0) {
-            ds_sum_out[(size_t)b * ds_rows + ds_row] = dsum;
-        }
+        float *dvp = dv_part + (size_t)b * H + h;
+        *dvp += __builtin_fmaf(-2.f, tr, dsum);
     }
 }
 
-// Forward pass of one decoder step (one query per sample) in one launch of one block per sample: scores with the
-// eight waves taking four keys each per batch and the lanes along h, softmax over the valid keys, context with a
-// thread per column.  tanh is taken from the exponential of the sum here (one exponential and one reciprocal per
-// element): a step is a few thousand elements per wave, nothing to save by factoring it.
-template <typename T>
-__global__ __launch_bounds__(ST_THREADS) void k_step_fwd(
+// ---- one block of sixteen waves per sample: forward, and the query side of the backward ------------------------------
+//
+// What bounds these is the rate at which one CU draws a sample's rows (about 100 KB/us when enough whole-row loads are under
+// way), so a wave loads whole pieces of rows (64 lanes x 16 bytes), 16 waves x 8 loads make a batch (64 rows x 512 columns), and
+// two batches are under way: where one batch holds a sample's keys and one its values (ONE), all rows of the step are
+// requested before anything is evaluated, else two batches of keys at a time, and the first two of the second half of the
+// step (V forward, K backward) before the softmax in between.  Both passes have the same frame: a value per key from the rows of one matrix (score from K,
+// dP from V), a step on the row of values (softmax, its backward), then sums over the keys into columns (context from V, dQp
+// from K), which the waves form for their rows and add up in LDS.
+// (With eight waves, four keys at a time and a thread per column, one trip to memory after the other, a step of 80 samples,
+// 100 keys, H = Dv = 512 took 20 us; this takes 9.1.  64 samples of 50 keys: 8.0 with a column's values in registers, 6.6.)
+constexpr int SB_W = 16;                  // waves
+constexpr int SB_THREADS = 64 * SB_W;
+constexpr int SB_U = 4;                   // rows per wave and batch: row w + 16 u
+constexpr int SB_ROWS = SB_W * SB_U;
+constexpr int SB_C = 2;                   // 256-wide chunks of columns per batch
+constexpr int SB_COLS = 256 * SB_C;
+
+// Where the group of four columns that belongs at `col` is loaded from (NARROW: rows of fewer than four elements).
+template <bool NARROW> __device__ __forceinline__ int piece_at(int width, int col) { return NARROW ? col : min(col, width - 4); }
+
+// A batch of a wave's rows: rows j0 + w + 16 u below L, columns c0 + 256 c + 4 lane.  Groups of four that reach past the width
+// are loaded as the row's last four; chunks from `end` on are not loaded.  Row and chunk are scalars, the lane's place a small
+// offset to them.
+template <typename T> struct RowBatch {
+    RawKey<T> x[SB_C][SB_U];
+    template <bool NARROW>
+    __device__ __forceinline__ void load(const T *base, int width, int end, int L, int j0, int c0, int lane, int w) {
+        const int back = c0 > 0 ? 4 : 0;  // so that no offset is negative
+        unsigned off[SB_C];
+#pragma unroll
+        for (int c = 0; c < SB_C; ++c)
+            off[c] = (unsigned)min(256 * c + 4 * lane + back, width - 4 - c0 + back) * (unsigned)sizeof(T);
+        const T *first = base + (c0 - back);
+#pragma unroll
+        for (int u = 0; u < SB_U; ++u) {
+            const int j = j0 + w + SB_W * u;
+            if (j < L) {                                          // uniform
+                const T *row = first + (size_t)j * width;
+#pragma unroll
+                for (int c = 0; c < SB_C; ++c) {
+                    if (c0 + 256 * c >= end) x[c][u].zero();      // uniform
+                    else if (NARROW) x[c][u].load_some(row, width - 4 * lane);
+                    else x[c][u].load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(row) + off[c]), 0);
+                }
+            } else {
+#pragma unroll
+                for (int c = 0; c < SB_C; ++c) x[c][u].zero();
+            }
+        }
+    }
+    __device__ __forceinline__ void pin() {
+#pragma unroll
+        for (int c = 0; c < SB_C; ++c)
+#pragma unroll
+            for (int u = 0; u < SB_U; ++u) x[c][u].pin();
+    }
+};
+// Walks the rows of one matrix in batches: all chunks of columns of 64 rows before the next 64 (ROWS_OUTER), or all rows of a
+// chunk of columns before the next chunk.  The same in all lanes.
+template <bool ROWS_OUTER> struct Walk {
+    int begin, width, L, j, c;            // columns begin .. width - 1
+    __device__ __forceinline__ Walk(int begin_, int width_, int L_) : begin(begin_), width(width_), L(L_), j(0), c(begin_) {}
+    __device__ __forceinline__ Walk after() const {
+        Walk n = *this;
+        n.next();
+        return n;
+    }
+    __device__ __forceinline__ bool more() const { return ROWS_OUTER ? j < L : c < width; }
+    __device__ __forceinline__ void next() {
+        if (ROWS_OUTER) {
+            c += SB_COLS;
+            if (c >= width) {
+                c = begin;
+                j += SB_ROWS;
+            }
+        } else {
+            j += SB_ROWS;
+            if (j >= L) {
+                j = 0;
+                c += SB_COLS;
+            }
+        }
+    }
+};
+
+// Four columns of a vector at c0 + 256 c + 4 lane; columns past the width, and those that a last group loaded as the row's last
+// four repeats, are zero if `masked`.
+template <bool NARROW, typename T>
+__device__ __forceinline__ float4 vec_piece(const T *p, int width, int col, bool masked) {
+    const int at = piece_at<NARROW>(width, col);
+    RawKey<T> raw;
+    if (NARROW) raw.load_some(p, width - col);
+    else raw.load(p, (size_t)(unsigned)at);
+    float4 r = raw.get();
+    if (masked) {
+        if (at + 0 < col) r.x = 0.f;
+        if (at + 1 < col) r.y = 0.f;
+        if (at + 2 < col) r.z = 0.f;
+        if (at + 3 < col) r.w = 0.f;
+    }
+    return r;
+}
+
+// Partial sums of the waves, [wave][column of the chunk], added in wave order: column t of thread t < SB_COLS.
+__device__ __forceinline__ float sum_over_waves(float (&s_part)[SB_W][SB_COLS], const float4 (&acc)[SB_C], int lane, int w) {
+    lds_barrier();                                                // the previous use of s_part is over
+#pragma unroll
+    for (int c = 0; c < SB_C; ++c) *reinterpret_cast<float4 *>(&s_part[w][256 * c + 4 * lane]) = acc[c];
+    lds_barrier();
+    float tot = 0.f;
+    if (threadIdx.x < SB_COLS) {
+#pragma unroll
+        for (int k = 0; k < SB_W; ++k) tot += s_part[k][threadIdx.x];
+    }
+    return tot;
+}
+
+// Forward: S[j] = -2 sum_h v[h] r, r = 1 / (exp(2 (q + k)) + 1) (tanh = 1 - 2 r; the key-independent sum of v drops out of the
+// softmax).  One exponential and one reciprocal per element: nothing to save by factoring when every key meets one query.
+template <typename T, bool NARROW, bool ONE>
+__global__ __launch_bounds__(SB_THREADS) void k_step_fwd(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ V, const T *__restrict__ v,
-    const int *__restrict__ key_len, float *__restrict__ C, float *__restrict__ P, int Tk, int H, int Dv) {
+    const int *__restrict__ key_len, float *__restrict__ C, float *__restrict__ P, int Tk, int H, int Dv, int part) {
     extern __shared__ float s_step[];     // [Tk] scores, then probabilities
     float *s_s = s_step;
+    __shared__ __align__(16) float s_part[SB_W][SB_COLS];
     const int b = blockIdx.x;
     const int lane = lane_id(), w = wave_id();
     const int L = clamp_len(key_len[b], Tk);
     float *Pb = P + (size_t)b * Tk;
     float *Cb = C + (size_t)b * Dv;
     if (L == 0) {                         // no valid key: zeros
-        for (int j = threadIdx.x; j < Tk; j += ST_THREADS) Pb[j] = 0.f;
-        for (int d = threadIdx.x; d < Dv; d += ST_THREADS) Cb[d] = 0.f;
+        if (blockIdx.y > 0) return;
+        for (int j = threadIdx.x; j < Tk; j += SB_THREADS) Pb[j] = 0.f;
+        for (int d = threadIdx.x; d < Dv; d += SB_THREADS) Cb[d] = 0.f;
         return;
     }
     const T *qb = Qp + (size_t)b * H;
     const T *Kb = Kp + (size_t)b * Tk * H;
     const T *Vb = V + (size_t)b * Tk * Dv;
-    const int n_batch = (L + 8 * ST_KB - 1) / (8 * ST_KB);
-    const int H4 = (H % 4 == 0) ? H : 0;  // rows are read four elements at a time when every row starts aligned
+    // two batches at a time: of the first matrix, or (ONE: each matrix is a single batch) one of both
+    RowBatch<T> x[2];
+    const int d_lo = blockIdx.y * part, d_hi = min(d_lo + part, Dv);     // this block's columns of the context
+    Walk<true> kw(0, H, L);
+    Walk<false> vw(d_lo, d_hi, L);
+    auto load_keys = [&](RowBatch<T> &r, const Walk<true> &at) {
+        if (at.more()) r.template load<NARROW>(Kb, H, H, L, at.j, at.c, lane, w);
+    };
+    auto load_values = [&](RowBatch<T> &r, const Walk<false> &at) {
+        if (at.more()) r.template load<false>(Vb, Dv, d_hi, L, at.j, at.c, lane, w);
+    };
+    if (ONE) load_keys(x[0], kw);
+    float4 q4[SB_C], v4[SB_C];
+    auto load_qv = [&](int h0) {
+#pragma unroll
+        for (int c = 0; c < SB_C; ++c) {
+            q4[c] = vec_piece<NARROW>(qb, H, h0 + 256 * c + 4 * lane, false);
+            v4[c] = vec_piece<NARROW>(v, H, h0 + 256 * c + 4 * lane, true);
+        }
+    };
+    load_qv(0);
+    if (ONE) load_values(x[1], vw);
 
-    // ---- scores: S[j] = sum_h v[h] tanh(q[h] + k[j,h]),  tanh = 1 - 2 / (exp(2 (q + k)) + 1)
-    for (int n = 0; n < n_batch; ++n) {
-        const int j0 = 8 * ST_KB * n + ST_KB * w;
-        float acc[ST_KB] = {0.f, 0.f, 0.f, 0.f};
-        if (j0 < L) {                                             // wave-uniform
-            for (int h = 4 * lane; h < H4; h += 256) {
-                const float4 q4 = ld4(qb, (size_t)h), v4 = ld4(v, (size_t)h);
-                float4 k4[ST_KB];
+    float acc[SB_U];
+    auto scores = [&](RowBatch<T> &kx, int j0, int h0) {
+        if (h0 == 0) {
 #pragma unroll
-                for (int u = 0; u < ST_KB; ++u) k4[u] = ld4(Kb, (size_t)min(j0 + u, L - 1) * H + h);
+            for (int u = 0; u < SB_U; ++u) acc[u] = 0.f;
+        }
+        if (H > SB_COLS && (j0 > 0 || h0 > 0)) load_qv(h0);
+        kx.pin();
 #pragma unroll
-                for (int u = 0; u < ST_KB; ++u) {
+        for (int c = 0; c < SB_C; ++c) {
+            if (h0 + 256 * c >= H) continue;                      // uniform
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const float x = kTwoLog2e * (comp4(q4, c) + comp4(k4[u], c));
-                        acc[u] += comp4(v4, c) * __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f);
-                    }
-                }
-            }
-            for (int h = H4 + lane; h < H; h += 64) {             // rows that do not start aligned: one element at a time
-                const float qh = ld(qb, (size_t)h), vh = ld(v, (size_t)h);
+            for (int u = 0; u < SB_U; ++u) {
+                if (j0 + w + SB_W * u >= L) continue;             // uniform
+                const float4 k4 = kx.x[c][u].get();
 #pragma unroll
-                for (int u = 0; u < ST_KB; ++u) {
-                    const float x = kTwoLog2e * (qh + ld(Kb, (size_t)min(j0 + u, L - 1) * H + h));
-                    acc[u] += vh * __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < ST_KB; ++u) {
-                const float tot = wave_sum(acc[u]);
-                if (lane == 0 && j0 + u < L) s_s[j0 + u] = tot;
+                for (int e = 0; e < 4; ++e)
+                    acc[u] = __builtin_fmaf(comp4(v4[c], e), r_from_sum(kTwoLog2e * comp4(q4[c], e), kTwoLog2e * comp4(k4, e)), acc[u]);
             }
         }
+        if (h0 + SB_COLS >= H) {                                  // the scores of these rows are complete
+            const float tot = wave_transpose_sum<SB_U>(acc);      // key u in lanes 16 u ..
+            const int j = j0 + w + SB_W * (lane >> 4);
+            if ((lane & 15) == 0 && j < L) s_s[j] = -2.f * tot;
+        }
+    };
+    if (ONE) {
+        scores(x[0], 0, 0);
+    } else {
+        while (kw.more()) {
+            load_keys(x[0], kw);
+            load_keys(x[1], kw.after());
+            scores(x[0], kw.j, kw.c);
+            kw.next();
+            if (kw.more()) scores(x[1], kw.j, kw.c);
+            kw.next();
+        }
+        load_values(x[0], vw);
+        load_values(x[1], vw.after());
     }
     lds_barrier();
 
@@ -249,187 +377,310 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_fwd(
     z = wave_sum(z);
     const float inv = 1.0f / z;
     lds_barrier();
-    for (int j = threadIdx.x; j < Tk; j += ST_THREADS) {
+    for (int j = threadIdx.x; j < Tk; j += SB_THREADS) {
         const float p = j < L ? fast_exp2((s_s[j] - mx) * 1.4426950408889634f) * inv : 0.f;
         if (j < L) s_s[j] = p;
-        store_streaming(&Pb[j], p);
+        if (blockIdx.y == 0) store_streaming(&Pb[j], p);
     }
     lds_barrier();
 
-    // ---- context: a thread per column, eight value rows in flight
-    for (int d = threadIdx.x; d < Dv; d += ST_THREADS) {
-        float acc = 0.f;
-        for (int j0 = 0; j0 < L; j0 += 8) {
-            float x[8];
+    // ---- context
+    float4 accC[SB_C];
+    auto context = [&](RowBatch<T> &vx, int j0, int d0) {
+        if (j0 == 0) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = ld(Vb, (size_t)min(j0 + u, L - 1) * Dv + d);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (j0 + u < L) acc = __builtin_fmaf(s_s[j0 + u], x[u], acc);
+            for (int c = 0; c < SB_C; ++c) accC[c] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        store_streaming(&Cb[d], acc);
+        vx.pin();
+#pragma unroll
+        for (int u = 0; u < SB_U; ++u) {
+            if (j0 + w + SB_W * u >= L) continue;                 // uniform
+            const float p = s_s[j0 + w + SB_W * u];
+#pragma unroll
+            for (int c = 0; c < SB_C; ++c) {
+                const float4 x = vx.x[c][u].get();
+                accC[c].x = __builtin_fmaf(p, x.x, accC[c].x);
+                accC[c].y = __builtin_fmaf(p, x.y, accC[c].y);
+                accC[c].z = __builtin_fmaf(p, x.z, accC[c].z);
+                accC[c].w = __builtin_fmaf(p, x.w, accC[c].w);
+            }
+        }
+        if (j0 + SB_ROWS >= L) {
+            const float tot = sum_over_waves(s_part, accC, lane, w);
+            const int d = d0 + (int)threadIdx.x;
+            if (threadIdx.x < SB_COLS && d < d_hi) store_streaming(&Cb[d], tot);
+        }
+    };
+    if (ONE) {
+        context(x[1], 0, d_lo);
+        return;
+    }
+    for (;;) {
+        context(x[0], vw.j, vw.c);
+        vw.next();
+        if (vw.more()) context(x[1], vw.j, vw.c);
+        vw.next();
+        if (!vw.more()) break;
+        load_values(x[0], vw);
+        load_values(x[1], vw.after());
     }
 }
 
-// ---------------------------------------------------------------------------------------------------------------
-// Short key axes (Tk <= 64, the sentence lengths of Section 2's translation model) with H and Dv up to 512.
-// A step on a few dozen keys is a chain of trips to memory, not arithmetic: measured at 64 samples of 50 keys, the
-// general kernels spend their time in four dependent rounds of key loads (two batches of keys, two chunks of h)
-// after a first trip for key_len, and in waiting for the acknowledgement of the P stores before the value rows are
-// used.  Here every load of the step is requested before the first result is awaited -- key rows are clamped with
-// Tk, not with the length, so nothing waits for key_len; rows at or beyond the length are loaded and never used
-// -- and all stores come last.  Wave w takes keys w, w + 8, ...; with at most 64 keys every wave holds the whole
-// score row (one key per lane), so the softmax needs no LDS pass and the context takes its weights by lane reads.
-constexpr int SS_KEYS = 64;               // keys a short step covers at most
-constexpr int SS_KU = SS_KEYS / ST_W;     // keys per wave
-constexpr int SS_CH = 2;                  // chunks of 256 along h
-constexpr int SS_MAX_WIDTH = 256 * SS_CH;
-
-template <typename T>
-__global__ __launch_bounds__(ST_THREADS) void k_step_fwd_short(
-    const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ V, const T *__restrict__ v,
-    const int *__restrict__ key_len, float *__restrict__ C, float *__restrict__ P, int Tk, int H, int Dv) {
-    __shared__ float s_s[SS_KEYS];
+// The query side of the backward step: dP[j] = sum_d dC[d] V[j,d], dS = P (dP - sum_j P dP), dQp[h] = v[h] sum_j dS (1 - t^2) with
+// t re-evaluated (1 - t^2 = 4 r (1 - r)).  Also leaves the step's row of dS (row `ds_row` of the sample's `ds_rows` rows of
+// `ds_pitch` floats, zeros at masked keys and pads) and its sum.
+template <typename T, bool NARROW, bool ONE>
+__global__ __launch_bounds__(SB_THREADS) void k_step_bwd_query(
+    const float *__restrict__ dC, const float *__restrict__ P, const T *__restrict__ Qp, const T *__restrict__ Kp,
+    const T *__restrict__ V, const T *__restrict__ v, const int *__restrict__ key_len, float *__restrict__ dQp,
+    float *__restrict__ ds_out, float *__restrict__ ds_sum_out, int ds_rows, int ds_row, int ds_pitch, int Tk, int H, int Dv,
+    int part) {
+    extern __shared__ float s_step[];     // [Tk] P, then [Tk] dP, later dS
+    float *s_p = s_step, *s_dp = s_step + Tk;
+    __shared__ __align__(16) float s_part[SB_W][SB_COLS];
     const int b = blockIdx.x;
-    const int lane = lane_id();
-    const int w = __builtin_amdgcn_readfirstlane(wave_id());
+    const int lane = lane_id(), w = wave_id();
+    const int L = clamp_len(key_len[b], Tk);
+    float *ds_dst = ds_out + ((size_t)b * ds_rows + ds_row) * ds_pitch;
+    const bool first = blockIdx.y == 0;   // of the sample's blocks: it leaves the row of dS
+    if (!first && L == 0) return;
+    if (first)
+        for (int j = L + (int)threadIdx.x; j < ds_pitch; j += SB_THREADS) ds_dst[j] = 0.f;
+    if (L == 0) {                         // no valid key: the query gets no gradient
+        if (threadIdx.x == 0) ds_sum_out[(size_t)b * ds_rows + ds_row] = 0.f;
+        for (int h = threadIdx.x; h < H; h += SB_THREADS) dQp[(size_t)b * H + h] = 0.f;
+        return;
+    }
+    const float *dCb = dC + (size_t)b * Dv;
+    const float *Pb = P + (size_t)b * Tk;
     const T *qb = Qp + (size_t)b * H;
     const T *Kb = Kp + (size_t)b * Tk * H;
     const T *Vb = V + (size_t)b * Tk * Dv;
+    RowBatch<T> x[2];                     // see k_step_fwd
+    const int h_lo = blockIdx.y * part, h_hi = min(h_lo + part, H);      // this block's part of dQp
+    Walk<true> vw(0, Dv, L);
+    Walk<false> kw(h_lo, h_hi, L);
+    auto load_values = [&](RowBatch<T> &r, const Walk<true> &at) {
+        if (at.more()) r.template load<false>(Vb, Dv, Dv, L, at.j, at.c, lane, w);
+    };
+    auto load_keys = [&](RowBatch<T> &r, const Walk<false> &at) {
+        if (at.more()) r.template load<NARROW>(Kb, H, h_hi, L, at.j, at.c, lane, w);
+    };
+    if (ONE) load_values(x[0], vw);
+    float4 c4[SB_C], q4[SB_C];
+    auto load_dc = [&](int d0) {
+#pragma unroll
+        for (int c = 0; c < SB_C; ++c) c4[c] = vec_piece<false>(dCb, Dv, d0 + 256 * c + 4 * lane, true);
+    };
+    auto load_q = [&](int h0) {
+#pragma unroll
+        for (int c = 0; c < SB_C; ++c) q4[c] = vec_piece<NARROW>(qb, H, h0 + 256 * c + 4 * lane, false);
+    };
+    load_dc(0);
+    const float p_first = Pb[min((int)threadIdx.x, L - 1)];
+    load_q(h_lo);
+    if (ONE) load_keys(x[1], kw);
 
-    // ---- every request of the step
-    const int len_raw = key_len[b];
-    float4 q4[SS_CH], v4[SS_CH], k4[SS_CH][SS_KU];
+    float acc[SB_U];
+    auto dots = [&](RowBatch<T> &vx, int j0, int d0) {
+        if (d0 == 0) {
 #pragma unroll
-    for (int c = 0; c < SS_CH; ++c) {
-        if (256 * c < H) {                                        // block-uniform
-            const int h = 256 * c + 4 * lane;
-            const int hc = min(h, H - 4);
-            q4[c] = ld4(qb, (size_t)hc);
-            v4[c] = ld4(v, (size_t)hc);
-            if (h >= H) v4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int u = 0; u < SS_KU; ++u) k4[c][u] = ld4(Kb, (size_t)min(w + ST_W * u, Tk - 1) * H + hc);
+            for (int u = 0; u < SB_U; ++u) acc[u] = 0.f;
         }
-    }
-    float vrow[SS_KEYS];                                          // this thread's column of the value rows
-    const int d_own = min((int)threadIdx.x, Dv - 1);
+        if (Dv > SB_COLS && (j0 > 0 || d0 > 0)) load_dc(d0);
+        vx.pin();
 #pragma unroll
-    for (int j = 0; j < SS_KEYS; ++j)
-        if (j < Tk) vrow[j] = ld(Vb, (size_t)j * Dv + d_own);
-    const int L = clamp_len(len_raw, Tk);
-
-    // ---- scores: S[j] = sum_h v[h] tanh(q[h] + k[j,h]),  tanh = 1 - 2 / (exp(2 (q + k)) + 1)
+        for (int c = 0; c < SB_C; ++c)
 #pragma unroll
-    for (int u = 0; u < SS_KU; ++u) {
-        const int j = w + ST_W * u;
-        if (j < L) {                                              // wave-uniform
-            float acc = 0.f;
-#pragma unroll
-            for (int c = 0; c < SS_CH; ++c) {
-                if (256 * c < H) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float x = kTwoLog2e * (comp4(q4[c], e) + comp4(k4[c][u], e));
-                        acc += comp4(v4[c], e) * __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f);
-                    }
-                }
+            for (int u = 0; u < SB_U; ++u) {
+                const float4 x = vx.x[c][u].get();
+                acc[u] += (c4[c].x * x.x + c4[c].y * x.y) + (c4[c].z * x.z + c4[c].w * x.w);
             }
-            const float tot = wave_sum(acc);
-            if (lane == 0) s_s[j] = tot;
+        if (d0 + SB_COLS >= Dv) {
+            const float tot = wave_transpose_sum<SB_U>(acc);
+            const int j = j0 + w + SB_W * (lane >> 4);
+            if ((lane & 15) == 0 && j < L) s_dp[j] = tot;
         }
+    };
+    if (ONE) {
+        dots(x[0], 0, 0);
+    } else {
+        while (vw.more()) {
+            load_values(x[0], vw);
+            load_values(x[1], vw.after());
+            dots(x[0], vw.j, vw.c);
+            vw.next();
+            if (vw.more()) dots(x[1], vw.j, vw.c);
+            vw.next();
+        }
+        load_keys(x[0], kw);
+        load_keys(x[1], kw.after());
     }
+    if ((int)threadIdx.x < L) s_p[threadIdx.x] = p_first;
+    for (int j = threadIdx.x + SB_THREADS; j < L; j += SB_THREADS) s_p[j] = Pb[j];
+    __syncthreads();
+
+    // ---- the row sums, formed by every wave for itself (same arithmetic, same result in all waves)
+    float r = 0.f;
+    for (int j = lane; j < L; j += 64) r += s_p[j] * s_dp[j];
+    r = wave_sum(r);
+    float dsum = 0.f;
+    for (int j = lane; j < L; j += 64) dsum += s_p[j] * (s_dp[j] - r);
+    dsum = wave_sum(dsum);                // zero in exact arithmetic; kept so that the key-side sums are exact in fp32
+    lds_barrier();
+    for (int j = threadIdx.x; j < L; j += SB_THREADS) {
+        const float ds = s_p[j] * (s_dp[j] - r);
+        s_dp[j] = ds;
+        if (first) ds_dst[j] = ds;
+    }
+    if (first && threadIdx.x == 0) ds_sum_out[(size_t)b * ds_rows + ds_row] = dsum;
     lds_barrier();
 
-    // ---- softmax over the valid keys, one key per lane, the same in every wave
-    const float sc = lane < L ? s_s[lane] : -INFINITY;
-    const float mx = wave_max(sc);
-    const float ex = lane < L ? fast_exp2((sc - mx) * 1.4426950408889634f) : 0.f;
-    const float z = wave_sum(ex);
-    const float p = lane < L ? ex * (1.0f / z) : 0.f;
-
-    // ---- context: a thread per column, the value rows are in registers
-    float acc = 0.f;
+    float4 accQ[SB_C];
+    auto query = [&](RowBatch<T> &kx, int j0, int h0) {
+        if (j0 == 0) {
+            if (h0 > h_lo) load_q(h0);
 #pragma unroll
-    for (int j = 0; j < SS_KEYS; ++j)
-        if (j < L) acc = __builtin_fmaf(lane_value(p, j), vrow[j], acc);
-    if ((int)threadIdx.x < Dv) store_streaming(&C[(size_t)b * Dv + threadIdx.x], acc);
-    if (w == 0 && lane < Tk) store_streaming(&P[(size_t)b * Tk + lane], p);
+            for (int c = 0; c < SB_C; ++c) accQ[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        kx.pin();
+#pragma unroll
+        for (int u = 0; u < SB_U; ++u) {
+            if (j0 + w + SB_W * u >= L) continue;                 // uniform
+            const float ds = s_dp[j0 + w + SB_W * u];
+#pragma unroll
+            for (int c = 0; c < SB_C; ++c) {
+                if (h0 + 256 * c >= h_hi) continue;               // uniform
+                const float4 k4 = kx.x[c][u].get();
+                float g[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float rr = r_from_sum(kTwoLog2e * comp4(q4[c], e), kTwoLog2e * comp4(k4, e));
+                    g[e] = ds * __builtin_fmaf(-rr, rr, rr);
+                }
+                accQ[c].x += g[0];
+                accQ[c].y += g[1];
+                accQ[c].z += g[2];
+                accQ[c].w += g[3];
+            }
+        }
+        if (j0 + SB_ROWS >= L) {
+            const float tot = sum_over_waves(s_part, accQ, lane, w);
+            // thread t holds the sum of the lane that loaded column piece_at(4 (t / 4)) + t % 4 of this chunk: a last group of
+            // fewer than four columns lies further right than its place
+            const int g4 = h0 + ((int)threadIdx.x & ~3), h = piece_at<NARROW>(H, g4) + ((int)threadIdx.x & 3);
+            if (threadIdx.x < SB_COLS && g4 < h_hi && h >= g4 && h < H)
+                store_streaming(&dQp[(size_t)b * H + h], 4.f * ld(v, (size_t)h) * tot);
+        }
+    };
+    if (ONE) {
+        query(x[1], 0, h_lo);
+        return;
+    }
+    for (;;) {
+        query(x[0], kw.j, kw.c);
+        kw.next();
+        if (kw.more()) query(x[1], kw.j, kw.c);
+        kw.next();
+        if (!kw.more()) break;
+        load_keys(x[0], kw);
+        load_keys(x[1], kw.after());
+    }
 }
 
-static bool step_fwd_short_ok(const AttnShape &s) {
-    return s.Tk <= SS_KEYS && s.H % 4 == 0 && s.H >= 4 && s.H <= SS_MAX_WIDTH && s.Dv <= ST_THREADS;
+// Blocks per sample: while the chip has room, the columns that the second half of the step sums into are split in parts of
+// whole multiples of `unit`; every block of a sample forms the values per key for itself.  256 columns where the second half
+// re-evaluates tanh (7.0 -> 6.0 us at 100 samples of 50 keys, H = 512; 18.3 -> 11.1 at 2 of 128, H = 1024), 512 for the context,
+// which 256 slowed down (9.0 -> 9.6 us at 80 samples of 100 keys).
+static int step_parts(int B, int width, int unit) {
+    const int units = (width + unit - 1) / unit, room = 256 / B;
+    return room < 2 || units < 2 ? 1 : (room < units ? room : units);
+}
+static int step_part_width(int width, int unit, int parts) { return ((width + unit - 1) / unit + parts - 1) / parts * unit; }
+static bool step_one_batch(const AttnShape &s) { return s.Tk <= SB_ROWS && s.H <= SB_COLS && s.Dv <= SB_COLS; }
+constexpr size_t SB_MOST_LDS = 64 * 1024;     // next to the 32 KB in which the waves' sums meet
+
+template <typename T, bool NARROW, bool ONE>
+static hipError_t launch_step_fwd_t(const AttnShape &s, size_t lds, const void *Qp, const void *Kp, const void *V, const void *v,
+                                    const int *key_len, float *C, float *P, hipStream_t st) {
+    if (lds > 16 * 1024) {
+        static LdsGrants granted;
+        hipError_t e = ensure_dynamic_lds((const void *)k_step_fwd<T, NARROW, ONE>, lds, granted);
+        if (e != hipSuccess) return e;
+    }
+    const int parts = step_parts(s.B, s.Dv, SB_COLS);
+    k_step_fwd<T, NARROW, ONE><<<dim3(s.B, parts), SB_THREADS, lds, st>>>((const T *)Qp, (const T *)Kp, (const T *)V, (const T *)v,
+                                                                          key_len, C, P, s.Tk, s.H, s.Dv,
+                                                                          step_part_width(s.Dv, SB_COLS, parts));
+    return hipGetLastError();
 }
 
 hipError_t launch_step_fwd(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,
                            const int *key_len, float *C, float *P, hipStream_t st) {
-    if (step_fwd_short_ok(s)) {
-        if (s.bf16)
-            k_step_fwd_short<bf16_t><<<s.B, ST_THREADS, 0, st>>>((const bf16_t *)Qp, (const bf16_t *)Kp,
-                                                                 (const bf16_t *)V, (const bf16_t *)v, key_len, C, P,
-                                                                 s.Tk, s.H, s.Dv);
-        else
-            k_step_fwd_short<float><<<s.B, ST_THREADS, 0, st>>>((const float *)Qp, (const float *)Kp, (const float *)V,
-                                                                (const float *)v, key_len, C, P, s.Tk, s.H, s.Dv);
-        return hipGetLastError();
-    }
     const size_t lds = (size_t)s.Tk * sizeof(float);
-    if (lds > 64 * 1024) return hipErrorInvalidValue;
-    if (lds > 48 * 1024) {
-        static LdsGrants granted_bf16, granted_f32;
-        hipError_t e = s.bf16 ? ensure_dynamic_lds((const void *)k_step_fwd<bf16_t>, lds, granted_bf16)
-                              : ensure_dynamic_lds((const void *)k_step_fwd<float>, lds, granted_f32);
-        if (e != hipSuccess) return e;
-    }
-    if (s.bf16)
-        k_step_fwd<bf16_t><<<s.B, ST_THREADS, lds, st>>>((const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)V,
-                                                         (const bf16_t *)v, key_len, C, P, s.Tk, s.H, s.Dv);
-    else
-        k_step_fwd<float><<<s.B, ST_THREADS, lds, st>>>((const float *)Qp, (const float *)Kp, (const float *)V,
-                                                        (const float *)v, key_len, C, P, s.Tk, s.H, s.Dv);
-    return hipGetLastError();
+    if (lds > SB_MOST_LDS) return hipErrorInvalidValue;
+#define ECHO_STEP(T, NARROW, ONE) launch_step_fwd_t<T, NARROW, ONE>(s, lds, Qp, Kp, V, v, key_len, C, P, st)
+    if (s.H < 4) return s.bf16 ? ECHO_STEP(bf16_t, true, false) : ECHO_STEP(float, true, false);
+    if (step_one_batch(s)) return s.bf16 ? ECHO_STEP(bf16_t, false, true) : ECHO_STEP(float, false, true);
+    return s.bf16 ? ECHO_STEP(bf16_t, false, false) : ECHO_STEP(float, false, false);
+#undef ECHO_STEP
 }
 
 size_t step_lds_bytes(const AttnShape &s) { return 2 * (size_t)s.Tk * sizeof(float); }
 
-template <typename T, bool DEFER>
-static hipError_t launch_step_bwd_t(const AttnShape &s, const float *dC, const float *P, const void *Qp,
-                                    const void *Kp, const void *V, const void *v, const int *key_len, float *dQp,
-                                    float *dKp, float *dV, float *dv_part, float *ds_out, float *ds_sum_out,
-                                    int ds_rows, int ds_row, hipStream_t st) {
+template <typename T>
+static hipError_t launch_step_bwd_t(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
+                                    const void *V, const void *v, const int *key_len, float *dQp, float *dKp, float *dV,
+                                    float *dv_part, hipStream_t st) {
     const size_t lds = step_lds_bytes(s);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     if (lds > 40 * 1024) {
         static LdsGrants granted;
-        hipError_t e = ensure_dynamic_lds((const void *)k_step_bwd<T, DEFER>, lds, granted);
+        hipError_t e = ensure_dynamic_lds((const void *)k_step_bwd<T>, lds, granted);
         if (e != hipSuccess) return e;
     }
     const int n_hs = (s.H + 63) / 64;
     const int cw = (s.Dv + n_hs - 1) / n_hs;                     // columns of dV per h slice
     dim3 grid(n_hs, s.B);
-    k_step_bwd<T, DEFER><<<grid, ST_THREADS, lds, st>>>(dC, P, (const T *)Qp, (const T *)Kp, (const T *)V,
-                                                        (const T *)v, key_len, dQp, dKp, dV, dv_part, ds_out,
-                                                        ds_sum_out, ds_rows, ds_row, ds_pitch(s.Tk), s.Tk, s.H, s.Dv,
-                                                        cw);
+    k_step_bwd<T><<<grid, ST_THREADS, lds, st>>>(dC, P, (const T *)Qp, (const T *)Kp, (const T *)V, (const T *)v, key_len, dQp,
+                                                 dKp, dV, dv_part, s.Tk, s.H, s.Dv, cw);
     return hipGetLastError();
 }
 
 hipError_t launch_step_bwd(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
                            const void *V, const void *v, const int *key_len, float *dQp, float *dKp, float *dV,
                            float *dv_part, hipStream_t st) {
-    return s.bf16 ? launch_step_bwd_t<bf16_t, false>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, nullptr,
-                                                     nullptr, 1, 0, st)
-                  : launch_step_bwd_t<float, false>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, nullptr,
-                                                    nullptr, 1, 0, st);
+    return s.bf16 ? launch_step_bwd_t<bf16_t>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, st)
+                  : launch_step_bwd_t<float>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, st);
+}
+
+template <typename T, bool NARROW, bool ONE>
+static hipError_t launch_step_bwd_query_t(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
+                                          const void *V, const void *v, const int *key_len, float *dQp, float *ds_out,
+                                          float *ds_sum_out, int steps, int step, hipStream_t st) {
+    const size_t lds = step_lds_bytes(s);
+    if (lds > SB_MOST_LDS) return hipErrorInvalidValue;
+    if (lds > 16 * 1024) {
+        static LdsGrants granted;
+        hipError_t e = ensure_dynamic_lds((const void *)k_step_bwd_query<T, NARROW, ONE>, lds, granted);
+        if (e != hipSuccess) return e;
+    }
+    const int parts = step_parts(s.B, s.H, 256);
+    k_step_bwd_query<T, NARROW, ONE><<<dim3(s.B, parts), SB_THREADS, lds, st>>>(
+        dC, P, (const T *)Qp, (const T *)Kp, (const T *)V, (const T *)v, key_len, dQp, ds_out, ds_sum_out, steps, step,
+        ds_pitch(s.Tk), s.Tk, s.H, s.Dv, step_part_width(s.H, 256, parts));
+    return hipGetLastError();
 }
 
 hipError_t launch_step_bwd_query(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
                                  const void *V, const void *v, const int *key_len, float *dQp, float *ds_out,
                                  float *ds_sum_out, int steps, int step, hipStream_t st) {
-    return s.bf16 ? launch_step_bwd_t<bf16_t, true>(s, dC, P, Qp, Kp, V, v, key_len, dQp, nullptr, nullptr, nullptr,
-                                                    ds_out, ds_sum_out, steps, step, st)
-                  : launch_step_bwd_t<float, true>(s, dC, P, Qp, Kp, V, v, key_len, dQp, nullptr, nullptr, nullptr,
-                                                   ds_out, ds_sum_out, steps, step, st);
+#define ECHO_QUERY(T, NARROW, ONE) \
+    launch_step_bwd_query_t<T, NARROW, ONE>(s, dC, P, Qp, Kp, V, v, key_len, dQp, ds_out, ds_sum_out, steps, step, st)
+    if (s.H < 4) return s.bf16 ? ECHO_QUERY(bf16_t, true, false) : ECHO_QUERY(float, true, false);
+    if (step_one_batch(s)) return s.bf16 ? ECHO_QUERY(bf16_t, false, true) : ECHO_QUERY(float, false, true);
+    return s.bf16 ? ECHO_QUERY(bf16_t, false, false) : ECHO_QUERY(float, false, false);
+#undef ECHO_QUERY
 }
 
 }  // namespace echo

@@ -76,3 +76,45 @@ def test_launch_form(case):
     again = db.results()
     for k in first:
         assert np.array_equal(first[k], again[k]), (name, k, "not reproducible")
+
+
+STEPS = [
+    # name, B, Tk, H, Dv, dtype: one decoder step and its query gradient, the sample's block at the edges of its batches
+    # (64 rows, 512 columns): one batch of each matrix, one row and one column more, three batches, rows of one to three
+    # elements, tails of one to three columns, both storage types
+    ("one_batch_full", 3, 64, 512, 512, "f32"),
+    ("one_batch_bf16_tail", 70, 33, 301, 260, "bf16"),
+    ("one_more_row", 3, 65, 512, 512, "f32"),
+    ("one_more_column", 3, 20, 513, 516, "f32"),
+    ("three_batches_of_rows_and_columns", 2, 150, 1030, 1100, "f32"),
+    ("many_rows_bf16", 2, 331, 77, 40, "bf16"),
+    ("h_1", 3, 70, 1, 4, "f32"),
+    ("h_2_bf16", 3, 20, 2, 8, "bf16"),
+    ("h_3", 3, 130, 3, 516, "f32"),
+    ("h_4", 3, 66, 4, 4, "f32"),
+]
+
+
+@pytest.mark.parametrize("case", STEPS, ids=[c[0] for c in STEPS])
+def test_step_of_one_block_per_sample(case):
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import binding as eb, harness
+    name, B, Tk, H, Dv, dt = case
+    print("step", case, flush=True)
+    wl = Workload(name, B, 1, Tk, H, Dv, dt, 0.5, 1, Tk, dt == "bf16")
+    inputs = make_inputs(wl, seed=99 + len(name))
+    inputs["key_len"][0] = Tk
+    if B > 2:
+        inputs["key_len"][1] = 0
+    db = harness.DeviceBatch(wl, inputs, guard_bytes=4096)
+    db.poison_outputs()
+    ds = torch.full((eb.echo_attn_steps_ds_bytes(db.desc),), 0xFF, dtype=torch.uint8, device=db.device)
+    st = torch.cuda.current_stream(db.device)
+    eb.check(eb.echo_attn_step_fwd(db.desc, db.Qp, db.Kp, db.V, db.v, db.key_len, db.context, db.P, stream=st))
+    eb.check(eb.echo_attn_step_bwd_query(db.desc, 0, 1, db.dC, db.P, db.Qp, db.Kp, db.V, db.v, db.key_len, db.dQp, ds, stream=st))
+    eb.check(eb.echo_attn_steps_bwd_keys(db.desc, db.dC, db.P, db.Qp, db.Kp, db.v, db.key_len, ds, db.dKp, db.dV, db.dv, db.ws,
+                                         stream=st))
+    got = db.results()
+    assert db.check_guards() == []
+    assert_parity(got, oracle_outputs(inputs, workers=1), inputs, dt, name)
