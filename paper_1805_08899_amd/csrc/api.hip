@@ -171,6 +171,7 @@ echo_status_t bwd_impl(const echo_attn_desc_t *desc, const float *dContext, cons
     int *order = reinterpret_cast<int *>(ws + lay.order_off);
     unsigned long long *dv_flag = reinterpret_cast<unsigned long long *>(ws + lay.dvflag_off);
     ECHO_LAUNCH("bwd_pre", echo::launch_bwd_pre(s, dContext, V, P, key_len, dS, rowsum, order, dV, st));
+    if (echo::bwd_pre_in_parts(s)) ECHO_LAUNCH("ds_finish", echo::launch_ds_finish(s, P, key_len, dS, rowsum, st));
     if (!use_map && lay.mail_bytes > 0) {
         ECHO_LAUNCH("recompute_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, dQp, dKp, ws + lay.mail_off,
                                                                     next_launch_number(), dv, st));

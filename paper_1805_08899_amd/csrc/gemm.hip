@@ -419,41 +419,46 @@ __device__ __forceinline__ void dscore_block_dsplit(const float *__restrict__ dC
 // round), and the partial dP tiles go to planes of their own behind the staging regions as each key tile finishes
 // (there is no room to keep eight of them in registers next to two rounds of dC).  The general form above fetches
 // the dC slices again for every key tile and round and waits for them each time.
+constexpr int kPartKeys = 64;                    // keys of a block that forms a part of the rows of dP (PART)
 constexpr int kStagePitch = 132;                 // floats; 16 rows of it are a wave's region
-template <typename TV, int ROUNDS>
+template <typename TV, int ROUNDS, bool PART>
 __device__ __forceinline__ void dscore_block_dsplit_lds(const float *__restrict__ dC, const TV *__restrict__ V,
                                                         const float *__restrict__ P, const int *__restrict__ key_len,
                                                         float *__restrict__ dS, float *__restrict__ ds_rowsum,
                                                         float *__restrict__ s_stage, int b, int i0, int Tq, int Tk,
-                                                        int Dv, int pitch) {
+                                                        int Dv, int pitch, int j_first) {
     const int lane = lane_id(), w = wave_id();
     const int lm = lane & 15, lk = lane >> 4;
-    const int pitch16 = (Tk + 15) / 16 * 16 + 4;
+    const int pitch16 = PART ? kPartKeys + 4 : (Tk + 15) / 16 * 16 + 4;
     constexpr int region = 16 * kStagePitch;
-    constexpr int NT = ROUNDS == 1 ? kDsplitMaxTk / 16 : 1;       // dP tiles kept in registers
+    constexpr int MAX_JT = (PART ? kPartKeys : kDsplitMaxTk) / 16;
+    constexpr int NT = ROUNDS == 1 ? MAX_JT : 1;       // dP tiles kept in registers
     // the planes of partial dP: the staging regions themselves (one round) or planes behind them
     float *planes = ROUNDS == 1 ? s_stage : s_stage + 4 * region;
     const int plane = ROUNDS == 1 ? region : 16 * pitch16;
     // P of the rows this wave finishes (rows w, w+4, w+8, w+12 of the tile), two keys per lane
     float pr[4][2];
+    if (!PART) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int i = min(i0 + w + 4 * t, Tq - 1);
+        for (int t = 0; t < 4; ++t) {
+            const int i = min(i0 + w + 4 * t, Tq - 1);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) pr[t][u] = P[((size_t)b * Tq + i) * Tk + min(lane + 64 * u, Tk - 1)];
+            for (int u = 0; u < 2; ++u) pr[t][u] = P[((size_t)b * Tq + i) * Tk + min(lane + 64 * u, Tk - 1)];
+        }
     }
     constexpr int U = 8;                          // 16-wide slices of d per wave and round
     float *st = s_stage + w * region;             // this wave's region
     const int cr = lane >> 5, cc = 4 * (lane & 31);               // loading: row of the pair, column in the chunk
     const float *dCb = dC + (size_t)b * Tq * Dv;
-    const TV *Vb = V + (size_t)b * Tk * Dv;
+    const TV *Vb = V + ((size_t)b * Tk + j_first) * Dv;
+    const int n_keys = PART ? min(kPartKeys, Tk - j_first) : Tk;          // keys of this block, masked ones included
     float4 a[ROUNDS][U], bcur[U], bnxt[U];
     auto col_of = [&](int r) { return min((4 * r + w) * 16 * U + cc, Dv - 4); };   // clamped for loading
     auto load_v = [&](float4 (&dst)[U], int it) {                 // step it = (key tile, round): 16 keys, two per load
         const int jt = it / ROUNDS, r = it % ROUNDS;
         const int col = col_of(r);
 #pragma unroll
-        for (int u = 0; u < U; ++u) dst[u] = ld4(Vb + (size_t)min(jt * 16 + 2 * u + cr, Tk - 1) * Dv, (size_t)col);
+        for (int u = 0; u < U; ++u) dst[u] = ld4(Vb + (size_t)min(jt * 16 + 2 * u + cr, n_keys - 1) * Dv, (size_t)col);
     };
     auto through_lds = [&](float4 (&dst)[U], const float4 (&src)[U]) {
 #pragma unroll
@@ -469,7 +474,7 @@ __device__ __forceinline__ void dscore_block_dsplit_lds(const float *__restrict_
 #pragma unroll
         for (int u = 0; u < U; ++u) a[r][u] = ld4(dCb + (size_t)min(i0 + 2 * u + cr, Tq - 1) * Dv, (size_t)col);
     }
-    const int L = clamp_len(key_len[b], Tk);
+    const int L = clamp_len(key_len[b] - j_first, n_keys);
     const int n_jt = (L + 15) / 16;
     const int items = n_jt * ROUNDS;
 #pragma unroll
@@ -484,7 +489,7 @@ __device__ __forceinline__ void dscore_block_dsplit_lds(const float *__restrict_
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int jt = 0; jt < kDsplitMaxTk / 16; ++jt) {
+    for (int jt = 0; jt < MAX_JT; ++jt) {
         if (jt < n_jt) {                                           // uniform
 #pragma unroll
             for (int r = 0; r < ROUNDS; ++r) {
@@ -508,14 +513,105 @@ __device__ __forceinline__ void dscore_block_dsplit_lds(const float *__restrict_
     }
     if (ROUNDS == 1) {                            // the wave's plane of partial dP into its own region
 #pragma unroll
-        for (int jt = 0; jt < kDsplitMaxTk / 16; ++jt)
+        for (int jt = 0; jt < MAX_JT; ++jt)
             if (jt < n_jt) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) st[(4 * lk + q) * pitch16 + jt * 16 + lm] = acc[ROUNDS == 1 ? jt : 0][q];
             }
     }
     lds_barrier();
+    if (PART) {
+        // dP of the block's keys (the softmax backward needs whole rows: k_ds_finish); masked keys are not written
+        static_assert(kPartKeys == 64, "one key per lane");
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int rr = w + 4 * t, i = i0 + rr;
+            if (i < Tq && lane < L) {
+                const float *q = planes + rr * pitch16 + lane;
+                dS[((size_t)b * Tq + i) * pitch + j_first + lane] = ((q[0] + q[plane]) + q[2 * plane]) + q[3 * plane];
+            }
+        }
+        return;
+    }
     dsplit_finish(pr, planes, dS, ds_rowsum, b, i0, Tq, L, pitch, pitch16, plane);
+}
+
+// dV of 16 keys and 64 columns, the four waves taking a quarter of the query rows each and adding their tiles in LDS: for
+// launches of few blocks, where the length of a wave's walk over the rows decides.  s_part: 3 x 16 x 64 floats.
+__device__ __forceinline__ void dv_rows_block(const float *__restrict__ P, const float *__restrict__ dC,
+                                              const int *__restrict__ key_len, float *__restrict__ dV,
+                                              float *__restrict__ s_part, int Tq, int Tk, int Dv, int b, int by, int bx,
+                                              int acc_out) {
+    constexpr int U = 8;                      // k-steps of four rows whose loads are in flight together
+    const int L = clamp_len(key_len[b], Tk);
+    const int lane = lane_id(), w = wave_id();
+    const int lm = lane & 15, lk = lane >> 4;
+    const int m0 = by * 16, ncol = bx * 64 + 4 * lm;
+    const bool nok = ncol < Dv;
+    const float *Pb = P + (size_t)b * Tq * Tk + min(m0 + lm, Tk - 1);
+    const float *Cb = dC + (size_t)b * Tq * Dv + min(ncol, Dv - 4);
+    f32x4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (m0 < L) {                             // block-uniform
+        const int per = ((Tq + 15) / 16) * 4; // rows per wave, a multiple of four
+        const int k_lo = w * per, k_hi = min(k_lo + per, Tq);
+        for (int kb0 = k_lo; kb0 < k_hi; kb0 += 4 * U) {
+            float a[U];
+            float4 bv[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = min(kb0 + 4 * u + lk, Tq - 1);
+                a[u] = Pb[(size_t)k * Tk];
+                bv[u] = ld4(Cb, (size_t)k * Dv);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (kb0 + 4 * u < k_hi) {     // uniform
+                    // rows of the next wave or past Tq add nothing, nor do masked keys
+                    const float x = kb0 + 4 * u + lk < k_hi && m0 + lm < L ? a[u] : 0.f;
+                    acc[0] = mfma16(x, bv[u].x, acc[0]);
+                    acc[1] = mfma16(x, bv[u].y, acc[1]);
+                    acc[2] = mfma16(x, bv[u].z, acc[2]);
+                    acc[3] = mfma16(x, bv[u].w, acc[3]);
+                }
+            }
+        }
+        if (w > 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *reinterpret_cast<float4 *>(s_part + ((w - 1) * 16 + 4 * lk + r) * 64 + 4 * lm) =
+                    make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+        }
+        lds_barrier();
+    }
+    if (w > 0 || !nok) return;
+    float *ob = dV + (size_t)b * Tk * Dv;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + 4 * lk + r;
+        if (m < Tk) {
+            float4 o = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+            if (m0 < L) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const float4 x = *reinterpret_cast<const float4 *>(s_part + (k * 16 + 4 * lk + r) * 64 + 4 * lm);
+                    o.x += x.x;
+                    o.y += x.y;
+                    o.z += x.z;
+                    o.w += x.w;
+                }
+            }
+            if (acc_out) {                       // add to what the earlier decoder steps left
+                const float4 old = *reinterpret_cast<const float4 *>(ob + (size_t)m * Dv + ncol);
+                o.x += old.x;
+                o.y += old.y;
+                o.z += old.z;
+                o.w += old.w;
+            }
+            store4_streaming(ob + (size_t)m * Dv + ncol, o);
+        }
+    }
 }
 
 // dV of one sample for a panel of 64 keys and 256 columns, 64 columns per wave: dV[j, n] = sum_i P[i, j] dC[i, n].
@@ -745,8 +841,8 @@ __global__ __launch_bounds__(256, 3) void k_bwd_pre(const float *__restrict__ dC
         const int b = xcd + kXcd * (li / s_tiles), i0 = (li % s_tiles) * s_rows;
         if (b >= B) return;
         if (Tk <= kDsplitMaxTk) {
-            if (Dv <= 512) dscore_block_dsplit_lds<TV, 1>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
-            else if (Dv <= 1024) dscore_block_dsplit_lds<TV, 2>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
+            if (Dv <= 512) dscore_block_dsplit_lds<TV, 1, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
+            else if (Dv <= 1024) dscore_block_dsplit_lds<TV, 2, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
             else dscore_block_dsplit<TV>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
         } else {
             // a wave's key tiles in groups of four, or of five where that takes all of them at once (17 to 20 key tiles)
@@ -775,11 +871,121 @@ __global__ __launch_bounds__(256, 3) void k_bwd_pre(const float *__restrict__ dC
     }
 }
 
+// The same work for launches that k_bwd_pre would run in too few, too long blocks (key axes past 128 keys): dP in blocks of 16
+// query rows x 64 keys, dV in blocks of 16 keys x 64 columns, in no particular place; the softmax backward, which needs whole
+// rows, follows in a launch of its own (k_ds_finish).  Blocks 0 .. n_s - 1: dP; then dV; the last one ranks.
+template <typename TV, int ROUNDS>
+__global__ __launch_bounds__(256, 3) void k_bwd_pre_parts(const float *__restrict__ dC, const TV *__restrict__ V,
+                                                       const float *__restrict__ P, const int *__restrict__ key_len,
+                                                       float *__restrict__ dP, int *__restrict__ order,
+                                                       float *__restrict__ dV, int B, int fold, int Tq, int Tk, int Dv, int pitch,
+                                                       int row_tiles, int parts, int with_ds, int acc) {
+    extern __shared__ float s_dp[];
+    __shared__ int s_len[kMaxSortedB];
+    const int n_s = with_ds ? B * row_tiles * parts : 0;
+    int id = blockIdx.x;
+    if (id == (int)gridDim.x - 1) {
+        rank_block(key_len, order, s_len, B, Tk, 1, fold);
+        return;
+    }
+    if (id < n_s) {
+        const int b = id / (row_tiles * parts), rem = id % (row_tiles * parts);
+        const int i0 = (rem / parts) * 16, j_first = (rem % parts) * kPartKeys;
+        if (j_first >= clamp_len(key_len[b], Tk)) return;
+        dscore_block_dsplit_lds<TV, ROUNDS, true>(dC, V, P, key_len, dP, nullptr, s_dp, b, i0, Tq, Tk, Dv, pitch, j_first);
+        return;
+    }
+    id -= n_s;
+    const int cols = (Dv + 63) / 64, keys = (Tk + 15) / 16;
+    const int b = id / (cols * keys), rem = id % (cols * keys);
+    dv_rows_block(P, dC, key_len, dV, s_dp, Tq, Tk, Dv, b, rem / cols, rem % cols, acc);
+}
+
+// dS = P (dP - sum_j P dP) in place of dP, a wave per query row; zeros at masked keys and pads, and the rows' sums.
+__global__ __launch_bounds__(256) void k_ds_finish(const float *__restrict__ P, const int *__restrict__ key_len, float *dS,
+                                                   float *__restrict__ ds_rowsum, int rows, int Tq, int Tk, int pitch) {
+    const int row = blockIdx.x * 4 + wave_id();
+    if (row >= rows) return;
+    const int lane = lane_id();
+    const int L = clamp_len(key_len[row / Tq], Tk);
+    const float *p = P + (size_t)row * Tk;
+    float *ds = dS + (size_t)row * pitch;
+    constexpr int NP = 6;                                         // keys per lane held in registers (384)
+    float pr[NP], dp[NP];
+#pragma unroll
+    for (int c = 0; c < NP; ++c) {
+        const int j = lane + 64 * c;
+        pr[c] = j < L ? p[j] : 0.f;
+        dp[c] = j < L ? ds[j] : 0.f;
+    }
+    float r = 0.f;
+#pragma unroll
+    for (int c = 0; c < NP; ++c) r = __builtin_fmaf(pr[c], dp[c], r);
+    for (int j = lane + 64 * NP; j < L; j += 64) r = __builtin_fmaf(p[j], ds[j], r);
+    r = wave_sum(r);
+    float tot = 0.f;
+#pragma unroll
+    for (int c = 0; c < NP; ++c) {
+        const int j = lane + 64 * c;
+        const float x = pr[c] * (dp[c] - r);                      // zero at masked keys
+        if (j < pitch) store_streaming(&ds[j], x);
+        tot += x;
+    }
+    for (int j = lane + 64 * NP; j < pitch; j += 64) {
+        const float x = j < L ? p[j] * (ds[j] - r) : 0.f;
+        store_streaming(&ds[j], x);
+        tot += x;
+    }
+    tot = wave_sum(tot);
+    if (lane == 0) ds_rowsum[row] = tot;
+}
+
+// k_bwd_pre has one dS block per 32 query rows, which takes all keys and all of d; with at most 100 of them (200 if the rows are
+// wide, so that a block is long) the shorter blocks win what the extra launch costs (4 to 5 us).  Both launches together:
+// B = 1, T = 400, Dv = 512 70 -> 14 us; B = 4, T = 300, Dv = 1024 68 -> 30; B = 16, T = 300, Dv = 512 55 -> 44; B = 20, T = 150,
+// Dv = 300 25 -> 21; level at B = 40, T = 150, Dv = 256.
+bool bwd_pre_in_parts(const AttnShape &s) {
+    return s.Tk > kDsplitMaxTk && s.Dv <= 1024 && s.B <= kMaxSortedB &&
+           (long long)s.B * ((s.Tq + 31) / 32) <= (s.Dv >= 384 ? 200 : 100);
+}
+
+template <typename TV, int ROUNDS>
+static hipError_t launch_parts_t(const AttnShape &s, const float *dC, const void *V, const float *P, const int *key_len,
+                                 float *dS, int *order, float *dV, hipStream_t st, bool with_ds, int fold) {
+    const int row_tiles = (s.Tq + 15) / 16, parts = (s.Tk + kPartKeys - 1) / kPartKeys;
+    const long long blocks = 1 + (with_ds ? (long long)s.B * row_tiles * parts : 0) +
+                             (long long)s.B * ((s.Dv + 63) / 64) * ((s.Tk + 15) / 16);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const size_t lds = (size_t)(4 * 16 * kStagePitch + (ROUNDS > 1 ? 64 * (kPartKeys + 4) : 0)) * sizeof(float);
+    if (lds > 48 * 1024) {
+        static LdsGrants granted;
+        hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre_parts<TV, ROUNDS>, lds, granted);
+        if (e != hipSuccess) return e;
+    }
+    k_bwd_pre_parts<TV, ROUNDS><<<(unsigned)blocks, 256, lds, st>>>(dC, (const TV *)V, P, key_len, dS, order, dV, s.B, fold, s.Tq,
+                                                                    s.Tk, s.Dv, ds_pitch(s.Tk), row_tiles, parts,
+                                                                    with_ds ? 1 : 0, s.acc ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_ds_finish(const AttnShape &s, const float *P, const int *key_len, float *dS, float *ds_rowsum, hipStream_t st) {
+    const int rows = s.B * s.Tq;
+    k_ds_finish<<<(rows + 3) / 4, 256, 0, st>>>(P, key_len, dS, ds_rowsum, rows, s.Tq, s.Tk, ds_pitch(s.Tk));
+    return hipGetLastError();
+}
+
 hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, const float *P, const int *key_len,
                           float *dS, float *ds_rowsum, int *order, float *dV, hipStream_t st, bool with_ds) {
     const int sorted = s.B <= kMaxSortedB ? 1 : 0;
     const int n_hs = (s.H + 63) / 64;
     const int fold = (sorted && (long long)s.B * n_hs <= 512) ? 1 : 0;   // recompute grid in one round
+    if (bwd_pre_in_parts(s)) {
+        if (s.Dv <= 512)
+            return s.bf16 ? launch_parts_t<bf16_t, 1>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold)
+                          : launch_parts_t<float, 1>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold);
+        return s.bf16 ? launch_parts_t<bf16_t, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold)
+                      : launch_parts_t<float, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold);
+    }
     // dS row tile: 32 rows on long key axes while three such blocks still fit a CU's LDS (the sample's V rows then
     // pass through half as many blocks), 16 otherwise
     const int s_rows = (s.Tk > kDsplitMaxTk && s.Tk <= kDs32MaxTk && s.Tq > 16) ? 32 : 16;

@@ -57,6 +57,10 @@ constexpr int kMaxSortedB = 1024;
 // with_ds = false leaves dS and ds_rowsum alone (they are given) and launches only the dV and ranking blocks
 hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, const float *P, const int *key_len,
                           float *dS, float *ds_rowsum, int *order, float *dV, hipStream_t st, bool with_ds = true);
+// Small launches on long key axes: launch_bwd_pre leaves dP in the place of dS, and launch_ds_finish (with_ds only) turns it
+// into dS and its row sums.
+bool bwd_pre_in_parts(const AttnShape &s);
+hipError_t launch_ds_finish(const AttnShape &s, const float *P, const int *key_len, float *dS, float *ds_rowsum, hipStream_t st);
 // B3 + B4  fused recompute: dQp, dKp, per-sample partials of dv (dv_part [B,H]) and, by the blocks that start
 // last, dv[h] = sum_b dv_part[b,h] in index order (added to dv if s.acc).  dv_flag: ceil(H/64) x B words of
 // workspace in any state; epoch: a number no earlier launch on this workspace used (never 0).

@@ -41,6 +41,14 @@ CASES = [
     ("forward_row_mode_odd_h", 3, 21, 20, 250, 8, "f32", True),
     ("forward_row_mode_odd_h_bf16", 3, 21, 20, 511, 8, "bf16", False),
     ("forward_eight_waves_odd_h", 70, 61, 66, 777, 4, "f32", False),
+    # pre-kernel in parts (few blocks, more than 128 keys): parts of 64 keys with a short last one, masked parts, one and two
+    # rounds over the value columns, rows and columns that are no multiples of the tiles, few rows for the four waves of dV
+    ("pre_parts_one_key_in_the_last", 2, 45, 129, 40, 24, "f32", False),
+    ("pre_parts_two_rounds", 3, 33, 200, 24, 708, "f32", False),
+    ("pre_parts_full_round", 2, 17, 256, 24, 512, "f32", False),
+    ("pre_parts_few_rows_bf16", 4, 3, 137, 24, 68, "bf16", False),
+    ("pre_parts_two_rounds_bf16", 2, 70, 190, 24, 1024, "bf16", False),
+    ("pre_parts_keys_past_384", 1, 90, 470, 24, 40, "f32", False),
     ("forward_h_4", 2, 9, 13, 4, 4, "f32", False),
     ("forward_h_5", 2, 9, 13, 5, 4, "f32", False),
     ("forward_h_7_bf16", 2, 9, 70, 7, 4, "bf16", False),
