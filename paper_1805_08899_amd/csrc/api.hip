@@ -43,18 +43,22 @@ echo_status_t check_desc(const echo_attn_desc_t *d, AttnShape *s, int max_tk = k
 inline bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
 struct BwdWs {
-    size_t ds_off, rowsum_off, dvpart_off, order_off, dvflag_off, mail_off, mail_bytes, total;
+    size_t ds_off, rowsum_off, dvpart_off, order_off, dvflag_off, total;
+    bool split;                                          // launch_recompute_split is the form to take
 };
 BwdWs bwd_layout(const AttnShape &s) {
     BwdWs w;
+    // parts of dv and their flags: one part per sample, or what the form for few blocks asks for
+    size_t parts = 0, flags = 0;
+    w.split = echo::recompute_split_applies(s, &parts, &flags);
+    if (!w.split || parts < (size_t)s.B * s.H) parts = (size_t)s.B * s.H;
+    if (!w.split || flags < (size_t)s.B * ((s.H + 15) / 16)) flags = (size_t)s.B * ((s.H + 15) / 16);
     w.ds_off = 0;
     w.rowsum_off = align_up((size_t)s.B * s.Tq * echo::ds_pitch(s.Tk) * sizeof(float));
     w.dvpart_off = w.rowsum_off + align_up((size_t)s.B * s.Tq * sizeof(float));
-    w.order_off = w.dvpart_off + align_up((size_t)s.B * s.H * sizeof(float));
+    w.order_off = w.dvpart_off + align_up(parts * sizeof(float));
     w.dvflag_off = w.order_off + align_up((size_t)s.B * sizeof(int));
-    w.mail_off = w.dvflag_off + align_up((size_t)((s.H + 15) / 16) * s.B * sizeof(unsigned long long));
-    w.mail_bytes = echo::recompute_split_mail_bytes(s);
-    w.total = w.mail_off + align_up(w.mail_bytes);
+    w.total = w.dvflag_off + align_up(flags * sizeof(unsigned long long));
     return w;
 }
 // scores S [B,Tq,Tk] of the unfused forward kernels; the fused kernel keeps them in LDS and needs nothing
@@ -172,8 +176,8 @@ echo_status_t bwd_impl(const echo_attn_desc_t *desc, const float *dContext, cons
     unsigned long long *dv_flag = reinterpret_cast<unsigned long long *>(ws + lay.dvflag_off);
     ECHO_LAUNCH("bwd_pre", echo::launch_bwd_pre(s, dContext, V, P, key_len, dS, rowsum, order, dV, st));
     if (echo::bwd_pre_in_parts(s)) ECHO_LAUNCH("ds_finish", echo::launch_ds_finish(s, P, key_len, dS, rowsum, st));
-    if (!use_map && lay.mail_bytes > 0) {
-        ECHO_LAUNCH("recompute_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, dQp, dKp, ws + lay.mail_off,
+    if (!use_map && lay.split) {
+        ECHO_LAUNCH("recompute_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, dQp, dKp, dv_part, dv_flag,
                                                                     next_launch_number(), dv, st));
         return ECHO_OK;
     }
@@ -380,8 +384,8 @@ echo_status_t echo_attn_steps_bwd_keys(const echo_attn_desc_t *desc, const float
     int *order = reinterpret_cast<int *>(ws + lay.order_off);
     unsigned long long *dv_flag = reinterpret_cast<unsigned long long *>(ws + lay.dvflag_off);
     ECHO_LAUNCH("bwd_pre_dv", echo::launch_bwd_pre(s, dContext, nullptr, P, key_len, dS, rowsum, order, dV, st, false));
-    if (lay.mail_bytes > 0) {
-        ECHO_LAUNCH("recompute_keys_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, nullptr, dKp, ws + lay.mail_off,
+    if (lay.split) {
+        ECHO_LAUNCH("recompute_keys_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, nullptr, dKp, dv_part, dv_flag,
                                                                          next_launch_number(), dv, st));
         return ECHO_OK;
     }

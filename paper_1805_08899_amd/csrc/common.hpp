@@ -294,4 +294,69 @@ __device__ __forceinline__ int deal8_begin(int n, int w) {
     return (n >> 3) * w + __builtin_popcount(m & ((1u << w) - 1u));
 }
 
+// Parts of a sum handed by the blocks of a launch to the one that adds them, without a launch of its own: a part is written
+// through, its arrival awaited, then flagged with the launch's number; the block that adds, which must have been dispatched
+// after all that send, polls the flags (any initial state), reads the parts and sets the flags back to zero, so that a
+// captured launch, whose number is fixed, can be replayed.  (A release fence would make every block wait for its XCD's L2 to
+// write back everything; slots that carry the number next to every value need no wait at the sender but measured slower, 21.4
+// -> 24.0 us per recompute launch at B = 64: four times the bytes, all of them polled past the L2.)
+// Sender: the first wave of its block; `on`: this lane has a part.
+__device__ __forceinline__ void send_part(float *part, float x, bool on, unsigned long long *flag, unsigned long long epoch) {
+    if (on) store_agent(part, x);
+    wait_all_memory_ops();
+    if (lane_id() == 0) store_agent(flag, epoch);
+}
+// Receiver: all W waves of a block.  Parts p = 0 .. n - 1 of column h at parts[p * H + h], flagged by flags[p]; skip(p): part p is
+// not sent.  HW columns per block: lanes past HW take parts of their own.  Every lane adds its parts in order, then lane groups
+// and waves are added in order.  The result is in lanes < HW of wave 0, NaN if a part did not arrive within kSpinLimitTicks.
+// s_sum: 64 W floats; s_seen: W words.
+template <int HW, int W, typename Skip>
+__device__ __forceinline__ float sum_parts(const float *parts, unsigned long long *flags, int n, int H, int h,
+                                           unsigned long long epoch, Skip skip, float *s_sum, int *s_seen) {
+    constexpr int THREADS = 64 * W, NS = 64 / HW, STEP = W * NS;
+    const int lane = lane_id(), w = wave_id();
+    const long long t0 = wall_clock64();
+    bool seen = true;
+    for (int p = threadIdx.x; p < n; p += THREADS) {
+        if (skip(p)) continue;
+        while (load_agent(&flags[p]) != epoch) {
+            __builtin_amdgcn_s_sleep(4);
+            if (wall_clock64() - t0 > kSpinLimitTicks) {
+                seen = false;
+                break;
+            }
+        }
+    }
+    const int wave_seen = __all(seen) ? 1 : 0;
+    if (lane == 0) s_seen[w] = wave_seen;
+    lds_barrier();
+    bool all_seen = true;
+#pragma unroll
+    for (int k = 0; k < W; ++k) all_seen = all_seen && s_seen[k] != 0;
+    float sum = 0.f;
+    if (h < H && all_seen) {
+        for (int p0 = w * NS + lane / HW; p0 < n; p0 += 8 * STEP) {
+            float x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int p = p0 + STEP * u;
+                x[u] = p < n && !skip(p) ? load_agent(&parts[(size_t)p * H + h]) : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += x[u];
+        }
+    }
+    s_sum[w * 64 + lane] = sum;
+    lds_barrier();
+    float tot = 0.f;
+    if (w == 0 && lane < HW) {
+        for (int k = 0; k < W; ++k)
+#pragma unroll
+            for (int g = 0; g < NS; ++g) tot += s_sum[k * 64 + g * HW + lane];
+        if (!all_seen) tot = __builtin_nanf("");            // make the failure visible
+    }
+    for (int p = threadIdx.x; p < n; p += THREADS) store_agent(&flags[p], 0ull);
+    return tot;
+}
+
 }  // namespace echo

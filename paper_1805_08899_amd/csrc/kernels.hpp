@@ -62,7 +62,7 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
 bool bwd_pre_in_parts(const AttnShape &s);
 hipError_t launch_ds_finish(const AttnShape &s, const float *P, const int *key_len, float *dS, float *ds_rowsum, hipStream_t st);
 // B3 + B4  fused recompute: dQp, dKp, per-sample partials of dv (dv_part [B,H]) and, by the blocks that start
-// last, dv[h] = sum_b dv_part[b,h] in index order (added to dv if s.acc).  dv_flag: ceil(H/64) x B words of
+// last, dv[h] = sum_b dv_part[b,h] in index order (added to dv if s.acc).  dv_flag: ceil(H/16) x B words of
 // workspace in any state; epoch: a number no earlier launch on this workspace used (never 0).
 // tmap != nullptr reads tanh from the stashed map instead of recomputing it; dQp == nullptr: dQp is not wanted
 hipError_t launch_recompute(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
@@ -70,11 +70,12 @@ hipError_t launch_recompute(const AttnShape &s, const void *Qp, const void *Kp, 
                             float *dv_part, unsigned long long *dv_flag, unsigned long long epoch, float *dv,
                             hipStream_t st);
 // The same for launches that recompute.hip would run in too few blocks: every tanh twice, in many independent blocks.
-// mail: recompute_split_mail_bytes(s) bytes of workspace in any state (0: the shape does not take this form)
-size_t recompute_split_mail_bytes(const AttnShape &s);
+// parts, flags: as many floats and words of workspace in any state as recompute_split_applies says (false: the shape does not
+// take this form)
+bool recompute_split_applies(const AttnShape &s, size_t *part_floats, size_t *flag_words);
 hipError_t launch_recompute_split(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
-                                  const float *dS, float *dQp, float *dKp, void *mail, unsigned long long epoch, float *dv,
-                                  hipStream_t st);
+                                  const float *dS, float *dQp, float *dKp, float *parts, unsigned long long *flags,
+                                  unsigned long long epoch, float *dv, hipStream_t st);
 // B4  dv[h] = sum_b dv_part[b,h], fixed order
 hipError_t launch_dv_reduce(const AttnShape &s, const float *dv_part, float *dv, hipStream_t st);
 // One decoder step (Tq = 1) of the backward pass in one launch; dKp, dV and dv_part [B,H] are added to.

@@ -307,65 +307,22 @@ __global__ __launch_bounds__(RC_THREADS, 4) void k_recompute(
     s_dv[w][lane] = (accV[0] + accV[1]) + (accV[2] + accV[3]);
     lds_barrier();
     const int n_slots = gridDim.y;
-    unsigned long long *flags = dv_flag + (size_t)blockIdx.x * n_slots;      // of this slice of h, one per slot
+    unsigned long long *flags = dv_flag + (size_t)blockIdx.x * n_slots;      // of this slice of h, one per sample
     if (w == 0) {
-        if (hv) {
-            float tot = 0.f;
-#pragma unroll
-            for (int w2 = 0; w2 < RC_W; ++w2) tot += s_dv[w2][lane];
-            if constexpr (NS >= 2) tot = transpose_pair<32>(tot, tot, lane);
-            if constexpr (NS >= 4) tot = transpose_pair<16>(tot, tot, lane);
-            store_agent(&dv_part[(size_t)b * H + h], __builtin_fmaf(-2.f, tot, s_rowsum));
-        }
-        // B4 without a launch of its own: the part is published (written through, awaited, then flagged with
-        // this launch's number), and the block of the last slot, which starts last and holds the lightest
-        // sample, adds the parts of its slice of h once all of them are flagged.
-        wait_all_memory_ops();
-        if (lane == 0) store_agent(&flags[blockIdx.y], epoch);
-    }
-    if ((int)blockIdx.y != n_slots - 1) return;
-    lds_barrier();                                   // s_dv is reused below
-    const long long t_wait0 = wall_clock64();
-    int seen = 1;
-    for (int s0 = threadIdx.x; s0 < n_slots; s0 += RC_THREADS) {
-        while (load_agent(&flags[s0]) != epoch) {
-            __builtin_amdgcn_s_sleep(4);
-            if (wall_clock64() - t_wait0 > kSpinLimitTicks) {
-                seen = 0;
-                break;
-            }
-        }
-    }
-    // samples in index order, eight groups of them added group by group: the order of additions is fixed
-    float part = 0.f;
-    s_seen[w] = __all(seen) ? 1 : 0;
-    lds_barrier();
-    bool all_seen = true;
-#pragma unroll
-    for (int w2 = 0; w2 < RC_W; ++w2) all_seen = all_seen && s_seen[w2] != 0;
-    if (hv && all_seen) {
-        for (int b0 = w; b0 < n_slots; b0 += 8 * RC_W) {
-            float x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                x[u] = (b0 + RC_W * u < n_slots) ? load_agent(&dv_part[(size_t)(b0 + RC_W * u) * H + h]) : 0.f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) part += x[u];
-        }
-    }
-    s_dv[w][lane] = part;
-    lds_barrier();
-    if (w == 0 && hv) {
         float tot = 0.f;
 #pragma unroll
         for (int w2 = 0; w2 < RC_W; ++w2) tot += s_dv[w2][lane];
-        if (!all_seen) tot = __builtin_nanf("");      // a part never arrived: make the failure visible
-        dv[h] = acc ? dv[h] + tot : tot;
+        if constexpr (NS >= 2) tot = transpose_pair<32>(tot, tot, lane);
+        if constexpr (NS >= 4) tot = transpose_pair<16>(tot, tot, lane);
+        send_part(&dv_part[(size_t)b * H + h], __builtin_fmaf(-2.f, tot, s_rowsum), hv && (NS == 1 || sub == 0), &flags[b], epoch);
     }
-    // leave the flags cleared: a replay of a captured launch carries the same launch number
-    for (int s0 = threadIdx.x; s0 < n_slots; s0 += RC_THREADS) store_agent(&flags[s0], 0ull);
+    // B4 without a launch of its own: the block of the last slot, which starts last and holds the lightest sample, adds the
+    // parts of its slice of h
+    if ((int)blockIdx.y != n_slots - 1) return;
+    lds_barrier();                                   // s_dv is reused below
+    const float tot = sum_parts<HW, RC_W>(dv_part, flags, n_slots, H, h, epoch, [](int) { return false; }, &s_dv[0][0], s_seen);
+    if (w == 0 && lane < HW && hv) dv[h] = acc ? dv[h] + tot : tot;
 }
-
 
 template <typename T, bool STASH, int HW>
 static hipError_t launch_recompute_t(const AttnShape &s, const void *Qp, const void *Kp, const void *v,

@@ -14,8 +14,8 @@
 // rows are staged in LDS, one range of y at a time.  With YS > 1 the waves' sums meet in LDS at the end.  The order of all
 // additions is fixed.
 //
-// dv: every key-owning block hands its part (per column of h) to the last block of the slice through a mail slot; that
-// block, which starts last, adds the parts in order.
+// dv: every key-owning block hands its part (per column of h) to the last block of the slice, which starts last and adds the
+// parts in order (send_part, sum_parts).
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -81,7 +81,7 @@ __device__ __forceinline__ void rs_chunk(const float (&fx)[RS_R], const float (&
 template <typename T, int HW, bool KEYS>
 __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__restrict__ Y, const T *__restrict__ v,
                                          const float *__restrict__ ds, int pitch, float *__restrict__ out, bool add,
-                                         MailSlot *__restrict__ mail, unsigned long long epoch, int x_first, int n_x,
+                                         float *part, unsigned long long *flag, unsigned long long epoch, int x_first, int n_x,
                                          int n_out, int n_y, int H, int h0, int ys, int y_tile, float *__restrict__ s_d,
                                          float *__restrict__ s_red) {
     constexpr int NS = 64 / HW;
@@ -228,7 +228,7 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
         }
         if constexpr (NS >= 2) tot += __shfl_xor(tot, 32);
         if constexpr (NS >= 4) tot += __shfl_xor(tot, 16);
-        if (sub == 0 && hv) mail_put(mail + h, __builtin_fmaf(-2.f, tot, dtot), epoch);   // sum dS t = sum dS - 2 sum dS r
+        send_part(part + h, __builtin_fmaf(-2.f, tot, dtot), sub == 0 && hv, flag, epoch);   // sum dS t = sum dS - 2 sum dS r
     }
 }
 
@@ -236,8 +236,8 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
 template <typename T, int HW>
 __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ v, const int *__restrict__ order,
-    const float *__restrict__ dS, float *__restrict__ dQp, float *__restrict__ dKp, MailSlot *__restrict__ mail,
-    unsigned long long epoch, float *__restrict__ dv, int Tq, int Tk, int H, int pitch, RsAxis ka, RsAxis qa, int acc) {
+    const float *__restrict__ dS, float *__restrict__ dQp, float *__restrict__ dKp, float *parts,
+    unsigned long long *flags, unsigned long long epoch, float *__restrict__ dv, int Tq, int Tk, int H, int pitch, RsAxis ka, RsAxis qa, int acc) {
     __shared__ __align__(16) float s_d[RS_TILE];
     __shared__ __align__(16) float s_red[RS_W * RS_R * 64 + RS_W * 64 + RS_W];
     __shared__ int s_seen[RS_W];
@@ -246,14 +246,15 @@ __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
     const int h0 = blockIdx.x * HW;
     const int n_slots = gridDim.y;
     const int z = blockIdx.z;
+    unsigned long long *slice_flags = flags + (size_t)blockIdx.x * n_slots * ka.groups;
     const T *qb = Qp + (size_t)b * Tq * H, *kb = Kp + (size_t)b * Tk * H;
     const float *dsb = dS + (size_t)b * Tq * pitch;
     if (z < ka.groups) {
         const int x0 = z * rs_rows(HW, ka.ys);
         if (x0 < L) {
             rs_block<T, HW, true>(kb, qb, v, dsb, pitch, dKp + (size_t)b * Tk * H, acc != 0,
-                                  mail + ((size_t)blockIdx.y * ka.groups + z) * H, epoch, x0, L, Tk, Tq, H, h0, ka.ys,
-                                  ka.y_tile, s_d, s_red);
+                                  parts + ((size_t)blockIdx.y * ka.groups + z) * H, slice_flags + blockIdx.y * ka.groups + z,
+                                  epoch, x0, L, Tk, Tq, H, h0, ka.ys, ka.y_tile, s_d, s_red);
         } else if (!acc) {                                  // masked keys only: exact zeros
             const int n = min(rs_rows(HW, ka.ys), Tk - x0), lh = threadIdx.x % HW;
             for (int x = threadIdx.x / HW; x < n; x += RS_THREADS / HW)
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
         const int x0 = (z - ka.groups) * rs_rows(HW, qa.ys);
         float *out = dQp + (size_t)b * Tq * H;
         if (L > 0) {
-            rs_block<T, HW, false>(qb, kb, v, dsb, pitch, out, false, nullptr, 0, x0, Tq, Tq, L, H, h0, qa.ys, qa.y_tile,
+            rs_block<T, HW, false>(qb, kb, v, dsb, pitch, out, false, nullptr, nullptr, 0, x0, Tq, Tq, L, H, h0, qa.ys, qa.y_tile,
                                    s_d, s_red);
         } else {
             const int n = min(rs_rows(HW, qa.ys), Tq - x0), lh = threadIdx.x % HW;
@@ -273,71 +274,14 @@ __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
     }
     if (z != (int)gridDim.z - 1 || (int)blockIdx.y != n_slots - 1) return;
 
-    // ---- the last block of the slice: dv = the parts of all samples and key groups, each wave every eighth in order,
-    // then the waves in order.  All blocks it waits for were dispatched before it.
+    // ---- the last block of the slice: dv = the parts of all samples and key groups; groups past a sample's last valid key
+    // send nothing
     lds_barrier();                                          // s_red is reused
-    const int lane = lane_id(), w = wave_id();
-    const int h = h0 + lane % HW;
-    const int key_rows = rs_rows(HW, ka.ys);
-    const int n_parts = n_slots * ka.groups;
-    constexpr int U = 4, STEP = RS_W * 64 / HW;             // parts in flight per lane; lanes past HW take parts of their own
-    const int p_first = w * (64 / HW) + lane / HW;
-    const long long t0 = wall_clock64();
-    float sum = 0.f;
-    bool ok = true;
-    if (h < H) {
-        for (int p0 = p_first; p0 < n_parts; p0 += U * STEP) {
-            float x[U];
-            bool there[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int p = p0 + u * STEP;
-                x[u] = 0.f;
-                // groups past the sample's last valid key send nothing
-                there[u] = p >= n_parts || (p % ka.groups) * key_rows >= (order[min(p, n_parts - 1) / ka.groups] >> 16);
-            }
-            for (;;) {
-                bool all = true;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (there[u]) continue;
-                    MailSlot *s = mail + (size_t)(p0 + u * STEP) * H + h;
-                    float y;
-                    if (mail_try(s, epoch, y)) {
-                        x[u] = y;
-                        there[u] = true;
-                        store_agent(&s->w0, 0ull);
-                        store_agent(&s->w1, 0ull);
-                    } else {
-                        all = false;
-                    }
-                }
-                if (all) break;
-                if (wall_clock64() - t0 > kSpinLimitTicks) {
-                    ok = false;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-            if (!ok) break;
-#pragma unroll
-            for (int u = 0; u < U; ++u) sum += x[u];
-        }
-    }
-    s_red[w * 64 + lane] = sum;
-    const int all_ok = __all(ok) ? 1 : 0;
-    if (lane == 0) s_seen[w] = all_ok;
-    lds_barrier();
-    if (w == 0 && lane < HW && h < H) {
-        float tot = 0.f;
-        bool seen = true;
-        for (int k = 0; k < RS_W; ++k) {
-            for (int g = 0; g < 64 / HW; ++g) tot += s_red[k * 64 + g * HW + lane];
-            seen = seen && s_seen[k] != 0;
-        }
-        if (!seen) tot = __builtin_nanf("");                // a part never arrived: make the failure visible
-        dv[h] = acc ? dv[h] + tot : tot;
-    }
+    const int h = h0 + lane_id() % HW, key_rows = rs_rows(HW, ka.ys);
+    const float tot = sum_parts<HW, RS_W>(parts, slice_flags, n_slots * ka.groups, H, h, epoch,
+                                          [&](int p) { return (p % ka.groups) * key_rows >= (order[p / ka.groups] >> 16); },
+                                          s_red, s_seen);
+    if (wave_id() == 0 && lane_id() < HW && h < H) dv[h] = acc ? dv[h] + tot : tot;
 }
 
 // ---- host side ------------------------------------------------------------------------------------------------------
@@ -345,7 +289,7 @@ __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
 constexpr int RS_ROUND = 512;              // two blocks on every compute unit (128 registers per lane)
 constexpr float RS_BLOCK_US = 4.0f, RS_CHUNK_US = 1.1f;
 constexpr int RS_MOST_BLOCKS = 192;
-constexpr size_t RS_MOST_SLOTS = 1 << 18;  // 4 MB of mail
+constexpr size_t RS_MOST_PARTS = 1 << 20;  // floats: 4 MB
 
 // Blocks of one kind per sample and slice when n_x rows are owned and ys waves share a row group.
 static int rs_groups(int hw, int ys, int n_x) { return (n_x + rs_rows(hw, ys) - 1) / rs_rows(hw, ys); }
@@ -400,45 +344,48 @@ static RsPlan rs_plan(const AttnShape &s) {
 // 53 -> 13 us at B = 3, T = 200, H = 76; above it evaluating every tanh twice loses).  Samples of hardly more than a key tile
 // and a row per wave stay with the other form, which is then done before this one has exchanged its parts of dv (7.4
 // against 9.5 us at B = 50, T = 9 / 15).
-size_t recompute_split_mail_bytes(const AttnShape &s) {
-    if ((long long)s.B * ((s.H + 15) / 16) > RS_MOST_BLOCKS || (long long)s.Tq * s.Tk <= 150) return 0;
+bool recompute_split_applies(const AttnShape &s, size_t *part_floats, size_t *flag_words) {
+    if ((long long)s.B * ((s.H + 15) / 16) > RS_MOST_BLOCKS || (long long)s.Tq * s.Tk <= 150) return false;
     const RsPlan p = rs_plan(s);
-    const size_t slots = (size_t)s.B * p.ka.groups * s.H;
-    return slots <= RS_MOST_SLOTS ? slots * sizeof(MailSlot) : 0;
+    *part_floats = (size_t)s.B * p.ka.groups * s.H;
+    *flag_words = (size_t)s.B * p.ka.groups * ((s.H + p.hw - 1) / p.hw);
+    return *part_floats <= RS_MOST_PARTS;
 }
 
 template <typename T, int HW>
 static hipError_t launch_split_t(const AttnShape &s, const RsPlan &p, const void *Qp, const void *Kp, const void *v, const int *order,
-                                 const float *dS, float *dQp, float *dKp, MailSlot *mail, unsigned long long epoch, float *dv,
+                                 const float *dS, float *dQp, float *dKp, float *parts, unsigned long long *flags, unsigned long long epoch,
+                                 float *dv,
                                  hipStream_t st) {
     const RsAxis ka = p.ka;
     RsAxis qa = p.qa;
     if (!dQp) qa.groups = 0;
     dim3 grid((s.H + HW - 1) / HW, s.B, ka.groups + qa.groups);
     if (grid.z > 65535) return hipErrorInvalidValue;
-    k_recompute_split<T, HW><<<grid, RS_THREADS, 0, st>>>((const T *)Qp, (const T *)Kp, (const T *)v, order, dS, dQp, dKp, mail,
+    k_recompute_split<T, HW><<<grid, RS_THREADS, 0, st>>>((const T *)Qp, (const T *)Kp, (const T *)v, order, dS, dQp, dKp, parts, flags,
                                                           epoch, dv, s.Tq, s.Tk, s.H, ds_pitch(s.Tk), ka, qa, s.acc ? 1 : 0);
     return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t launch_split_hw(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
-                                  const float *dS, float *dQp, float *dKp, void *mail, unsigned long long epoch, float *dv,
+                                  const float *dS, float *dQp, float *dKp, float *parts, unsigned long long *flags, unsigned long long epoch,
+                                  float *dv,
                                   hipStream_t st) {
-    MailSlot *m = static_cast<MailSlot *>(mail);
     const RsPlan p = rs_plan(s);
     switch (p.hw) {
-        case 16: return launch_split_t<T, 16>(s, p, Qp, Kp, v, order, dS, dQp, dKp, m, epoch, dv, st);
-        case 32: return launch_split_t<T, 32>(s, p, Qp, Kp, v, order, dS, dQp, dKp, m, epoch, dv, st);
-        default: return launch_split_t<T, 64>(s, p, Qp, Kp, v, order, dS, dQp, dKp, m, epoch, dv, st);
+        case 16: return launch_split_t<T, 16>(s, p, Qp, Kp, v, order, dS, dQp, dKp, parts, flags, epoch, dv, st);
+        case 32: return launch_split_t<T, 32>(s, p, Qp, Kp, v, order, dS, dQp, dKp, parts, flags, epoch, dv, st);
+        default: return launch_split_t<T, 64>(s, p, Qp, Kp, v, order, dS, dQp, dKp, parts, flags, epoch, dv, st);
     }
 }
 
 hipError_t launch_recompute_split(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
-                                  const float *dS, float *dQp, float *dKp, void *mail, unsigned long long epoch, float *dv,
+                                  const float *dS, float *dQp, float *dKp, float *parts, unsigned long long *flags, unsigned long long epoch,
+                                  float *dv,
                                   hipStream_t st) {
-    return s.bf16 ? launch_split_hw<bf16_t>(s, Qp, Kp, v, order, dS, dQp, dKp, mail, epoch, dv, st)
-                  : launch_split_hw<float>(s, Qp, Kp, v, order, dS, dQp, dKp, mail, epoch, dv, st);
+    return s.bf16 ? launch_split_hw<bf16_t>(s, Qp, Kp, v, order, dS, dQp, dKp, parts, flags, epoch, dv, st)
+                  : launch_split_hw<float>(s, Qp, Kp, v, order, dS, dQp, dKp, parts, flags, epoch, dv, st);
 }
 
 }  // namespace echo
