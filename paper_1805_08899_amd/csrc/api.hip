@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <string>
@@ -45,14 +46,16 @@ inline bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) &
 struct BwdWs {
     size_t ds_off, rowsum_off, dvpart_off, order_off, dvflag_off, total;
     bool split;                                          // launch_recompute_split is the form to take
+    bool small;                                          // launch_bwd_small is (instead of all other launches)
 };
 BwdWs bwd_layout(const AttnShape &s) {
     BwdWs w;
-    // parts of dv and their flags: one part per sample, or what the form for few blocks asks for
-    size_t parts = 0, flags = 0;
-    w.split = echo::recompute_split_applies(s, &parts, &flags);
-    if (!w.split || parts < (size_t)s.B * s.H) parts = (size_t)s.B * s.H;
-    if (!w.split || flags < (size_t)s.B * ((s.H + 15) / 16)) flags = (size_t)s.B * ((s.H + 15) / 16);
+    // parts of dv and their flags: one part per sample, or what the forms for few blocks ask for
+    size_t parts = (size_t)s.B * s.H, flags = (size_t)s.B * ((s.H + 15) / 16), p = 0, f = 0;
+    w.split = echo::recompute_split_applies(s, &p, &f);
+    if (w.split) parts = std::max(parts, p), flags = std::max(flags, f);
+    w.small = echo::bwd_small_applies(s, &p, &f);
+    if (w.small) parts = std::max(parts, p), flags = std::max(flags, f);
     w.ds_off = 0;
     w.rowsum_off = align_up((size_t)s.B * s.Tq * echo::ds_pitch(s.Tk) * sizeof(float));
     w.dvpart_off = w.rowsum_off + align_up((size_t)s.B * s.Tq * sizeof(float));
@@ -174,6 +177,11 @@ echo_status_t bwd_impl(const echo_attn_desc_t *desc, const float *dContext, cons
     float *dv_part = reinterpret_cast<float *>(ws + lay.dvpart_off);
     int *order = reinterpret_cast<int *>(ws + lay.order_off);
     unsigned long long *dv_flag = reinterpret_cast<unsigned long long *>(ws + lay.dvflag_off);
+    if (!use_map && lay.small) {
+        ECHO_LAUNCH("bwd_small", echo::launch_bwd_small(s, dContext, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, dv_part, dv_flag,
+                                                        next_launch_number(), dv, st));
+        return ECHO_OK;
+    }
     ECHO_LAUNCH("bwd_pre", echo::launch_bwd_pre(s, dContext, V, P, key_len, dS, rowsum, order, dV, st));
     if (echo::bwd_pre_in_parts(s)) ECHO_LAUNCH("ds_finish", echo::launch_ds_finish(s, P, key_len, dS, rowsum, st));
     if (!use_map && lay.split) {

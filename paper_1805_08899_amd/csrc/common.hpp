@@ -234,6 +234,10 @@ __device__ __forceinline__ void group_transpose_sum(float (&a)[N]) {
     TransposeSumStep<N, G / 2>::run(a, lane_id());
 }
 
+__device__ __forceinline__ f32x4 mfma16(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 // Barrier for data exchanged through LDS only: waits for this wave's LDS operations, not for its global
 // loads and stores (__syncthreads() would also wait for every prefetch and store in flight).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

@@ -76,6 +76,11 @@ bool recompute_split_applies(const AttnShape &s, size_t *part_floats, size_t *fl
 hipError_t launch_recompute_split(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order,
                                   const float *dS, float *dQp, float *dKp, float *parts, unsigned long long *flags,
                                   unsigned long long epoch, float *dv, hipStream_t st);
+// The whole backward of a small batch in one launch (instead of launch_bwd_pre and launch_recompute).  parts, flags: as above.
+bool bwd_small_applies(const AttnShape &s, size_t *part_floats, size_t *flag_words);
+hipError_t launch_bwd_small(const AttnShape &s, const float *dC, const float *P, const void *V, const void *Qp, const void *Kp,
+                            const void *v, const int *key_len, float *dQp, float *dKp, float *dV, float *parts,
+                            unsigned long long *flags, unsigned long long epoch, float *dv, hipStream_t st);
 // B4  dv[h] = sum_b dv_part[b,h], fixed order
 hipError_t launch_dv_reduce(const AttnShape &s, const float *dv_part, float *dv, hipStream_t st);
 // One decoder step (Tq = 1) of the backward pass in one launch; dKp, dV and dv_part [B,H] are added to.

@@ -14,6 +14,8 @@
 // rows are staged in LDS, one range of y at a time.  With YS > 1 the waves' sums meet in LDS at the end.  The order of all
 // additions is fixed.
 //
+// k_bwd_small is the same with everything that comes before it: the whole backward of a small batch in one launch.
+//
 // dv: every key-owning block hands its part (per column of h) to the last block of the slice, which starts last and adds the
 // parts in order (send_part, sum_parts).
 #include "common.hpp"
@@ -34,6 +36,10 @@ struct RsAxis {                            // how a kind of block cuts its axes 
 };
 // rows of one block
 __host__ __device__ constexpr int rs_rows(int hw, int ys) { return RS_W / ys * RS_R * (64 / hw); }
+
+// row pitch of the staged dS: an odd multiple of four floats, so that the lane groups of a narrow slice read their rows from
+// different banks
+__host__ __device__ constexpr int rs_pitch(int y_tile) { return RS_C * ((y_tile / RS_C) | 1); }
 
 // One chunk: eight rows of a lane against four y.  EXACT: fx, fy hold 2 log2e x and the exponential of the sum is taken.
 template <bool EXACT, bool DV>
@@ -77,13 +83,17 @@ __device__ __forceinline__ void rs_chunk(const float (&fx)[RS_R], const float (&
 }
 
 // X: rows of the owned axis [n_x valid rows, row stride H], Y: rows of the axis summed over [n_y rows].  out: rows of the
-// result.  KEYS: x = keys, y = queries (dKp, dv), else x = queries, y = keys (dQp).  ds: the sample's dS [query][key].
-template <typename T, int HW, bool KEYS>
+// result.  KEYS: x = keys, y = queries (dKp, dv), else x = queries, y = keys (dQp).
+// stage(y0, ny): puts the dS entries of the block's rows for y0 .. y0 + ny - 1 into s_d [row][y], zeros where they are to add
+// nothing, and returns this thread's share of their sum; it is called after the first loads of the block (or range) have
+// been requested, and a barrier follows it.  s_red: RS_W RS_R 64 floats, s_v: RS_W 65 floats.
+template <typename T, int HW, bool KEYS, typename Stage>
 __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__restrict__ Y, const T *__restrict__ v,
-                                         const float *__restrict__ ds, int pitch, float *__restrict__ out, bool add,
-                                         float *part, unsigned long long *flag, unsigned long long epoch, int x_first, int n_x,
-                                         int n_out, int n_y, int H, int h0, int ys, int y_tile, float *__restrict__ s_d,
-                                         float *__restrict__ s_red) {
+                                         float *__restrict__ out, bool add, float *part,
+                                         unsigned long long *flag, unsigned long long epoch, int x_first, int n_x,
+                                         int n_out, int n_y, int H, int h0, int ys, int y_tile,
+                                         const float *__restrict__ s_d, int d_pitch, float *__restrict__ s_red,
+                                         float *__restrict__ s_v, Stage stage) {
     constexpr int NS = 64 / HW;
     typedef RawElem<T> Raw;
     const int lane = lane_id(), w = wave_id();
@@ -92,7 +102,6 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
     const bool hv = h < H;
     const int hc = hv ? h : H - 1;
     const int yg = w & (ys - 1), xg = w / ys;
-    const int rows = rs_rows(HW, ys);                       // of this block
     const int xl = xg * RS_R * NS + sub;                    // this lane's rows: x_first + xl + NS a
     const bool wave_on = x_first + xg * RS_R * NS < n_x;    // the wave has valid rows
 
@@ -106,9 +115,6 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
     for (int a = 0; a < RS_R; ++a) acc[a] = 0.f;
     bool x_big = false, first = true;
     float d_sum = 0.f;
-    // an odd multiple of four floats: the lane groups of a narrow slice read four rows at once from different banks
-    const int d_pitch = RS_C * ((y_tile / RS_C) | 1);
-
     for (int y0 = 0; y0 < n_y; y0 += y_tile) {
         const int ny = min(y_tile, n_y - y0);
         const int ny4 = (ny + RS_C - 1) & ~(RS_C - 1);
@@ -120,36 +126,7 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
         };
         fetch(RS_C * yg);
         if (!first) lds_barrier();                          // everybody is done with the previous range
-        // dS of (rows, range), four entries of a dS row per load, all loads of the range under way together; the pads of a
-        // dS row and its masked keys are stored zeros, rows past the end become zeros here: they add nothing
-        constexpr int U = (RS_TILE / 4 + RS_THREADS - 1) / RS_THREADS;
-        const int n_vec = rows * ny4 / 4, per_row = KEYS ? rows / 4 : ny4 / 4;
-        const float inv = fast_rcp((float)per_row);         // (e + 0.5) inv: exact quotient for e < 2^16
-        float4 d4[U];
-        int at[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int e = (int)threadIdx.x + u * RS_THREADS;
-            const int r = (int)(((float)e + 0.5f) * inv), c = 4 * (e - r * per_row);
-            const int xr = KEYS ? c : r, yr = KEYS ? r : c;
-            at[u] = e < n_vec ? xr * d_pitch + yr : -1;
-            d4[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (KEYS ? (e < n_vec && yr < ny && x_first + xr < pitch) : (e < n_vec && x_first + xr < n_x))
-                d4[u] = KEYS ? ld4(ds, (size_t)(y0 + yr) * pitch + x_first + xr) : ld4(ds, (size_t)(x_first + xr) * pitch + y0 + yr);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (at[u] < 0) continue;
-            if (KEYS) {
-                s_d[at[u]] = d4[u].x;
-                s_d[at[u] + d_pitch] = d4[u].y;
-                s_d[at[u] + 2 * d_pitch] = d4[u].z;
-                s_d[at[u] + 3 * d_pitch] = d4[u].w;
-                d_sum += (d4[u].x + d4[u].y) + (d4[u].z + d4[u].w);
-            } else {
-                *reinterpret_cast<float4 *>(s_d + at[u]) = d4[u];
-            }
-        }
+        d_sum += stage(y0, ny);
         if (first) {
             asm volatile("" : "+v"(v_raw));
 #pragma unroll
@@ -185,6 +162,8 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
     }
 
     const float v4 = hv ? 4.f * Raw::value(v_raw) : 0.f;
+    int x_out = x_first + xl;
+    asm volatile("" : "+v"(x_out));                         // addresses formed here, not kept since the loads
     auto store = [&](int x, float val) {
         if (x >= n_out || !hv) return;
         float *dst = out + (size_t)x * H + h;
@@ -198,13 +177,12 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
     };
     if (ys == 1) {
 #pragma unroll
-        for (int a = 0; a < RS_R; ++a) store(x_first + xl + NS * a, v4 * acc[a]);
+        for (int a = 0; a < RS_R; ++a) store(x_out + NS * a, v4 * acc[a]);
     } else {
 #pragma unroll
         for (int a = 0; a < RS_R; ++a) s_red[(w * RS_R + a) * 64 + lane] = acc[a];
     }
     if (KEYS) {
-        float *s_v = s_red + RS_W * RS_R * 64;              // [RS_W][64], then RS_W sums of dS
         s_v[w * 64 + lane] = (acc_v[0] + acc_v[1]) + (acc_v[2] + acc_v[3]);
         d_sum = wave_sum(d_sum);
         if (lane == 0) s_v[RS_W * 64 + w] = d_sum;
@@ -215,11 +193,10 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
         for (int a = yg; a < RS_R; a += ys) {
             float tot = 0.f;
             for (int k = 0; k < ys; ++k) tot += s_red[((xg * ys + k) * RS_R + a) * 64 + lane];
-            store(x_first + xl + NS * a, v4 * tot);
+            store(x_out + NS * a, v4 * tot);
         }
     }
     if (KEYS && w == 0) {
-        const float *s_v = s_red + RS_W * RS_R * 64;
         float tot = 0.f, dtot = 0.f;
 #pragma unroll
         for (int k = 0; k < RS_W; ++k) {
@@ -230,6 +207,46 @@ __device__ __forceinline__ void rs_block(const T *__restrict__ X, const T *__res
         if constexpr (NS >= 4) tot += __shfl_xor(tot, 16);
         send_part(part + h, __builtin_fmaf(-2.f, tot, dtot), sub == 0 && hv, flag, epoch);   // sum dS t = sum dS - 2 sum dS r
     }
+}
+
+// Stager from memory: the sample's dS [query][key], rows x_first ..; n_x valid rows.
+template <int HW, bool KEYS>
+__device__ __forceinline__ float rs_stage(const float *__restrict__ ds, int pitch, int x_first, int n_x, int ys, int y0, int ny,
+                                          float *__restrict__ s_d, int d_pitch) {
+    const int rows = rs_rows(HW, ys);
+    const int ny4 = (ny + RS_C - 1) & ~(RS_C - 1);
+    float d_sum = 0.f;
+    // dS of (rows, range), four entries of a dS row per load, all loads of the range under way together; the pads of a
+    // dS row and its masked keys are stored zeros, rows past the end become zeros here: they add nothing
+    constexpr int U = (RS_TILE / 4 + RS_THREADS - 1) / RS_THREADS;
+    const int n_vec = rows * ny4 / 4, per_row = KEYS ? rows / 4 : ny4 / 4;
+    const float inv = fast_rcp((float)per_row);         // (e + 0.5) inv: exact quotient for e < 2^16
+    float4 d4[U];
+    int at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int e = (int)threadIdx.x + u * RS_THREADS;
+        const int r = (int)(((float)e + 0.5f) * inv), c = 4 * (e - r * per_row);
+        const int xr = KEYS ? c : r, yr = KEYS ? r : c;
+        at[u] = e < n_vec ? xr * d_pitch + yr : -1;
+        d4[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (KEYS ? (e < n_vec && yr < ny && x_first + xr < pitch) : (e < n_vec && x_first + xr < n_x))
+            d4[u] = KEYS ? ld4(ds, (size_t)(y0 + yr) * pitch + x_first + xr) : ld4(ds, (size_t)(x_first + xr) * pitch + y0 + yr);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (at[u] < 0) continue;
+        if (KEYS) {
+            s_d[at[u]] = d4[u].x;
+            s_d[at[u] + d_pitch] = d4[u].y;
+            s_d[at[u] + 2 * d_pitch] = d4[u].z;
+            s_d[at[u] + 3 * d_pitch] = d4[u].w;
+            d_sum += (d4[u].x + d4[u].y) + (d4[u].z + d4[u].w);
+        } else {
+            *reinterpret_cast<float4 *>(s_d + at[u]) = d4[u];
+        }
+    }
+    return d_sum;
 }
 
 // grid (slices of h, samples heaviest first, groups of keys then groups of queries)
@@ -252,9 +269,11 @@ __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
     if (z < ka.groups) {
         const int x0 = z * rs_rows(HW, ka.ys);
         if (x0 < L) {
-            rs_block<T, HW, true>(kb, qb, v, dsb, pitch, dKp + (size_t)b * Tk * H, acc != 0,
+            const int dp = rs_pitch(ka.y_tile);
+            rs_block<T, HW, true>(kb, qb, v, dKp + (size_t)b * Tk * H, acc != 0,
                                   parts + ((size_t)blockIdx.y * ka.groups + z) * H, slice_flags + blockIdx.y * ka.groups + z,
-                                  epoch, x0, L, Tk, Tq, H, h0, ka.ys, ka.y_tile, s_d, s_red);
+                                  epoch, x0, L, Tk, Tq, H, h0, ka.ys, ka.y_tile, s_d, dp, s_red, s_red + RS_W * RS_R * 64,
+                                  [&](int y0, int ny) { return rs_stage<HW, true>(dsb, pitch, x0, L, ka.ys, y0, ny, s_d, dp); });
         } else if (!acc) {                                  // masked keys only: exact zeros
             const int n = min(rs_rows(HW, ka.ys), Tk - x0), lh = threadIdx.x % HW;
             for (int x = threadIdx.x / HW; x < n; x += RS_THREADS / HW)
@@ -264,8 +283,10 @@ __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
         const int x0 = (z - ka.groups) * rs_rows(HW, qa.ys);
         float *out = dQp + (size_t)b * Tq * H;
         if (L > 0) {
-            rs_block<T, HW, false>(qb, kb, v, dsb, pitch, out, false, nullptr, nullptr, 0, x0, Tq, Tq, L, H, h0, qa.ys, qa.y_tile,
-                                   s_d, s_red);
+            const int dp = rs_pitch(qa.y_tile);
+            rs_block<T, HW, false>(qb, kb, v, out, false, nullptr, nullptr, 0, x0, Tq, Tq, L, H, h0, qa.ys, qa.y_tile, s_d, dp,
+                                   s_red, s_red + RS_W * RS_R * 64,
+                                   [&](int y0, int ny) { return rs_stage<HW, false>(dsb, pitch, x0, Tq, qa.ys, y0, ny, s_d, dp); });
         } else {
             const int n = min(rs_rows(HW, qa.ys), Tq - x0), lh = threadIdx.x % HW;
             for (int x = threadIdx.x / HW; x < n; x += RS_THREADS / HW)
@@ -284,10 +305,254 @@ __global__ __launch_bounds__(RS_THREADS, 4) void k_recompute_split(
     if (wave_id() == 0 && lane_id() < HW && h < H) dv[h] = acc ? dv[h] + tot : tot;
 }
 
+// ---- the whole backward in one launch -------------------------------------------------------------------------------
+
+constexpr int BS_ROWS = 64;                // most query rows and most keys
+constexpr int BS_PITCH = BS_ROWS + 4;      // floats: an odd multiple of 16 bytes
+
+// What a block of k_bwd_small keeps in LDS.
+struct BsLds {
+    float stage[2 * BS_ROWS * BS_PITCH];   // a piece of dC and of V; then dP, in parts; then (second half) the last reduction
+    float d[BS_ROWS * BS_PITCH];           // the dS entries of the block's rows
+    float s_v[RS_W * 64 + RS_W];
+    int seen[RS_W];
+};
+constexpr int BS_HALF = BS_ROWS * BS_PITCH;
+
+// dS of the block's rows from dC, V and P.  Every block forms the whole dP of its sample: the softmax backward needs whole rows,
+// and at up to 16 tiles of 16 x 16 this is cheaper than a launch of its own and the trip of dS through memory.  dC and V pass
+// through LDS in pieces of 64, 128 or 256 columns (64, 32 or 16 rows of each: two 16-byte loads of each per thread), the next
+// piece on its way in registers.  The tiles are dealt to the waves; with four or fewer, the columns of a piece are too.
+template <typename T>
+struct BsScores {
+    const float *dC;
+    const T *V;
+    int Tq, Tk, Dv, cols_log;              // columns of a piece: 1 << cols_log
+    float pr[8];                           // P of the rows this wave finishes: w, w + 8, ..; a key per lane
+    float4 c4[2];
+    RawKey<T> v4[2];
+
+    __device__ __forceinline__ void fetch(int d0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {      // rows and columns past the ends repeat the last ones
+            const int e = (int)threadIdx.x + u * RS_THREADS;
+            const int row = e >> (cols_log - 2), col = min(d0 + 4 * (e & ((1 << (cols_log - 2)) - 1)), Dv - 4);
+            c4[u] = ld4(dC, (size_t)min(row, Tq - 1) * Dv + col);
+            v4[u].load(V, (size_t)min(row, Tk - 1) * Dv + col);
+        }
+    }
+    // what does not depend on the sample's key count
+    __device__ __forceinline__ void start(const float *P) {
+        const int rows = max(Tq, Tk);
+        cols_log = rows <= 16 ? 8 : rows <= 32 ? 7 : 6;
+        fetch(0);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) pr[t] = P[min(wave_id() + 8 * t, Tq - 1) * Tk + min(lane_id(), Tk - 1)];
+    }
+    // dS into lds.d (KEYS: [key - x0][query], else [query - x0][key]), zeros beyond Tq and the L > 0 valid keys; returns this
+    // thread's share of the sum over the block's keys (KEYS)
+    template <bool KEYS>
+    __device__ __forceinline__ float finish(int x0, int rows, int L, BsLds &lds) {
+        const int lane = lane_id(), w = wave_id();
+        const int lm = lane & 15, lk = lane >> 4;
+        const int mt = (Tq + 15) / 16, nt = (L + 15) / 16;
+        // both counts rounded up to powers of two: waves side by side, one tile (of 16: two) each, and shares of a piece's columns
+        const int m_log = mt > 2 ? 2 : mt - 1, n_log = nt > 2 ? 2 : nt - 1;
+        const int dealt_log = min(m_log + n_log, 3), shares = RS_W >> dealt_log, share = w >> dealt_log;
+        const int tm = (w & ((1 << dealt_log) - 1)) >> n_log, tn = w & ((1 << n_log) - 1);      // tiles (tm, tn), (tm + 2, tn)
+        const int pitch = (1 << cols_log) + 4;
+        f32x4 acc[2];
+        acc[0] = acc[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int d0 = 0; d0 < Dv; d0 += 1 << cols_log) {
+            if (d0 > 0) lds_barrier();                       // everybody is done with the previous piece
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int e = (int)threadIdx.x + u * RS_THREADS;
+                const int row = e >> (cols_log - 2), col = 4 * (e & ((1 << (cols_log - 2)) - 1));
+                // columns past Dv add nothing
+                *reinterpret_cast<float4 *>(lds.stage + row * pitch + col) = d0 + col < Dv ? c4[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+                *reinterpret_cast<float4 *>(lds.stage + BS_HALF + row * pitch + col) = v4[u].get();
+            }
+            if (d0 + (1 << cols_log) < Dv) fetch(d0 + (1 << cols_log));
+            lds_barrier();
+            const int n_u = (min(1 << cols_log, Dv - d0) + 15) / 16;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                if (tm + 2 * t < mt && tn < nt && (t == 0 || m_log + n_log == 4)) {            // uniform
+                    const float *a_row = lds.stage + (16 * (tm + 2 * t) + lm) * pitch + 4 * lk;
+                    const float *b_row = lds.stage + BS_HALF + (16 * tn + lm) * pitch + 4 * lk;
+                    for (int u = share; u < n_u; u += shares) {
+                        const float4 a = *reinterpret_cast<const float4 *>(a_row + 16 * u);
+                        const float4 b = *reinterpret_cast<const float4 *>(b_row + 16 * u);
+                        acc[t] = mfma16(a.x, b.x, acc[t]);
+                        acc[t] = mfma16(a.y, b.y, acc[t]);
+                        acc[t] = mfma16(a.z, b.z, acc[t]);
+                        acc[t] = mfma16(a.w, b.w, acc[t]);
+                    }
+                }
+            }
+        }
+        lds_barrier();
+        // the shares' tiles, then their sums: shares x 16 mt rows fit, as shares mt <= 8
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (tm + 2 * t < mt && tn < nt && (t == 0 || m_log + n_log == 4)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    lds.stage[(16 * (share * mt + tm + 2 * t) + 4 * lk + q) * BS_PITCH + 16 * tn + lm] = acc[t][q];
+            }
+        }
+        lds_barrier();
+        // softmax backward, two rows of a wave at a time: dS = P (dP - sum_j P dP)
+        const bool on = lane < L;                            // elsewhere nothing has been written
+        float d_sum = 0.f;
+#pragma unroll
+        for (int t0 = 0; t0 < 8; t0 += 2) {
+            if (8 * t0 >= ((Tq + 3) & ~3)) break;            // uniform
+            float dp[2], prod[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int i = w + 8 * (t0 + t);
+                float x = 0.f;
+                for (int k = 0; k < shares; ++k) x += lds.stage[min(16 * mt * k + i, 2 * BS_ROWS - 1) * BS_PITCH + lane];
+                const bool valid = on && i < Tq;
+                if (!valid) pr[t0 + t] = 0.f;
+                dp[t] = valid ? x : 0.f;
+                prod[t] = pr[t0 + t] * dp[t];
+            }
+            const float tot = wave_transpose_sum<2>(prod);   // of row t in lanes 32 t .. 32 t + 31
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const float x = pr[t0 + t] * (dp[t] - lane_value(tot, 32 * t));
+                const int i = w + 8 * (t0 + t);
+                if (KEYS) {
+                    if (lane >= x0 && lane < x0 + rows) {
+                        lds.d[(lane - x0) * BS_PITCH + i] = x;
+                        d_sum += x;
+                    }
+                } else if (i >= x0 && i < x0 + rows) {
+                    lds.d[(i - x0) * BS_PITCH + lane] = x;
+                }
+            }
+        }
+        return d_sum;
+    }
+};
+
+// dV of all keys and 64 columns: wave w forms the tile of keys 16 (w % 4) from one half of the query rows (w / 4).
+// s_part: 4 x 16 x 64 floats.
+__device__ __forceinline__ void bs_dv(const float *__restrict__ P, const float *__restrict__ dC, float *__restrict__ dV,
+                                      float *__restrict__ s_part, int Tq, int Tk, int L, int Dv, int n0, bool add) {
+    const int lane = lane_id(), w = wave_id();
+    const int lm = lane & 15, lk = lane >> 4;
+    const int m0 = 16 * (w % 4), ncol = n0 + 4 * lm;
+    const int half = ((Tq + 7) / 8) * 4, k_lo = (w / 4) * half;
+    f32x4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (m0 < L) {                                            // uniform
+        float a[8];
+        float4 bv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int k = k_lo + 4 * u + lk;
+            const bool on = 4 * u + lk < half && k < Tq;
+            a[u] = on && m0 + lm < L ? P[(size_t)k * Tk + m0 + lm] : 0.f;
+            bv[u] = on && ncol < Dv ? ld4(dC, (size_t)k * Dv + ncol) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (4 * u < half) {                              // uniform
+                acc[0] = mfma16(a[u], bv[u].x, acc[0]);
+                acc[1] = mfma16(a[u], bv[u].y, acc[1]);
+                acc[2] = mfma16(a[u], bv[u].z, acc[2]);
+                acc[3] = mfma16(a[u], bv[u].w, acc[3]);
+            }
+        }
+    }
+    float *mine = s_part + (size_t)(w % 4) * 16 * 64 + 4 * lm;
+    if (w >= 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4 *>(mine + (4 * lk + q) * 64) = make_float4(acc[0][q], acc[1][q], acc[2][q], acc[3][q]);
+    }
+    lds_barrier();
+    if (w >= 4 || ncol >= Dv) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int m = m0 + 4 * lk + q;
+        if (m < Tk) {
+            const float4 x = *reinterpret_cast<const float4 *>(mine + (4 * lk + q) * 64);
+            float4 o = make_float4(acc[0][q] + x.x, acc[1][q] + x.y, acc[2][q] + x.z, acc[3][q] + x.w);
+            float *dst = dV + (size_t)m * Dv + ncol;
+            if (add) {
+                const float4 old = *reinterpret_cast<const float4 *>(dst);
+                o.x += old.x;
+                o.y += old.y;
+                o.z += old.z;
+                o.w += old.w;
+            }
+            store4_streaming(dst, o);
+        }
+    }
+}
+
+// grid (slices of h or pieces of 64 columns of dV, samples, 1 + groups of keys + groups of queries); z = 0: dV
+// Bound by its chain of trips: key count and rows, dP, dS, the exchange of dv.  One block per compute unit: within 128
+// registers (two) it spills and was slower at every grid it is taken for.
+template <typename T, int HW>
+__global__ __launch_bounds__(RS_THREADS, 2) void k_bwd_small(
+    const float *__restrict__ dC, const float *__restrict__ P, const T *__restrict__ V, const T *__restrict__ Qp,
+    const T *__restrict__ Kp, const T *__restrict__ v, const int *__restrict__ key_len, float *__restrict__ dQp,
+    float *__restrict__ dKp, float *__restrict__ dV, float *parts, unsigned long long *flags, unsigned long long epoch,
+    float *__restrict__ dv, int Tq, int Tk, int H, int Dv, RsAxis ka, RsAxis qa, int acc) {
+    __shared__ __align__(16) BsLds lds;
+    const int b = blockIdx.y, slice = blockIdx.x;
+    if (blockIdx.z == 0) {
+        if (64 * slice < Dv)
+            bs_dv(P + (size_t)b * Tq * Tk, dC + (size_t)b * Tq * Dv, dV + (size_t)b * Tk * Dv, lds.stage, Tq, Tk,
+                  clamp_len(key_len[b], Tk), Dv, 64 * slice, acc != 0);
+        return;
+    }
+    if (slice * HW >= H) return;
+    const int z = (int)blockIdx.z - 1;
+    const int h0 = slice * HW;
+    BsScores<T> scores{dC + (size_t)b * Tq * Dv, V + (size_t)b * Tk * Dv, Tq, Tk, Dv};
+    scores.start(P + (size_t)b * Tq * Tk);
+    const int L = clamp_len(key_len[b], Tk);
+    const int B = gridDim.y;
+    unsigned long long *slice_flags = flags + (size_t)slice * B * ka.groups;
+    const T *qb = Qp + (size_t)b * Tq * H, *kb = Kp + (size_t)b * Tk * H;
+    const bool keys = z < ka.groups;
+    const int rows = rs_rows(HW, keys ? ka.ys : qa.ys), x0 = (keys ? z : z - ka.groups) * rows;
+    float *out = keys ? dKp + (size_t)b * Tk * H : dQp + (size_t)b * Tq * H;
+    if (keys && x0 < L) {
+        rs_block<T, HW, true>(kb, qb, v, out, acc != 0, parts + ((size_t)b * ka.groups + z) * H, slice_flags + b * ka.groups + z,
+                              epoch, x0, L, Tk, Tq, H, h0, ka.ys, BS_ROWS, lds.d, BS_PITCH, lds.stage + BS_HALF,
+                              lds.s_v, [&](int, int) { return scores.template finish<true>(x0, rows, L, lds); });
+    } else if (!keys && L > 0) {
+        rs_block<T, HW, false>(qb, kb, v, out, false, nullptr, nullptr, 0, x0, Tq, Tq, L, H, h0, qa.ys, BS_ROWS, lds.d, BS_PITCH,
+                               lds.stage + BS_HALF, lds.s_v, [&](int, int) { return scores.template finish<false>(x0, rows, L, lds); });
+    } else if (!keys || !acc) {                              // masked keys only, or none valid: exact zeros
+        const int n = min(rows, (keys ? Tk : Tq) - x0), lh = threadIdx.x % HW;
+        for (int x = threadIdx.x / HW; x < n; x += RS_THREADS / HW)
+            if (h0 + lh < H) out[(size_t)(x0 + x) * H + h0 + lh] = 0.f;
+    }
+    if (z != ka.groups + qa.groups - 1 || b != B - 1) return;
+
+    lds_barrier();                                          // the reduction's region is reused
+    const int h = h0 + lane_id() % HW, key_rows = rs_rows(HW, ka.ys);
+    const float tot = sum_parts<HW, RS_W>(parts, slice_flags, B * ka.groups, H, h, epoch,
+                                          [&](int p) { return (p % ka.groups) * key_rows >= clamp_len(key_len[p / ka.groups], Tk); },
+                                          lds.s_v, lds.seen);
+    if (wave_id() == 0 && lane_id() < HW && h < H) dv[h] = acc ? dv[h] + tot : tot;
+}
+
 // ---- host side ------------------------------------------------------------------------------------------------------
 
 constexpr int RS_ROUND = 512;              // two blocks on every compute unit (128 registers per lane)
 constexpr float RS_BLOCK_US = 4.0f, RS_CHUNK_US = 1.1f;
+constexpr int BS_ROUND = 256;              // one block of k_bwd_small per compute unit
 constexpr int RS_MOST_BLOCKS = 192;
 constexpr size_t RS_MOST_PARTS = 1 << 20;  // floats: 4 MB
 
@@ -386,6 +651,50 @@ hipError_t launch_recompute_split(const AttnShape &s, const void *Qp, const void
                                   hipStream_t st) {
     return s.bf16 ? launch_split_hw<bf16_t>(s, Qp, Kp, v, order, dS, dQp, dKp, parts, flags, epoch, dv, st)
                   : launch_split_hw<float>(s, Qp, Kp, v, order, dS, dQp, dKp, parts, flags, epoch, dv, st);
+}
+
+// Taken for up to 64 query rows and keys while every block gets a compute unit of its own and what each block repeats, the dP of
+// its sample, stays short: about 0.6 us per piece of columns plus the products (a tile takes 32 clocks per four columns on one
+// of the four matrix cores).  A launch and the trips of dS through memory saved, together 4.9 + 6.4 -> 8.6 us at B = 4,
+// T = 6 / 7, H = 16; 5.9 + 6.8 -> 9.2 at B = 1, T = 33 / 53, H = 48; 6.2 + 8.7 -> 12.1 at B = 10, T = 24, H = 256; 5.5 + 8.0 -> 9.3
+// at B = 20, T = 16, H = 128 (340 blocks); level at B = 2, T = 20, H = 512; behind at B = 2, T = 64, Dv = 512 (14.9 -> 24) and
+// at B = 16, T = 40, H = 181 (16 -> 23).
+bool bwd_small_applies(const AttnShape &s, size_t *part_floats, size_t *flag_words) {
+    if (s.Tq > BS_ROWS || s.Tk > BS_ROWS || s.B > 2 * BS_ROUND) return false;
+    const RsPlan p = rs_plan(s);
+    const int slices = (s.H + p.hw - 1) / p.hw;
+    const long long blocks = (long long)s.B * ((s.Dv + 63) / 64 + (long long)slices * (p.ka.groups + p.qa.groups));
+    const int rows = s.Tq > s.Tk ? s.Tq : s.Tk, tiles = ((s.Tq + 15) / 16) * ((s.Tk + 15) / 16);
+    const int piece = rows <= 16 ? 256 : rows <= 32 ? 128 : 64;
+    const float us = 0.6f * ((s.Dv + piece - 1) / piece) + 8.f / 2400 * tiles * (s.Dv / 4);
+    if (!(blocks <= BS_ROUND ? us <= 3.5f : blocks <= 2 * BS_ROUND && us <= 1.2f)) return false;
+    *part_floats = (size_t)s.B * p.ka.groups * s.H;
+    *flag_words = (size_t)s.B * p.ka.groups * slices;
+    return true;
+}
+
+template <typename T, int HW>
+static hipError_t launch_small_t(const AttnShape &s, const RsPlan &p, const float *dC, const float *P, const void *V,
+                                 const void *Qp, const void *Kp, const void *v, const int *key_len, float *dQp, float *dKp, float *dV,
+                                 float *parts, unsigned long long *flags, unsigned long long epoch, float *dv, hipStream_t st) {
+    const int slices = (s.H + HW - 1) / HW, dv_cols = (s.Dv + 63) / 64;
+    dim3 grid(slices > dv_cols ? slices : dv_cols, s.B, 1 + p.ka.groups + p.qa.groups);
+    k_bwd_small<T, HW><<<grid, RS_THREADS, 0, st>>>(dC, P, (const T *)V, (const T *)Qp, (const T *)Kp, (const T *)v, key_len, dQp,
+                                                    dKp, dV, parts, flags, epoch, dv, s.Tq, s.Tk, s.H, s.Dv, p.ka, p.qa,
+                                                    s.acc ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_small(const AttnShape &s, const float *dC, const float *P, const void *V, const void *Qp, const void *Kp,
+                            const void *v, const int *key_len, float *dQp, float *dKp, float *dV, float *parts,
+                            unsigned long long *flags, unsigned long long epoch, float *dv, hipStream_t st) {
+    const RsPlan p = rs_plan(s);
+#define ECHO_SMALL(T)                                                                                                           switch (p.hw) {                                                                                                                 case 16: return launch_small_t<T, 16>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st);         case 32: return launch_small_t<T, 32>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st);         default: return launch_small_t<T, 64>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st);     }
+    if (s.bf16) {
+        ECHO_SMALL(bf16_t)
+    }
+    ECHO_SMALL(float)
+#undef ECHO_SMALL
 }
 
 }  // namespace echo

@@ -49,6 +49,17 @@ CASES = [
     ("pre_parts_few_rows_bf16", 4, 3, 137, 24, 68, "bf16", False),
     ("pre_parts_two_rounds_bf16", 2, 70, 190, 24, 1024, "bf16", False),
     ("pre_parts_keys_past_384", 1, 90, 470, 24, 40, "f32", False),
+    # whole backward in one launch: one tile, remainders of the tiles, one row, one key, three tiles, all sixteen with two per wave,
+    # slices of 16 to 64 columns, several pieces of columns of each width, entries that need the exponential of the sum
+    ("small_one_tile", 4, 6, 7, 16, 16, "f32", True),
+    ("small_one_row_one_key", 3, 1, 1, 20, 4, "f32", False),
+    ("small_full", 2, 64, 64, 40, 96, "f32", True),
+    ("small_three_row_tiles", 3, 47, 16, 33, 68, "f32", False),
+    ("small_three_key_tiles_bf16", 3, 15, 33, 100, 132, "bf16", False),
+    ("small_pieces_of_256", 2, 16, 13, 64, 600, "f32", False),
+    ("small_pieces_of_128", 2, 17, 32, 70, 260, "f32", False),
+    ("small_slices_of_64", 10, 50, 60, 128, 64, "f32", True),
+    ("small_many_blocks_bf16", 25, 30, 29, 96, 100, "bf16", False),
     ("forward_h_4", 2, 9, 13, 4, 4, "f32", False),
     ("forward_h_5", 2, 9, 13, 5, 4, "f32", False),
     ("forward_h_7_bf16", 2, 9, 70, 7, 4, "bf16", False),
