@@ -7,7 +7,7 @@
 // backward pass 18.6 -> 14.5 us (its three launches are 7 of them), of a 50-step decoder sentence 609 -> 468 us.
 //
 // Arguments are matched by position or keyword; a device pointer is a torch tensor (contiguous), an integer address, None, or
-// any object with is_contiguous() and data_ptr().  The interpreter lock is released around the library call, as ctypes
+// any object (tensor subclasses among them) with is_contiguous() and data_ptr().  The interpreter lock is released around the library call, as ctypes
 // does.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -15,6 +15,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <exception>
 #include <tuple>
 #include <utility>
 
@@ -65,13 +66,21 @@ template <typename T> struct Ptr {
     using C = T *;
     void *p = nullptr;
     bool read(PyObject *o) {
-        if (THPVariable_Check(o)) {
-            const at::Tensor &t = THPVariable_Unpack(o);
-            if (!t.is_contiguous()) {
-                PyErr_SetString(PyExc_ValueError, "tensor must be contiguous");
+        if (THPVariable_CheckExact(o)) {                    // subclasses may override the two methods: they go through them below
+            try {                                           // tensors without storage (fake, functional, under a transform) throw
+                const at::Tensor &t = THPVariable_Unpack(o);
+                if (!t.is_contiguous()) {
+                    PyErr_SetString(PyExc_ValueError, "tensor must be contiguous");
+                    return false;
+                }
+                p = t.data_ptr();
+            } catch (const c10::Error &e) {
+                PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+                return false;
+            } catch (const std::exception &e) {
+                PyErr_SetString(PyExc_RuntimeError, e.what());
                 return false;
             }
-            p = t.data_ptr();
             return true;
         }
         if (o == Py_None) return true;
@@ -142,8 +151,16 @@ struct Bytes {                                             // workspace_bytes; N
     // `ws`: the argument in front of this one
     bool resolve(PyObject *ws) {
         if (given || ws == Py_None || PyLong_Check(ws)) return true;
-        if (THPVariable_Check(ws)) {
-            x = THPVariable_Unpack(ws).nbytes();
+        if (THPVariable_CheckExact(ws)) {                   // Ptr::read has accepted it: strided, with storage
+            try {
+                x = THPVariable_Unpack(ws).nbytes();
+            } catch (const c10::Error &e) {
+                PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+                return false;
+            } catch (const std::exception &e) {
+                PyErr_SetString(PyExc_RuntimeError, e.what());
+                return false;
+            }
             return true;
         }
         void *n = nullptr, *e = nullptr;

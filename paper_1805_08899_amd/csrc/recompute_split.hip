@@ -689,7 +689,12 @@ hipError_t launch_bwd_small(const AttnShape &s, const float *dC, const float *P,
                             const void *v, const int *key_len, float *dQp, float *dKp, float *dV, float *parts,
                             unsigned long long *flags, unsigned long long epoch, float *dv, hipStream_t st) {
     const RsPlan p = rs_plan(s);
-#define ECHO_SMALL(T)                                                                                                           switch (p.hw) {                                                                                                                 case 16: return launch_small_t<T, 16>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st);         case 32: return launch_small_t<T, 32>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st);         default: return launch_small_t<T, 64>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st);     }
+#define ECHO_SMALL(T)                                                                                                         \
+    switch (p.hw) {                                                                                                           \
+        case 16: return launch_small_t<T, 16>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st); \
+        case 32: return launch_small_t<T, 32>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st); \
+        default: return launch_small_t<T, 64>(s, p, dC, P, V, Qp, Kp, v, key_len, dQp, dKp, dV, parts, flags, epoch, dv, st); \
+    }
     if (s.bf16) {
         ECHO_SMALL(bf16_t)
     }

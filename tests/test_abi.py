@@ -202,3 +202,28 @@ def test_step_entry_points_validate():
     assert eb.echo_attn_step_fwd(eb.make_desc(4, 3, 7, 16, 16), A, A, A, A, A, A, A) == eb.ECHO_ERR_SHAPE
     assert eb.echo_attn_step_finish(one, None, A) == eb.ECHO_ERR_NULL
     assert eb.echo_attn_step_finish(one, A, A + 8) == eb.ECHO_ERR_ALIGN
+
+
+def test_tensor_without_storage_is_an_error():
+    """Under a transform the tensor at hand has no storage to point to: an exception, as from Tensor.data_ptr()."""
+    import torch
+    d = eb.make_desc(1, 1, 4, 4, 4)
+
+    def call(x):
+        with pytest.raises(RuntimeError):
+            eb.echo_attn_step_fwd(d, x, A, A, A, A, A, A, 0)
+        return x
+
+    torch.vmap(call)(torch.zeros(3, 4))
+
+
+def test_tensor_subclass_speaks_for_itself():
+    """A subclass that answers is_contiguous() and data_ptr() itself is asked, and a layout it refuses stays refused."""
+    import torch
+
+    class Refusing(torch.Tensor):
+        def is_contiguous(self, *args, **kwargs):
+            return False
+
+    with pytest.raises(ValueError):
+        eb.echo_attn_step_fwd(eb.make_desc(1, 1, 4, 4, 4), torch.zeros(4).as_subclass(Refusing), A, A, A, A, A, A, 0)
