@@ -340,22 +340,35 @@ static hipError_t launch_recompute_t(const AttnShape &s, const void *Qp, const v
     return hipGetLastError();
 }
 
+// Expected time of a launch with slices of `hw` columns, in units of one row of a wave against one key tile.  A block walks
+// every key tile once per pass over its rows; a tile costs the rows of a wave plus about three rows' worth of staging, sums and
+// barriers, the block itself about ten (its prologue, its part of dv).  The samples' mean key count is taken as 0.8 Tk.  Up to
+// RC_ROUND blocks the launch lasts as long as a full sample's block (heavy and light samples share a compute unit); beyond, the
+// blocks of a round pass through it one after the other, and half a block is lost at the end.
+static float recompute_time(const AttnShape &s, int hw) {
+    const int ns = 64 / hw, max_rows = RC_W * RC_RI * ns;
+    const float passes = (float)((s.Tq + max_rows - 1) / max_rows);
+    const float tile = (float)s.Tq / (RC_W * ns) + 3.f * passes;
+    const float full = tile * ((s.Tk + RC_RJ - 1) / RC_RJ) + 10.f, mean = 0.8f * tile * s.Tk / RC_RJ + 10.f;
+    const float blocks = (float)s.B * ((s.H + hw - 1) / hw);
+    const float all = blocks / RC_ROUND * mean + 0.5f * mean;
+    return blocks <= RC_ROUND || full > all ? full : all;
+}
+
 // Width of a block's slice of h: 64, 32 or 16.  A narrower slice means more blocks of less work each (lane groups share the
-// rows) and costs more per tanh (the staging and the sums of a key tile, about five rows' worth of time, are shared by fewer
-// rows of a wave), so it is taken only while the launch stays within one round of two blocks per compute unit: one block
-// per CU leaves half of the issue slots empty.  Measured (recompute launch): B = 32, T = 100, H = 512, 256 -> 512 blocks
-// 56 -> 33 us; B = 16, T = 300, H = 512, 128 -> 512 blocks 401 -> 145 us; with more than a round it loses (B = 64, T = 50,
-// H = 512, 512 -> 1024 blocks 20.7 -> 28.4 us), and with a wave's rows already down to three it gives nothing.  An H that
-// fits the narrower slice whole takes it in any case.
+// rows): it fills the chip, balances it better, makes do with fewer passes over the keys (one pass takes 64, 128 or 256 rows) and
+// leaves fewer columns idle, but a wave has fewer rows to share a key tile's fixed costs.  Taken where recompute_time
+// expects at least 2 % from it; over 104 shapes of 20 and more keys the whole backward was within 4 % of the best of the
+// three widths on all but one (7 %).  Measured (recompute launch): B = 32, T = 100, H = 512, 64 -> 32 columns 56 -> 33 us; B = 16, T = 300, H = 512, 64 ->
+// 16 401 -> 145.  Backward: B = 27, T = 181 / 233, H = 340, 32 -> 16 218 -> 176; B = 101, T = 199 / 240, H = 268, 64 -> 16 492 -> 412; B = 32,
+// T = 194 / 182, H = 577, 64 -> 16 295 -> 198; B = 58, T = 108 / 163, H = 568, 64 -> 32 155 -> 132.  The wider ones win
+// on few rows (B = 64, T = 50, H = 512: 30 us at 64 columns, 38 at 32) and where they fill one round just so (B = 32, T = 300, H =
+// 1024: 644 against 702).  With a wave's rows already down to three a narrower slice gives nothing.  An H that fits the
+// narrower slice whole takes it in any case.
 static int recompute_width(const AttnShape &s) {
     int hw = 64;
-    while (hw > 16) {
-        const int half = hw / 2;
-        const bool whole = s.H <= half;
-        const bool fits = (long long)s.B * ((s.H + half - 1) / half) <= RC_ROUND && s.Tq > 3 * RC_W;
-        if (!whole && !fits) break;
-        hw = half;
-    }
+    for (int narrow = 32; narrow >= 16; narrow /= 2)
+        if (s.H <= narrow || (s.Tq > 3 * RC_W && recompute_time(s, narrow) < 0.98f * recompute_time(s, hw))) hw = narrow;
     return hw;
 }
 

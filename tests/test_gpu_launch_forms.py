@@ -24,6 +24,10 @@ CASES = [
     ("slices_of_16", 25, 50, 21, 130, 8, "f32", True),
     ("slices_of_16_two_passes", 14, 259, 19, 240, 8, "f32", False),
     ("slices_of_16_bf16", 30, 35, 30, 112, 8, "bf16", False),
+    # more than one round of blocks: 16 columns with one and two passes and a masked tail of H, 32 columns
+    ("slices_of_16_two_rounds", 60, 140, 67, 201, 4, "f32", True),
+    ("slices_of_16_two_rounds_two_passes", 67, 259, 21, 130, 4, "bf16", False),
+    ("slices_of_32_two_rounds", 64, 100, 66, 300, 4, "f32", False),
     ("slices_of_32", 34, 45, 9, 470, 8, "f32", True),
     ("slices_of_32_two_passes", 20, 131, 9, 800, 4, "f32", False),
     ("slice_of_16_is_the_whole_h", 200, 9, 11, 16, 4, "f32", False),
