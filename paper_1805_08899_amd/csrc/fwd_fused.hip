@@ -3,7 +3,7 @@
 // (Section 2, attention steps 1-2; Section 4.1 scoring function; Section 6.1:
 // one fused kernel instead of many small ones, fewer launches and accesses).
 //
-// Block = (sample b, up to RT = 8 or 4 query rows), W waves: eight, or four in streaming mode at H <= 512 (four
+// Block = (sample b, up to RT = 8 or 4 query rows), W waves: eight, or four in most of streaming mode (four
 // such blocks share a CU and are in different phases of their lives, which keeps the vector units fed).  In streaming mode
 // the lanes may work as 64 / HL groups of HL = 32 or 16 that take different keys (a slice is then 4 HL columns of h).
 //   A  exp(2q) / v of the rows and 1 / v go to LDS (taken once per block).
@@ -1119,18 +1119,34 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
             default: return launch_fwd_fused_t<T, 8, 64, 4, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
         }
     }
-    // Streaming mode on a grid that blocks of eight rows do not fill: blocks of four rows, of eight waves (two blocks on a CU)
-    // while there is hardly more than one for a CU, else of four waves (four blocks on a CU).
+    // Streaming mode, and H past 256 columns a slice (three slices, or more than four): at most two keys per wave leave
+    // the lane groups of a narrow slice without keys of their own (B = 74, T = 3 / 4, H = 660: 9.8 us in them, 9.1 here).
+    if (s.Tk <= 16) return launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+    // A grid that blocks of eight rows do not fill: blocks of four rows, of eight waves (two blocks on a CU) while there is
+    // hardly more than one for a CU (short key axes give eight waves little each: B = 44, T = 24 / 40, H = 860, 264 blocks: 26 us against
+    // 21.8), else of four waves (four blocks on a CU, 1024 at a time).
     // B = 4, T = 300, H = 1024: 172 -> 71 us; B = 37, T = 61 / 83, H = 300: 28.8 -> 18.6; B = 16, T = 100, H = 512: 31 -> 21.
-    if (n4 <= 300) return launch_fwd_fused_t<T, 4, 16, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
-    if (n4 <= (s.H > 512 ? 512 : 800)) return launch_fwd_fused_t<T, 4, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
-    // Full grids, up to H = 512: blocks of four waves, four of them on a CU (9 % faster than eight-wave blocks at B = 128,
-    // T = 100, H = 512); beyond that the row tile's LDS allows only three such blocks and the eight-wave block, two per CU,
-    // keeps more waves resident (four-wave blocks measured 2 % slower at H = 1024).  Slices of 128 columns, two lane groups:
-    // a pass takes eight keys, and its reduction and addressing are shared by twice as many (81 -> 77 us at that shape);
-    // slices of 64 where H fills them better (B = 23, T = 217 / 286, H = 40: 79 -> 35 us).
-    if (s.H <= 512) {
-        if (12 * fwd_h_pad(s.H, 16) <= 11 * fwd_h_pad(s.H, 32)) return launch_fwd_fused_t<T, 8, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    // Up to about a round of them at H <= 512 (B = 24, T = 180 / 134, H = 492, 1080 blocks: 57 -> 44; B = 21, T = 227, H = 47, 1197 blocks: level).
+    // Beyond H = 512 the other forms cost more per block; where slices of 256 columns waste an eighth of their lanes or more, a round
+    // and a half on long key axes (B = 20, T = 213 / 186, H = 776: 88 -> 70; B = 58, T = 108 / 163, H = 568: 78 -> 70) and one round on
+    // short ones (B = 164, T = 29 / 25, H = 596, 1312 blocks: 30.1 against 25.4 below), else two thirds of one (B = 75, T =
+    // 31 / 33, H = 767, 600 blocks: 22.5 -> 20.1; B = 28, T = 134 / 103, H = 672, 952 blocks: 52 against 47 below).
+    const int p16 = fwd_h_pad(s.H, 16), p32 = fwd_h_pad(s.H, 32), p64 = fwd_h_pad(s.H, 64);
+    const bool wide_wastes = s.H <= 1024 && 8 * p16 <= 7 * p64;
+    if (n4 <= (s.Tk > 64 ? 300 : 240)) return launch_fwd_fused_t<T, 4, 16, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+    if (n4 <= (s.H <= 512 ? 1100 : wide_wastes ? (s.Tk > 64 ? 1600 : 1024) : 650))
+        return launch_fwd_fused_t<T, 4, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    // Full grids: blocks of four waves, four of them on a CU (9 % faster than eight-wave blocks at B = 128, T = 100, H = 512).
+    // Slices of 128 columns, two lane groups: a pass takes eight keys, and its reduction and addressing are shared by twice as
+    // many (81 -> 77 us at that shape); slices of 64 where H fills them better (B = 23, T = 217 / 286, H = 40: 79 -> 35 us) and
+    // up to 128 columns in any case (B = 253, T = 197 / 260, H = 112: 240 -> 228; B = 66, T = 140, H = 124 in bf16: 59 -> 55).
+    // They hold beyond H = 512 as long as four row tiles fit a CU's LDS (H <= 768) or slices of 256 waste lanes (H = 516, B = 103, T =
+    // 123 / 90: 105 -> 85; H = 884, B = 113, T = 106 in bf16: 162 -> 147; H = 760, B = 139, T = 82 / 128: 139 -> 130); where they
+    // waste none, the eight-wave block, two per CU, keeps more waves resident (H = 1024, B = 32, T = 300: 301 against 307; in bf16
+    // at B = 128, T = 50 42 against 45) and balances better on less than two rounds (B = 28, T = 134, H = 672: 47 against 58), in bf16 than three (B = 77, T = 94 / 81, H =
+    // 752, 924 blocks: 52.6 against 54.0).
+    if (s.H <= 512 || wide_wastes || (s.H <= 768 && n8 >= (s.bf16 ? 1600 : 850))) {
+        if (s.H <= 128 || 12 * p16 <= 11 * p32) return launch_fwd_fused_t<T, 8, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
         return launch_fwd_fused_t<T, 8, 32, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
     }
     return launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);

@@ -41,6 +41,15 @@ CASES = [
     ("forward_slices_of_64", 110, 30, 66, 41, 4, "f32", True),
     ("forward_slices_of_128", 110, 29, 66, 102, 4, "f32", True),
     ("forward_slices_of_128_bf16", 110, 31, 70, 103, 4, "bf16", False),
+    # the same forms beyond H = 512, up to 128 columns, and on few keys
+    ("forward_four_rows_wide_h", 41, 90, 66, 530, 4, "f32", True),
+    ("forward_slices_of_64_wide_h", 60, 220, 33, 517, 4, "f32", True),
+    ("forward_slices_of_128_wide_h_bf16", 90, 76, 50, 590, 4, "bf16", False),
+    ("forward_full_slices_of_64", 140, 30, 66, 41, 4, "f32", True),
+    ("forward_full_slices_of_128", 140, 29, 66, 243, 4, "f32", True),
+    ("forward_full_slices_of_128_bf16", 140, 31, 70, 241, 4, "bf16", False),
+    ("forward_full_slices_of_256", 50, 53, 40, 1001, 4, "f32", True),
+    ("forward_few_keys", 9, 5, 11, 662, 8, "f32", True),
     ("forward_spread_small_batch", 9, 150, 67, 36, 8, "f32", False),
     ("forward_row_mode_odd_h", 3, 21, 20, 250, 8, "f32", True),
     ("forward_row_mode_odd_h_bf16", 3, 21, 20, 511, 8, "bf16", False),
