@@ -553,6 +553,7 @@ __global__ __launch_bounds__(RS_THREADS, 2) void k_bwd_small(
 constexpr int RS_ROUND = 512;              // two blocks on every compute unit (128 registers per lane)
 constexpr float RS_BLOCK_US = 4.0f, RS_CHUNK_US = 1.1f;
 constexpr int BS_ROUND = 256;              // one block of k_bwd_small per compute unit
+constexpr int BS_MOST_BLOCKS = 340;
 constexpr int RS_MOST_BLOCKS = 192;
 constexpr size_t RS_MOST_PARTS = 1 << 20;  // floats: 4 MB
 
@@ -608,9 +609,11 @@ static RsPlan rs_plan(const AttnShape &s) {
 // blocks the two forms meet, 10.7 against 11.6 us at B = 16, T = 40, H = 181; below it this one is ahead by up to 4 times,
 // 53 -> 13 us at B = 3, T = 200, H = 76; above it evaluating every tanh twice loses).  Samples of hardly more than a key tile
 // and a row per wave stay with the other form, which is then done before this one has exchanged its parts of dv (7.4
-// against 9.5 us at B = 50, T = 9 / 15).
+// against 9.5 us at B = 50, T = 9 / 15), and close to the limit those of up to 600 pairs do (T = 20, H = 32, B = 90, 180 blocks: 9.2
+// against 10.2; ahead again at T = 30, H = 48, B = 60: 10.3 against 11.2).
 bool recompute_split_applies(const AttnShape &s, size_t *part_floats, size_t *flag_words) {
-    if ((long long)s.B * ((s.H + 15) / 16) > RS_MOST_BLOCKS || (long long)s.Tq * s.Tk <= 150) return false;
+    const long long blocks = (long long)s.B * ((s.H + 15) / 16), pairs = (long long)s.Tq * s.Tk;
+    if (blocks > RS_MOST_BLOCKS || pairs <= (blocks > 160 ? 600 : 150)) return false;
     const RsPlan p = rs_plan(s);
     *part_floats = (size_t)s.B * p.ka.groups * s.H;
     *flag_words = (size_t)s.B * p.ka.groups * ((s.H + p.hw - 1) / p.hw);
@@ -658,16 +661,17 @@ hipError_t launch_recompute_split(const AttnShape &s, const void *Qp, const void
 // of the four matrix cores).  A launch and the trips of dS through memory saved, together 4.9 + 6.4 -> 8.6 us at B = 4,
 // T = 6 / 7, H = 16; 5.9 + 6.8 -> 9.2 at B = 1, T = 33 / 53, H = 48; 6.2 + 8.7 -> 12.1 at B = 10, T = 24, H = 256; 5.5 + 8.0 -> 9.3
 // at B = 20, T = 16, H = 128 (340 blocks); level at B = 2, T = 20, H = 512; behind at B = 2, T = 64, Dv = 512 (14.9 -> 24) and
-// at B = 16, T = 40, H = 181 (16 -> 23).
+// at B = 16, T = 40, H = 181 (16 -> 23).  Past one block per compute unit only a third more than a round: 380 blocks at B = 38, T =
+// 11, H = 224 lose (13.4 -> 15.3).
 bool bwd_small_applies(const AttnShape &s, size_t *part_floats, size_t *flag_words) {
-    if (s.Tq > BS_ROWS || s.Tk > BS_ROWS || s.B > 2 * BS_ROUND) return false;
+    if (s.Tq > BS_ROWS || s.Tk > BS_ROWS || s.B > BS_MOST_BLOCKS) return false;
     const RsPlan p = rs_plan(s);
     const int slices = (s.H + p.hw - 1) / p.hw;
     const long long blocks = (long long)s.B * ((s.Dv + 63) / 64 + (long long)slices * (p.ka.groups + p.qa.groups));
     const int rows = s.Tq > s.Tk ? s.Tq : s.Tk, tiles = ((s.Tq + 15) / 16) * ((s.Tk + 15) / 16);
     const int piece = rows <= 16 ? 256 : rows <= 32 ? 128 : 64;
     const float us = 0.6f * ((s.Dv + piece - 1) / piece) + 8.f / 2400 * tiles * (s.Dv / 4);
-    if (!(blocks <= BS_ROUND ? us <= 3.5f : blocks <= 2 * BS_ROUND && us <= 1.2f)) return false;
+    if (!(blocks <= BS_ROUND ? us <= 3.5f : blocks <= BS_MOST_BLOCKS && us <= 1.2f)) return false;
     *part_floats = (size_t)s.B * p.ka.groups * s.H;
     *flag_words = (size_t)s.B * p.ka.groups * slices;
     return true;
