@@ -23,8 +23,9 @@
 //   D  context = P V on the matrix cores: v_mfma_f32_4x4x1 treats the 64 lanes
 //      as 16 column groups of 4, so a lane owns one output column and reads V
 //      rows with plain coalesced loads (in batches of rows, one batch ahead; all rows at once,
-//      before the softmax, when the key axis is short: ContextAllRows; two waves per group of 256
-//      columns with half of the keys each when there are twice as many waves as groups: ContextSplitKeys).
+//      before the softmax, when the key axis is short: ContextAllRows; several waves per group of columns
+//      with a share of the keys each when there are at least twice as many waves as groups: ContextSplitKeys,
+//      ContextKeyShares).
 //
 // A block's whole pass is short compared with a trip to memory, so loads are
 // issued well before they are consumed: the first key slice leaves before the
@@ -646,6 +647,132 @@ struct ContextSplitKeys {
     }
 };
 
+// The same for any width of the value rows up to 128 columns per wave (groups of 64 CPL columns): SHARES waves share a column
+// group, so that no wave walks the whole key axis one trip to memory after the other while others have no columns at all.  The
+// partial tiles meet in LDS (s_x: fw_share_floats floats that nobody reads any more, the staged query rows): the upper half of the
+// shares is added to the lower half until one is left, which writes the context rows.
+// Against one wave per group of 64 columns: B = 2, T = 242 / 308, H = 159, Dv = 28 21.5 -> 16.5 us; B = 7, T = 188 / 274, H = 185,
+// Dv = 464 in bf16 38.8 -> 30.4; B = 13, T = 103 / 145, H = Dv = 288 in bf16 22.3 -> 18.8; full grids gain less (B = 14, T = 428 / 337,
+// H = Dv = 508 167 -> 157; B = 100, T = 341 / 363, H = 74, Dv = 140 level).  Whole groups of 256 columns for every two waves stay
+// with the form above (this one takes 1 us longer at B = 128, T = 100, H = Dv = 512), and kernels with all lanes along a
+// slice of h take no part: they are the form of large H and rows, and with the additional code the launch at B = 128, T =
+// 50, H = Dv = 1024 in bf16 became 0.8 us longer.
+template <typename T, int RT, int CPL, int W, int SHARES>
+struct ContextKeyShares {
+    static constexpr int KB = CPL == 4 ? 8 : FW_KB, NR4 = RT / 4, PLANE = RT * 64 * CPL;
+    typedef RowPiece<T, CPL> Piece;
+    Piece vcur[KB], vnxt[KB];
+    static constexpr int GROUPS = W / SHARES;     // column groups that the waves are dealt to; the last one may be past Dv
+    int g, share, k0, k1;               // column group, which share of the keys, keys k0 .. k1 - 1 (multiples of 4)
+
+    __device__ __forceinline__ void fetch(Piece (&dst)[KB], const T *vb, int Dv, int L, int lane, int kb0) {
+        const BufferRows<T> rows(vb, (unsigned)L * (unsigned)Dv);
+        const unsigned col = (unsigned)min((g * 64 + lane) * CPL, Dv - CPL) * (unsigned)sizeof(T);
+        const unsigned pitch = (unsigned)Dv * (unsigned)sizeof(T);
+#pragma unroll
+        for (int kk = 0; kk < KB; ++kk) dst[kk].load(rows, col, (unsigned)min(kb0 + kk, L - 1) * pitch);
+    }
+    __device__ __forceinline__ void start(const T *vb, int Dv, int L, int Lp, int lane, int w) {
+        g = w % GROUPS;
+        share = w / GROUPS;
+        const int nq = Lp / 4;
+        k0 = 4 * ((nq * share + SHARES - 1) / SHARES);
+        k1 = g * 64 * CPL < Dv ? 4 * ((nq * (share + 1) + SHARES - 1) / SHARES) : k0;
+        if (k0 < k1) fetch(vcur, vb, Dv, L, lane, k0);
+    }
+    __device__ __forceinline__ void run(const T *vb, const float *s_S, int spitch, float *s_x, float *Cb, int Dv, int L,
+                                        int ni, int lane) {
+        const int lr = lane & 3;
+        f32x4 acc[CPL][NR4];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c)
+#pragma unroll
+            for (int t = 0; t < NR4; ++t) acc[c][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        int kb0 = k0;
+        auto batch = [&](Piece (&cur)[KB], Piece (&nxt)[KB]) {
+            if (kb0 + KB < k1) fetch(nxt, vb, Dv, L, lane, kb0 + KB);
+#pragma unroll
+            for (int kk = 0; kk < KB; ++kk) cur[kk].pin();
+#pragma unroll
+            for (int k4 = 0; k4 < KB; k4 += 4) {
+                if (kb0 + k4 < k1) {
+                    float4 pr[NR4];
+#pragma unroll
+                    for (int t = 0; t < NR4; ++t)
+                        pr[t] = *reinterpret_cast<const float4 *>(s_S + (4 * t + lr) * spitch + kb0 + k4);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c)
+#pragma unroll
+                            for (int t = 0; t < NR4; ++t)
+                                acc[c][t] = __builtin_amdgcn_mfma_f32_4x4x1f32(comp(pr[t], q), cur[k4 + q].value(c),
+                                                                               acc[c][t], 0, 0, 0);
+                }
+            }
+            kb0 += KB;
+        };
+        while (kb0 < k1) {
+            batch(vcur, vnxt);
+            if (kb0 >= k1) break;
+            batch(vnxt, vcur);
+        }
+        typedef float CVec __attribute__((ext_vector_type(CPL)));
+#pragma unroll
+        for (int half = SHARES / 2; half >= 1; half /= 2) {
+            if (share >= half && share < 2 * half) {
+                float *mine = s_x + ((share - half) * GROUPS + g) * PLANE + lane * CPL;
+#pragma unroll
+                for (int t = 0; t < NR4; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        CVec x;
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) x[c] = acc[c][t][r];
+                        *reinterpret_cast<CVec *>(mine + (4 * t + r) * 64 * CPL) = x;
+                    }
+            }
+            lds_barrier();
+            if (share < half) {
+                const float *other = s_x + (share * GROUPS + g) * PLANE + lane * CPL;
+#pragma unroll
+                for (int t = 0; t < NR4; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        if (half == 1 && 4 * t + r >= ni) continue;       // uniform; not written below
+                        const CVec x = *reinterpret_cast<const CVec *>(other + (4 * t + r) * 64 * CPL);
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) acc[c][t][r] += x[c];
+                    }
+            }
+            if (half > 1) lds_barrier();                             // the planes are written again
+        }
+        const int n = (g * 64 + lane) * CPL;
+        if (share == 0 && n < Dv) {
+#pragma unroll
+            for (int t = 0; t < NR4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (4 * t + r < ni) {
+                        float x[CPL];
+#pragma unroll
+                        for (int c = 0; c < CPL; ++c) x[c] = acc[c][t][r];
+                        ColVec<CPL>::store(&Cb[(size_t)(4 * t + r) * Dv + n], x);
+                    }
+        }
+    }
+};
+
+// Columns a lane takes in that form, and when it is the form to take: two waves at least for every column group, and more keys
+// than two or three batches of rows, which one wave has under way at once (B = 137, T = 7 / 8, H = 592, Dv = 104: 9.1 us without, 9.7
+// with).
+__host__ __device__ constexpr int fw_share_cpl(int Dv) { return Dv <= 64 ? 1 : Dv <= 128 ? 2 : 4; }
+__host__ __device__ constexpr bool fw_shares_keys(int Tk, int Dv, int waves) { return Dv <= 128 * waves && Tk > 36; }
+// LDS floats for the partial tiles: half of the shares of every column group, at most rt x 64 cpl x waves / 2
+__host__ __device__ constexpr int fw_share_floats(int rt, int Tk, int Dv, int waves) {
+    return fw_shares_keys(Tk, Dv, waves) ? rt * 64 * fw_share_cpl(Dv) * waves / 2 : 0;
+}
+
 // The context phase for short key axes (at most 64 keys) and at most one group of 64 columns per wave: a lane owns
 // one column and requests ALL value rows of it at once, before the softmax, so that they arrive while the block waits
 // for its last scores and normalises them; the products then find their operands in registers.  (With batches of
@@ -802,7 +929,8 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
     extern __shared__ __align__(16) float smem[];
     float *s_e = smem;                       // [RT][Hp]  exp(2q) / v
     float *s_c = s_e + RT * Hp;              // [Hp]      1 / v
-    float *s_S = s_c + Hp;                   // [RT][spitch]  scores, then probabilities
+    // [RT][spitch] scores, then probabilities (behind the partial tiles of the context, if these need more room)
+    float *s_S = smem + max((RT + 1) * Hp, fw_share_floats(RT, Tk, Dv, W));
     __shared__ float s_red[2 * W];
 
     const int lane = lane_id(), w = wave_id();
@@ -1021,22 +1149,36 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
         cp.start(vb, Dv, L, lane, w);
         softmax();
         cp.run(s_S, spitch, Cb, Dv, Lp, ni, lane, w);
-    } else if (Dv % 256 == 0 && 2 * (Dv / 256) == W && Dv <= Hp) {   // two waves per group of 256 columns
+    } else if (Dv == 128 * W && Dv <= Hp) {                     // two waves per group of 256 columns, all groups whole
         ContextSplitKeys<T, RT> cp;
         cp.start(vb, Dv, L, Lp, lane, w);
         softmax();
         cp.run(vb, s_S, spitch, s_e, Cb, Dv, L, ni, lane);
+    } else if ((ROWMODE || HL < 64) && fw_shares_keys(Tk, Dv, W)) {
+        auto shared = [&](auto cp) {
+            cp.start(vb, Dv, L, Lp, lane, w);
+            softmax();
+            cp.run(vb, s_S, spitch, smem, Cb, Dv, L, ni, lane);
+        };
+        if constexpr (!ROWMODE && HL < 64) {                    // (row mode: wider than 64 W columns here)
+            if (Dv <= 64) return shared(ContextKeyShares<T, RT, 1, W, W>());
+            if (Dv <= 128) return shared(ContextKeyShares<T, RT, 2, W, W>());
+            if (Dv <= 256) return shared(ContextKeyShares<T, RT, 4, W, W>());
+            if constexpr (W == 8)
+                if (Dv <= 512) return shared(ContextKeyShares<T, RT, 4, W, 4>());
+        }
+        if constexpr (ROWMODE || HL < 64) shared(ContextKeyShares<T, RT, 4, W, 2>());
     } else if (Dv >= 1024) {                                    // at least four waves with columns to work on
         ContextPhase<T, RT, 4> cp;
         cp.start(vb, Dv, L, lane, w);
         softmax();
         cp.run(vb, s_S, spitch, Cb, Dv, L, Lp, ni, lane, w, W);
-    } else if (Dv >= 512) {
+    } else if (ROWMODE || Dv >= 512) {
         ContextPhase<T, RT, 2> cp;
         cp.start(vb, Dv, L, lane, w);
         softmax();
         cp.run(vb, s_S, spitch, Cb, Dv, L, Lp, ni, lane, w, W);
-    } else {
+    } else if constexpr (!ROWMODE) {
         ContextPhase<T, RT, 1> cp;
         cp.start(vb, Dv, L, lane, w);
         softmax();
@@ -1049,16 +1191,20 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
 // two waves per SIMD instead of four that measured 20-25 % slower on the large workloads.)
 
 static int fwd_h_pad(int H, int hl) { return (H + 4 * hl - 1) / (4 * hl) * (4 * hl); }
-static size_t fwd_lds_bytes(const AttnShape &s, int rt, int hl) {
-    const int Hp = fwd_h_pad(s.H, hl);
+// floats in front of the scores: the staged query rows and 1 / v, later the partial tiles of the context
+static int fwd_score_offset(const AttnShape &s, int rt, int hl, int waves) {
+    const int rows = (rt + 1) * fwd_h_pad(s.H, hl), tiles = fw_share_floats(rt, s.Tk, s.Dv, waves);
+    return rows > tiles ? rows : tiles;
+}
+static size_t fwd_lds_bytes(const AttnShape &s, int rt, int hl, int waves) {
     const int spitch = ((s.Tk + 3) & ~3) + 4;
-    return ((size_t)rt * (Hp + spitch) + Hp) * sizeof(float);
+    return ((size_t)fwd_score_offset(s, rt, hl, waves) + (size_t)rt * spitch) * sizeof(float);
 }
 
 bool fwd_fused_supported(const AttnShape &s) {
     // the context phase addresses a sample's value rows by 32-bit byte offsets (BufferRows)
     const bool v_in_range = (long long)s.Tk * s.Dv * (s.bf16 ? 2 : 4) < (1LL << 31);
-    return s.H >= 4 && fwd_lds_bytes(s, 8, 64) <= 150 * 1024 && v_in_range;
+    return s.H >= 4 && fwd_lds_bytes(s, 8, 64, FW_W) <= 150 * 1024 && v_in_range;
 }
 
 // Row mode needs the longest key share of a wave, ceil(Tk / 8) keys, times the slices of h to fit the
@@ -1074,7 +1220,7 @@ static hipError_t launch_fwd_fused_t(const AttnShape &s, const void *Qp, const v
                                      const int *key_len, float *C, float *P, hipStream_t st) {
     const int Hp = fwd_h_pad(s.H, HL);
     const int spitch = ((s.Tk + 3) & ~3) + 4;
-    const size_t lds = fwd_lds_bytes(s, RT, HL);
+    const size_t lds = fwd_lds_bytes(s, RT, HL, W);
     if (lds > 48 * 1024) {   // beyond the default dynamic LDS limit
         static LdsGrants granted;
         hipError_t e = ensure_dynamic_lds((const void *)k_fwd_fused<T, RT, HL, ROWNS, W>, lds, granted);

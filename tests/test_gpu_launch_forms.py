@@ -50,6 +50,24 @@ CASES = [
     ("forward_full_slices_of_128_bf16", 140, 31, 70, 241, 4, "bf16", False),
     ("forward_full_slices_of_256", 50, 53, 40, 1001, 4, "f32", True),
     ("forward_few_keys", 9, 5, 11, 662, 8, "f32", True),
+    # context with a share of the keys per wave: one, two and four columns per lane, one to four groups of columns with a short
+    # last one, shares without keys (few valid keys), four and eight waves, blocks of four and eight rows
+    ("context_shares_4_columns", 140, 30, 66, 44, 4, "f32", False),
+    ("context_shares_60_columns_bf16", 41, 30, 70, 44, 60, "bf16", False),
+    ("context_shares_64_columns", 3, 45, 70, 90, 64, "f32", False),
+    ("context_shares_68_columns", 140, 29, 67, 36, 68, "f32", False),
+    ("context_shares_128_columns_bf16", 3, 45, 70, 90, 128, "bf16", False),
+    ("context_shares_132_columns", 41, 31, 131, 52, 132, "f32", False),
+    ("context_shares_256_columns", 140, 30, 66, 20, 256, "f32", False),
+    ("context_shares_260_columns", 3, 9, 300, 40, 260, "f32", False),
+    ("context_shares_512_columns_bf16", 41, 30, 66, 40, 512, "bf16", False),
+    ("context_few_keys_104_columns", 9, 5, 11, 662, 104, "f32", False),
+    ("context_36_keys_of_wide_h", 9, 13, 36, 601, 300, "f32", False),
+    ("context_shares_37_keys", 9, 13, 37, 601, 300, "f32", False),
+    ("context_no_shares_516_columns", 41, 30, 66, 40, 516, "f32", False),
+    ("context_shares_516_columns_eight_waves", 3, 45, 70, 36, 516, "f32", False),
+    ("context_shares_row_mode_1000_columns", 5, 21, 50, 512, 1000, "f32", False),
+    ("context_shares_wide_h", 50, 53, 40, 1001, 772, "bf16", False),
     ("forward_spread_small_batch", 9, 150, 67, 36, 8, "f32", False),
     ("forward_row_mode_odd_h", 3, 21, 20, 250, 8, "f32", True),
     ("forward_row_mode_odd_h_bf16", 3, 21, 20, 511, 8, "bf16", False),
