@@ -1192,35 +1192,35 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
 
 static int fwd_h_pad(int H, int hl) { return (H + 4 * hl - 1) / (4 * hl) * (4 * hl); }
 // floats in front of the scores: the staged query rows and 1 / v, later the partial tiles of the context
-static int fwd_score_offset(const AttnShape &s, int rt, int hl, int waves) {
-    const int rows = (rt + 1) * fwd_h_pad(s.H, hl), tiles = fw_share_floats(rt, s.Tk, s.Dv, waves);
+static int fwd_score_offset(const AttnShape &s, int Hp, int rt, int waves) {
+    const int rows = (rt + 1) * Hp, tiles = fw_share_floats(rt, s.Tk, s.Dv, waves);
     return rows > tiles ? rows : tiles;
 }
-static size_t fwd_lds_bytes(const AttnShape &s, int rt, int hl, int waves) {
+static size_t fwd_lds_bytes(const AttnShape &s, int Hp, int rt, int waves) {
     const int spitch = ((s.Tk + 3) & ~3) + 4;
-    return ((size_t)fwd_score_offset(s, rt, hl, waves) + (size_t)rt * spitch) * sizeof(float);
+    return ((size_t)fwd_score_offset(s, Hp, rt, waves) + (size_t)rt * spitch) * sizeof(float);
 }
 
 bool fwd_fused_supported(const AttnShape &s) {
     // the context phase addresses a sample's value rows by 32-bit byte offsets (BufferRows)
     const bool v_in_range = (long long)s.Tk * s.Dv * (s.bf16 ? 2 : 4) < (1LL << 31);
-    return s.H >= 4 && fwd_lds_bytes(s, 8, 64, FW_W) <= 150 * 1024 && v_in_range;
+    return s.H >= 4 && fwd_lds_bytes(s, fwd_h_pad(s.H, 64), 8, FW_W) <= 150 * 1024 && v_in_range;
 }
 
 // Row mode needs the longest key share of a wave, ceil(Tk / 8) keys, times the slices of h to fit the
 // registers set aside for it; it is built for 1, 2 and 4 slices (H up to 256, 512, 1024).
 static int fwd_row_mode_slices(const AttnShape &s) {
-    const int ns = (s.H + FW_ST - 1) / FW_ST;
-    if (ns != 1 && ns != 2 && ns != 4) return 0;
-    return (s.Tk + FW_W - 1) / FW_W <= fw_row_max_keys(ns) ? ns : 0;
+    const int ns = (s.H + FW_ST - 1) / FW_ST, built = ns == 3 ? 4 : ns;
+    if (built > 4) return 0;
+    return (s.Tk + FW_W - 1) / FW_W <= fw_row_max_keys(built) ? built : 0;
 }
 
 template <typename T, int RT, int HL, int ROWNS, int W>
 static hipError_t launch_fwd_fused_t(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,
                                      const int *key_len, float *C, float *P, hipStream_t st) {
-    const int Hp = fwd_h_pad(s.H, HL);
+    const int Hp = ROWNS > 0 ? ROWNS * FW_ST : fwd_h_pad(s.H, HL);
     const int spitch = ((s.Tk + 3) & ~3) + 4;
-    const size_t lds = fwd_lds_bytes(s, RT, HL, W);
+    const size_t lds = fwd_lds_bytes(s, Hp, RT, W);
     if (lds > 48 * 1024) {   // beyond the default dynamic LDS limit
         static LdsGrants granted;
         hipError_t e = ensure_dynamic_lds((const void *)k_fwd_fused<T, RT, HL, ROWNS, W>, lds, granted);
@@ -1257,16 +1257,20 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
     // Row mode: all lanes along h, so a last slice that H fills badly leaves lanes idle; on a small grid, where latency and
     // not arithmetic decides, it is still the fastest (B = 128, T = 60, H = 64: 23.4 us against 14.6 in narrow slices;
     // B = 1, T = 53, H = 48: 7.2 against 7.6).
+    // An H of three slices takes the form for four on grids that stay below a round of it, idle lanes included (B = 20, T = 5 / 4,
+    // H = 712: 9.8 -> 7.4 us; B = 13, T = 18 / 20, H = 576 in bf16: 11.3 -> 9.5; B = 60, T = 40 / 32, H = 768, 300 blocks in bf16: 17.3 -> 15.5; but
+    // B = 60, T = 30 / 28, H = 530, 240 blocks: 12.7 -> 14.1).
     const int row_ns = fwd_row_mode_slices(s);
-    if (row_ns > 0 && (5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
+    const bool three = s.H > 2 * FW_ST && s.H <= 3 * FW_ST;
+    if (row_ns > 0 && (three ? 4 * FW_ST * n8 <= 420LL * s.H : 5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
         switch (row_ns) {
             case 1: return launch_fwd_fused_t<T, 8, 64, 1, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
             case 2: return launch_fwd_fused_t<T, 8, 64, 2, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
             default: return launch_fwd_fused_t<T, 8, 64, 4, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
         }
     }
-    // Streaming mode, and H past 256 columns a slice (three slices, or more than four): at most two keys per wave leave
-    // the lane groups of a narrow slice without keys of their own (B = 74, T = 3 / 4, H = 660: 9.8 us in them, 9.1 here).
+    // Streaming mode.  At most two keys per wave leave the lane groups of a narrow slice without keys of their own (B = 74, T = 3 / 4,
+    // H = 660: 9.8 us in them, 9.1 in slices of 256).
     if (s.Tk <= 16) return launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
     // A grid that blocks of eight rows do not fill: blocks of four rows, of eight waves (two blocks on a CU) while there is
     // hardly more than one for a CU (short key axes give eight waves little each: B = 44, T = 24 / 40, H = 860, 264 blocks: 26 us against

@@ -49,6 +49,9 @@ CASES = [
     ("forward_full_slices_of_128", 140, 29, 66, 243, 4, "f32", True),
     ("forward_full_slices_of_128_bf16", 140, 31, 70, 241, 4, "bf16", False),
     ("forward_full_slices_of_256", 50, 53, 40, 1001, 4, "f32", True),
+    ("forward_row_mode_three_slices", 9, 21, 32, 513, 8, "f32", True),
+    ("forward_row_mode_three_slices_bf16", 9, 5, 20, 767, 516, "bf16", False),
+    ("forward_few_keys_full_grid", 180, 22, 13, 600, 4, "f32", True),
     ("forward_few_keys", 9, 5, 11, 662, 8, "f32", True),
     # context with a share of the keys per wave: one, two and four columns per lane, one to four groups of columns with a short
     # last one, shares without keys (few valid keys), four and eight waves, blocks of four and eight rows
@@ -61,7 +64,7 @@ CASES = [
     ("context_shares_256_columns", 140, 30, 66, 20, 256, "f32", False),
     ("context_shares_260_columns", 3, 9, 300, 40, 260, "f32", False),
     ("context_shares_512_columns_bf16", 41, 30, 66, 40, 512, "bf16", False),
-    ("context_few_keys_104_columns", 9, 5, 11, 662, 104, "f32", False),
+    ("context_few_keys_104_columns", 180, 20, 11, 662, 104, "f32", False),
     ("context_36_keys_of_wide_h", 9, 13, 36, 601, 300, "f32", False),
     ("context_shares_37_keys", 9, 13, 37, 601, 300, "f32", False),
     ("context_no_shares_516_columns", 41, 30, 66, 40, 516, "f32", False),
