@@ -280,8 +280,10 @@ __device__ __forceinline__ float sum_over_waves(float (&s_part)[SB_W][SB_COLS], 
     return tot;
 }
 
-// Forward: S[j] = -2 sum_h v[h] r, r = 1 / (exp(2 (q + k)) + 1) (tanh = 1 - 2 r; the key-independent sum of v drops out of the
-// softmax).  One exponential and one reciprocal per element: nothing to save by factoring when every key meets one query.
+// Forward: S[j] = sum_h v[h] tanh(q[h] + k[j,h]), tanh = 1 - 2 / (exp(2 (q + k)) + 1).  One exponential and one reciprocal per
+// element: nothing to save by factoring when every key meets one query.  The exponent is taken from q + k, so that its rounding
+// error follows the sum and not the operands where these cancel, and the terms v tanh are summed, not v / (exp(2 (q + k)) + 1), whose
+// partial sums stay large where the tanh terms are small.
 template <typename T, bool NARROW, bool ONE>
 __global__ __launch_bounds__(SB_THREADS) void k_step_fwd(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ V, const T *__restrict__ v,
@@ -342,14 +344,16 @@ __global__ __launch_bounds__(SB_THREADS) void k_step_fwd(
                 if (j0 + w + SB_W * u >= L) continue;             // uniform
                 const float4 k4 = kx.x[c][u].get();
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    acc[u] = __builtin_fmaf(comp4(v4[c], e), r_from_sum(kTwoLog2e * comp4(q4[c], e), kTwoLog2e * comp4(k4, e)), acc[u]);
+                for (int e = 0; e < 4; ++e) {
+                    const float x = kTwoLog2e * (comp4(q4[c], e) + comp4(k4, e));
+                    acc[u] = __builtin_fmaf(comp4(v4[c], e), __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f), acc[u]);
+                }
             }
         }
         if (h0 + SB_COLS >= H) {                                  // the scores of these rows are complete
             const float tot = wave_transpose_sum<SB_U>(acc);      // key u in lanes 16 u ..
             const int j = j0 + w + SB_W * (lane >> 4);
-            if ((lane & 15) == 0 && j < L) s_s[j] = -2.f * tot;
+            if ((lane & 15) == 0 && j < L) s_s[j] = tot;
         }
     };
     if (ONE) {
@@ -555,7 +559,7 @@ __global__ __launch_bounds__(SB_THREADS) void k_step_bwd_query(
                 float g[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float rr = r_from_sum(kTwoLog2e * comp4(q4[c], e), kTwoLog2e * comp4(k4, e));
+                    const float rr = fast_rcp(fast_exp2(__builtin_fmaf(kTwoLog2e, comp4(k4, e), kTwoLog2e * comp4(q4[c], e))) + 1.0f);
                     g[e] = ds * __builtin_fmaf(-rr, rr, rr);
                 }
                 accQ[c].x += g[0];
