@@ -556,6 +556,7 @@ constexpr int BS_ROUND = 256;              // one block of k_bwd_small per compu
 constexpr int BS_MOST_BLOCKS = 340;
 constexpr int RS_MOST_BLOCKS = 192;
 constexpr size_t RS_MOST_PARTS = 1 << 20;  // floats: 4 MB
+constexpr int RS_MOST_GROUPS = 65535;      // the groups are a grid's z
 
 // Blocks of one kind per sample and slice when n_x rows are owned and ys waves share a row group.
 static int rs_groups(int hw, int ys, int n_x) { return (n_x + rs_rows(hw, ys) - 1) / rs_rows(hw, ys); }
@@ -610,14 +611,15 @@ static RsPlan rs_plan(const AttnShape &s) {
 // 53 -> 13 us at B = 3, T = 200, H = 76; above it evaluating every tanh twice loses).  Samples of hardly more than a key tile
 // and a row per wave stay with the other form, which is then done before this one has exchanged its parts of dv (7.4
 // against 9.5 us at B = 50, T = 9 / 15), and close to the limit those of up to 600 pairs do (T = 20, H = 32, B = 90, 180 blocks: 9.2
-// against 10.2; ahead again at T = 30, H = 48, B = 60: 10.3 against 11.2).
+// against 10.2; ahead again at T = 30, H = 48, B = 60: 10.3 against 11.2).  Row counts whose groups no grid holds (B = 1, Tk = 32,
+// H = 4: from 524 thousand rows on) stay with the other form, which walks them in passes.
 bool recompute_split_applies(const AttnShape &s, size_t *part_floats, size_t *flag_words) {
     const long long blocks = (long long)s.B * ((s.H + 15) / 16), pairs = (long long)s.Tq * s.Tk;
     if (blocks > RS_MOST_BLOCKS || pairs <= (blocks > 160 ? 600 : 150)) return false;
     const RsPlan p = rs_plan(s);
     *part_floats = (size_t)s.B * p.ka.groups * s.H;
     *flag_words = (size_t)s.B * p.ka.groups * ((s.H + p.hw - 1) / p.hw);
-    return *part_floats <= RS_MOST_PARTS;
+    return *part_floats <= RS_MOST_PARTS && p.ka.groups + p.qa.groups <= RS_MOST_GROUPS;
 }
 
 template <typename T, int HW>
@@ -629,7 +631,6 @@ static hipError_t launch_split_t(const AttnShape &s, const RsPlan &p, const void
     RsAxis qa = p.qa;
     if (!dQp) qa.groups = 0;
     dim3 grid((s.H + HW - 1) / HW, s.B, ka.groups + qa.groups);
-    if (grid.z > 65535) return hipErrorInvalidValue;
     k_recompute_split<T, HW><<<grid, RS_THREADS, 0, st>>>((const T *)Qp, (const T *)Kp, (const T *)v, order, dS, dQp, dKp, parts, flags,
                                                           epoch, dv, s.Tq, s.Tk, s.H, ds_pitch(s.Tk), ka, qa, s.acc ? 1 : 0);
     return hipGetLastError();

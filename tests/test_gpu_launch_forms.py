@@ -19,6 +19,8 @@ CASES = [
     ("split_one_key", 3, 70, 1, 40, 4, "f32", False),
     ("split_many_ranges", 1, 700, 300, 20, 4, "f32", False),
     ("split_bf16", 2, 37, 261, 100, 8, "bf16", False),
+    # few blocks of the other form, but more groups of query rows than a grid holds: that form, in passes
+    ("split_groups_past_a_grid", 1, 530000, 32, 4, 4, "f32", False),
     # recomputation with slices of 16 columns (four lane groups): rows not a multiple of four, more than one pass of 256
     # rows; 32 columns: fewer rows than lane groups would like, two passes; the whole of a narrow H in one slice
     ("slices_of_16", 25, 50, 21, 130, 8, "f32", True),
