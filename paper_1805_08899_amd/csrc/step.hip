@@ -26,11 +26,17 @@ constexpr int ST_KB = 4;                  // keys per wave and batch: a batch of
 // keys 32 n + 4 w .. + 3 of every batch n; the first batch's K, old dKp and old dV are requested before dP is
 // formed.  dP is formed by every h slice of a sample for itself (a few ten thousand multiply-adds, V comes from
 // the L2 that the slices of a sample share).
-template <typename T>
+//
+// DEFER: the key-side sums are left to one batched call at the end of the sentence.  The step then only reads: it
+// writes dQp, and the block of the first h slice writes the step's row of dS (row `ds_row` of the sample's
+// `ds_rows` rows of `ds_pitch` floats, zeros at masked keys and pads) and its sum; dKp, dV and dv_part are not
+// touched.
+template <typename T, bool DEFER>
 __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
     const float *__restrict__ dC, const float *__restrict__ P, const T *__restrict__ Qp, const T *__restrict__ Kp,
     const T *__restrict__ V, const T *__restrict__ v, const int *__restrict__ key_len, float *__restrict__ dQp,
-    float *__restrict__ dKp, float *__restrict__ dV, float *__restrict__ dv_part, int Tk, int H, int Dv, int cw) {
+    float *__restrict__ dKp, float *__restrict__ dV, float *__restrict__ dv_part, float *__restrict__ ds_out,
+    float *__restrict__ ds_sum_out, int ds_rows, int ds_row, int ds_pitch, int Tk, int H, int Dv, int cw) {
     extern __shared__ float s_step[];     // [Tk] P, then [Tk] dP
     float *s_p = s_step, *s_dp = s_step + Tk;
     __shared__ float s_q[ST_W][64], s_r[ST_W][64];
@@ -40,6 +46,11 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
     const bool hv = h < H;
     const int hc = hv ? h : H - 1;
     const int L = clamp_len(key_len[b], Tk);
+    float *ds_dst = DEFER ? ds_out + ((size_t)b * ds_rows + ds_row) * ds_pitch : nullptr;
+    if (DEFER && hs == 0) {               // masked keys and pads of the stored dS row: zeros
+        for (int j = L + (int)threadIdx.x; j < ds_pitch; j += ST_THREADS) ds_dst[j] = 0.f;
+        if (L == 0 && threadIdx.x == 0) ds_sum_out[(size_t)b * ds_rows + ds_row] = 0.f;
+    }
     if (L == 0) {                         // no valid key: the query gets no gradient, the sums get nothing
         if (w == 0 && hv) dQp[(size_t)b * H + h] = 0.f;
         return;
@@ -60,8 +71,8 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
     for (int u = 0; u < ST_KB; ++u) {
         const int j = min(ST_KB * w + u, L - 1);
         k0[u] = ld(Kb, (size_t)j * H + hc);
-        oldk0[u] = dKb[(size_t)j * H + hc];
-        oldv0[u] = dVb[(size_t)j * Dv + c0];
+        oldk0[u] = DEFER ? 0.f : dKb[(size_t)j * H + hc];
+        oldv0[u] = DEFER ? 0.f : dVb[(size_t)j * Dv + c0];
     }
     const float sq = kTwoLog2e * ld(Qp, (size_t)b * H + hc);
     float v_raw = ld(v, (size_t)hc);     // scaled behind the barrier below: as a guarded load with its scaling it was
@@ -120,7 +131,7 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
             } else {
                 const size_t at = (size_t)min(j0 + u, L - 1) * H + hc;
                 k[u] = ld(Kb, at);
-                oldk[u] = dKb[at];
+                oldk[u] = DEFER ? 0.f : dKb[at];
             }
         }
 #pragma unroll
@@ -131,10 +142,11 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
                 const float g = ds * __builtin_fmaf(-rr, rr, rr);
                 accQ += g;
                 accR = __builtin_fmaf(ds, rr, accR);
-                if (hv) store_streaming(&dKb[(size_t)(j0 + u) * H + h], __builtin_fmaf(v4, g, oldk[u]));
+                if (!DEFER && hv) store_streaming(&dKb[(size_t)(j0 + u) * H + h], __builtin_fmaf(v4, g, oldk[u]));
+                if (DEFER && hs == 0 && lane == 0) ds_dst[j0 + u] = ds;
             }
         }
-        for (int c = c_lo + lane, m = 0; c < c_hi; c += 64, ++m) {
+        for (int c = c_lo + lane, m = 0; !DEFER && c < c_hi; c += 64, ++m) {
             const float dc = dCb[c];
 #pragma unroll
             for (int u = 0; u < ST_KB; ++u) {
@@ -157,8 +169,105 @@ __global__ __launch_bounds__(ST_THREADS) void k_step_bwd(
             tr += s_r[k2][lane];
         }
         store_streaming(&dQp[(size_t)b * H + h], v4 * tq);
-        float *dvp = dv_part + (size_t)b * H + h;
-        *dvp += __builtin_fmaf(-2.f, tr, dsum);
+        if (!DEFER) {
+            float *dvp = dv_part + (size_t)b * H + h;
+            *dvp += __builtin_fmaf(-2.f, tr, dsum);
+        } else if (hs == 0 && lane == 0) {
+            ds_sum_out[(size_t)b * ds_rows + ds_row] = dsum;
+        }
+    }
+}
+
+// Forward pass of one decoder step in one block of eight waves per sample, for steps of few keys (see step_fwd_takes_rows): scores
+// with the eight waves taking four keys each per batch and the lanes along h, softmax over the valid keys, context with a thread
+// per column.  tanh is taken from the exponential of the sum here (one exponential and one reciprocal per
+// element): a step is a few thousand elements per wave, nothing to save by factoring it.
+template <typename T>
+__global__ __launch_bounds__(ST_THREADS) void k_step_fwd_rows(
+    const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ V, const T *__restrict__ v,
+    const int *__restrict__ key_len, float *__restrict__ C, float *__restrict__ P, int Tk, int H, int Dv) {
+    extern __shared__ float s_step[];     // [Tk] scores, then probabilities
+    float *s_s = s_step;
+    const int b = blockIdx.x;
+    const int lane = lane_id(), w = wave_id();
+    const int L = clamp_len(key_len[b], Tk);
+    float *Pb = P + (size_t)b * Tk;
+    float *Cb = C + (size_t)b * Dv;
+    if (L == 0) {                         // no valid key: zeros
+        for (int j = threadIdx.x; j < Tk; j += ST_THREADS) Pb[j] = 0.f;
+        for (int d = threadIdx.x; d < Dv; d += ST_THREADS) Cb[d] = 0.f;
+        return;
+    }
+    const T *qb = Qp + (size_t)b * H;
+    const T *Kb = Kp + (size_t)b * Tk * H;
+    const T *Vb = V + (size_t)b * Tk * Dv;
+    const int n_batch = (L + 8 * ST_KB - 1) / (8 * ST_KB);
+    const int H4 = (H % 4 == 0) ? H : 0;  // rows are read four elements at a time when every row starts aligned
+
+    // ---- scores: S[j] = sum_h v[h] tanh(q[h] + k[j,h]),  tanh = 1 - 2 / (exp(2 (q + k)) + 1)
+    for (int n = 0; n < n_batch; ++n) {
+        const int j0 = 8 * ST_KB * n + ST_KB * w;
+        float acc[ST_KB] = {0.f, 0.f, 0.f, 0.f};
+        if (j0 < L) {                                             // wave-uniform
+            for (int h = 4 * lane; h < H4; h += 256) {
+                const float4 q4 = ld4(qb, (size_t)h), v4 = ld4(v, (size_t)h);
+                float4 k4[ST_KB];
+#pragma unroll
+                for (int u = 0; u < ST_KB; ++u) k4[u] = ld4(Kb, (size_t)min(j0 + u, L - 1) * H + h);
+#pragma unroll
+                for (int u = 0; u < ST_KB; ++u) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float x = kTwoLog2e * (comp4(q4, c) + comp4(k4[u], c));
+                        acc[u] += comp4(v4, c) * __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f);
+                    }
+                }
+            }
+            for (int h = H4 + lane; h < H; h += 64) {             // rows that do not start aligned: one element at a time
+                const float qh = ld(qb, (size_t)h), vh = ld(v, (size_t)h);
+#pragma unroll
+                for (int u = 0; u < ST_KB; ++u) {
+                    const float x = kTwoLog2e * (qh + ld(Kb, (size_t)min(j0 + u, L - 1) * H + h));
+                    acc[u] += vh * __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < ST_KB; ++u) {
+                const float tot = wave_sum(acc[u]);
+                if (lane == 0 && j0 + u < L) s_s[j0 + u] = tot;
+            }
+        }
+    }
+    lds_barrier();
+
+    // ---- softmax over the valid keys: every wave forms the maximum and the sum itself (same arithmetic in all)
+    float mx = -INFINITY;
+    for (int j = lane; j < L; j += 64) mx = fmaxf(mx, s_s[j]);
+    mx = wave_max(mx);
+    float z = 0.f;
+    for (int j = lane; j < L; j += 64) z += fast_exp2((s_s[j] - mx) * 1.4426950408889634f);
+    z = wave_sum(z);
+    const float inv = 1.0f / z;
+    lds_barrier();
+    for (int j = threadIdx.x; j < Tk; j += ST_THREADS) {
+        const float p = j < L ? fast_exp2((s_s[j] - mx) * 1.4426950408889634f) * inv : 0.f;
+        if (j < L) s_s[j] = p;
+        store_streaming(&Pb[j], p);
+    }
+    lds_barrier();
+
+    // ---- context: a thread per column, eight value rows in flight
+    for (int d = threadIdx.x; d < Dv; d += ST_THREADS) {
+        float acc = 0.f;
+        for (int j0 = 0; j0 < L; j0 += 8) {
+            float x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = ld(Vb, (size_t)min(j0 + u, L - 1) * Dv + d);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (j0 + u < L) acc = __builtin_fmaf(s_s[j0 + u], x[u], acc);
+        }
+        store_streaming(&Cb[d], acc);
     }
 }
 
@@ -282,8 +391,8 @@ __device__ __forceinline__ float sum_over_waves(float (&s_part)[SB_W][SB_COLS], 
 
 // Forward: S[j] = sum_h v[h] tanh(q[h] + k[j,h]), tanh = 1 - 2 / (exp(2 (q + k)) + 1).  One exponential and one reciprocal per
 // element: nothing to save by factoring when every key meets one query.  The exponent is taken from q + k, so that its rounding
-// error follows the sum and not the operands where these cancel, and the terms v tanh are summed, not v / (exp(2 (q + k)) + 1), whose
-// partial sums stay large where the tanh terms are small.
+// error follows the sum and not the operands where these cancel, and the terms v tanh are summed, not v / (exp(2 (q + k)) + 1),
+// whose partial sums stay large where the tanh terms are small.
 template <typename T, bool NARROW, bool ONE>
 __global__ __launch_bounds__(SB_THREADS) void k_step_fwd(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ V, const T *__restrict__ v,
@@ -433,7 +542,7 @@ __global__ __launch_bounds__(SB_THREADS) void k_step_fwd(
 // The query side of the backward step: dP[j] = sum_d dC[d] V[j,d], dS = P (dP - sum_j P dP), dQp[h] = v[h] sum_j dS (1 - t^2) with
 // t re-evaluated (1 - t^2 = 4 r (1 - r)).  Also leaves the step's row of dS (row `ds_row` of the sample's `ds_rows` rows of
 // `ds_pitch` floats, zeros at masked keys and pads) and its sum.
-template <typename T, bool NARROW, bool ONE>
+template <typename T, bool ONE>
 __global__ __launch_bounds__(SB_THREADS) void k_step_bwd_query(
     const float *__restrict__ dC, const float *__restrict__ P, const T *__restrict__ Qp, const T *__restrict__ Kp,
     const T *__restrict__ V, const T *__restrict__ v, const int *__restrict__ key_len, float *__restrict__ dQp,
@@ -468,7 +577,7 @@ __global__ __launch_bounds__(SB_THREADS) void k_step_bwd_query(
         if (at.more()) r.template load<false>(Vb, Dv, Dv, L, at.j, at.c, lane, w);
     };
     auto load_keys = [&](RowBatch<T> &r, const Walk<false> &at) {
-        if (at.more()) r.template load<NARROW>(Kb, H, h_hi, L, at.j, at.c, lane, w);
+        if (at.more()) r.template load<false>(Kb, H, h_hi, L, at.j, at.c, lane, w);
     };
     if (ONE) load_values(x[0], vw);
     float4 c4[SB_C], q4[SB_C];
@@ -478,7 +587,7 @@ __global__ __launch_bounds__(SB_THREADS) void k_step_bwd_query(
     };
     auto load_q = [&](int h0) {
 #pragma unroll
-        for (int c = 0; c < SB_C; ++c) q4[c] = vec_piece<NARROW>(qb, H, h0 + 256 * c + 4 * lane, false);
+        for (int c = 0; c < SB_C; ++c) q4[c] = vec_piece<false>(qb, H, h0 + 256 * c + 4 * lane, false);
     };
     load_dc(0);
     const float p_first = Pb[min((int)threadIdx.x, L - 1)];
@@ -572,7 +681,7 @@ __global__ __launch_bounds__(SB_THREADS) void k_step_bwd_query(
             const float tot = sum_over_waves(s_part, accQ, lane, w);
             // thread t holds the sum of the lane that loaded column piece_at(4 (t / 4)) + t % 4 of this chunk: a last group of
             // fewer than four columns lies further right than its place
-            const int g4 = h0 + ((int)threadIdx.x & ~3), h = piece_at<NARROW>(H, g4) + ((int)threadIdx.x & 3);
+            const int g4 = h0 + ((int)threadIdx.x & ~3), h = piece_at<false>(H, g4) + ((int)threadIdx.x & 3);
             if (threadIdx.x < SB_COLS && g4 < h_hi && h >= g4 && h < H)
                 store_streaming(&dQp[(size_t)b * H + h], 4.f * ld(v, (size_t)h) * tot);
         }
@@ -619,10 +728,37 @@ static hipError_t launch_step_fwd_t(const AttnShape &s, size_t lds, const void *
     return hipGetLastError();
 }
 
+// Steps that the block of eight waves does sooner (us per launch, it against the sixteen waves).  Past 256 samples: four of its
+// blocks share a compute unit that one block of sixteen waves fills, so those take a second round (H = 640, 300 samples of 4
+// keys: 5.3 against 10.4, of 17: 9.0 against 11.5, of 32: 14.4 against 13.6; in bf16 level at 17).  On few keys its chain is
+// the shorter one, but its trips to memory, one per 32 keys and 256 columns, are not overlapped: ahead up to 16 keys while the
+// rows are narrow (H = 75, bf16, 10 keys: 3.8 against 4.2; not in f32 beside value rows of more than a batch: H = 8, Dv = 972,
+// 13 keys: 5.9 against 4.7), up to 10 past 128 samples (level at H = 772, 160 samples of 10 keys), else up to 6 in f32 (H =
+// 516, 40 samples of 4 keys: 5.0 against 5.4).  A row of fewer than four elements gives the sixteen waves no whole pieces to
+// load: level at 32 keys, past 256 samples at 100 (12.3 against 14.0). Where one batch of whole groups of four holds the step,
+// all its rows are under way at once and the sixteen waves are ahead from the first key on.
+static bool step_fwd_takes_rows(const AttnShape &s) {
+    const bool two_rounds = s.B > 256;
+    if (s.H < 4) return s.Tk <= (two_rounds ? 100 : 32);
+    if (s.H % 4 == 0 && step_one_batch(s)) return false;
+    if (two_rounds) return s.Tk <= (s.bf16 ? 17 : 32);
+    if (s.H <= 128 && (s.bf16 || s.Dv <= SB_COLS)) return s.Tk <= 16;
+    return s.Tk <= (s.B > 128 ? 10 : s.bf16 ? 0 : 6);
+}
+
 hipError_t launch_step_fwd(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,
                            const int *key_len, float *C, float *P, hipStream_t st) {
     const size_t lds = (size_t)s.Tk * sizeof(float);
     if (lds > SB_MOST_LDS) return hipErrorInvalidValue;
+    if (step_fwd_takes_rows(s)) {
+        if (s.bf16)
+            k_step_fwd_rows<bf16_t><<<s.B, ST_THREADS, lds, st>>>((const bf16_t *)Qp, (const bf16_t *)Kp, (const bf16_t *)V,
+                                                                  (const bf16_t *)v, key_len, C, P, s.Tk, s.H, s.Dv);
+        else
+            k_step_fwd_rows<float><<<s.B, ST_THREADS, lds, st>>>((const float *)Qp, (const float *)Kp, (const float *)V,
+                                                                 (const float *)v, key_len, C, P, s.Tk, s.H, s.Dv);
+        return hipGetLastError();
+    }
 #define ECHO_STEP(T, NARROW, ONE) launch_step_fwd_t<T, NARROW, ONE>(s, lds, Qp, Kp, V, v, key_len, C, P, st)
     if (s.H < 4) return s.bf16 ? ECHO_STEP(bf16_t, true, false) : ECHO_STEP(float, true, false);
     if (step_one_batch(s)) return s.bf16 ? ECHO_STEP(bf16_t, false, true) : ECHO_STEP(float, false, true);
@@ -632,33 +768,38 @@ hipError_t launch_step_fwd(const AttnShape &s, const void *Qp, const void *Kp, c
 
 size_t step_lds_bytes(const AttnShape &s) { return 2 * (size_t)s.Tk * sizeof(float); }
 
-template <typename T>
-static hipError_t launch_step_bwd_t(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
-                                    const void *V, const void *v, const int *key_len, float *dQp, float *dKp, float *dV,
-                                    float *dv_part, hipStream_t st) {
+template <typename T, bool DEFER>
+static hipError_t launch_step_bwd_t(const AttnShape &s, const float *dC, const float *P, const void *Qp,
+                                    const void *Kp, const void *V, const void *v, const int *key_len, float *dQp,
+                                    float *dKp, float *dV, float *dv_part, float *ds_out, float *ds_sum_out,
+                                    int ds_rows, int ds_row, hipStream_t st) {
     const size_t lds = step_lds_bytes(s);
     if (lds > 64 * 1024) return hipErrorInvalidValue;
     if (lds > 40 * 1024) {
         static LdsGrants granted;
-        hipError_t e = ensure_dynamic_lds((const void *)k_step_bwd<T>, lds, granted);
+        hipError_t e = ensure_dynamic_lds((const void *)k_step_bwd<T, DEFER>, lds, granted);
         if (e != hipSuccess) return e;
     }
     const int n_hs = (s.H + 63) / 64;
     const int cw = (s.Dv + n_hs - 1) / n_hs;                     // columns of dV per h slice
     dim3 grid(n_hs, s.B);
-    k_step_bwd<T><<<grid, ST_THREADS, lds, st>>>(dC, P, (const T *)Qp, (const T *)Kp, (const T *)V, (const T *)v, key_len, dQp,
-                                                 dKp, dV, dv_part, s.Tk, s.H, s.Dv, cw);
+    k_step_bwd<T, DEFER><<<grid, ST_THREADS, lds, st>>>(dC, P, (const T *)Qp, (const T *)Kp, (const T *)V,
+                                                        (const T *)v, key_len, dQp, dKp, dV, dv_part, ds_out,
+                                                        ds_sum_out, ds_rows, ds_row, ds_pitch(s.Tk), s.Tk, s.H, s.Dv,
+                                                        cw);
     return hipGetLastError();
 }
 
 hipError_t launch_step_bwd(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
                            const void *V, const void *v, const int *key_len, float *dQp, float *dKp, float *dV,
                            float *dv_part, hipStream_t st) {
-    return s.bf16 ? launch_step_bwd_t<bf16_t>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, st)
-                  : launch_step_bwd_t<float>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, st);
+    return s.bf16 ? launch_step_bwd_t<bf16_t, false>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, nullptr,
+                                                     nullptr, 1, 0, st)
+                  : launch_step_bwd_t<float, false>(s, dC, P, Qp, Kp, V, v, key_len, dQp, dKp, dV, dv_part, nullptr,
+                                                    nullptr, 1, 0, st);
 }
 
-template <typename T, bool NARROW, bool ONE>
+template <typename T, bool ONE>
 static hipError_t launch_step_bwd_query_t(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
                                           const void *V, const void *v, const int *key_len, float *dQp, float *ds_out,
                                           float *ds_sum_out, int steps, int step, hipStream_t st) {
@@ -666,24 +807,55 @@ static hipError_t launch_step_bwd_query_t(const AttnShape &s, const float *dC, c
     if (lds > SB_MOST_LDS) return hipErrorInvalidValue;
     if (lds > 16 * 1024) {
         static LdsGrants granted;
-        hipError_t e = ensure_dynamic_lds((const void *)k_step_bwd_query<T, NARROW, ONE>, lds, granted);
+        hipError_t e = ensure_dynamic_lds((const void *)k_step_bwd_query<T, ONE>, lds, granted);
         if (e != hipSuccess) return e;
     }
     const int parts = step_parts(s.B, s.H, 256);
-    k_step_bwd_query<T, NARROW, ONE><<<dim3(s.B, parts), SB_THREADS, lds, st>>>(
+    k_step_bwd_query<T, ONE><<<dim3(s.B, parts), SB_THREADS, lds, st>>>(
         dC, P, (const T *)Qp, (const T *)Kp, (const T *)V, (const T *)v, key_len, dQp, ds_out, ds_sum_out, steps, step,
         ds_pitch(s.Tk), s.Tk, s.H, s.Dv, step_part_width(s.H, 256, parts));
     return hipGetLastError();
 }
 
+// Query gradients for which k_step_bwd is done sooner: its blocks of eight waves, one per 64 columns of h, request K together
+// with V and four of them share a compute unit, but every one forms dP of its sample again.  (us per launch, this form against
+// the sixteen waves, f32 with Dv = H; over 2180 shapes about 30 are more than 5 % slower than the better form.)
+//   Up to a block for every fourth compute unit: up to 300 keys (H = 640, 4 samples of 32: 4.0 against 5.6); where the sixteen
+//   waves need several batches for a row, at up to 32 blocks any number (H = 640, 1 sample of 400: 14.8 against 16.8).
+//   Beyond, while the value rows that the blocks read together stay below 32 MB, 16 where a row is one batch of the sixteen
+//   waves (H = 312, 21 samples of 160, 21 MB: 12.7 against 10.4; not past 256 samples, where these take a second round) or
+//   where short rows make the many blocks the cost (bf16, more than a block per unit), and
+//     up to a block per unit: up to 300 keys (H = 75, 100 samples of 200: 11.4 against 11.6);
+//     more: one batch of 32 keys (H = 75, 160 samples of 32: 4.8 against 5.0, of 48: 5.9 against 5.4) on at most 900 blocks (H
+//     = 640, 100 samples of 4: 5.0 against 5.3), 600 where one batch of the sixteen waves holds the step (H = 256, 100 samples
+//     of 32: 4.4 against 4.6; H = 301, 160 samples of 4, 800 blocks: 5.1 against 4.6);
+//     past 256 samples 100 keys on at most 1500 blocks (H = 128, 300 samples of 32: 5.3 against 7.6; H = 256, 300 samples of
+//     32, 39 MB: 9.1 against 7.6).
+// One slice of h repeats nothing: always past 256 samples (H = 32, 300 samples of 100: 8.5 against 12.9).  Rows of fewer than
+// four elements in any case (H = 3, 64 samples of 17: 4.3 against 6.0).
+static bool step_bwd_takes_slices(const AttnShape &s) {
+    const long long slices = (s.H + 63) / 64, blocks = slices * s.B;
+    if (s.H < 4 || (slices == 1 && s.B > 256)) return true;
+    if (blocks <= 64) return s.Tk <= 300 || (blocks <= 32 && s.H > SB_COLS);
+    const bool one_column_batch = s.H <= SB_COLS && s.Dv <= SB_COLS;
+    const long long bytes = blocks * s.Tk * s.Dv * (s.bf16 ? 2 : 4);
+    if (bytes > ((one_column_batch && s.B <= 256) || (s.bf16 && blocks > 256) ? 16 << 20 : 32 << 20)) return false;
+    if (blocks <= 256) return s.Tk <= 300;
+    return s.B > 256 ? blocks <= 1500 && s.Tk <= 100 : blocks <= (step_one_batch(s) ? 600 : 900) && s.Tk <= 32;
+}
+
 hipError_t launch_step_bwd_query(const AttnShape &s, const float *dC, const float *P, const void *Qp, const void *Kp,
                                  const void *V, const void *v, const int *key_len, float *dQp, float *ds_out,
                                  float *ds_sum_out, int steps, int step, hipStream_t st) {
-#define ECHO_QUERY(T, NARROW, ONE) \
-    launch_step_bwd_query_t<T, NARROW, ONE>(s, dC, P, Qp, Kp, V, v, key_len, dQp, ds_out, ds_sum_out, steps, step, st)
-    if (s.H < 4) return s.bf16 ? ECHO_QUERY(bf16_t, true, false) : ECHO_QUERY(float, true, false);
-    if (step_one_batch(s)) return s.bf16 ? ECHO_QUERY(bf16_t, false, true) : ECHO_QUERY(float, false, true);
-    return s.bf16 ? ECHO_QUERY(bf16_t, false, false) : ECHO_QUERY(float, false, false);
+    if (step_bwd_takes_slices(s))
+        return s.bf16 ? launch_step_bwd_t<bf16_t, true>(s, dC, P, Qp, Kp, V, v, key_len, dQp, nullptr, nullptr, nullptr, ds_out,
+                                                        ds_sum_out, steps, step, st)
+                      : launch_step_bwd_t<float, true>(s, dC, P, Qp, Kp, V, v, key_len, dQp, nullptr, nullptr, nullptr, ds_out,
+                                                       ds_sum_out, steps, step, st);
+#define ECHO_QUERY(T, ONE) \
+    launch_step_bwd_query_t<T, ONE>(s, dC, P, Qp, Kp, V, v, key_len, dQp, ds_out, ds_sum_out, steps, step, st)
+    if (step_one_batch(s)) return s.bf16 ? ECHO_QUERY(bf16_t, true) : ECHO_QUERY(float, true);
+    return s.bf16 ? ECHO_QUERY(bf16_t, false) : ECHO_QUERY(float, false);
 #undef ECHO_QUERY
 }
 

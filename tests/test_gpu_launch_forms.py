@@ -147,11 +147,36 @@ STEPS = [
     ("h_2_bf16", 3, 20, 2, 8, "bf16"),
     ("h_3", 3, 130, 3, 516, "f32"),
     ("h_4", 3, 66, 4, 4, "f32"),
+    # forward in blocks of eight waves: the last count of keys that takes it and the first that does not, by width, number of
+    # samples and type; columns and value columns that are no multiples of its 256 and 512
+    ("rows_16_keys", 5, 16, 75, 620, "f32"),
+    ("rows_not_17_keys", 5, 17, 75, 620, "bf16"),
+    ("rows_6_keys_wide", 5, 6, 1001, 1004, "f32"),
+    ("rows_not_7_keys_wide", 5, 7, 1001, 1004, "f32"),
+    ("rows_10_keys_past_128_samples", 129, 10, 516, 36, "bf16"),
+    ("rows_32_keys_past_256_samples", 257, 32, 131, 880, "f32"),
+    ("rows_17_keys_past_256_samples_bf16", 257, 17, 428, 516, "bf16"),
+    ("rows_one_key", 300, 1, 514, 4, "f32"),
+    ("rows_h_3_100_keys", 260, 100, 3, 8, "f32"),
+    # query gradient in blocks per 64 columns: one key, one and several batches of 32 keys, a last slice of one column, the limits
+    # on keys, blocks and value bytes
+    ("slices_one_key", 7, 1, 65, 4, "f32"),
+    ("slices_300_keys", 4, 300, 700, 40, "bf16"),
+    ("slices_not_301_keys", 4, 301, 512, 40, "f32"),
+    ("slices_any_keys_32_blocks", 2, 410, 1024, 1024, "f32"),
+    ("slices_16_mb", 100, 163, 128, 128, "f32"),
+    ("slices_not_past_16_mb", 100, 164, 128, 128, "f32"),
+    ("slices_26_mb_of_wide_rows", 20, 100, 640, 644, "bf16"),
+    ("slices_900_blocks", 100, 32, 520, 20, "f32"),
+    ("slices_not_901_blocks", 101, 5, 520, 20, "bf16"),
+    ("slices_not_601_blocks_of_one_batch", 121, 9, 301, 20, "f32"),
+    ("slices_1500_blocks", 300, 33, 301, 20, "f32"),
+    ("slices_one_past_256_samples", 257, 70, 64, 24, "bf16"),
 ]
 
 
 @pytest.mark.parametrize("case", STEPS, ids=[c[0] for c in STEPS])
-def test_step_of_one_block_per_sample(case):
+def test_step_of_one_query(case):
     import torch
     assert torch.cuda.is_available(), "needs the GPU"
     from paper_1805_08899_amd import binding as eb, harness

@@ -29,10 +29,12 @@ def _check_probabilities(P, S, H, terms, sums, key_len, name):
 
 
 STEPS = [
-    # name, B, Tk, H, entry point: one batch of rows and columns, several, rows of fewer than four elements, four blocks a sample
+    # name, B, Tk, H, entry point: one batch of rows and columns, several, rows of fewer than four elements, few keys in eight waves, four blocks a
+    # sample
     ("one_batch", 3, 20, 48, "step"),
     ("several_batches", 2, 150, 600, "step"),
     ("narrow_rows", 3, 40, 3, "step"),
+    ("few_keys", 3, 6, 45, "step"),
     ("four_blocks", 3, 20, 48, "fwd"),
 ]
 
