@@ -734,15 +734,17 @@ static hipError_t launch_step_fwd_t(const AttnShape &s, size_t lds, const void *
 // the shorter one, but its trips to memory, one per 32 keys and 256 columns, are not overlapped: ahead up to 16 keys while the
 // rows are narrow (H = 75, bf16, 10 keys: 3.8 against 4.2; not in f32 beside value rows of more than a batch: H = 8, Dv = 972,
 // 13 keys: 5.9 against 4.7), up to 10 past 128 samples (level at H = 772, 160 samples of 10 keys), else up to 6 in f32 (H =
-// 516, 40 samples of 4 keys: 5.0 against 5.4).  A row of fewer than four elements gives the sixteen waves no whole pieces to
-// load: level at 32 keys, past 256 samples at 100 (12.3 against 14.0). Where one batch of whole groups of four holds the step,
-// all its rows are under way at once and the sixteen waves are ahead from the first key on.
+// 516, 40 samples of 4 keys: 5.0 against 5.4); rows that do not start aligned it reads element by element (H = 587, 88 samples
+// of 5 keys: 6.3 against 5.9; up to 4 keys past 128 samples).  A row of fewer than four elements gives the sixteen waves no
+// whole pieces to load: level at 32 keys, past 256 samples at 100 (12.3 against 14.0). Where one batch of whole groups of four
+// holds the step, all its rows are under way at once and the sixteen waves are ahead from the first key on.
 static bool step_fwd_takes_rows(const AttnShape &s) {
     const bool two_rounds = s.B > 256;
     if (s.H < 4) return s.Tk <= (two_rounds ? 100 : 32);
     if (s.H % 4 == 0 && step_one_batch(s)) return false;
     if (two_rounds) return s.Tk <= (s.bf16 ? 17 : 32);
     if (s.H <= 128 && (s.bf16 || s.Dv <= SB_COLS)) return s.Tk <= 16;
+    if (s.H % 4 != 0) return s.B > 128 && s.Tk <= 4;
     return s.Tk <= (s.B > 128 ? 10 : s.bf16 ? 0 : 6);
 }
 

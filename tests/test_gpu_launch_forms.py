@@ -151,8 +151,10 @@ STEPS = [
     # samples and type; columns and value columns that are no multiples of its 256 and 512
     ("rows_16_keys", 5, 16, 75, 620, "f32"),
     ("rows_not_17_keys", 5, 17, 75, 620, "bf16"),
-    ("rows_6_keys_wide", 5, 6, 1001, 1004, "f32"),
-    ("rows_not_7_keys_wide", 5, 7, 1001, 1004, "f32"),
+    ("rows_6_keys_wide", 5, 6, 1000, 1004, "f32"),
+    ("rows_not_7_keys_wide", 5, 7, 1000, 1004, "f32"),
+    ("rows_4_keys_of_odd_h", 129, 4, 587, 20, "f32"),
+    ("rows_not_5_keys_of_odd_h", 129, 5, 587, 20, "bf16"),
     ("rows_10_keys_past_128_samples", 129, 10, 516, 36, "bf16"),
     ("rows_32_keys_past_256_samples", 257, 32, 131, 880, "f32"),
     ("rows_17_keys_past_256_samples_bf16", 257, 17, 428, 516, "bf16"),
