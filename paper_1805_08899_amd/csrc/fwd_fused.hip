@@ -1257,12 +1257,11 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
     // Row mode: all lanes along h, so a last slice that H fills badly leaves lanes idle; on a small grid, where latency and
     // not arithmetic decides, it is still the fastest (B = 128, T = 60, H = 64: 23.4 us against 14.6 in narrow slices;
     // B = 1, T = 53, H = 48: 7.2 against 7.6).
-    // An H of three slices takes the form for four on grids that stay below a round of it, idle lanes included (B = 20, T = 5 / 4,
-    // H = 712: 9.8 -> 7.4 us; B = 13, T = 18 / 20, H = 576 in bf16: 11.3 -> 9.5; B = 60, T = 40 / 32, H = 768, 300 blocks in bf16: 17.3 -> 15.5; but
-    // B = 60, T = 30 / 28, H = 530, 240 blocks: 12.7 -> 14.1).
+    // An H of three slices takes the form for four, idle lanes included, on grids up to a round of its blocks (B = 20, T = 5 / 4, H =
+    // 712: 9.8 -> 7.4 us; 240 shapes of 18 to 32 keys up to 512 blocks: the fastest of all forms, or within 6 % of it, on all).
     const int row_ns = fwd_row_mode_slices(s);
     const bool three = s.H > 2 * FW_ST && s.H <= 3 * FW_ST;
-    if (row_ns > 0 && (three ? 4 * FW_ST * n8 <= 420LL * s.H : 5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
+    if (row_ns > 0 && (three ? n8 <= 512 : 5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
         switch (row_ns) {
             case 1: return launch_fwd_fused_t<T, 8, 64, 1, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
             case 2: return launch_fwd_fused_t<T, 8, 64, 2, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
@@ -1273,19 +1272,31 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
     // H = 660: 9.8 us in them, 9.1 in slices of 256).
     if (s.Tk <= 16) return launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
     // A grid that blocks of eight rows do not fill: blocks of four rows, of eight waves (two blocks on a CU) while there is
-    // hardly more than one for a CU (short key axes give eight waves little each: B = 44, T = 24 / 40, H = 860, 264 blocks: 26 us against
-    // 21.8), else of four waves (four blocks on a CU, 1024 at a time).
-    // B = 4, T = 300, H = 1024: 172 -> 71 us; B = 37, T = 61 / 83, H = 300: 28.8 -> 18.6; B = 16, T = 100, H = 512: 31 -> 21.
-    // Up to about a round of them at H <= 512 (B = 24, T = 180 / 134, H = 492, 1080 blocks: 57 -> 44; B = 21, T = 227, H = 47, 1197 blocks: level).
-    // Beyond H = 512 the other forms cost more per block; where slices of 256 columns waste an eighth of their lanes or more, a round
-    // and a half on long key axes (B = 20, T = 213 / 186, H = 776: 88 -> 70; B = 58, T = 108 / 163, H = 568: 78 -> 70) and one round on
-    // short ones (B = 164, T = 29 / 25, H = 596, 1312 blocks: 30.1 against 25.4 below), else two thirds of one (B = 75, T =
-    // 31 / 33, H = 767, 600 blocks: 22.5 -> 20.1; B = 28, T = 134 / 103, H = 672, 952 blocks: 52 against 47 below).
+    // hardly more than one for a CU, else of four waves (four blocks on a CU, 1024 at a time), up to about a round of them at H <= 512.
+    // B = 4, T = 300, H = 1024: 172 -> 71 us; B = 37, T = 61 / 83, H = 300: 28.8 -> 18.6; B = 16, T = 100, H = 512: 31 -> 21; B = 24, T =
+    // 180 / 134, H = 492, 1080 blocks: 57 -> 44; B = 21, T = 227, H = 47, 1197 blocks: level.
+    // Beyond H = 512 a block of four rows exponentiates keys for half as many rows, and the block of eight rows, eight waves and all
+    // lanes along h is the fastest from about one of them per CU on, where slices of 256 columns waste an eighth of their lanes up to
+    // 460 (1296 shapes of 18 to 250 keys; against four rows in four waves: B = 28, T = 80, H = 1024, 280 blocks of eight rows, 59 -> 41 us
+    // in bf16, 38.8 -> 35.7 in f32; B = 22, T = 100, H = 768 in bf16 52 -> 42).  Below that the four rows in eight waves pay while their
+    // blocks run all at once or hardly more (H = 640: T = 100, 375 of them, 23 against 35; T = 50, 221, 15 against 20; H = 516, T = 64,
+    // 560: 26 against 25), less far on short key axes, where in f32, and in bf16 just past them, the four rows in four waves
+    // come between (that last shape 22; H = 640, T = 50, 377 blocks: 16.8 against 17.9).
     const int p16 = fwd_h_pad(s.H, 16), p32 = fwd_h_pad(s.H, 32), p64 = fwd_h_pad(s.H, 64);
     const bool wide_wastes = s.H <= 1024 && 8 * p16 <= 7 * p64;
-    if (n4 <= (s.Tk > 64 ? 300 : 240)) return launch_fwd_fused_t<T, 4, 16, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
-    if (n4 <= (s.H <= 512 ? 1100 : wide_wastes ? (s.Tk > 64 ? 1600 : 1024) : 650))
-        return launch_fwd_fused_t<T, 4, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    if (s.H <= 512) {
+        if (n4 <= (s.Tk > 64 ? 300 : 240)) return launch_fwd_fused_t<T, 4, 16, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+        if (n4 <= 1100) return launch_fwd_fused_t<T, 4, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    } else if (s.Tk > 32 || s.H > 1024) {
+        // largest grids of four-row blocks, of eight and of four waves
+        const int most8 = s.Tk > 64 ? (s.H <= 768 ? 580 : 512) : s.bf16 && (wide_wastes || s.Tk > 40) ? 420 : 240;
+        if (n4 <= most8) return launch_fwd_fused_t<T, 4, 16, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
+        const int most4 = s.Tk > 64 ? 0 : s.bf16 ? (wide_wastes && s.Tk > 48 ? 600 : 0) : wide_wastes ? 600 : 440;
+        if (n4 <= most4) return launch_fwd_fused_t<T, 4, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    }
+    if (s.H > 512 && wide_wastes && n8 <= 600)
+        return n8 <= 460 ? launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st)
+                         : launch_fwd_fused_t<T, 4, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
     // Full grids: blocks of four waves, four of them on a CU (9 % faster than eight-wave blocks at B = 128, T = 100, H = 512).
     // Slices of 128 columns, two lane groups: a pass takes eight keys, and its reduction and addressing are shared by twice as
     // many (81 -> 77 us at that shape); slices of 64 where H fills them better (B = 23, T = 217 / 286, H = 40: 79 -> 35 us) and

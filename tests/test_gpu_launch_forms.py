@@ -51,6 +51,18 @@ CASES = [
     ("forward_full_slices_of_128", 140, 29, 66, 243, 4, "f32", True),
     ("forward_full_slices_of_128_bf16", 140, 31, 70, 241, 4, "bf16", False),
     ("forward_full_slices_of_256", 50, 53, 40, 1001, 4, "f32", True),
+    # beyond H = 512: four rows in eight waves at their last grid, four rows in four waves next to it on short key axes, then eight
+    # rows in eight waves, and four rows in four waves again where slices of 256 columns waste lanes
+    ("forward_wide_four_rows_eight_waves", 36, 61, 70, 530, 4, "f32", True),
+    ("forward_wide_four_rows_eight_waves_bf16", 26, 62, 40, 643, 36, "bf16", False),
+    ("forward_wide_four_rows_four_waves", 37, 61, 60, 530, 4, "f32", False),
+    ("forward_wide_four_rows_four_waves_bf16", 37, 61, 60, 530, 68, "bf16", False),
+    ("forward_wide_four_rows_four_waves_700", 27, 61, 40, 700, 4, "f32", True),
+    ("forward_wide_eight_rows", 45, 61, 70, 516, 132, "f32", True),
+    ("forward_wide_eight_rows_bf16", 27, 61, 40, 767, 4, "bf16", False),
+    ("forward_wide_four_rows_again", 64, 61, 70, 637, 4, "f32", False),
+    ("forward_three_slices_512_blocks", 128, 25, 27, 516, 12, "f32", True),
+    ("forward_three_slices_past_512_blocks", 129, 25, 27, 516, 12, "f32", False),
     ("forward_row_mode_three_slices", 9, 21, 32, 513, 8, "f32", True),
     ("forward_row_mode_three_slices_bf16", 9, 5, 20, 767, 516, "bf16", False),
     ("forward_few_keys_full_grid", 180, 22, 13, 600, 4, "f32", True),
