@@ -972,10 +972,9 @@ hipError_t launch_ds_finish(const AttnShape &s, const float *P, const int *key_l
 }
 
 hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, const float *P, const int *key_len,
-                          float *dS, float *ds_rowsum, int *order, float *dV, hipStream_t st, bool with_ds) {
+                          float *dS, float *ds_rowsum, int *order, float *dV, bool one_round, hipStream_t st, bool with_ds) {
     const int sorted = s.B <= kMaxSortedB ? 1 : 0;
-    const int n_hs = (s.H + 63) / 64;
-    const int fold = (sorted && (long long)s.B * n_hs <= 512) ? 1 : 0;   // recompute grid in one round
+    const int fold = sorted && one_round ? 1 : 0;
     if (bwd_pre_in_parts(s)) {
         if (s.Dv <= 512)
             return s.bf16 ? launch_parts_t<bf16_t, 1>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold)

@@ -316,8 +316,7 @@ __global__ __launch_bounds__(RC_THREADS, 4) void k_recompute(
         if constexpr (NS >= 4) tot = transpose_pair<16>(tot, tot, lane);
         send_part(&dv_part[(size_t)b * H + h], __builtin_fmaf(-2.f, tot, s_rowsum), hv && (NS == 1 || sub == 0), &flags[b], epoch);
     }
-    // B4 without a launch of its own: the block of the last slot, which starts last and holds the lightest sample, adds the
-    // parts of its slice of h
+    // B4 without a launch of its own: the block of the last slot, which starts last, adds the parts of its slice of h
     if ((int)blockIdx.y != n_slots - 1) return;
     lds_barrier();                                   // s_dv is reused below
     const float tot = sum_parts<HW, RC_W>(dv_part, flags, n_slots, H, h, epoch, [](int) { return false; }, &s_dv[0][0], s_seen);
@@ -370,6 +369,11 @@ static int recompute_width(const AttnShape &s) {
     for (int narrow = 32; narrow >= 16; narrow /= 2)
         if (s.H <= narrow || (s.Tq > 3 * RC_W && recompute_time(s, narrow) < 0.98f * recompute_time(s, hw))) hw = narrow;
     return hw;
+}
+
+bool recompute_in_one_round(const AttnShape &s, bool stash) {
+    const int hw = stash ? 64 : recompute_width(s);
+    return (long long)s.B * ((s.H + hw - 1) / hw) <= RC_ROUND;
 }
 
 template <typename T>

@@ -212,3 +212,41 @@ def test_step_of_one_query(case):
     got = db.results()
     assert db.check_guards() == []
     assert_parity(got, oracle_outputs(inputs, workers=1), inputs, dt, name)
+
+
+ORDERS = [
+    # name, B, Tq, Tk, H, folded: slices of 64 columns in one round; more than a round of slices of 16 where slices of 64 would be
+    # one; every tanh twice in independent blocks
+    ("one_round", 64, 50, 50, 512, True),
+    ("narrow_slices_past_a_round", 28, 80, 80, 300, False),
+    ("split", 5, 200, 200, 76, False),
+]
+
+
+@pytest.mark.parametrize("case", ORDERS, ids=[c[0] for c in ORDERS])
+def test_order_of_the_samples_in_the_recompute_grid(case):
+    """Heaviest sample first; in a grid that runs all at once the second half lightest first, so that heavy and light blocks meet on
+    a compute unit.  The order is the run of `sample | keys << 16` words that the backward leaves in its workspace."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import harness
+    name, B, Tq, Tk, H, folded = case
+    print("order", case, flush=True)
+    wl = Workload(name, B, Tq, Tk, H, 4, "f32", 0.5, 1, Tk, False)
+    inputs = make_inputs(wl, seed=17)
+    inputs["key_len"] = np.random.default_rng(17).integers(1, Tk + 1, B).astype(np.int32)
+    db = harness.DeviceBatch(wl, inputs)
+    db.poison_outputs()
+    db.fwd()
+    db.bwd()
+    torch.cuda.synchronize()
+    words = db.ws.view(torch.int32).cpu().numpy()
+    is_entry = np.zeros(words.size, dtype=bool)
+    for b, L in enumerate(inputs["key_len"]):
+        is_entry |= words == (b | int(L) << 16)
+    runs = [k for k in np.flatnonzero(is_entry) if is_entry[k:k + B].all() and len(set(words[k:k + B] & 0xffff)) == B]
+    assert len(runs) == 1, runs
+    lengths = words[runs[0]:runs[0] + B] >> 16
+    half = (B + 1) // 2 if folded else B
+    assert (np.diff(lengths[:half]) <= 0).all() and (np.diff(lengths[half:]) >= 0).all(), lengths
+    assert lengths[:half].min() >= lengths[half:].max(initial=0)
