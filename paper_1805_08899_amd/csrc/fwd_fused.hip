@@ -166,13 +166,27 @@ struct KeyStream {
     __device__ __forceinline__ void advance() { fetch(); }
 };
 
+// For an H that is no multiple of four: minus half of the sum of v over columns of a lane, added to the lane's sums of v r.  What is
+// summed over the lanes is then sum_h v (r - 1/2) = -1/2 sum_h v tanh, small where the tanh terms are, and not sum_h v r, half of
+// which never changes.  (Scores of such an H from k_score, whose sums per lane end the same way, gave probabilities with an error of
+// 1.03e-7 over 60 drawn shapes; without this it is 1.27e-7, with it 1.07e-7.)  The same arithmetic for all keys of a row, so that the
+// constant drops out of the softmax.
+__device__ __forceinline__ float lane_centre(const float *__restrict__ s_c, int hl, int n_slices, int slice) {
+    float sum = 0.f;
+    for (int s = 0; s < n_slices; ++s) {
+        const float4 c = *reinterpret_cast<const float4 *>(s_c + s * slice + 4 * hl);        // 1 / v, kHugeC for zero
+        sum += (fast_rcp(c.x) + fast_rcp(c.y)) + (fast_rcp(c.z) + fast_rcp(c.w));
+    }
+    return -0.5f * sum;
+}
+
 // Streaming mode, one pass of one wave: up to NJ keys per lane group, nj in all, starting at column jcol0 of the score tile,
 // all rows of the block, all slices of h, factor path only.  s_e: LDS rows of exp(2q)/v, pitch Hp; s_c: 1/v.  NI > 0: exactly
 // NI rows are live, known at compile time (no per-row branches, the next row's LDS read is issued a row ahead);
-// NI == 0: the first ni.  What is written is the score without its key-independent term: -2 sum_h v r.
+// NI == 0: the first ni.  TAIL: see lane_centre().
 // qe_max, c_max: the block's largest |exp(2q)/v| and |1/v|.  Returns true if the operands may leave the
 // range of the factor path, in which case nothing was written and the caller must redo the pass exactly.
-template <typename T, int RT, int HL, int NJ, int NI>
+template <typename T, int RT, int HL, int NJ, int NI, bool TAIL>
 __device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const float *__restrict__ s_c, int Hp, int ni, int nj,
                                         KeyStream<T, HL> &ks, float qe_max, float c_max, float *__restrict__ s_S,
                                         int spitch, int jcol0) {
@@ -212,6 +226,17 @@ __device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const flo
                 fw_row_keys<NJ>(fq, cv, fk, acc[a]);
             }
         }
+        if constexpr (TAIL) {
+            // at least every four slices, so that the sums stay small within the lane too; formed here: a register kept through
+            // the slices costs 25 spilled ones
+            if ((s & 3) == 3 || s + 1 == ks.NS) {
+                const float half_v = lane_centre(s_c + (s & ~3) * SS, hl, (s & 3) + 1, SS);
+#pragma unroll
+                for (int a = 0; a < NR; ++a)
+#pragma unroll
+                    for (int c = 0; c < NJ; ++c) acc[a][c] += half_v;
+            }
+        }
     }
     // the negation also sends a NaN bound (NaN or infinite operands) to the exact path
     if (__any(!(__builtin_fmaf(qe_max, kmax, c_max) < kPairLimit))) return true;
@@ -241,6 +266,7 @@ template <typename T>
 __device__ __noinline__ void fw_pass_exact(const T *__restrict__ qrow0, int ni, const T *__restrict__ krow0, int nj,
                                            int H, const T *__restrict__ v, float *__restrict__ s_S, int spitch,
                                            int jcol0) {
+    const float centre = (H & 3) != 0 ? 0.5f : 0.f;            // as lane_centre()
     const int lane = lane_id();
     for (int a = 0; a < ni; ++a) {
         for (int c = 0; c < nj; ++c) {
@@ -248,7 +274,7 @@ __device__ __noinline__ void fw_pass_exact(const T *__restrict__ qrow0, int ni, 
             for (int h = lane; h < H; h += 64) {
                 const float sq = kTwoLog2e * ld(qrow0, (size_t)a * H + h);
                 const float sk = kTwoLog2e * ld(krow0, (size_t)c * H + h);
-                acc = __builtin_fmaf(ld(v, h), r_from_sum(sq, sk), acc);
+                acc = __builtin_fmaf(ld(v, h), r_from_sum(sq, sk) - centre, acc);
             }
             acc = wave_sum(acc);
             if (lane == 0) s_S[a * spitch + jcol0 + c] = -2.f * acc;
@@ -263,7 +289,7 @@ __device__ __noinline__ void fw_pass_exact(const T *__restrict__ qrow0, int ni, 
 // Returns true (nothing written) if the operands may leave the range of the factor path.
 template <typename T, int NS, int NKM, int NK, int C0 = 0>
 __device__ __forceinline__ bool fw_rows(const RawKey<T> (&raw)[NS][NKM], const float *__restrict__ s_e,
-                                        const float *__restrict__ s_c, int Hp, int ni, float qe_max, float c_max,
+                                        const float *__restrict__ s_c, int Hp, int ni, float acc0, float qe_max, float c_max,
                                         float *__restrict__ s_S, int spitch, int jcol0) {
     const int lane = lane_id();
     float fk[NS][4][NK];
@@ -286,7 +312,7 @@ __device__ __forceinline__ bool fw_rows(const RawKey<T> (&raw)[NS][NKM], const f
     for (int a = 0; a < ni; ++a) {
         float acc[NK];
 #pragma unroll
-        for (int c = 0; c < NK; ++c) acc[c] = 0.f;
+        for (int c = 0; c < NK; ++c) acc[c] = acc0;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             // operands of the next slice (of the next row after the last slice; the row past the last one
@@ -335,7 +361,7 @@ __device__ __forceinline__ bool fw_rows(const RawKey<T> (&raw)[NS][NKM], const f
 
 template <typename T, int NS, int NKM>
 __device__ __forceinline__ bool fw_rows_n(int nk, const RawKey<T> (&raw)[NS][NKM], const float *__restrict__ s_e,
-                                          const float *__restrict__ s_c, int Hp, int ni, float qe_max, float c_max,
+                                          const float *__restrict__ s_c, int Hp, int ni, float acc0, float qe_max, float c_max,
                                           float *__restrict__ s_S, int spitch, int jcol0) {
     // More than twelve 16-byte groups of exponentials (keys x slices) do not fit the registers next to the row
     // loop's operands: the loop would fetch them back from scratch memory row after row.  Such a share is
@@ -343,11 +369,11 @@ __device__ __forceinline__ bool fw_rows_n(int nk, const RawKey<T> (&raw)[NS][NKM
 #define FW_ROWS_CASE(N)                                                                                       \
     case N:                                                                                                   \
         if constexpr (N <= NKM && NS * N <= 12) {                                                             \
-            return fw_rows<T, NS, NKM, N>(raw, s_e, s_c, Hp, ni, qe_max, c_max, s_S, spitch, jcol0);          \
+            return fw_rows<T, NS, NKM, N>(raw, s_e, s_c, Hp, ni, acc0, qe_max, c_max, s_S, spitch, jcol0);          \
         } else if constexpr (N <= NKM) {                                                                      \
             constexpr int A = (N + 1) / 2;                                                                    \
-            const bool r1 = fw_rows<T, NS, NKM, A, 0>(raw, s_e, s_c, Hp, ni, qe_max, c_max, s_S, spitch, jcol0);         \
-            const bool r2 = fw_rows<T, NS, NKM, N - A, A>(raw, s_e, s_c, Hp, ni, qe_max, c_max, s_S, spitch, jcol0 + A); \
+            const bool r1 = fw_rows<T, NS, NKM, A, 0>(raw, s_e, s_c, Hp, ni, acc0, qe_max, c_max, s_S, spitch, jcol0);         \
+            const bool r2 = fw_rows<T, NS, NKM, N - A, A>(raw, s_e, s_c, Hp, ni, acc0, qe_max, c_max, s_S, spitch, jcol0 + A); \
             return r1 || r2;                                                                                  \
         }                                                                                                     \
         break;
@@ -916,7 +942,8 @@ template <int W> __device__ __forceinline__ int deal_begin(int n, int w) {
     else return (int)((unsigned)(n * w) / (unsigned)W);
 }
 
-template <typename T, int RT, int HL, int ROWNS, int W>
+// TAIL: H is no multiple of four (kernels of their own: the few instructions that only such an H needs cost the others 0.4 %)
+template <typename T, int RT, int HL, int ROWNS, int W, bool TAIL>
 __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
     const T *__restrict__ Qp, const T *__restrict__ Kp, const T *__restrict__ V, const T *__restrict__ v,
     const int *__restrict__ key_len, float *__restrict__ C, float *__restrict__ P,
@@ -1021,7 +1048,6 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
 
     float c_m = 0.f;
     unsigned qe_bits = 0;                                      // largest |exp(2q) / v|, as its bits (NaN above all numbers)
-    const bool tail = (H & 3) != 0;
     for (int s = w & (ns2 - 1), h = st_col; s < ns; s += ns2, h += ns2 * FW_ST) {
         if (s >= ns2) load_v(h);
         float cc[4], cy[4];                                    // 1 / v, and the same with 0 where v counts as zero
@@ -1033,7 +1059,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
                 float vq = comp(v4, q);
                 // a last group of fewer than four columns holds the row's last four: those of the group before it count
                 // here as zero
-                if (tail && min(h, H - 4) + q < h) vq = 0.f;
+                if (TAIL && min(h, H - 4) + q < h) vq = 0.f;
                 const bool v_on = fabsf(vq) >= kTinyV;         // false for columns past H (v read as 0)
                 cc[q] = v_on ? fast_rcp(vq) : kHugeC;
                 cy[q] = v_on ? cc[q] : 0.f;
@@ -1089,7 +1115,8 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
         for (int s = 0; s < ROWNS; ++s)
 #pragma unroll
             for (int c = 0; c < NKM; ++c) raw[s][c].pin();
-        if (fw_rows_n<T, ROWNS, NKM>(nk, raw, s_e, s_c, Hp, ni, qe_max, c_max, s_S, spitch, k_lo))
+        const float acc0 = TAIL ? lane_centre(s_c, lane, ROWNS, FW_ST) : 0.f;
+        if (fw_rows_n<T, ROWNS, NKM>(nk, raw, s_e, s_c, Hp, ni, acc0, qe_max, c_max, s_S, spitch, k_lo))
             fw_pass_exact<T>(qb, ni, kb + (size_t)k_lo * H, nk, H, v, s_S, spitch, k_lo);
     } else {
         for (int p = 0; p < ks.npass; ++p) {                   // passes of up to FW_NJ keys
@@ -1098,9 +1125,9 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
             bool redo = true;
 #define FW_CASE(N)                                                                                                   \
     case N:                                                                                                          \
-        redo = (ni == RT)       ? fw_pass<T, RT, HL, N, RT>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0)     \
-               : (ni == RT - 1) ? fw_pass<T, RT, HL, N, RT - 1>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0) \
-                                : fw_pass<T, RT, HL, N, 0>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0);     \
+        redo = (ni == RT)       ? fw_pass<T, RT, HL, N, RT, TAIL>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0)     \
+               : (ni == RT - 1) ? fw_pass<T, RT, HL, N, RT - 1, TAIL>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0) \
+                                : fw_pass<T, RT, HL, N, 0, TAIL>(s_e, s_c, Hp, ni, nj, ks, qe_max, c_max, s_S, spitch, j0);     \
         break;
             switch ((nj + ks.KG - 1) / ks.KG) {
                 FW_CASE(1) FW_CASE(2) FW_CASE(3) FW_CASE(4)
@@ -1215,15 +1242,15 @@ static int fwd_row_mode_slices(const AttnShape &s) {
     return (s.Tk + FW_W - 1) / FW_W <= fw_row_max_keys(built) ? built : 0;
 }
 
-template <typename T, int RT, int HL, int ROWNS, int W>
-static hipError_t launch_fwd_fused_t(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,
+template <typename T, int RT, int HL, int ROWNS, int W, bool TAIL>
+static hipError_t launch_fwd_fused_k(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,
                                      const int *key_len, float *C, float *P, hipStream_t st) {
     const int Hp = ROWNS > 0 ? ROWNS * FW_ST : fwd_h_pad(s.H, HL);
     const int spitch = ((s.Tk + 3) & ~3) + 4;
     const size_t lds = fwd_lds_bytes(s, Hp, RT, W);
     if (lds > 48 * 1024) {   // beyond the default dynamic LDS limit
         static LdsGrants granted;
-        hipError_t e = ensure_dynamic_lds((const void *)k_fwd_fused<T, RT, HL, ROWNS, W>, lds, granted);
+        hipError_t e = ensure_dynamic_lds((const void *)k_fwd_fused<T, RT, HL, ROWNS, W, TAIL>, lds, granted);
         if (e != hipSuccess) return e;
     }
     const int samples_per_xcd = (s.B + FW_XCD - 1) / FW_XCD;
@@ -1244,10 +1271,17 @@ static hipError_t launch_fwd_fused_t(const AttnShape &s, const void *Qp, const v
     const int spread = ranked && s.B < FW_SPREAD_B && samples_per_xcd * tiles > FW_CU_PER_XCD ? 1 : 0;
     const long long grid = spread ? (long long)s.B * tiles : (long long)FW_XCD * samples_per_xcd * tiles;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    k_fwd_fused<T, RT, HL, ROWNS, W><<<(unsigned)grid, 64 * W, lds, st>>>(
+    k_fwd_fused<T, RT, HL, ROWNS, W, TAIL><<<(unsigned)grid, 64 * W, lds, st>>>(
         (const T *)Qp, (const T *)Kp, (const T *)V, (const T *)v, key_len, C, P, s.B, s.Tq, s.Tk, s.H, s.Dv, tiles,
         s.Tq / tiles, Hp, spitch, ranked + spread);
     return hipGetLastError();
+}
+
+template <typename T, int RT, int HL, int ROWNS, int W>
+static hipError_t launch_fwd_fused_t(const AttnShape &s, const void *Qp, const void *Kp, const void *V, const void *v,
+                                     const int *key_len, float *C, float *P, hipStream_t st) {
+    return s.H % 4 == 0 ? launch_fwd_fused_k<T, RT, HL, ROWNS, W, false>(s, Qp, Kp, V, v, key_len, C, P, st)
+                        : launch_fwd_fused_k<T, RT, HL, ROWNS, W, true>(s, Qp, Kp, V, v, key_len, C, P, st);
 }
 
 template <typename T>

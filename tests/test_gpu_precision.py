@@ -73,3 +73,31 @@ def test_step_scores_of_operands_that_cancel(case):
         ws = torch.empty(eb.echo_attn_fwd_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
         eb.check(eb.echo_attn_fwd(desc, up(q), up(k), V, up(v), up(key_len), ctx, P, ws, stream=st))
     _check_probabilities(P.cpu().numpy(), S, H, terms, sums, key_len, name)
+
+
+@pytest.mark.parametrize("shape", [(2, 40, 70, 1001), (40, 64, 66, 1001), (3, 20, 20, 1001)],
+                         ids=["four_rows", "eight_rows", "row_mode"])
+def test_forward_scores_of_small_terms_at_odd_h(shape):
+    """Equal weights and tanh terms of a few hundredths: the scores are small against sum_h v / (exp(2 (q + k)) + 1), half of sum |v|.
+    Added over the lanes, sums of that size are rounded at 250 to 500 (1.5e-5 per addition); with the constant half taken off per
+    lane first, what is left are roundings of the terms (about 3 U each, sqrt(1001) of them) and of sums up to 8 within a lane
+    (half a unit 4.8e-7 each, sqrt(500) of them in all), doubled: 2 (6e-6 + 6e-6) if all errors were at their limits, and about half of
+    that as a root mean square."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import binding as eb
+    B, Tq, Tk, H = shape
+    print("odd H precision", shape, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    q, k = (0.02 * torch.randn(B, T, H, generator=g, device="cuda") for T in (Tq, Tk))
+    v, V = torch.ones(H, device="cuda"), torch.randn(B, Tk, 4, generator=g, device="cuda")
+    key_len = torch.full((B,), Tk, dtype=torch.int32, device="cuda")
+    ctx, P = torch.empty(B, Tq, 4, device="cuda"), torch.empty(B, Tq, Tk, device="cuda")
+    desc = eb.make_desc(B, Tq, Tk, H, 4, "f32")
+    ws = torch.empty(eb.echo_attn_fwd_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    eb.check(eb.echo_attn_fwd(desc, q, k, V, v, key_len, ctx, P, ws, stream=torch.cuda.current_stream()))
+    off = torch.stack([P[b].double().log() - torch.tanh(q[b].double()[:, None] + k[b].double()).sum(-1) for b in range(min(B, 4))])
+    rms = float((off - off.mean(-1, keepdim=True)).square().mean().sqrt())
+    print(f"root mean square of the score errors {rms:.2e}", flush=True)
+    assert rms <= 1.2e-5, rms
