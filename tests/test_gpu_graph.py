@@ -10,12 +10,13 @@ from parity import assert_parity, oracle_outputs
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("form", ["general_kernels", "step_kernels", "key_side_deferred"])
+@pytest.mark.parametrize("form", ["general_kernels", "step_kernels", "key_side_deferred", "key_side_deferred_split"])
 def test_decoder_steps_from_a_graph(form):
     import torch
     assert torch.cuda.is_available(), "needs the GPU"
     from paper_1805_08899_amd import binding as eb, harness
-    B, T, Tk, Hh, Dv = 8, 5, 30, 256, 128
+    # (150 query-key pairs stay below the recomputation in many independent blocks, 180 take it)
+    B, T, Tk, Hh, Dv = 8, 6 if form.endswith("split") else 5, 30, 256, 128
     wl = Workload("graph_steps", B, T, Tk, Hh, Dv, "f32", 0.5, 3, Tk)
     inputs = make_inputs(wl, seed=99)
     ref = oracle_outputs(inputs, workers=1)
@@ -73,7 +74,7 @@ def test_decoder_steps_from_a_graph(form):
                                              ds_rows, dK, dV, dv, ws_sent, stream=st))
 
     sentence = {"general_kernels": sentence_general, "step_kernels": sentence_step_kernels,
-                "key_side_deferred": sentence_deferred}[form]
+                "key_side_deferred": sentence_deferred, "key_side_deferred_split": sentence_deferred}[form]
 
     def snapshot():
         torch.cuda.synchronize(dev)
@@ -105,3 +106,51 @@ def test_decoder_steps_from_a_graph(form):
         got = snapshot()
         for k, v in eager.items():
             assert np.array_equal(got[k], v), f"replay {replay}: {k} differs from the eager launches"
+
+
+BACKWARDS = [
+    # name, B, Tq, Tk, H, Dv: every tanh twice in independent blocks (also behind the pre-kernel in parts), the whole backward in one
+    # launch, slices of 16 columns in more than a round; all exchange their parts of dv through flags in the workspace
+    ("split", 3, 61, 83, 90, 8),
+    ("split_pre_kernel_in_parts", 2, 33, 150, 64, 24),
+    ("small", 10, 24, 30, 64, 32),
+    ("narrow_slices", 28, 40, 40, 300, 8),
+]
+
+
+@pytest.mark.parametrize("case", BACKWARDS, ids=[c[0] for c in BACKWARDS])
+def test_backward_from_a_graph(case):
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import harness
+    name, B, Tq, Tk, Hh, Dv = case
+    print("graph", case, flush=True)
+    wl = Workload("graph_" + name, B, Tq, Tk, Hh, Dv, "f32", 0.5, 1, Tk)
+    inputs = make_inputs(wl, seed=7)
+    db = harness.DeviceBatch(wl, inputs)
+    db.poison_outputs()
+    db.fwd()
+    db.bwd()
+    eager = db.results()
+    assert_parity(eager, oracle_outputs(inputs, workers=1), inputs, "f32", name)
+    side = torch.cuda.Stream(device=db.device)
+    side.wait_stream(torch.cuda.current_stream(db.device))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            db.fwd()
+            db.bwd()
+    torch.cuda.current_stream(db.device).wait_stream(side)
+    for replay in range(3):
+        if replay:
+            db.fwd()                                      # the program's own eager work, through the same workspace
+            db.bwd()
+        torch.cuda.synchronize(db.device)
+        for t in (db.context, db.P, db.dQp, db.dKp, db.dV, db.dv):
+            t.fill_(float("nan"))
+        if replay == 2:
+            db.ws.fill_(0xFF)
+        graph.replay()
+        got = db.results()
+        for k, v in eager.items():
+            assert np.array_equal(got[k], v), f"{name}, replay {replay}: {k} differs from the eager launches"

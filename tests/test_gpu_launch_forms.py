@@ -250,3 +250,54 @@ def test_order_of_the_samples_in_the_recompute_grid(case):
     half = (B + 1) // 2 if folded else B
     assert (np.diff(lengths[:half]) <= 0).all() and (np.diff(lengths[half:]) >= 0).all(), lengths
     assert lengths[:half].min() >= lengths[half:].max(initial=0)
+
+
+ACCUMULATE = [
+    # name, B, Tq, Tk, H, Dv, dtype: the accumulating call through every tanh twice in independent blocks (several groups of keys, the
+    # last ones masked; behind the pre-kernel in parts), the whole backward in one launch, slices of 16 and 32 columns
+    ("split", 3, 61, 83, 90, 8, "f32"),
+    ("split_bf16", 2, 37, 261, 100, 8, "bf16"),
+    ("split_pre_kernel_in_parts", 2, 33, 150, 64, 24, "f32"),
+    ("small", 10, 24, 30, 64, 32, "f32"),
+    ("slices_of_16", 25, 50, 21, 130, 8, "f32"),
+    ("slices_of_32", 34, 45, 9, 470, 8, "f32"),
+]
+
+
+@pytest.mark.parametrize("case", ACCUMULATE, ids=[c[0] for c in ACCUMULATE])
+def test_accumulating_backward(case):
+    """dKp, dV and dv are added to what the buffers hold, in one rounding of the sum; where a masked key adds nothing the buffer
+    stays as it is, bit for bit.  dQp is overwritten."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import binding as eb, harness
+    name, B, Tq, Tk, H, Dv, dt = case
+    print("accumulate", case, flush=True)
+    wl = Workload(name, B, Tq, Tk, H, Dv, dt, 0.5, 1, Tk, dt == "bf16")
+    inputs = make_inputs(wl, seed=41 + len(name))
+    inputs["key_len"][0] = Tk // 3                        # whole groups of masked keys
+    inputs["key_len"][1] = 0
+    db = harness.DeviceBatch(wl, inputs, guard_bytes=4096)
+    db.poison_outputs()
+    db.fwd()
+    db.bwd()
+    alone = db.results()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    held = {}
+    for k in ("dKp", "dV", "dv"):
+        t = getattr(db, k)
+        t.copy_(torch.randn(t.shape, generator=g, device="cuda"))
+        held[k] = t.cpu().numpy()
+    db.dQp.fill_(float("nan"))
+    eb.check(eb.echo_attn_bwd_accumulate(db.desc, db.dC, db.P, db.Qp, db.Kp, db.V, db.v, db.key_len, db.dQp, db.dKp, db.dV, db.dv,
+                                         db.ws, stream=torch.cuda.current_stream(db.device)))
+    got = db.results()
+    assert db.check_guards() == []
+    assert np.array_equal(got["dQp"], alone["dQp"])
+    for k, base in held.items():
+        # over several passes of rows a kernel adds to the buffer more than once: a few roundings of the larger of sum and parts
+        size = np.abs(base) + np.abs(alone[k])
+        assert (np.abs(got[k] - (base.astype(np.float64) + alone[k])) <= 4 * 2.0 ** -24 * size + 1e-30).all(), k
+    for b, L in enumerate(np.clip(inputs["key_len"], 0, Tk)):
+        assert np.array_equal(got["dKp"][b, L:], held["dKp"][b, L:]) and np.array_equal(got["dV"][b, L:], held["dV"][b, L:])
