@@ -64,10 +64,11 @@ BwdWs bwd_layout(const AttnShape &s) {
     w.total = w.dvflag_off + align_up(flags * sizeof(unsigned long long));
     return w;
 }
-// scores S [B,Tq,Tk] of the unfused forward kernels; the fused kernel keeps them in LDS and needs nothing
+// scores S [B,Tq,Tk] of the unfused forward kernels; the fused kernel keeps them in LDS and needs nothing.  (An H that is no
+// multiple of 4 took the unfused kernels once; callers' sizes and the refusal of less have stayed, the bytes are not touched.)
 size_t fwd_bytes(const AttnShape &s, bool want_map) {
     if (!want_map && s.Tq == 1 && echo::step_split_mail_bytes(s) > 0) return align_up(echo::step_split_mail_bytes(s));
-    if (!want_map && s.H % 4 == 0 && echo::fwd_fused_supported(s)) return 0;   // (other H: asked for, not used)
+    if (!want_map && s.H % 4 == 0 && echo::fwd_fused_supported(s)) return 0;
     return align_up((size_t)s.B * s.Tq * s.Tk * sizeof(float));
 }
 

@@ -262,27 +262,6 @@ __device__ __forceinline__ void wait_all_memory_ops() { asm volatile("s_waitcnt 
 // wave ends whatever happens; the results of that launch are then marked invalid (NaN).
 constexpr long long kSpinLimitTicks = 200000000LL;
 
-// One float handed from one block of a launch to another without ordering between stores: two 64-bit words, each holding
-// the value next to one half of the launch's 64-bit number.  The receiver takes it once both halves and both copies of the
-// value agree, so the area may start in any state, and sets the slot back to zero, so that a captured launch, whose number
-// is fixed, can be replayed.
-constexpr unsigned long long kMailSalt = 0x9E3779B9ull;
-struct alignas(16) MailSlot {
-    unsigned long long w0, w1;
-};
-
-__device__ __forceinline__ void mail_put(MailSlot *s, float x, unsigned long long epoch) {
-    const unsigned long long bits = __float_as_uint(x);
-    store_agent(&s->w0, ((epoch & 0xffffffffull) << 32) | bits);
-    store_agent(&s->w1, ((((epoch >> 32) ^ kMailSalt) & 0xffffffffull) << 32) | bits);
-}
-__device__ __forceinline__ bool mail_try(const MailSlot *s, unsigned long long epoch, float &x) {
-    const unsigned long long a = load_agent(&s->w0), b = load_agent(&s->w1);
-    x = __uint_as_float((unsigned)a);
-    return (a >> 32) == (epoch & 0xffffffffull) && (b >> 32) == (((epoch >> 32) ^ kMailSalt) & 0xffffffffull) &&
-           (unsigned)a == (unsigned)b;
-}
-
 __device__ __forceinline__ int clamp_len(int len, int Tk) { return len < 0 ? 0 : (len > Tk ? Tk : len); }
 
 // n items dealt to the 8 waves of a block as contiguous ranges of n / 8 or n / 8 + 1 items: first item of wave w

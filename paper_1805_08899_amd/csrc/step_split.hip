@@ -34,6 +34,27 @@ constexpr int SP_GROUPS = SP_THREADS / SP_COLS;    // row groups per block after
 constexpr int SP_ROWS = SP_KEYS / SP_GROUPS;  // rows per thread (16)
 constexpr int SP_MAX_WIDTH = 256 * SP_CH;     // H and Dv up to 512
 
+// One float handed from one block of a launch to another without ordering between stores: two 64-bit words, each holding
+// the value next to one half of the launch's 64-bit number.  The receiver takes it once both halves and both copies of the
+// value agree, so the area may start in any state, and sets the slot back to zero, so that a captured launch, whose number
+// is fixed, can be replayed.
+constexpr unsigned long long kMailSalt = 0x9E3779B9ull;
+struct alignas(16) MailSlot {
+    unsigned long long w0, w1;
+};
+
+__device__ __forceinline__ void mail_put(MailSlot *s, float x, unsigned long long epoch) {
+    const unsigned long long bits = __float_as_uint(x);
+    store_agent(&s->w0, ((epoch & 0xffffffffull) << 32) | bits);
+    store_agent(&s->w1, ((((epoch >> 32) ^ kMailSalt) & 0xffffffffull) << 32) | bits);
+}
+__device__ __forceinline__ bool mail_try(const MailSlot *s, unsigned long long epoch, float &x) {
+    const unsigned long long a = load_agent(&s->w0), b = load_agent(&s->w1);
+    x = __uint_as_float((unsigned)a);
+    return (a >> 32) == (epoch & 0xffffffffull) && (b >> 32) == (((epoch >> 32) ^ kMailSalt) & 0xffffffffull) &&
+           (unsigned)a == (unsigned)b;
+}
+
 __device__ __forceinline__ float comp4s(const float4 &x, int c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; }
 
 // On entry s_val holds this part's values at its keys (j < L, j % 4 == part); on return it holds the values of all

@@ -65,7 +65,7 @@ def test_rejects_bad_arguments_without_launching():
     good = eb.make_desc(4, 6, 7, 16, 16)
     for name in ("Qp", "Kp", "V", "v", "key_len", "context", "P"):
         assert _fwd(good, **{name: None}) == eb.ECHO_ERR_NULL, name
-    # H = 18 is not a multiple of 4: the forward pass keeps its scores in the workspace and must be given one
+    # H = 18 is not a multiple of 4: the call asks for room for the scores (which its one kernel leaves alone) and must be given it
     unfused = eb.make_desc(4, 6, 7, 18, 16)
     assert eb.echo_attn_fwd_workspace_bytes(unfused) >= 4 * 6 * 7 * 4
     assert _fwd(unfused, workspace=None) == eb.ECHO_ERR_NULL
