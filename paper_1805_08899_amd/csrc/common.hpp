@@ -131,6 +131,24 @@ __device__ __forceinline__ float r_from_sum(float sq, float sk) {
     return fast_rcp(fast_exp2(sq + sk) + 1.0f);
 }
 
+// A batch of transcendental instructions (reciprocals, exponentials) between these two goes before whatever the other waves of the
+// SIMD have to issue.  Measured on small kernels of nothing but the loop bodies, four waves on a SIMD: a transcendental
+// instruction holds the vector unit for 8.2 clocks whatever the mix, a plain one takes 2.3 as long as two waves have plain ones to
+// issue, but 3.8 when it falls between the transcendental ones of another wave.  Waves left to themselves drift into that interleaving;
+// with the batches in front they run them back to back and then share the plain instructions: the forward's pairs of tanh 12.1 -> 10.3
+// clocks per element and wave, the recomputation's 24.6 -> 21.1 (plain instructions in front instead: 13.2 and 27.6).  The
+// fences keep the batch between the two priority changes.
+__device__ __forceinline__ void trans_begin() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_sched_barrier(0);
+}
+__device__ __forceinline__ void trans_end() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 

@@ -89,12 +89,12 @@ __device__ __forceinline__ void fw_row_keys(const float4 &fq, const float4 &cv, 
             sm[h2][c] = t[2 * h2][c] + t[2 * h2 + 1][c];
             pr[h2][c] = t[2 * h2][c] * t[2 * h2 + 1][c];
         }
-    __builtin_amdgcn_sched_barrier(0);
+    trans_begin();
 #pragma unroll
     for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll
         for (int c = 0; c < NJ; ++c) pr[h2][c] = fast_rcp(pr[h2][c]);
-    __builtin_amdgcn_sched_barrier(0);
+    trans_end();
 #pragma unroll
     for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll
@@ -203,6 +203,9 @@ __device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const flo
 
     for (int s = 0; s < ks.NS; ++s) {
         float fk[4][NJ];
+        // in front of the other waves, as the reciprocals (whose trans_end() ends it): 1 to 3 % of the launch where a wave walks many
+        // keys; the blocks of four rows, on small grids, lose 2 % by it
+        if constexpr (RT == 8) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int c = 0; c < NJ; ++c) {
 #pragma unroll

@@ -66,10 +66,10 @@ __device__ __forceinline__ void rc_tile(const float (&fq)[RC_RI], const float (&
 #pragma unroll
             for (int c = 0; c < NJ; ++c)
                 r[c] = MODE == RC_FACTOR ? __builtin_fmaf(fq[a], fk[c], 1.0f) : fast_exp2(fq[a] + fk[c]) + 1.0f;
-            __builtin_amdgcn_sched_barrier(0);
+            trans_begin();
 #pragma unroll
             for (int c = 0; c < NJ; ++c) r[c] = fast_rcp(r[c]);
-            __builtin_amdgcn_sched_barrier(0);
+            trans_end();
         }
 #pragma unroll
         for (int c = 0; c < NJ; ++c) u[c] = __builtin_fmaf(-r[c], r[c], r[c]);      // r (1 - r) = (1 - t^2) / 4

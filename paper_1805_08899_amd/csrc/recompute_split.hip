@@ -56,12 +56,12 @@ __device__ __forceinline__ void rs_chunk(const float (&fx)[RS_R], const float (&
 #pragma unroll
             for (int c = 0; c < RS_C; ++c)
                 r[a][c] = EXACT ? fast_exp2(fx[a0 + a] + fy[c]) + 1.0f : __builtin_fmaf(fx[a0 + a], fy[c], 1.0f);
-        __builtin_amdgcn_sched_barrier(0);
+        trans_begin();
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int c = 0; c < RS_C; ++c) r[a][c] = fast_rcp(r[a][c]);
-        __builtin_amdgcn_sched_barrier(0);
+        trans_end();
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
