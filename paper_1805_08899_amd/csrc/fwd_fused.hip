@@ -395,36 +395,6 @@ __device__ __forceinline__ bool fw_rows_n(int nk, const RawKey<T> (&raw)[NS][NKM
 // The batches of value rows of all of a wave's column groups form one sequence; the loads of the next batch are
 // issued before the current one is multiplied.  Keys past L carry P = 0, the last valid row stands in for them;
 // no branches around the loads, so that they stay in flight across the arithmetic of the batch before.
-// Rows of a matrix read through a buffer descriptor: element address = base + vector byte offset + scalar byte offset,
-// both 32-bit, range-checked by the hardware against the n_elems elements the descriptor covers (a load past them
-// returns zero).  The descriptor's last word is the raw 32-bit data format of this architecture family.
-template <typename T> struct BufferRows {
-    __amdgpu_buffer_rsrc_t rsrc;
-    __device__ __forceinline__ BufferRows(const T *base, unsigned n_elems)
-        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base), 0, (int)(n_elems * (unsigned)sizeof(T)),
-                                                  0x00020000)) {}
-    // the element as loaded (16-bit types: the bits, zero-extended); value() turns it into the number.  Two steps so
-    // that nothing but the load sits where the loads are issued (an operation on the loaded value there makes the
-    // compiler wait for every load in turn)
-    using Raw = std::conditional_t<sizeof(T) == 4, float, unsigned short>;
-    __device__ __forceinline__ Raw load_raw(unsigned v_off, unsigned s_off) const {
-        if constexpr (sizeof(T) == 4) {
-            return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, v_off, s_off, 0));
-        } else {
-            return __builtin_amdgcn_raw_buffer_load_b16(rsrc, v_off, s_off, 0);
-        }
-    }
-    // (16-bit types: the empty statement keeps the conversion behind whatever barrier precedes the call)
-    static __device__ __forceinline__ float value(Raw raw) {
-        if constexpr (sizeof(T) == 4) {
-            return raw;
-        } else {
-            asm volatile("" : "+v"(raw));
-            return __uint_as_float((unsigned)raw << 16);
-        }
-    }
-};
-
 // CPL consecutive columns of one row as they come from memory through a buffer descriptor (f32: CPL words;
 // 16-bit types: CPL / 2 words, one for CPL = 1).  Loading and converting are separate steps: see BufferRows.
 template <typename T, int CPL> struct RowPiece {

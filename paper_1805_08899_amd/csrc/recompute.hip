@@ -371,8 +371,19 @@ static int recompute_width(const AttnShape &s) {
     return hw;
 }
 
+// The form of recompute_rows.hip where its expected time is 5 % ahead, 13 % on grids just past a round (whose few blocks more cost it,
+// with its slices of 64 columns, more than the estimate says: 515 blocks at B = 103, T = 83 / 68, H = 272 84.7 us backward against 76.5).
+// Over 420 shapes of 60 to 480 rows from 256 of its blocks on the whole backward takes 0.953 of the time without it, 0.950 with the
+// better of the two each time; over the 209 that take it 0.908, five of them 2 to 5 % more.  B = 128, T = 100, H = 512 135 -> 119 us;
+// B = 32, T = 300, H = 1024 604 -> 516; B = 64, T = 200 / 30, H = 512 65 -> 58.
+static bool recompute_takes_rows(const AttnShape &s) {
+    const float rows = recompute_rows_time(s);
+    const long long blocks = (long long)s.B * ((s.H + 63) / 64);
+    return rows > 0.f && rows * (blocks > RC_ROUND && blocks <= RC_ROUND * 5 / 4 ? 1.13f : 1.05f) < recompute_time(s, recompute_width(s));
+}
+
 bool recompute_in_one_round(const AttnShape &s, bool stash) {
-    const int hw = stash ? 64 : recompute_width(s);
+    const int hw = stash || recompute_takes_rows(s) ? 64 : recompute_width(s);
     return (long long)s.B * ((s.H + hw - 1) / hw) <= RC_ROUND;
 }
 
@@ -393,6 +404,8 @@ hipError_t launch_recompute(const AttnShape &s, const void *Qp, const void *Kp, 
                             const float *dS, const float *ds_rowsum, const float *tmap, float *dQp, float *dKp,
                             float *dv_part, unsigned long long *dv_flag, unsigned long long epoch, float *dv,
                             hipStream_t st) {
+    if (!tmap && recompute_takes_rows(s))
+        return launch_recompute_rows(s, Qp, Kp, v, order, dS, ds_rowsum, dQp, dKp, dv_part, dv_flag, epoch, dv, st);
     return s.bf16 ? launch_recompute_w<bf16_t>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag,
                                                epoch, dv, st)
                   : launch_recompute_w<float>(s, Qp, Kp, v, order, dS, ds_rowsum, tmap, dQp, dKp, dv_part, dv_flag,

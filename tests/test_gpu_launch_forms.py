@@ -34,6 +34,18 @@ CASES = [
     ("slices_of_32_two_passes", 20, 131, 9, 800, 4, "f32", False),
     ("slice_of_16_is_the_whole_h", 200, 9, 11, 16, 4, "f32", False),
     ("slice_of_32_is_the_whole_h", 200, 9, 11, 31, 4, "f32", False),
+    # recomputation with up to 25 rows per lane: its fewest rows and the next ones that do not take it, odd
+    # rows, columns and keys, all counts of keys in the first step, two lane groups and one, one to three passes, numbers of rows that
+    # do and do not deal evenly; entries beyond the factor limit in the first step and in a later one
+    ("rows_of_25_two_groups_60", 125, 60, 47, 130, 4, "f32", True),
+    ("rows_of_25_not_59", 125, 59, 47, 130, 4, "f32", False),
+    ("rows_of_25_72_bf16", 182, 72, 29, 128, 4, "bf16", False),
+    ("rows_of_25_two_groups_100", 199, 100, 29, 127, 4, "f32", True),
+    ("rows_of_25_one_group_101_bf16", 150, 101, 20, 185, 8, "bf16", False),
+    ("rows_of_25_one_group_130", 202, 130, 13, 126, 4, "f32", True),
+    ("rows_of_25_one_group_200", 221, 200, 13, 128, 4, "f32", False),
+    ("rows_of_25_two_passes", 236, 201, 13, 99, 4, "f32", True),
+    ("rows_of_25_three_passes", 447, 405, 8, 48, 4, "f32", False),
     # forward: blocks of four rows (eight waves, four waves), of eight rows with slices of 64 and 128 columns; a small batch
     # spread over the XCDs; H that is no multiple of four (tails of one to three columns, in both storage types), H of a
     # single group of four and just past it
@@ -220,6 +232,8 @@ ORDERS = [
     ("one_round", 64, 50, 50, 512, True),
     ("narrow_slices_past_a_round", 28, 80, 80, 300, False),
     ("split", 5, 200, 200, 76, False),
+    ("rows_of_25_one_round", 73, 72, 29, 320, True),
+    ("rows_of_25_past_a_round", 140, 72, 40, 320, False),
 ]
 
 
@@ -261,6 +275,9 @@ ACCUMULATE = [
     ("small", 10, 24, 30, 64, 32, "f32"),
     ("slices_of_16", 25, 50, 21, 130, 8, "f32"),
     ("slices_of_32", 34, 45, 9, 470, 8, "f32"),
+    ("rows_of_25", 182, 72, 29, 128, 8, "f32"),
+    # (one pass over the rows: of two passes' parts, up to |p1| + |p2| each off by 2 U, the bound below sees only the sum)
+    ("rows_of_25_one_group", 202, 130, 13, 126, 4, "bf16"),
 ]
 
 

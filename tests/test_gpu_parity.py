@@ -340,6 +340,7 @@ STEP_CASES = [
     ("steps_132_keys", 3, 5, 132, 64, 72, "f32"),                          # dV by panels of 64 keys, accumulating
     ("steps_with_empty_samples", 9, 2, 6, 32, 16, "f32"),                  # key_len drawn from 0..Tk
     ("steps_batch_beyond_the_four_block_form", 70, 2, 20, 64, 32, "f32"),  # 4 B blocks would not all run at once
+    ("steps_72_of_many_samples", 182, 72, 29, 128, 8, "f32"),              # key side with up to 25 rows per lane, no dQp
 ]
 
 
