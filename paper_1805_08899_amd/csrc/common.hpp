@@ -29,6 +29,17 @@ __device__ __forceinline__ float4 ld4(const bf16_t *p, size_t i) {
     r.w = __uint_as_float(u.y & 0xffff0000u);
     return r;
 }
+// The same in two steps, for loads that wait in registers: four elements as they stand in memory, and their values.
+template <typename T> using Raw4 = std::conditional_t<sizeof(T) == 4, float4, uint2>;
+template <typename T> __device__ __forceinline__ Raw4<T> ld4_raw(const T *p, size_t i) {
+    return *reinterpret_cast<const Raw4<T> *>(p + i);
+}
+__device__ __forceinline__ float4 value4(float4 x) { return x; }
+__device__ __forceinline__ float4 value4(uint2 u) {
+    asm volatile("" : "+v"(u.x), "+v"(u.y));      // the conversion stays behind whatever barrier precedes the call
+    return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                       __uint_as_float(u.y & 0xffff0000u));
+}
 
 // An element as loaded, and the number it stands for, as two steps: a load that sits in a guarded branch together
 // with the first operation on its value (for bf16 the shift that widens it) makes the compiler wait for the load

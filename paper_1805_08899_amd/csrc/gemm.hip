@@ -6,6 +6,8 @@
 //
 // Operand layout of one 16x16x4 step, lane l:  A[m = l%16][k = l/16],
 // B[k = l/16][n = l%16], D[m = 4*(l/16) + r][n = l%16] in accumulator r.
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -107,126 +109,17 @@ hipError_t launch_context(const AttnShape &s, const float *P, const void *V, con
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// dS for (b, 16 query rows).  Waves take key tiles of 16 in turn and compute
-// dP[i, j] = sum_d dC[i, d] V[j, d] into LDS; then each wave finishes four
-// rows: r = sum_j P dP, dS = P (dP - r).  dS rows have pitch `pitch` floats and
-// are zero at j >= L_b (pads included).  Dv must be a multiple of 4.
-// A lane loads four consecutive d of its row for both operands and spends
-// them on four MFMA steps, so the k index of step c is d0 + 4*(l/16) + c on
-// both sides.
-template <typename TV, int G, int RB>
-__device__ __forceinline__ void dscore_block(const float *__restrict__ dC, const TV *__restrict__ V,
-                                             const float *__restrict__ P, const int *__restrict__ key_len,
-                                             float *__restrict__ dS, float *__restrict__ ds_rowsum,
-                                             float *__restrict__ s_dp, int b, int i0, int Tq, int Tk, int Dv,
-                                             int pitch) {
-    const int L = clamp_len(key_len[b], Tk);
+// The finishing phase of a dS block on a long key axis: dP of its 4 NR rows stands in LDS, wave w turns rows w, w + 4, ...
+// into dS = P (dP - sum_j P dP), with zeros at masked keys and pads.
+template <int NR>
+__device__ __forceinline__ void dscore_finish(const float *__restrict__ P, float *__restrict__ dS,
+                                              float *__restrict__ ds_rowsum, const float *__restrict__ s_dp, int b, int i0,
+                                              int Tq, int Tk, int L, int pitch, int pitch16) {
     const int lane = lane_id(), w = wave_id();
-    const int lm = lane & 15, lk = lane >> 4;
-    const int pitch16 = (Tk + 15) / 16 * 16 + 4;
-    const float *dCb = dC + (size_t)b * Tq * Dv;
-    const TV *Vb = V + (size_t)b * Tk * Dv;
-
-    // Wave w takes key tiles w, w+4, ..., G at a time so that one fragment of dC feeds G products (the
-    // kernel is bound by what the L2 can deliver, not by the matrix cores); tiles past the sample's last one are
-    // neither loaded nor multiplied.  RB = 2: the block owns 32 query rows, two fragments of dC, so that every
-    // V fragment feeds two products and the sample's V rows pass through half as many blocks.  The sum over d runs
-    // in stages of U 16-wide slices; the loads of the next stage are in flight while the current one is multiplied.
-    // Rows and keys past the end are clamped for loading; what they produce is never read.  Columns past Dv are zeroed.
-    const int n_jt = (L + 15) / 16;
-    constexpr int U = RB == 2 ? 1 : 2;
-    const int n_st = (Dv + 16 * U - 1) / (16 * U);            // stages
-    const bool ragged = Dv % (16 * U) != 0;
-    const float *dCrow[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) dCrow[rb] = dCb + (size_t)min(i0 + 16 * rb + lm, Tq - 1) * Dv;
-    for (int jt0 = w; jt0 < n_jt; jt0 += 4 * G) {              // this wave's tiles jt0, jt0 + 4, jt0 + 8, ...
-        const TV *vrow[G];
-#pragma unroll
-        for (int k = 0; k < G; ++k) vrow[k] = Vb + (size_t)min((jt0 + 4 * k) * 16 + lm, Tk - 1) * Dv;
-        float4 a[RB][U], bv[G][U], an[RB][U], bn[G][U];
-#pragma unroll
-        for (int k = 0; k < G; ++k)
-#pragma unroll
-            for (int u = 0; u < U; ++u) bv[k][u] = bn[k][u] = make_float4(0.f, 0.f, 0.f, 0.f);
-        // key tiles of this group that exist (the same in all lanes): the others are neither loaded nor multiplied
-        bool live[G];
-#pragma unroll
-        for (int k = 0; k < G; ++k) live[k] = jt0 + 4 * k < n_jt;
-        auto load = [&](float4 (&da)[RB][U], float4 (&db)[G][U], int st) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int d = min((st * U + u) * 16 + 4 * lk, Dv - 4);
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) da[rb][u] = ld4(dCrow[rb], (size_t)d);
-#pragma unroll
-                for (int k = 0; k < G; ++k)
-                    if (live[k]) db[k][u] = ld4(vrow[k], (size_t)d);
-            }
-        };
-        load(a, bv, 0);
-        f32x4 acc[RB][G];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int k = 0; k < G; ++k) acc[rb][k] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        for (int st = 0; st < n_st; ++st) {
-            load(an, bn, min(st + 1, n_st - 1));
-            if (ragged && st == n_st - 1) {                      // columns past Dv add nothing
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if ((st * U + u) * 16 + 4 * lk >= Dv) {
-#pragma unroll
-                        for (int rb = 0; rb < RB; ++rb) a[rb][u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-                    for (int k = 0; k < G; ++k) if (live[k]) acc[rb][k] = mfma16(a[rb][u].x, bv[k][u].x, acc[rb][k]);
-                }
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-                    for (int k = 0; k < G; ++k) if (live[k]) acc[rb][k] = mfma16(a[rb][u].y, bv[k][u].y, acc[rb][k]);
-                }
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-                    for (int k = 0; k < G; ++k) if (live[k]) acc[rb][k] = mfma16(a[rb][u].z, bv[k][u].z, acc[rb][k]);
-                }
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-                    for (int k = 0; k < G; ++k) if (live[k]) acc[rb][k] = mfma16(a[rb][u].w, bv[k][u].w, acc[rb][k]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb) a[rb][u] = an[rb][u];
-#pragma unroll
-                for (int k = 0; k < G; ++k) bv[k][u] = bn[k][u];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-            const int jt = jt0 + 4 * k;
-            if (jt < n_jt) {
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) s_dp[(16 * rb + 4 * lk + r) * pitch16 + jt * 16 + lm] = acc[rb][k][r];
-            }
-        }
-    }
     // P of the rows this wave finishes (w, w + 4, ...), the first NP keys per lane of each: requested together
     // before the barrier (the registers of the product loop are free by now), where loading row after row inside
     // the loop below put one trip to memory behind the other
-    constexpr int NP = 5, NR = 4 * RB;
+    constexpr int NP = 5;
     float pr[NR][NP];
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
@@ -272,6 +165,231 @@ __device__ __forceinline__ void dscore_block(const float *__restrict__ dC, const
     }
 }
 
+// ---------------------------------------------------------------------------
+// dS for (b, 16 query rows).  Waves take key tiles of 16 in turn and compute
+// dP[i, j] = sum_d dC[i, d] V[j, d] into LDS; then each wave finishes four
+// rows: r = sum_j P dP, dS = P (dP - r).  dS rows have pitch `pitch` floats and
+// are zero at j >= L_b (pads included).  Dv must be a multiple of 4.
+// A lane loads four consecutive d of its row for both operands and spends
+// them on four MFMA steps, so the k index of step c is d0 + 4*(l/16) + c on
+// both sides.
+template <typename TV, int G>
+__device__ __forceinline__ void dscore_block(const float *__restrict__ dC, const TV *__restrict__ V,
+                                             const float *__restrict__ P, const int *__restrict__ key_len,
+                                             float *__restrict__ dS, float *__restrict__ ds_rowsum,
+                                             float *__restrict__ s_dp, int b, int i0, int Tq, int Tk, int Dv,
+                                             int pitch) {
+    const int L = clamp_len(key_len[b], Tk);
+    const int lane = lane_id(), w = wave_id();
+    const int lm = lane & 15, lk = lane >> 4;
+    const int pitch16 = (Tk + 15) / 16 * 16 + 4;
+    const float *dCb = dC + (size_t)b * Tq * Dv;
+    const TV *Vb = V + (size_t)b * Tk * Dv;
+
+    // Wave w takes key tiles w, w+4, ..., G at a time so that one fragment of dC feeds G products (the
+    // kernel is bound by what the L2 can deliver, not by the matrix cores); tiles past the sample's last one are
+    // neither loaded nor multiplied.  The sum over d runs
+    // in stages of U 16-wide slices; the loads of the next stage are in flight while the current one is multiplied.
+    // Rows and keys past the end are clamped for loading; what they produce is never read.  Columns past Dv are zeroed.
+    const int n_jt = (L + 15) / 16;
+    constexpr int U = 2;
+    const int n_st = (Dv + 16 * U - 1) / (16 * U);            // stages
+    const bool ragged = Dv % (16 * U) != 0;
+    const float *dCrow = dCb + (size_t)min(i0 + lm, Tq - 1) * Dv;
+    for (int jt0 = w; jt0 < n_jt; jt0 += 4 * G) {              // this wave's tiles jt0, jt0 + 4, jt0 + 8, ...
+        const TV *vrow[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) vrow[k] = Vb + (size_t)min((jt0 + 4 * k) * 16 + lm, Tk - 1) * Dv;
+        float4 a[U], bv[G][U], an[U], bn[G][U];
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+#pragma unroll
+            for (int u = 0; u < U; ++u) bv[k][u] = bn[k][u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        // key tiles of this group that exist (the same in all lanes): the others are neither loaded nor multiplied
+        bool live[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) live[k] = jt0 + 4 * k < n_jt;
+        auto load = [&](float4 (&da)[U], float4 (&db)[G][U], int st) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int d = min((st * U + u) * 16 + 4 * lk, Dv - 4);
+                da[u] = ld4(dCrow, (size_t)d);
+#pragma unroll
+                for (int k = 0; k < G; ++k)
+                    if (live[k]) db[k][u] = ld4(vrow[k], (size_t)d);
+            }
+        };
+        load(a, bv, 0);
+        f32x4 acc[G];
+#pragma unroll
+        for (int k = 0; k < G; ++k) acc[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int st = 0; st < n_st; ++st) {
+            load(an, bn, min(st + 1, n_st - 1));
+            if (ragged && st == n_st - 1) {                      // columns past Dv add nothing
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if ((st * U + u) * 16 + 4 * lk >= Dv) a[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int k = 0; k < G; ++k) if (live[k]) acc[k] = mfma16(a[u].x, bv[k][u].x, acc[k]);
+#pragma unroll
+                for (int k = 0; k < G; ++k) if (live[k]) acc[k] = mfma16(a[u].y, bv[k][u].y, acc[k]);
+#pragma unroll
+                for (int k = 0; k < G; ++k) if (live[k]) acc[k] = mfma16(a[u].z, bv[k][u].z, acc[k]);
+#pragma unroll
+                for (int k = 0; k < G; ++k) if (live[k]) acc[k] = mfma16(a[u].w, bv[k][u].w, acc[k]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a[u] = an[u];
+#pragma unroll
+                for (int k = 0; k < G; ++k) bv[k][u] = bn[k][u];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            const int jt = jt0 + 4 * k;
+            if (jt < n_jt) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) s_dp[(4 * lk + r) * pitch16 + jt * 16 + lm] = acc[k][r];
+            }
+        }
+    }
+    dscore_finish<4>(P, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, L, pitch, pitch16);
+}
+
+// The same for 32 query rows and at most kDs32MaxTk keys, operands through LDS.  Read straight from memory in operand
+// layout, each quarter of a wave asks for the same 16 bytes of 16 rows, and rows a multiple of 128 bytes apart queue in the
+// L1; and a wave of the 1.25 blocks per CU of the long shapes waited for one slice of d at a time.  Here a wave loads whole
+// row pieces of 16 U columns of d (a chunk), writes them into its own rows of LDS and reads them back in operand layout
+// (conflict-free at this pitch); the slices of ALL its key tiles for the next chunk are in flight while the current chunk
+// is multiplied, each tile's registers being refilled as soon as its slice stands in LDS.  The number of its tiles is a
+// template parameter: with conditions around the loads the compiler waits for the newest of them.  The 32 rows of dC, the
+// same for the four waves, are staged by all of them into one of two buffers (one barrier per chunk).
+// The backward pass in us, operands straight from memory -> this: B = 32, T = 300, Dv = 1024 532 -> 513 (this launch 146 ->
+// 135); bf16 B = 49, Tq = 442, Tk = 376, Dv = 512 473 -> 421; bf16 B = 130, Tq = 259, Tk = 314, Dv = 1000 1003 -> 893;
+// B = 105, Tq = 348, Tk = 308, Dv = 512 366 -> 345; B = 64, T = 144, Dv = 512 126.8 -> 121.8; Dv = 44, a single chunk:
+// level (0.999 to 1.011 of the time over seven shapes).  Blocks of 16 rows in this form, twice as many: 0 to 9 % slower.
+constexpr int kDs32MaxTk = 384;      // 32 rows x (Tk + 4) floats: 48.5 KB of LDS at most, three blocks per CU
+__host__ __device__ constexpr int staged_pitch(int u) { return 16 * u + 4; }
+constexpr int kStagedFloats = (4 * 16 + 2 * 32) * staged_pitch(4);     // the wider chunk's regions
+
+// The products of a wave that owns NL key tiles (w, w + 4, ...) of the block, U 16-wide slices of d per chunk.
+template <typename TV, int NL, int U>
+__device__ __forceinline__ void dscore_staged_tiles(const float *__restrict__ dCb, const TV *__restrict__ Vb,
+                                                    float *__restrict__ s_dp, int n_rows, int Tk, int Dv, int pitch16) {
+    constexpr int KC = 16 * U, RPL = 16 / U, PITCH = staged_pitch(U);      // columns of a chunk, rows per load
+    const int lane = lane_id(), w = wave_id();
+    const int lm = lane & 15, lk = lane >> 4;
+    float *sa = s_dp + 4 * 16 * PITCH;            // dC of the chunk: two buffers of 32 rows
+    float *st = s_dp + w * 16 * PITCH;            // this wave's key tile
+    const int lr = lane / (4 * U), cc = 4 * (lane % (4 * U));              // loading: row of the load, column in the chunk
+    const int n_ch = (Dv + KC - 1) / KC;
+    const int last_q = (n_rows - 1) * Dv, last_k = (Tk - 1) * Dv;          // rows past the end are clamped to these
+    float4 an[U / 2];
+    Raw4<TV> nxt[NL > 0 ? NL : 1][U];
+    int lane_row = lr * Dv;
+    // Offsets within the sample in 32 bits, formed anew from lane_row each time: the compiler would keep one of them per
+    // row of every tile in a register instead, and spill.
+    auto load_a = [&](int ch) {
+        const int col = min(ch * KC + cc, Dv - 4);
+        asm volatile("" : "+v"(lane_row));
+#pragma unroll
+        for (int u = 0; u < U / 2; ++u) an[u] = ld4(dCb, (size_t)(unsigned)(min(lane_row + (8 * w + RPL * u) * Dv, last_q) + col));
+    };
+    auto store_a = [&](int ch) {                  // columns past Dv add nothing
+        float *dst = sa + (ch & 1) * 32 * PITCH;
+#pragma unroll
+        for (int u = 0; u < U / 2; ++u)
+            *reinterpret_cast<float4 *>(dst + (8 * w + RPL * u + lr) * PITCH + cc) =
+                ch * KC + cc < Dv ? an[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    auto load_v = [&](int ch, int k) {
+        const int col = min(ch * KC + cc, Dv - 4);
+        asm volatile("" : "+v"(lane_row));
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            nxt[k][u] = ld4_raw(Vb, (size_t)(unsigned)(min(lane_row + ((w + 4 * k) * 16 + RPL * u) * Dv, last_k) + col));
+    };
+    load_a(0);
+#pragma unroll
+    for (int k = 0; k < NL; ++k) load_v(0, k);
+    store_a(0);
+    if (n_ch > 1) load_a(1);
+    f32x4 acc[2][NL > 0 ? NL : 1];
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+        for (int k = 0; k < NL; ++k) acc[rb][k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto chunk = [&](int ch, auto last) {         // last: nothing follows that would have to be loaded
+        constexpr bool LAST = decltype(last)::value;
+        lds_barrier();                            // dC of this chunk is there, and that of the last one no longer read
+        if constexpr (!LAST) {
+            store_a(ch + 1);
+            load_a(min(ch + 2, n_ch - 1));
+        }
+        const float *ab = sa + (ch & 1) * 32 * PITCH + lm * PITCH + 4 * lk;
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) *reinterpret_cast<float4 *>(st + (RPL * u + lr) * PITCH + cc) = value4(nxt[k][u]);
+            if constexpr (!LAST) load_v(ch + 1, k);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float4 bv = *reinterpret_cast<const float4 *>(st + lm * PITCH + 16 * u + 4 * lk);
+                const float4 a0 = *reinterpret_cast<const float4 *>(ab + 16 * u);
+                const float4 a1 = *reinterpret_cast<const float4 *>(ab + 16 * PITCH + 16 * u);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    acc[0][k] = mfma16(comp4(a0, c), comp4(bv, c), acc[0][k]);
+                    acc[1][k] = mfma16(comp4(a1, c), comp4(bv, c), acc[1][k]);
+                }
+            }
+        }
+    };
+    for (int ch = 0; ch < n_ch - 1; ++ch) chunk(ch, std::false_type{});
+    chunk(n_ch - 1, std::true_type{});
+    lds_barrier();                                // the staging regions become the rows of dP
+#pragma unroll
+    for (int k = 0; k < NL; ++k)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s_dp[(16 * rb + 4 * lk + r) * pitch16 + (w + 4 * k) * 16 + lm] = acc[rb][k][r];
+}
+
+template <typename TV>
+__device__ __forceinline__ void dscore_block_staged(const float *__restrict__ dC, const TV *__restrict__ V,
+                                                    const float *__restrict__ P, const int *__restrict__ key_len,
+                                                    float *__restrict__ dS, float *__restrict__ ds_rowsum,
+                                                    float *__restrict__ s_dp, int b, int i0, int Tq, int Tk, int Dv,
+                                                    int pitch) {
+    const int L = clamp_len(key_len[b], Tk);
+    const int pitch16 = (Tk + 15) / 16 * 16 + 4;
+    const int n_jt = (L + 15) / 16;
+    const int most = (n_jt + 3) / 4;              // key tiles of the block's first wave
+    const int mine = __builtin_amdgcn_readfirstlane((n_jt - wave_id() + 3) / 4);
+    const float *dCb = dC + ((size_t)b * Tq + i0) * Dv;
+    const TV *Vb = V + (size_t)b * Tk * Dv;
+    const int n_rows = min(32, Tq - i0);
+    // the four waves meet at one barrier per chunk, so the width of a chunk is the block's, not the wave's
+    if (most == 6) {
+        if (mine == 6) dscore_staged_tiles<TV, 6, 2>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16);
+        else dscore_staged_tiles<TV, 5, 2>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16);
+    } else {
+        switch (mine) {
+            case 5: dscore_staged_tiles<TV, 5, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
+            case 4: dscore_staged_tiles<TV, 4, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
+            case 3: dscore_staged_tiles<TV, 3, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
+            case 2: dscore_staged_tiles<TV, 2, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
+            case 1: dscore_staged_tiles<TV, 1, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
+            default: dscore_staged_tiles<TV, 0, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
+        }
+    }
+    dscore_finish<8>(P, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, L, pitch, pitch16);
+}
 
 // The same for short key axes (Tk <= kDsplitMaxTk): latency, not arithmetic, decides here, so the four waves
 // split d instead of the key tiles.  Wave w owns the columns d of every fourth 128-wide chunk, keeps its slice
@@ -280,7 +398,6 @@ __device__ __forceinline__ void dscore_block(const float *__restrict__ dC, const
 // are added in wave order by the finishing phase, whose P rows were requested at the very start.
 // Rows and keys past the end are clamped for loading; what they produce is never read.
 constexpr int kDsplitMaxTk = 128;
-constexpr int kDs32MaxTk = 384;      // 32 rows x (Tk + 4) floats: 48.5 KB of LDS at most, three blocks per CU
 
 // The finishing phase of a dS block for short key axes: the four waves' planes of partial dP are added in wave order,
 // then dS = P (dP - sum_j P dP) for rows w, w+4, w+8, w+12 of the tile (pr: their P, two keys per lane).
@@ -837,19 +954,18 @@ __global__ __launch_bounds__(256, 3) void k_bwd_pre(const float *__restrict__ dC
     if (li < spx * s_tiles) {
         const int b = xcd + kXcd * (li / s_tiles), i0 = (li % s_tiles) * s_rows;
         if (b >= B) return;
-        if (Tk <= kDsplitMaxTk) {
+        if (KT == 1 || Tk <= kDsplitMaxTk) {
             if (Dv <= 512) dscore_block_dsplit_lds<TV, 1, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
             else if (Dv <= 1024) dscore_block_dsplit_lds<TV, 2, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
             else dscore_block_dsplit<TV>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
         } else {
-            // a wave's key tiles in groups of four, or of five where that takes all of them at once (17 to 20 key tiles)
-            const bool five = (Tk + 15) / 16 > 16 && (Tk + 15) / 16 <= 20;
             if (s_rows == 32) {
-                if (five) dscore_block<TV, 5, 2>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
-                else dscore_block<TV, 4, 2>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
+                dscore_block_staged<TV>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
             } else {
-                if (five) dscore_block<TV, 5, 1>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
-                else dscore_block<TV, 4, 1>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
+                // a wave's key tiles in groups of four, or of five where that takes all of them at once (17 to 20 key tiles)
+                if ((Tk + 15) / 16 > 16 && (Tk + 15) / 16 <= 20)
+                    dscore_block<TV, 5>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
+                else dscore_block<TV, 4>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
             }
         }
         return;
@@ -983,8 +1099,8 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
                       : launch_parts_t<float, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold);
     }
     // dS row tile: 32 rows on long key axes while three such blocks still fit a CU's LDS (the sample's V rows then
-    // pass through half as many blocks), 16 otherwise
-    const int s_rows = (s.Tk > kDsplitMaxTk && s.Tk <= kDs32MaxTk && s.Tq > 16) ? 32 : 16;
+    // pass through half as many blocks) and the staged form's 32-bit offsets hold, 16 otherwise
+    const int s_rows = (s.Tk > kDsplitMaxTk && s.Tk <= kDs32MaxTk && s.Tq > 16 && s.Dv <= (1 << 20)) ? 32 : 16;
     const int s_tiles = with_ds ? (s.Tq + s_rows - 1) / s_rows : 0;
     // dV blocks per sample.  Short key axes (at most four key tiles, one per wave): a block owns 64 columns and all
     // keys, so its slice of dC is read once (dv_cols_block).  Up to 128 keys: a block per 16 keys and 256 columns
@@ -1003,7 +1119,8 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     const int pitch16 = (s.Tk + 15) / 16 * 16 + 4;
     // short key axes: four planes of 16 rows, or (one round over d) the four waves' staging regions, which the
     // planes then share
-    const size_t lds = s.Tk > kDsplitMaxTk ? (size_t)s_rows * pitch16 * sizeof(float)
+    const size_t lds = s_rows == 32             ? (size_t)std::max(32 * pitch16, kStagedFloats) * sizeof(float)
+                       : s.Tk > kDsplitMaxTk ? (size_t)s_rows * pitch16 * sizeof(float)
                        : s.Dv <= 512       ? (size_t)4 * 16 * kStagePitch * sizeof(float)
                        : s.Dv <= 1024      ? (size_t)(4 * 16 * kStagePitch + 64 * pitch16) * sizeof(float)
                                            : (size_t)64 * pitch16 * sizeof(float);

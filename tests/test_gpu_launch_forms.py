@@ -109,6 +109,14 @@ CASES = [
     ("pre_parts_few_rows_bf16", 4, 3, 137, 24, 68, "bf16", False),
     ("pre_parts_two_rounds_bf16", 2, 70, 190, 24, 1024, "bf16", False),
     ("pre_parts_keys_past_384", 1, 90, 470, 24, 40, "f32", False),
+    # the same without parts: 32 query rows per block, operands through LDS, one to six key tiles per wave (and none, where a sample
+    # is short), value rows of less than a chunk, exactly one, one and a bit, two and a bit; more than 384 keys
+    ("pre_staged_keys_129", 101, 32, 129, 8, 4, "f32", False),
+    ("pre_staged_four_tiles", 51, 65, 255, 8, 68, "f32", False),
+    ("pre_staged_five_tiles_bf16", 40, 97, 319, 8, 132, "bf16", False),
+    ("pre_staged_six_tiles", 60, 33, 384, 8, 60, "f32", False),
+    ("pre_staged_six_tiles_bf16", 102, 17, 333, 8, 64, "bf16", False),
+    ("pre_rows_of_16_keys_past_384", 60, 50, 390, 8, 44, "f32", False),
     # whole backward in one launch: one tile, remainders of the tiles, one row, one key, three tiles, all sixteen with two per wave,
     # slices of 16 to 64 columns, several pieces of columns of each width, entries that need the exponential of the sum
     ("small_one_tile", 4, 6, 7, 16, 16, "f32", True),
