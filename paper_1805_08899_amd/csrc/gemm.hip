@@ -1108,7 +1108,9 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // longer blocks balance worse and a wave's batches of loads are too short to cover a trip to memory), and so
     // were panels of 64 keys (backward 139.5 -> 147 us at B = 128, T = 100: the second panel is half empty).
     // Beyond 128 keys, Tk a multiple of four: panels of 64 keys x 256 columns (dv_tile64; backward 635 -> 629 us
-    // at B = 32, T = 300, H = 1024, where this launch now runs at 60 % of the matrix cores' fp32 peak).
+    // at B = 32, T = 300, H = 1024).  Where Tk is no multiple of four the panels would have to load P by single floats: 0.83 to 0.94
+    // of the backward's time with value rows of 1000 columns and full samples, but 1.03 to 1.14 of it with up to 300 columns or
+    // short samples, so the blocks of 16 keys stay there.
     const int per_wave = ((s.Tk + 15) / 16 + 3) / 4;
     const int kt = per_wave <= 1 ? 1 : (s.Tk % 4 == 0 && s.Tk > kDsplitMaxTk ? 2 : 0);
     const int v_groups = kt == 1   ? (s.Dv + 63) / 64
