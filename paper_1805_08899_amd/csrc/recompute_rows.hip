@@ -342,14 +342,19 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
                         s_rows[at * RR_COLS + ln] = rr_row_exact(sq, kb, j0, L, H, hc, dsb + (size_t)(i_pass0 + i) * pitch, 1, unused);
                     }
                 }
-                for (int j = j0 + w; j < L; j += W) {
-                    const float sk = kTwoLog2e * ld(kb, (size_t)j * H + hc);
-                    const float tot = rr_row_exact(sk, qb, i_pass0, i_pass0 + nrows, H, hc, dsb + j, (size_t)pitch, s_dv[W + w][ln]);
-                    if (h0 + ln < H) {
-                        float *dst = dKb + (size_t)j * H + hc;
-                        *dst = pass == 0 && !acc ? 4.f * RawElem<T>::value(vo_raw) * tot : *dst + 4.f * RawElem<T>::value(vo_raw) * tot;
+                // a key's wave is that of the steps, the same in every pass: a pass adds to what the wave itself has stored
+                auto keys = [&](int from, int to) {
+                    for (int j = from + w; j < to; j += W) {
+                        const float sk = kTwoLog2e * ld(kb, (size_t)j * H + hc);
+                        const float tot = rr_row_exact(sk, qb, i_pass0, i_pass0 + nrows, H, hc, dsb + j, (size_t)pitch, s_dv[W + w][ln]);
+                        if (h0 + ln < H) {
+                            float *dst = dKb + (size_t)j * H + hc;
+                            *dst = pass == 0 && !acc ? 4.f * RawElem<T>::value(vo_raw) * tot : *dst + 4.f * RawElem<T>::value(vo_raw) * tot;
+                        }
                     }
-                }
+                };
+                if (st == 0) keys(0, n0);
+                keys(st == 0 ? n0 : j0, L);
                 lds_barrier();
 #pragma unroll
                 for (int a = 0; a < R; ++a) acc_q[a] += ln < HW ? s_rows[(rg * R + a) * RR_COLS + slice * HW + ln] : 0.f;

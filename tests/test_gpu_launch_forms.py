@@ -165,6 +165,48 @@ def test_launch_form(case):
         assert np.array_equal(first[k], again[k]), (name, k, "not reproducible")
 
 
+def put_rows(inputs, dt, tensor, where, x):
+    """inputs[tensor][where] = x, an x that both storage types hold exactly."""
+    inputs[tensor][where] = x
+    if dt == "bf16":
+        inputs[tensor + "_bits"][where] = np.float32(x).view(np.uint32) >> 16
+
+
+LARGE_ROWS = [
+    # name, B, Tq, Tk, H, Dv, dtype, queries beyond the factor limit as (sample, row): recomputation with up to 25 rows per lane in
+    # several passes, one of them on the factor path and one not, with a first step that does not deal its keys evenly to the waves
+    ("first_pass", 236, 201, 13, 99, 4, "f32", [(0, 7)]),
+    ("last_pass", 236, 201, 21, 99, 4, "f32", [(3, 190)]),
+    ("middle_pass_bf16", 331, 405, 9, 99, 4, "bf16", [(0, 200), (5, 150)]),
+]
+
+
+@pytest.mark.parametrize("case", LARGE_ROWS, ids=[c[0] for c in LARGE_ROWS])
+def test_passes_with_and_without_large_entries(case):
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import harness
+    name, B, Tq, Tk, H, Dv, dt, rows = case
+    print("large rows", case, flush=True)
+    wl = Workload(name, B, Tq, Tk, H, Dv, dt, 0.5, 1, Tk, dt == "bf16")
+    inputs = make_inputs(wl, seed=71 + len(name))
+    for b, row in rows:
+        put_rows(inputs, dt, "Qp", (b, row, slice(None, None, 2)), 40.5)
+        put_rows(inputs, dt, "Kp", (b, slice(None, None, 3), slice(None, None, 2)), -39.75)    # (still within the limit)
+        inputs["key_len"][b] = Tk
+    db = harness.DeviceBatch(wl, inputs, guard_bytes=4096)
+    db.poison_outputs()
+    db.fwd()
+    db.bwd()
+    got = db.results()
+    assert db.check_guards() == []
+    assert_parity(got, oracle_outputs(inputs, workers=1), inputs, dt, name)
+    db.bwd()
+    again = db.results()
+    for k in got:
+        assert np.array_equal(got[k], again[k]), (name, k, "not reproducible")
+
+
 STEPS = [
     # name, B, Tk, H, Dv, dtype: one decoder step and its query gradient, the sample's block at the edges of its batches
     # (64 rows, 512 columns): one batch of each matrix, one row and one column more, three batches, rows of one to three
