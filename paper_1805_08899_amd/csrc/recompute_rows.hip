@@ -19,6 +19,9 @@
 // recompute.hip's (dQp: eight keys, then the steps; dKp: halves of a lane's rows; dv: a step, then the steps), so that the errors
 // against float64 are no larger: B = 57, T = 100, H = 512 dQp 4.7e-7 of the tensor's norm in both, dKp 2.0e-7 in both, dv 5.4e-7 in
 // both; B = 30, T = 300, H = 1024 1.1e-6, 2.0e-7 and 6.8e-7, dv there 2.8e-6.
+// Entries beyond the factor limit cost the wave or the step concerned an exponential and an addition per evaluation, and no digits.  The whole
+// backward in us without such entries / with one row of them in every sample / with nothing else in a column: B = 128, T = 100, H = 512
+// 122 / 137 / 158 (through k_recompute 144 / 144 / 165), B = 32, T = 304, H = 1024 629 / 680 / 866 (815 / 843 / 1092).
 // Measured, the launch without the pre-kernel: B = 128, T = 100, H = 512 97 -> 82 us; B = 32, T = 300, H = 1024 455 -> 366.
 #include <type_traits>
 
@@ -34,10 +37,12 @@ constexpr int RR_NJ = 8;                   // keys of a lane per step
 constexpr int RR_COLS = 64;                // columns of h per block
 constexpr int RR_ROUND = 512;              // blocks that run at a time: two on every compute unit
 
-// One row of a lane against its first NJ (even) keys of the step: x = exp(2q), fk = exp(2k), r = 1 / (exp(2(q+k)) + 1) = 1 / (x fk + 1).
+// One row of a lane against its first NJ (even) keys of the step.
+//   BY_SUM false: x = exp(2q), fk = exp(2k)         r = 1 / (exp(2(q+k)) + 1) = 1 / (x fk + 1)
+//   BY_SUM true : x = 2 log2e q, fk = 2 log2e k     r = 1 / (exp2(x + fk) + 1), for operands beyond the factor limit
 // The empty statements keep the compiler from evaluating the first instructions of all rows up front and from moving the sums into
 // a later block, either of which takes registers by the dozen.
-template <int NJ>
+template <int NJ, bool BY_SUM>
 __device__ __forceinline__ void rr_row(float x, float (&fk)[RR_NJ], const float *__restrict__ d_row, float &acc_q,
                                        float (&acc_k)[RR_NJ], float (&acc_v)[4]) {
 #pragma unroll
@@ -47,8 +52,14 @@ __device__ __forceinline__ void rr_row(float x, float (&fk)[RR_NJ], const float 
     const float d[RR_NJ] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
     float r[NJ];
 #pragma unroll
-    for (int c = 0; c < NJ; ++c) r[c] = __builtin_fmaf(x, fk[c], 1.0f);
+    for (int c = 0; c < NJ; ++c) r[c] = BY_SUM ? x + fk[c] : __builtin_fmaf(x, fk[c], 1.0f);
     trans_begin();
+    if (BY_SUM) {
+#pragma unroll
+        for (int c = 0; c < NJ; ++c) r[c] = fast_exp2(r[c]);
+#pragma unroll
+        for (int c = 0; c < NJ; ++c) r[c] += 1.0f;
+    }
 #pragma unroll
     for (int c = 0; c < NJ; ++c) r[c] = fast_rcp(r[c]);
     trans_end();
@@ -74,21 +85,6 @@ __device__ __forceinline__ void rr_row(float x, float (&fk)[RR_NJ], const float 
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Sums over y of one row x of the other axis, by the exponential of the sum: correct for any finite operands, only reached for
-// those beyond the factor limit.  Lanes along h.  d + y * d_step: dS of (x, y).  Returns sum d r (1 - r); sum_r += sum d r.
-template <typename T>
-__device__ __forceinline__ float rr_row_exact(float sx, const T *__restrict__ ys, int y0, int y1, int H, unsigned hc,
-                                              const float *__restrict__ d, size_t d_step, float &sum_r) {
-    float sum = 0.f;
-    for (int y = y0; y < y1; ++y) {
-        const float r = r_from_sum(sx, kTwoLog2e * ld(ys, (size_t)y * H + hc));
-        const float dy = d[y * d_step];
-        sum = __builtin_fmaf(dy, __builtin_fmaf(-r, r, r), sum);
-        sum_r = __builtin_fmaf(dy, r, sum_r);
-    }
-    return sum;
-}
-
 // grid (64-column pieces of h, samples in the order of the ranking)
 template <typename T, int G, int R>
 __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
@@ -108,9 +104,10 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
     __shared__ __align__(16) float s_rows[ROWS * RR_COLS > 2 * PART ? ROWS * RR_COLS : 2 * PART];
     __shared__ float s_fk[2][STEP][RR_COLS];               // exp(2k) of a step's keys
     __shared__ __align__(16) float s_ds[2][ROWS * DP];
-    __shared__ float s_dv[2 * W][64];
+    __shared__ float s_dv[W][64];
     __shared__ float s_rowsum;
-    __shared__ int s_big[2];                               // set: what is staged for an even (odd) step is beyond the factor limit
+    __shared__ __align__(8) unsigned char s_kbig[2][W];    // a key that wave w has staged is beyond the factor limit
+    __shared__ int s_qbig[RG];                             // a row of the group is
     __shared__ int s_seen[W];
 
     // the phases that wait on memory go first when they have something to issue: next to the loop of the CU's other block a
@@ -119,7 +116,7 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
     const int packed = order[blockIdx.y];
     const int b = packed & 0xffff, L = packed >> 16;
     const int lane = lane_id(), w = wave_id();
-    const int grp = lane / HW, slice = w % G, rg = w / G;
+    const int slice = w % G, rg = w / G;
     const int col = slice * HW + lane % HW;                // this lane's column of the block's in the evaluations
     const int h0 = blockIdx.x * RR_COLS, ho = h0 + lane;   // and the column it loads and stores
     const bool hov = ho < H;
@@ -141,7 +138,6 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
         if (lane == 0) s_rowsum = rs;
     };
     if (L == 0 && w == W - 1) sum_rows();
-    s_dv[W + w][lane] = 0.f;                               // what the exact sums give of column ho
 
     // The sample's part of dv, sum dS t = sum dS - 2 sum dS r, leaves before dQp does, so that its trip to memory and back (see
     // send_part) passes behind that.
@@ -157,8 +153,6 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
                 for (int g = 0; g < RG; ++g)
 #pragma unroll
                     for (int k = 0; k < G; ++k) tot += s_dv[ln / HW + G * g][k * HW + ln % HW];
-#pragma unroll
-                for (int k = 0; k < W; ++k) tot += s_dv[W + k][ln];
             }
             if (h0 + ln < H) store_agent(&dv_part[(size_t)b * H + h0 + ln], __builtin_fmaf(-2.f, tot, s_rowsum));
         }
@@ -182,6 +176,7 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
         const int t_row = threadIdx.x / T_PER_ROW;
         const int t_rg = t_row / R;
         const BufferRows<T> k_rows(kb, (unsigned)L * (unsigned)H);
+        const BufferRows<T> q_rows(qb, (unsigned)Tq * (unsigned)H);
         const BufferRows<float> d_rows(dsb, (unsigned)Tq * (unsigned)pitch);
         const unsigned row_bytes = (unsigned)H * (unsigned)sizeof(T);
         f32x4 dx;
@@ -195,14 +190,15 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
             for (int k = 0; k < KPW; ++k) k_raw[k] = k_rows.load_raw(at_col, (unsigned)min(j0 + w + W * k, L - 1) * row_bytes);
             dx = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d_rows.rsrc, d_at, (unsigned)j0 * 4u, 0));
         };
-        auto commit = [&](int buf, bool big, int ln, int cnt) {
+        auto commit = [&](int buf, int ln, int cnt) {
+            bool big = false;
 #pragma unroll
             for (int k = 0; k < KPW; ++k) {
                 const float x = BufferRows<T>::value(k_raw[k]);
                 s_fk[buf][w + W * k][ln] = fast_exp2(kTwoLog2e * x);
                 big |= fabsf(x) > kFactorLimit;
             }
-            if (__any(big)) s_big[buf] = 1;
+            s_kbig[buf][w] = __any(big) ? 1 : 0;
             const int row_at = w * (64 / T_PER_ROW) + ln / T_PER_ROW, key = 4 * (ln % T_PER_ROW);
             if (row_at >= ROWS) return;
             float *row = &s_ds[buf][row_at * DP];
@@ -218,7 +214,6 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
             const int i_t = t_rg < RG && t_i < nrows * (t_rg + 1) / RG ? i_pass0 + t_i : -1;
             const unsigned d_at = i_t >= 0 ? (unsigned)(i_t * pitch + 4 * (int)(threadIdx.x % T_PER_ROW)) * 4u : 0x80000000u;
             fetch(0, d_at, lane);
-            bool big = false;
             // the rows, four columns per lane and four rows per wave-level load; positions [row group][row of the group]
             {
                 constexpr int PER = (ROWS + 31) / 32;
@@ -236,7 +231,7 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
                 }
                 if (pass == 0 && w == W - 1) sum_rows();
                 asm volatile("" : "+v"(vo_raw));
-                if (threadIdx.x < 2) s_big[threadIdx.x] = 0;
+                if (threadIdx.x < RG) s_qbig[threadIdx.x] = 0;
                 lds_barrier();
 #pragma unroll
                 for (int u = 0; u < PER; ++u) xr[u].pin();
@@ -244,14 +239,15 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
                 for (int u = 0; u < PER; ++u) {
                     const int at = t / 16 + 32 * u;
                     const float4 x = xr[u].get();
-                    big |= fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))) > kFactorLimit;
-                    if (ROWS % 32 == 0 || at < ROWS)
+                    if (ROWS % 32 == 0 || at < ROWS) {
                         *reinterpret_cast<float4 *>(&s_rows[at * RR_COLS + c4]) =
                             make_float4(fast_exp2(kTwoLog2e * x.x), fast_exp2(kTwoLog2e * x.y), fast_exp2(kTwoLog2e * x.z),
                                         fast_exp2(kTwoLog2e * x.w));
+                        if (fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(x.z), fabsf(x.w))) > kFactorLimit) s_qbig[at / R] = 1;
+                    }
                 }
             }
-            commit(0, big, lane, n0);
+            commit(0, lane, n0);
             lds_barrier();
             float fq[R], acc_q[R];
 #pragma unroll
@@ -259,10 +255,19 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
                 fq[a] = s_rows[(rg * R + a) * RR_COLS + col];
                 acc_q[a] = 0.f;
             }
+            const bool q_big = __builtin_amdgcn_readfirstlane(s_qbig[rg]) != 0;
             lds_barrier();                                             // the region is used for the steps' sums from here on
 
-            auto step = [&](auto n, int st, int j0, int cnt) {
+            // Operands beyond the factor limit: the exponential of the sum, in all steps for a wave with such a row, in the step for
+            // such a key.  2 log2e k of the step and, as its turn comes, 2 log2e q of a row are then read from memory (q kept in registers spills,
+            // k in LDS beside exp(2k) costs the factor path 2 to 3 %); the sums and their order are those of the factor path.
+            auto by_sum = [&](int st) {
+                const uint2 f = *reinterpret_cast<const uint2 *>(&s_kbig[st & 1][0]);
+                return q_big || __builtin_amdgcn_readfirstlane(f.x | f.y) != 0;
+            };
+            auto step = [&](auto n, auto mode, int st, int j0, int cnt) {
                 constexpr int NJ = decltype(n)::value;                 // keys of a lane
+                constexpr bool BY_SUM = decltype(mode)::value;
                 const int buf = st & 1;
                 const bool more = st + 1 < n_steps;
                 int ln = lane;
@@ -271,26 +276,52 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
 #pragma unroll
                 for (int k = 0; k < RR_NJ; ++k) acc_k[k] = 0.f;
                 float fk[RR_NJ];
+                unsigned at_col = 0;                                   // BY_SUM
+                if constexpr (BY_SUM) {
+                    at_col = (unsigned)min(h0 + slice * HW + ln % HW, H - 1) * (unsigned)sizeof(T);
+                    typename BufferRows<T>::Raw raw[RR_NJ];
 #pragma unroll
-                for (int k = 0; k < RR_NJ; ++k) fk[k] = s_fk[buf][k * G + ln / HW][slice * HW + ln % HW];
+                    for (int k = 0; k < RR_NJ; ++k) raw[k] = k_rows.load_raw(at_col + (unsigned)min(j0 + k * G + ln / HW, L - 1) * row_bytes, 0);
+#pragma unroll
+                    for (int k = 0; k < RR_NJ; ++k) fk[k] = kTwoLog2e * BufferRows<T>::value(raw[k]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < RR_NJ; ++k) fk[k] = s_fk[buf][k * G + ln / HW][slice * HW + ln % HW];
+                }
                 if (more) fetch(j0 + cnt, d_at, ln);
                 int ds_at = (buf * ROWS + rg * R) * DP + ln / HW * RR_NJ;
                 asm volatile("" : "+v"(ds_at));                        // one address, the rows are its immediate offsets
                 const float *ds_tile = &s_ds[0][0] + ds_at;
+                // the sums over the rows in two parts: shorter chains of additions
+                auto first_part = [&]() {
 #pragma unroll
-                for (int a = 0; a < R; ++a) {
-                    rr_row<NJ>(fq[a], fk, ds_tile + a * DP, acc_q[a], acc_k, acc_v);
-                    if (a == R / 2 - 1) {                              // the sums over the rows in two parts: shorter chains of additions
+                    for (int k = 0; k < NJ; ++k) {
+                        s_rows[buf * PART + (w * RR_NJ + k) * 64 + ln] = acc_k[k];
+                        acc_k[k] = 0.f;
+                    }
+                };
+                if constexpr (BY_SUM) {
+                    int i0 = i_pass0 + nrows * rg / RG;
+                    asm volatile("" : "+s"(i0));                       // the rows' offsets are not kept through the steps
+                    auto load = [&](int a) { return q_rows.load_raw(at_col, (unsigned)min(i0 + a, Tq - 1) * row_bytes); };
+                    auto raw = load(0);
 #pragma unroll
-                        for (int k = 0; k < NJ; ++k) {
-                            s_rows[buf * PART + (w * RR_NJ + k) * 64 + ln] = acc_k[k];
-                            acc_k[k] = 0.f;
-                        }
+                    for (int a = 0; a < R; ++a) {
+                        const float x = kTwoLog2e * BufferRows<T>::value(raw);
+                        if (a + 1 < R) raw = load(a + 1);
+                        rr_row<NJ, true>(x, fk, ds_tile + a * DP, acc_q[a], acc_k, acc_v);
+                        if (a == R / 2 - 1) first_part();
+                    }
+                } else {
+#pragma unroll
+                    for (int a = 0; a < R; ++a) {
+                        rr_row<NJ, false>(fq[a], fk, ds_tile + a * DP, acc_q[a], acc_k, acc_v);
+                        if (a == R / 2 - 1) first_part();
                     }
                 }
                 tot_v += (acc_v[0] + acc_v[1]) + (acc_v[2] + acc_v[3]);
                 if (FRESH) asm volatile("" : "+v"(ln));
-                if (more) commit(buf ^ 1, false, ln, STEP);
+                if (more) commit(buf ^ 1, ln, STEP);
 #pragma unroll
                 for (int k = 0; k < NJ; ++k) s_rows[buf * PART + (w * RR_NJ + k) * 64 + ln] += acc_k[k];
                 lds_barrier();
@@ -312,54 +343,27 @@ __global__ __launch_bounds__(RR_THREADS, 4) void k_recompute_rows(
                     }
                 }
             };
-            auto in_range = [&](int st) { return __builtin_amdgcn_readfirstlane(s_big[st & 1]) == 0; };     // the same for the block
             __builtin_amdgcn_s_setprio(0);
             int st = 0;
-            if (in_range(0)) {
-                switch ((n0 + 2 * G - 1) / (2 * G)) {                  // pairs of keys of a lane
-                    case 1: step(std::integral_constant<int, 2>(), 0, 0, n0); break;
-                    case 2: step(std::integral_constant<int, 4>(), 0, 0, n0); break;
-                    case 3: step(std::integral_constant<int, 6>(), 0, 0, n0); break;
-                    default: step(std::integral_constant<int, 8>(), 0, 0, n0); break;
-                }
-                for (st = 1; st < n_steps && in_range(st); ++st) step(std::integral_constant<int, RR_NJ>(), st, n0 + (st - 1) * STEP, STEP);
+            const int pairs = (n0 + 2 * G - 1) / (2 * G);              // of keys of a lane in the first step
+            if (pairs < 4 && !by_sum(0)) {
+                if (pairs == 1) step(std::integral_constant<int, 2>(), std::false_type{}, 0, 0, n0);
+                else if (pairs == 2) step(std::integral_constant<int, 4>(), std::false_type{}, 0, 0, n0);
+                else step(std::integral_constant<int, 6>(), std::false_type{}, 0, 0, n0);
+                st = 1;
+            }
+            auto full_step = [&](auto mode) {
+                step(std::integral_constant<int, RR_NJ>(), mode, st, st == 0 ? 0 : n0 + (st - 1) * STEP, st == 0 ? n0 : STEP);
+            };
+            // (loops of their own: with the two kinds of step as branches of one loop the compiler keeps two copies of acc_q and spills)
+            while (st < n_steps) {
+                for (; st < n_steps && !by_sum(st); ++st) full_step(std::false_type{});
+                for (; st < n_steps && by_sum(st); ++st) full_step(std::true_type{});
             }
             __builtin_amdgcn_s_setprio(3);
             const bool last = i_pass0 + rows_per_pass >= Tq;
             if (last) s_dv[w][lane] = tot_v;
             lds_barrier();                                             // everybody is done with the last step's sums
-            if (st < n_steps) {
-                // an operand beyond the factor limit: the rest of the pass with whole rows of each axis in turn
-                const int j0 = st == 0 ? 0 : n0 + (st - 1) * STEP;
-                float unused = 0.f;
-                int ln = lane;
-                asm volatile("" : "+v"(ln));
-                const unsigned hc = (unsigned)min(h0 + ln, H - 1);
-                for (int at = w; at < ROWS; at += W) {
-                    const int g = at / R, i = nrows * g / RG + at - g * R;
-                    if (i < nrows * (g + 1) / RG) {
-                        const float sq = kTwoLog2e * ld(qb, (size_t)(i_pass0 + i) * H + hc);
-                        s_rows[at * RR_COLS + ln] = rr_row_exact(sq, kb, j0, L, H, hc, dsb + (size_t)(i_pass0 + i) * pitch, 1, unused);
-                    }
-                }
-                // a key's wave is that of the steps, the same in every pass: a pass adds to what the wave itself has stored
-                auto keys = [&](int from, int to) {
-                    for (int j = from + w; j < to; j += W) {
-                        const float sk = kTwoLog2e * ld(kb, (size_t)j * H + hc);
-                        const float tot = rr_row_exact(sk, qb, i_pass0, i_pass0 + nrows, H, hc, dsb + j, (size_t)pitch, s_dv[W + w][ln]);
-                        if (h0 + ln < H) {
-                            float *dst = dKb + (size_t)j * H + hc;
-                            *dst = pass == 0 && !acc ? 4.f * RawElem<T>::value(vo_raw) * tot : *dst + 4.f * RawElem<T>::value(vo_raw) * tot;
-                        }
-                    }
-                };
-                if (st == 0) keys(0, n0);
-                keys(st == 0 ? n0 : j0, L);
-                lds_barrier();
-#pragma unroll
-                for (int a = 0; a < R; ++a) acc_q[a] += ln < HW ? s_rows[(rg * R + a) * RR_COLS + slice * HW + ln] : 0.f;
-                lds_barrier();
-            }
             if (last) put_part();
             if (dQp) {
                 // the lane groups' sums (of two neighbouring rows lanes 32 and up keep the second), then whole rows out through LDS
