@@ -48,3 +48,10 @@ def assert_parity(got, ref, inputs, in_dtype, what=""):
         if L == 0:
             assert not got["context"][b].any() and not got["dQp"][b].any(), (what, "empty sample", b)
     return report
+
+
+def put_rows(inputs, dt, tensor, where, x):
+    """inputs[tensor][where] = x, an x that both storage types hold exactly."""
+    inputs[tensor][where] = x
+    if dt == "bf16":
+        inputs[tensor + "_bits"][where] = np.float32(x).view(np.uint32) >> 16

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from paper_1805_08899_amd.workloads import Workload, make_inputs
-from parity import assert_parity, oracle_outputs
+from parity import assert_parity, oracle_outputs, put_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -110,12 +110,17 @@ CASES = [
     ("pre_parts_two_rounds_bf16", 2, 70, 190, 24, 1024, "bf16", False),
     ("pre_parts_keys_past_384", 1, 90, 470, 24, 40, "f32", False),
     # the same without parts: 32 query rows per block, operands through LDS, one to six key tiles per wave (and none, where a sample
-    # is short), value rows of less than a chunk, exactly one, one and a bit, two and a bit; more than 384 keys
+    # is short), value rows of less than a chunk, exactly one, one and a bit, two and a bit; with six tiles, whose chunks are half as
+    # wide, also two and a bit and three and a bit; 16 rows, tiles in groups of five; more than 384 keys
     ("pre_staged_keys_129", 101, 32, 129, 8, 4, "f32", False),
     ("pre_staged_four_tiles", 51, 65, 255, 8, 68, "f32", False),
     ("pre_staged_five_tiles_bf16", 40, 97, 319, 8, 132, "bf16", False),
     ("pre_staged_six_tiles", 60, 33, 384, 8, 60, "f32", False),
     ("pre_staged_six_tiles_bf16", 102, 17, 333, 8, 64, "bf16", False),
+    ("pre_staged_six_tiles_three_chunks_bf16", 102, 17, 333, 8, 76, "bf16", False),
+    ("pre_staged_six_tiles_four_chunks", 60, 33, 384, 8, 100, "f32", False),
+    ("pre_rows_of_16_five_tiles", 101, 16, 300, 8, 44, "f32", False),
+    ("pre_rows_of_16_five_tiles_bf16", 105, 15, 317, 8, 132, "bf16", False),
     ("pre_rows_of_16_keys_past_384", 60, 50, 390, 8, 44, "f32", False),
     # whole backward in one launch: one tile, remainders of the tiles, one row, one key, three tiles, all sixteen with two per wave,
     # slices of 16 to 64 columns, several pieces of columns of each width, entries that need the exponential of the sum
@@ -163,13 +168,6 @@ def test_launch_form(case):
     again = db.results()
     for k in first:
         assert np.array_equal(first[k], again[k]), (name, k, "not reproducible")
-
-
-def put_rows(inputs, dt, tensor, where, x):
-    """inputs[tensor][where] = x, an x that both storage types hold exactly."""
-    inputs[tensor][where] = x
-    if dt == "bf16":
-        inputs[tensor + "_bits"][where] = np.float32(x).view(np.uint32) >> 16
 
 
 LARGE_ROWS = [
@@ -317,7 +315,7 @@ def test_order_of_the_samples_in_the_recompute_grid(case):
 
 
 ACCUMULATE = [
-    # name, B, Tq, Tk, H, Dv, dtype: the accumulating call through every tanh twice in independent blocks (several groups of keys, the
+    # name, B, Tq, Tk, H, Dv, dtype[, queries per pass]: the accumulating call through every tanh twice in independent blocks (several groups of keys, the
     # last ones masked; behind the pre-kernel in parts), the whole backward in one launch, slices of 16 and 32 columns
     ("split", 3, 61, 83, 90, 8, "f32"),
     ("split_bf16", 2, 37, 261, 100, 8, "bf16"),
@@ -326,8 +324,11 @@ ACCUMULATE = [
     ("slices_of_16", 25, 50, 21, 130, 8, "f32"),
     ("slices_of_32", 34, 45, 9, 470, 8, "f32"),
     ("rows_of_25", 182, 72, 29, 128, 8, "f32"),
-    # (one pass over the rows: of two passes' parts, up to |p1| + |p2| each off by 2 U, the bound below sees only the sum)
     ("rows_of_25_one_group", 202, 130, 13, 126, 4, "bf16"),
+    # more than one pass over the queries, large entries (in the first and the last sample, a query and a key each)
+    ("rows_of_25_two_passes", 236, 201, 13, 99, 4, "f32", 101),
+    ("rows_of_25_three_passes_large", 331, 405, 9, 99, 4, "f32", 135),
+    ("rows_of_25_large_bf16", 182, 72, 29, 128, 8, "bf16"),
 ]
 
 
@@ -338,17 +339,33 @@ def test_accumulating_backward(case):
     import torch
     assert torch.cuda.is_available(), "needs the GPU"
     from paper_1805_08899_amd import binding as eb, harness
-    name, B, Tq, Tk, H, Dv, dt = case
+    name, B, Tq, Tk, H, Dv, dt, *per_pass = case
     print("accumulate", case, flush=True)
     wl = Workload(name, B, Tq, Tk, H, Dv, dt, 0.5, 1, Tk, dt == "bf16")
     inputs = make_inputs(wl, seed=41 + len(name))
     inputs["key_len"][0] = Tk // 3                        # whole groups of masked keys
     inputs["key_len"][1] = 0
+    if "large" in name:
+        inputs["key_len"][B - 1] = Tk
+        for b, row, key in ((0, 5, 0), (B - 1, Tq - 3, Tk - 2)):
+            put_rows(inputs, dt, "Qp", (b, row, slice(None, None, 2)), 44.0)
+            put_rows(inputs, dt, "Kp", (b, key, slice(None, None, 3)), -43.5)
     db = harness.DeviceBatch(wl, inputs, guard_bytes=4096)
     db.poison_outputs()
     db.fwd()
     db.bwd()
     alone = db.results()
+    if "large" in name:
+        assert_parity(alone, oracle_outputs(inputs, workers=1), inputs, dt, name)
+    # what the passes over the queries add to dKp one after the other: dS of the other passes' queries zero with their dC
+    parts = []
+    for first in range(0, Tq, per_pass[0]) if per_pass else ():
+        whole = db.dC.clone()
+        db.dC[:, :first] = 0
+        db.dC[:, first + per_pass[0]:] = 0
+        db.bwd()
+        parts.append(np.abs(db.results()["dKp"]))
+        db.dC.copy_(whole)
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
     held = {}
@@ -363,8 +380,9 @@ def test_accumulating_backward(case):
     assert db.check_guards() == []
     assert np.array_equal(got["dQp"], alone["dQp"])
     for k, base in held.items():
-        # over several passes of rows a kernel adds to the buffer more than once: a few roundings of the larger of sum and parts
-        size = np.abs(base) + np.abs(alone[k])
-        assert (np.abs(got[k] - (base.astype(np.float64) + alone[k])) <= 4 * 2.0 ** -24 * size + 1e-30).all(), k
+        # a few roundings of the larger of sum and parts: over n passes n of sums of up to all parts, and n - 1 in `alone`
+        size = np.abs(base) + (sum(parts) if parts and k == "dKp" else np.abs(alone[k]))
+        roundings = max(4, 2 * len(parts))
+        assert (np.abs(got[k] - (base.astype(np.float64) + alone[k])) <= roundings * 2.0 ** -24 * size + 1e-30).all(), k
     for b, L in enumerate(np.clip(inputs["key_len"], 0, Tk)):
         assert np.array_equal(got["dKp"][b, L:], held["dKp"][b, L:]) and np.array_equal(got["dV"][b, L:], held["dV"][b, L:])

@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from paper_1805_08899_amd.workloads import WORKLOADS, Workload, make_inputs
-from parity import KEYS, assert_parity, oracle_outputs, rel_err
+from parity import KEYS, assert_parity, oracle_outputs, put_rows, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -341,6 +341,7 @@ STEP_CASES = [
     ("steps_with_empty_samples", 9, 2, 6, 32, 16, "f32"),                  # key_len drawn from 0..Tk
     ("steps_batch_beyond_the_four_block_form", 70, 2, 20, 64, 32, "f32"),  # 4 B blocks would not all run at once
     ("steps_72_of_many_samples", 182, 72, 29, 128, 8, "f32"),              # key side with up to 25 rows per lane, no dQp
+    ("steps_72_with_large_entries", 182, 72, 29, 128, 8, "bf16"),          # the same by the exponential of the sum
 ]
 
 
@@ -357,6 +358,10 @@ def test_decoder_steps_match_the_batched_layer(H, case):
     inputs = make_inputs(wl, seed=4321 + T)
     if "empty" in name:
         inputs["key_len"][0] = 0                          # at least one sample without a valid key
+    if "large" in name:
+        inputs["key_len"][:2] = Tk
+        put_rows(inputs, dt, "Qp", (0, 7, slice(None, None, 2)), 44.0)
+        put_rows(inputs, dt, "Kp", (slice(2), slice(3, None, 9), slice(None, None, 3)), -43.5)
     ref = oracle_outputs(inputs, workers=1)
     full = H.DeviceBatch(wl, inputs)                     # device copies of Kp, V, v, key_len, dC
     step_desc = eb.make_desc(B, 1, Tk, Hh, Dv, dt)
