@@ -72,7 +72,7 @@ hipError_t launch_recompute(const AttnShape &s, const void *Qp, const void *Kp, 
                             hipStream_t st);
 // Whether launch_recompute's blocks (with a stashed map: stash) all run at once
 bool recompute_in_one_round(const AttnShape &s, bool stash);
-// The same for grids that fill the chip, from 60 query rows on; launch_recompute takes it where it is expected to be ahead
+// The same for grids of more than half a round of blocks, from 60 query rows on; launch_recompute takes it where it is expected to be ahead
 float recompute_rows_time(const AttnShape &s);
 hipError_t launch_recompute_rows(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order, const float *dS,
                                  const float *ds_rowsum, float *dQp, float *dKp, float *dv_part, unsigned long long *dv_flag,

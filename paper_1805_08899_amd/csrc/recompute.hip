@@ -21,7 +21,7 @@
 // STASH reads t from a stored map instead (the keep-the-feature-map baseline,
 // comparison only).
 //
-// Full grids of samples with many query rows take the form of recompute_rows.hip (recompute_takes_rows).
+// Samples of many query rows take the form of recompute_rows.hip on grids of more than half a round of blocks (recompute_takes_rows).
 #include "common.hpp"
 #include "kernels.hpp"
 

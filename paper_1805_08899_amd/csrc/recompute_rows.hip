@@ -1,4 +1,5 @@
-// The fused recomputation (recompute.hip) in the form for grids that fill the chip and samples of many query rows.
+// The fused recomputation (recompute.hip) in the form for samples of many query rows on grids of more than half of the blocks that run
+// at a time (recompute_takes_rows: from about 280 of 512 on).
 //
 // k_recompute deals the query rows of a sample to eight waves, eight rows each at most, and meets at a barrier for every eight
 // keys; what a wave adds to a key, one value per column and eight evaluations, passes through LDS.  Here a lane owns up to 25
@@ -13,7 +14,7 @@
 // the lane groups' dQp are added by lane exchanges and leave as whole rows.  Rows, keys and dS reach the lanes through LDS.
 //
 // Bound by issue slots, nine per tanh as in recompute.hip (five plain instructions and a reciprocal).  The register file decides its
-// shape: a lane's rows are a compile-time number (instances for 13 to 25), all waves evaluate as many, and a row that a wave does not
+// shape: a lane's rows are a compile-time number (15 to 25 with G = 2, 13 to 25 with G = 1), all waves evaluate as many, and a row that a wave does not
 // have carries a zero dS; counted at run time the compiler keeps two copies of the sums.  No instance spills: with a dozen spilled
 // registers the prologue alone took 10 us instead of 3 (T = 50, H = 512, B = 64).  Sums are kept in chains as short as
 // recompute.hip's (dQp: eight keys, then the steps; dKp: halves of a lane's rows; dv: a step, then the steps), so that the errors
@@ -432,19 +433,23 @@ static hipError_t launch_rows_r(const AttnShape &s, const void *Qp, const void *
     return hipGetLastError();
 }
 
-// From 60 rows on with two groups of lanes, from 101 with one, in one pass or in equal ones: 13 to 25 rows per lane.
+// From 60 rows on with two groups of lanes, 15 to 25 per lane; from 101 with one, in one pass or in equal ones, 13 to 25.
 template <typename T, int G>
 static hipError_t launch_rows_t(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order, const float *dS,
                                 const float *ds_rowsum, float *dQp, float *dKp, float *dv_part, unsigned long long *dv_flag,
                                 unsigned long long epoch, float *dv, hipStream_t st) {
 #define ECHO_R(N) \
-    case N: return launch_rows_r<T, G, N>(s, Qp, Kp, v, order, dS, ds_rowsum, dQp, dKp, dv_part, dv_flag, epoch, dv, st)
+    case N:                                                                                                                     \
+        if constexpr (G == 1 || N >= 15)                                                                                        \
+            return launch_rows_r<T, G, N>(s, Qp, Kp, v, order, dS, ds_rowsum, dQp, dKp, dv_part, dv_flag, epoch, dv, st);       \
+        break
     switch (rr_rows(s.Tq, RR_W / G)) {
         ECHO_R(13); ECHO_R(14); ECHO_R(15); ECHO_R(16); ECHO_R(17); ECHO_R(18); ECHO_R(19); ECHO_R(20); ECHO_R(21); ECHO_R(22);
         ECHO_R(23); ECHO_R(24); ECHO_R(25);
-        default: return hipErrorInvalidValue;
+        default: break;
     }
 #undef ECHO_R
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_recompute_rows(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order, const float *dS,

@@ -1,4 +1,4 @@
-"""Registers that the compiler keeps in memory, as the built library's own kernel descriptions give them."""
+"""What the built library's own kernel descriptions say: registers that the compiler keeps in memory, instances."""
 import os
 import re
 import shutil
@@ -49,3 +49,18 @@ def test_no_instance_spills(kernel, tmp_path):
     found = {n: v for n, v in _kernels(tmp_path).items() if re.search(r"\d" + kernel + r"I", n)}
     assert found, "no such kernel in the library"
     assert not {n: v for n, v in found.items() if v != (0, 0)}
+
+
+def test_every_instance_of_the_recomputation_by_rows_can_be_launched(tmp_path):
+    """Lane groups and rows per lane of a sample of Tq rows: two groups up to 100 rows, which four row groups share, then one and passes
+    of up to 200 rows, which eight share."""
+    reached = set()
+    for Tq in range(60, 3000):
+        groups = 2 if Tq <= 100 else 1
+        passes = -(-Tq // (25 * 8 // groups))
+        rows = -(-Tq // passes)
+        reached.add((groups, -(-rows // (8 // groups))))
+    for dtype in ("f", "NS_6bf16_tE"):
+        pattern = re.compile(r"k_recompute_rowsI" + dtype + r"Li(\d)ELi(\d+)EE")
+        built = {tuple(int(x) for x in m.groups()) for m in map(pattern.search, _kernels(tmp_path)) if m}
+        assert built == reached
