@@ -183,8 +183,8 @@ echo_status_t bwd_impl(const echo_attn_desc_t *desc, const float *dContext, cons
                                                         next_launch_number(), dv, st));
         return ECHO_OK;
     }
-    const bool one_round = (use_map || !lay.split) && echo::recompute_in_one_round(s, use_map);   // (split: heaviest first)
-    ECHO_LAUNCH("bwd_pre", echo::launch_bwd_pre(s, dContext, V, P, key_len, dS, rowsum, order, dV, one_round, st));
+    const int first = use_map || !lay.split ? echo::recompute_first_samples(s, use_map) : 0;   // (split: heaviest first)
+    ECHO_LAUNCH("bwd_pre", echo::launch_bwd_pre(s, dContext, V, P, key_len, dS, rowsum, order, dV, first, st));
     if (echo::bwd_pre_in_parts(s)) ECHO_LAUNCH("ds_finish", echo::launch_ds_finish(s, P, key_len, dS, rowsum, st));
     if (!use_map && lay.split) {
         ECHO_LAUNCH("recompute_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, dQp, dKp, dv_part, dv_flag,
@@ -393,8 +393,8 @@ echo_status_t echo_attn_steps_bwd_keys(const echo_attn_desc_t *desc, const float
     float *dv_part = reinterpret_cast<float *>(ws + lay.dvpart_off);
     int *order = reinterpret_cast<int *>(ws + lay.order_off);
     unsigned long long *dv_flag = reinterpret_cast<unsigned long long *>(ws + lay.dvflag_off);
-    const bool one_round = !lay.split && echo::recompute_in_one_round(s, false);
-    ECHO_LAUNCH("bwd_pre_dv", echo::launch_bwd_pre(s, dContext, nullptr, P, key_len, dS, rowsum, order, dV, one_round, st, false));
+    const int first = lay.split ? 0 : echo::recompute_first_samples(s, false);
+    ECHO_LAUNCH("bwd_pre_dv", echo::launch_bwd_pre(s, dContext, nullptr, P, key_len, dS, rowsum, order, dV, first, st, false));
     if (lay.split) {
         ECHO_LAUNCH("recompute_keys_split", echo::launch_recompute_split(s, Qp, Kp, v, order, dS, nullptr, dKp, dv_part, dv_flag,
                                                                          next_launch_number(), dv, st));

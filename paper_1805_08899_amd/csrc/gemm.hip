@@ -904,17 +904,16 @@ __device__ __forceinline__ void dv_cols_block(const float *__restrict__ P, const
     }
 }
 
-// For the recompute kernel: order[r] = b | L_b << 16 for the sample b with the
-// r-th most valid keys (ties by index), or r-th in index order when `sorted` is 0.  With `fold` the second
-// half runs lightest first: when the whole recompute grid is resident at once,
-// blocks y and y + B/2 meet on one CU (two blocks per CU, placed in launch
-// order), so heavy samples are paired with light ones.
+// For the recompute kernel: order[n] = b | L_b << 16, the samples by valid keys, the most first (ties by index), or in index order
+// when `sorted` is 0.  first > 0: sample n's blocks share their compute units with those of sample first + n (n < B - first), the
+// samples between have theirs alone (recompute_first_samples).  The 2 first - B heaviest then stay alone, and of the others the
+// heavier half meets the lighter one, the heaviest the lightest.  (One alone: in the middle of the samples, whose unit it may share.)
 __device__ __forceinline__ void rank_block(const int *__restrict__ key_len, int *__restrict__ order,
-                                           int *__restrict__ s_len, int B, int Tk, int sorted, int fold) {
+                                           int *__restrict__ s_len, int B, int Tk, int sorted, int first) {
     if (sorted)
         for (int o = threadIdx.x; o < B; o += 256) s_len[o] = clamp_len(key_len[o], Tk);
     lds_barrier();
-    const int half = (B + 1) / 2;
+    const int paired = B - first, alone = first - paired > 1 ? first - paired : 0;
     for (int cand = threadIdx.x; cand < B; cand += 256) {
         int r = cand;
         const int lc = sorted ? s_len[cand] : clamp_len(key_len[cand], Tk);
@@ -925,7 +924,9 @@ __device__ __forceinline__ void rank_block(const int *__restrict__ key_len, int 
                 r += (lo > lc) || (lo == lc && o < cand);
             }
         }
-        order[(fold && r >= half) ? half + (B - 1 - r) : r] = cand | (lc << 16);
+        int at = r;
+        if (first > 0) at = r < alone ? paired + r : r < first ? r - alone : first + (B - 1 - r);
+        order[at] = cand | (lc << 16);
     }
 }
 
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(256, 3) void k_bwd_pre(const float *__restrict__ dC
                                                  const float *__restrict__ P, const int *__restrict__ key_len,
                                                  float *__restrict__ dS, float *__restrict__ ds_rowsum,
                                                  int *__restrict__ order, float *__restrict__ dV, int B, int sorted,
-                                                 int fold,
+                                                 int first,
                                                  int Tq, int Tk, int Dv, int pitch, int s_tiles, int s_rows, int v_groups, int acc) {
     extern __shared__ float s_dp[];           // [s_rows][pitch16]; four planes of 16 rows when Tk <= kDsplitMaxTk
     __shared__ int s_len[kMaxSortedB];
@@ -949,7 +950,7 @@ __global__ __launch_bounds__(256, 3) void k_bwd_pre(const float *__restrict__ dC
     const int per_b = v_groups;                               // dV blocks per sample: one per 64 columns
     const int per_xcd = spx * (s_tiles + per_b);
     if ((int)blockIdx.x == kXcd * per_xcd) {
-        rank_block(key_len, order, s_len, B, Tk, sorted, fold);
+        rank_block(key_len, order, s_len, B, Tk, sorted, first);
         return;
     }
     const int xcd = blockIdx.x % kXcd;
@@ -994,14 +995,14 @@ template <typename TV, int ROUNDS>
 __global__ __launch_bounds__(256, 3) void k_bwd_pre_parts(const float *__restrict__ dC, const TV *__restrict__ V,
                                                        const float *__restrict__ P, const int *__restrict__ key_len,
                                                        float *__restrict__ dP, int *__restrict__ order,
-                                                       float *__restrict__ dV, int B, int fold, int Tq, int Tk, int Dv, int pitch,
+                                                       float *__restrict__ dV, int B, int first, int Tq, int Tk, int Dv, int pitch,
                                                        int row_tiles, int parts, int with_ds, int acc) {
     extern __shared__ float s_dp[];
     __shared__ int s_len[kMaxSortedB];
     const int n_s = with_ds ? B * row_tiles * parts : 0;
     int id = blockIdx.x;
     if (id == (int)gridDim.x - 1) {
-        rank_block(key_len, order, s_len, B, Tk, 1, fold);
+        rank_block(key_len, order, s_len, B, Tk, 1, first);
         return;
     }
     if (id < n_s) {
@@ -1067,7 +1068,7 @@ bool bwd_pre_in_parts(const AttnShape &s) {
 
 template <typename TV, int ROUNDS>
 static hipError_t launch_parts_t(const AttnShape &s, const float *dC, const void *V, const float *P, const int *key_len,
-                                 float *dS, int *order, float *dV, hipStream_t st, bool with_ds, int fold) {
+                                 float *dS, int *order, float *dV, hipStream_t st, bool with_ds, int first) {
     const int row_tiles = (s.Tq + 15) / 16, parts = (s.Tk + kPartKeys - 1) / kPartKeys;
     const long long blocks = 1 + (with_ds ? (long long)s.B * row_tiles * parts : 0) +
                              (long long)s.B * ((s.Dv + 63) / 64) * ((s.Tk + 15) / 16);
@@ -1078,7 +1079,7 @@ static hipError_t launch_parts_t(const AttnShape &s, const float *dC, const void
         hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre_parts<TV, ROUNDS>, lds, granted);
         if (e != hipSuccess) return e;
     }
-    k_bwd_pre_parts<TV, ROUNDS><<<(unsigned)blocks, 256, lds, st>>>(dC, (const TV *)V, P, key_len, dS, order, dV, s.B, fold, s.Tq,
+    k_bwd_pre_parts<TV, ROUNDS><<<(unsigned)blocks, 256, lds, st>>>(dC, (const TV *)V, P, key_len, dS, order, dV, s.B, first, s.Tq,
                                                                     s.Tk, s.Dv, ds_pitch(s.Tk), row_tiles, parts,
                                                                     with_ds ? 1 : 0, s.acc ? 1 : 0);
     return hipGetLastError();
@@ -1091,15 +1092,15 @@ hipError_t launch_ds_finish(const AttnShape &s, const float *P, const int *key_l
 }
 
 hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, const float *P, const int *key_len,
-                          float *dS, float *ds_rowsum, int *order, float *dV, bool one_round, hipStream_t st, bool with_ds) {
+                          float *dS, float *ds_rowsum, int *order, float *dV, int first, hipStream_t st, bool with_ds) {
     const int sorted = s.B <= kMaxSortedB ? 1 : 0;
-    const int fold = sorted && one_round ? 1 : 0;
+    if (!sorted) first = 0;
     if (bwd_pre_in_parts(s)) {
         if (s.Dv <= 512)
-            return s.bf16 ? launch_parts_t<bf16_t, 1>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold)
-                          : launch_parts_t<float, 1>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold);
-        return s.bf16 ? launch_parts_t<bf16_t, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold)
-                      : launch_parts_t<float, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, fold);
+            return s.bf16 ? launch_parts_t<bf16_t, 1>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first)
+                          : launch_parts_t<float, 1>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first);
+        return s.bf16 ? launch_parts_t<bf16_t, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first)
+                      : launch_parts_t<float, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first);
     }
     // dS row tile: 32 rows on long key axes while three such blocks still fit a CU's LDS (the sample's V rows then
     // pass through half as many blocks) and the staged form's 32-bit offsets hold, 16 otherwise
@@ -1137,7 +1138,7 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
             if (e != hipSuccess) return e;                                                                          \
         }                                                                                                           \
         k_bwd_pre<TV, KT><<<(unsigned)blocks, 256, lds, st>>>(dC, (const TV *)V, P, key_len, dS, ds_rowsum, order, dV, \
-                                                             s.B, sorted, fold, s.Tq, s.Tk, s.Dv, ds_pitch(s.Tk),  \
+                                                             s.B, sorted, first, s.Tq, s.Tk, s.Dv, ds_pitch(s.Tk),  \
                                                              s_tiles, s_rows, v_groups, s.acc ? 1 : 0);                     \
     } while (0)
 #define ECHO_PRE_KT(TV)                                 \

@@ -52,12 +52,12 @@ hipError_t launch_context(const AttnShape &s, const float *P, const void *V, con
 // B1 + B2 and the sample ranking in one launch:
 //   dV = P^T . dC (MFMA);  dP = dC . V^T (MFMA) then dS = P (dP - rowsum(P dP)), dS has row pitch ds_pitch(Tk),
 //   ds_rowsum[b*Tq+i] = sum_j dS;
-//   order[r] = b | L_b << 16 for the sample with the r-th most valid keys, the second half of the samples lightest first if
-//   one_round (the launch that uses it keeps all its blocks running at once: recompute_in_one_round); index order if B > kMaxSortedB
+//   order[n] = b | L_b << 16: samples by valid keys, the most first; with first > 0 (the launch that uses it runs all its blocks at once,
+//   samples first and up beside those from 0 on: recompute_first_samples) paired heavy with light; index order if B > kMaxSortedB
 constexpr int kMaxSortedB = 1024;
 // with_ds = false leaves dS and ds_rowsum alone (they are given) and launches only the dV and ranking blocks
 hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, const float *P, const int *key_len,
-                          float *dS, float *ds_rowsum, int *order, float *dV, bool one_round, hipStream_t st, bool with_ds = true);
+                          float *dS, float *ds_rowsum, int *order, float *dV, int first, hipStream_t st, bool with_ds = true);
 // Small launches on long key axes: launch_bwd_pre leaves dP in the place of dS, and launch_ds_finish (with_ds only) turns it
 // into dS and its row sums.
 bool bwd_pre_in_parts(const AttnShape &s);
@@ -70,8 +70,9 @@ hipError_t launch_recompute(const AttnShape &s, const void *Qp, const void *Kp, 
                             const float *dS, const float *ds_rowsum, const float *tmap, float *dQp, float *dKp,
                             float *dv_part, unsigned long long *dv_flag, unsigned long long epoch, float *dv,
                             hipStream_t st);
-// Whether launch_recompute's blocks (with a stashed map: stash) all run at once
-bool recompute_in_one_round(const AttnShape &s, bool stash);
+// Where launch_recompute's blocks (with a stashed map: stash) all run at once the samples whose blocks get a compute unit first, at
+// least half of them; 0: they do not
+int recompute_first_samples(const AttnShape &s, bool stash);
 // The same for grids of more than half a round of blocks, from 60 query rows on; launch_recompute takes it where it is expected to be ahead
 float recompute_rows_time(const AttnShape &s);
 hipError_t launch_recompute_rows(const AttnShape &s, const void *Qp, const void *Kp, const void *v, const int *order, const float *dS,

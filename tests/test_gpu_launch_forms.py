@@ -275,24 +275,29 @@ def test_step_of_one_query(case):
 
 
 ORDERS = [
-    # name, B, Tq, Tk, H, folded: slices of 64 columns in one round; more than a round of slices of 16 where slices of 64 would be
-    # one; every tanh twice in independent blocks
-    ("one_round", 64, 50, 50, 512, True),
-    ("narrow_slices_past_a_round", 28, 80, 80, 300, False),
-    ("split", 5, 200, 200, 76, False),
-    ("rows_of_25_one_round", 73, 72, 29, 320, True),
-    ("rows_of_25_past_a_round", 140, 72, 40, 320, False),
+    # name, B, Tq, Tk, H, samples whose blocks are among the first 256 (0: more than 512 blocks): slices of 64 columns in one round; more
+    # than a round of slices of 16 where slices of 64 would be one; every tanh twice in independent blocks; parts of a round; an odd
+    # number of samples in one round less a block
+    ("one_round", 64, 50, 50, 512, 32),
+    ("narrow_slices_past_a_round", 28, 80, 80, 300, 0),
+    ("split", 5, 200, 200, 76, 0),
+    ("rows_of_25_one_round", 73, 72, 29, 320, 51),
+    ("rows_of_25_past_a_round", 140, 72, 40, 320, 0),
+    ("part_of_a_round", 41, 35, 28, 512, 32),
+    ("rows_of_25_part_of_a_round", 31, 128, 166, 816, 19),
+    ("one_alone", 73, 50, 30, 448, 37),
 ]
 
 
 @pytest.mark.parametrize("case", ORDERS, ids=[c[0] for c in ORDERS])
 def test_order_of_the_samples_in_the_recompute_grid(case):
-    """Heaviest sample first; in a grid that runs all at once the second half lightest first, so that heavy and light blocks meet on
-    a compute unit.  The order is the run of `sample | keys << 16` words that the backward leaves in its workspace."""
+    """Heaviest sample first; in a grid that runs all at once, where a block's compute unit also gets the block 256 later, heavy samples
+    meet light ones and the heaviest meet nobody.  The order is the run of `sample | keys << 16` words that the backward leaves in its
+    workspace."""
     import torch
     assert torch.cuda.is_available(), "needs the GPU"
     from paper_1805_08899_amd import harness
-    name, B, Tq, Tk, H, folded = case
+    name, B, Tq, Tk, H, first = case
     print("order", case, flush=True)
     wl = Workload(name, B, Tq, Tk, H, 4, "f32", 0.5, 1, Tk, False)
     inputs = make_inputs(wl, seed=17)
@@ -309,9 +314,15 @@ def test_order_of_the_samples_in_the_recompute_grid(case):
     runs = [k for k in np.flatnonzero(is_entry) if is_entry[k:k + B].all() and len(set(words[k:k + B] & 0xffff)) == B]
     assert len(runs) == 1, runs
     lengths = words[runs[0]:runs[0] + B] >> 16
-    half = (B + 1) // 2 if folded else B
-    assert (np.diff(lengths[:half]) <= 0).all() and (np.diff(lengths[half:]) >= 0).all(), lengths
-    assert lengths[:half].min() >= lengths[half:].max(initial=0)
+    if not first:
+        assert (np.diff(lengths) <= 0).all(), lengths
+        return
+    both, light = lengths[:B - first], lengths[first:]               # samples that meet
+    alone = lengths[B - first:first]
+    assert (np.diff(both) <= 0).all() and (np.diff(alone) <= 0).all() and (np.diff(light) >= 0).all(), lengths
+    if len(alone) > 1:
+        assert alone.min() >= both.max(initial=0), lengths
+    assert lengths[:first].min() >= light.max(initial=0), lengths
 
 
 ACCUMULATE = [
