@@ -175,11 +175,11 @@ __device__ __forceinline__ float r_from_sum(float sq, float sk) {
 }
 
 // A batch of transcendental instructions (reciprocals, exponentials) between these two goes before whatever the other waves of the
-// SIMD have to issue.  Measured on small kernels of nothing but the loop bodies, four waves on a SIMD: a transcendental
-// instruction holds the vector unit for 8.2 clocks whatever the mix, a plain one takes 2.3 as long as two waves have plain ones to
-// issue, but 3.8 when it falls between the transcendental ones of another wave.  Waves left to themselves drift into that interleaving;
-// with the batches in front they run them back to back and then share the plain instructions: the forward's pairs of tanh 12.1 -> 10.3
-// clocks per element and wave, the recomputation's 24.6 -> 21.1 (plain instructions in front instead: 13.2 and 27.6).  The
+// SIMD have to issue.  Measured on small kernels of nothing but the loop bodies, four waves on a SIMD: a
+// transcendental instruction holds the vector unit for 8.1 clocks, a plain one takes 2.1 as long as two waves have plain ones to
+// issue, but 2.7 to 5.5 next to waves with transcendental ones.  Waves left to themselves drift into that interleaving; with the batches in
+// front they run them back to back and then share the plain instructions: the forward's tanh, half a reciprocal each, 12.7 -> 10.0
+// clocks per evaluation and wave, the recomputation's 26.0 -> 20.4 (plain instructions in front instead: 12.7 and 28.4).  The
 // fences keep the batch between the two priority changes.
 __device__ __forceinline__ void trans_begin() {
     __builtin_amdgcn_sched_barrier(0);

@@ -377,9 +377,11 @@ static int recompute_width(const AttnShape &s) {
 
 // The form of recompute_rows.hip where its expected time is 5 % ahead, 13 % on grids just past a round (whose few blocks more cost it,
 // with its slices of 64 columns, more than the estimate says: 515 blocks at B = 103, T = 83 / 68, H = 272 84.7 us backward against 76.5).
-// Over 420 shapes of 60 to 480 rows from 256 of its blocks on the whole backward takes 0.953 of the time without it, 0.950 with the
-// better of the two each time; over the 209 that take it 0.908, five of them 2 to 5 % more.  B = 128, T = 100, H = 512 135 -> 119 us;
-// B = 32, T = 300, H = 1024 604 -> 516; B = 64, T = 200 / 30, H = 512 65 -> 58.
+// Over 420 shapes of 60 to 480 rows from 256 of its blocks on the whole backward takes 0.938 of the time without it, over the 244 that
+// take it 0.895, two of them 3 and 5 % more; over 600 of 240 to 1100 blocks and any H 0.965, over the 228 that take it 0.913, five of them 2
+// to 14 % more (most where the keys per sample differ much and the heaviest sample's block decides: B = 31, T = 128 / 166, H = 816 in
+// bf16, 17 to 166 keys, 74.6 us without it, 85.1 with).  A margin of 7 % would leave out 64 of them, 0.949 of the time on average.
+// B = 128, T = 100, H = 512 135 -> 119 us; B = 32, T = 300, H = 1024 604 -> 516; B = 64, T = 200 / 30, H = 512 65 -> 58.
 static bool recompute_takes_rows(const AttnShape &s) {
     const float rows = recompute_rows_time(s);
     const long long blocks = (long long)s.B * ((s.H + 63) / 64);

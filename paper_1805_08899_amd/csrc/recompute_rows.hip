@@ -410,8 +410,9 @@ static int rr_groups(int Tq) { return Tq <= RR_R * RR_W / 2 ? 2 : 1; }
 
 // Expected time of a launch in the units of recompute.hip's recompute_time (one row of a wave against eight keys of a lane): a step
 // costs a lane's rows and about one more, a block about twenty (prologue, dQp, its part of dv).  Negative: not for this form.  Fewer
-// than 60 rows leave a lane too few for the prologue to pay (T = 50, H = 512, B = 64 29.5 us backward against 28.5), rows are
-// addressed by 32-bit byte offsets.
+// than 60 rows leave a lane too few for the prologue to pay: over 504 shapes of 46 to 59 rows, 30 to 64 keys, half a round to eight rounds of
+// blocks, both types, the backward takes 1.019 of k_recompute's time (0.94 to 1.10; ahead, by 0.2 %, at a round and a half alone; B = 64, T = 50,
+// H = 512 29.6 us against 28.5, B = 128, T = 50, H = 1024 in bf16 71.6 against 70.5).  Rows are addressed by 32-bit byte offsets.
 float recompute_rows_time(const AttnShape &s) {
     const long long e = s.bf16 ? 2 : 4, most = 1LL << 31, T = s.Tq > s.Tk ? s.Tq : s.Tk;
     if (s.Tq < 60 || T * s.H * e >= most || (long long)s.Tq * ds_pitch(s.Tk) * 4 >= most) return -1.f;
