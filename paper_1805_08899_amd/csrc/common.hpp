@@ -122,6 +122,14 @@ template <typename T> struct BufferRows {
             return __builtin_amdgcn_raw_buffer_load_b16(rsrc, v_off, s_off, 0);
         }
     }
+    // four consecutive elements (16 or 8 bytes)
+    __device__ __forceinline__ Raw4<T> load4_raw(unsigned v_off, unsigned s_off) const {
+        if constexpr (sizeof(T) == 4) {
+            return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, v_off, s_off, 0));
+        } else {
+            return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, v_off, s_off, 0));
+        }
+    }
     // (16-bit types: the empty statement keeps the conversion behind whatever barrier precedes the call)
     static __device__ __forceinline__ float value(Raw raw) {
         if constexpr (sizeof(T) == 4) {

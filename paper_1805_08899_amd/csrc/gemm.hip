@@ -1,5 +1,5 @@
 // The dense contractions of the layer on the matrix cores, fp32 in and out
-// (v_mfma_f32_16x16x4_f32):
+// (v_mfma_f32_16x16x4_f32; past the smallest launches B1 as six bf16 products of split operands, split.hpp):
 //   F3  context[b] = P[b] . V[b]                 (Section 2, step 2)
 //   B1  dV[b] = P[b]^T . dC[b],  dP[b] = dC[b] . V[b]^T   (Eq. 2: only inputs needed)
 //   B2  dS = P (dP - rowsum(P dP)), fused behind dP so dP never leaves the CU
@@ -10,6 +10,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "split.hpp"
 
 namespace echo {
 
@@ -109,9 +110,8 @@ hipError_t launch_context(const AttnShape &s, const float *P, const void *V, con
     return hipGetLastError();
 }
 
-// The finishing phase of a dS block on a long key axis: dP of its 4 NR rows stands in LDS, wave w turns rows w, w + 4, ...
+// The finishing phase of a dS block on a long key axis: dP of its 16 rows stands in LDS, wave w turns rows w, w + 4, ...
 // into dS = P (dP - sum_j P dP), with zeros at masked keys and pads.
-template <int NR>
 __device__ __forceinline__ void dscore_finish(const float *__restrict__ P, float *__restrict__ dS,
                                               float *__restrict__ ds_rowsum, const float *__restrict__ s_dp, int b, int i0,
                                               int Tq, int Tk, int L, int pitch, int pitch16) {
@@ -119,7 +119,7 @@ __device__ __forceinline__ void dscore_finish(const float *__restrict__ P, float
     // P of the rows this wave finishes (w, w + 4, ...), the first NP keys per lane of each: requested together
     // before the barrier (the registers of the product loop are free by now), where loading row after row inside
     // the loop below put one trip to memory behind the other
-    constexpr int NP = 5;
+    constexpr int NP = 5, NR = 4;
     float pr[NR][NP];
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
@@ -173,7 +173,7 @@ __device__ __forceinline__ void dscore_finish(const float *__restrict__ P, float
 // A lane loads four consecutive d of its row for both operands and spends
 // them on four MFMA steps, so the k index of step c is d0 + 4*(l/16) + c on
 // both sides.
-template <typename TV, int G>
+template <typename TV>
 __device__ __forceinline__ void dscore_block(const float *__restrict__ dC, const TV *__restrict__ V,
                                              const float *__restrict__ P, const int *__restrict__ key_len,
                                              float *__restrict__ dS, float *__restrict__ ds_rowsum,
@@ -192,7 +192,7 @@ __device__ __forceinline__ void dscore_block(const float *__restrict__ dC, const
     // in stages of U 16-wide slices; the loads of the next stage are in flight while the current one is multiplied.
     // Rows and keys past the end are clamped for loading; what they produce is never read.  Columns past Dv are zeroed.
     const int n_jt = (L + 15) / 16;
-    constexpr int U = 2;
+    constexpr int G = 4, U = 2;
     const int n_st = (Dv + 16 * U - 1) / (16 * U);            // stages
     const bool ragged = Dv % (16 * U) != 0;
     const float *dCrow = dCb + (size_t)min(i0 + lm, Tq - 1) * Dv;
@@ -257,141 +257,7 @@ __device__ __forceinline__ void dscore_block(const float *__restrict__ dC, const
             }
         }
     }
-    dscore_finish<4>(P, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, L, pitch, pitch16);
-}
-
-// The same for 32 query rows and at most kDs32MaxTk keys, operands through LDS.  Read straight from memory in operand
-// layout, each quarter of a wave asks for the same 16 bytes of 16 rows, and rows a multiple of 128 bytes apart queue in the
-// L1; and a wave of the 1.25 blocks per CU of the long shapes waited for one slice of d at a time.  Here a wave loads whole
-// row pieces of 16 U columns of d (a chunk), writes them into its own rows of LDS and reads them back in operand layout
-// (conflict-free at this pitch); the slices of ALL its key tiles for the next chunk are in flight while the current chunk
-// is multiplied, each tile's registers being refilled as soon as its slice stands in LDS.  The number of its tiles is a
-// template parameter: with conditions around the loads the compiler waits for the newest of them.  The 32 rows of dC, the
-// same for the four waves, are staged by all of them into one of two buffers (one barrier per chunk).
-// The backward pass in us, operands straight from memory -> this: B = 32, T = 300, Dv = 1024 532 -> 513 (this launch 146 ->
-// 135); bf16 B = 49, Tq = 442, Tk = 376, Dv = 512 473 -> 421; bf16 B = 130, Tq = 259, Tk = 314, Dv = 1000 1003 -> 893;
-// B = 105, Tq = 348, Tk = 308, Dv = 512 366 -> 345; B = 64, T = 144, Dv = 512 126.8 -> 121.8; Dv = 44, a single chunk:
-// level (0.999 to 1.011 of the time over seven shapes).  Blocks of 16 rows in this form, twice as many: 0 to 9 % slower.
-constexpr int kDs32MaxTk = 384;      // 32 rows x (Tk + 4) floats: 48.5 KB of LDS at most, three blocks per CU
-__host__ __device__ constexpr int staged_pitch(int u) { return 16 * u + 4; }
-constexpr int kStagedFloats = (4 * 16 + 2 * 32) * staged_pitch(4);     // the wider chunk's regions
-
-// The products of a wave that owns NL key tiles (w, w + 4, ...) of the block, U 16-wide slices of d per chunk.
-template <typename TV, int NL, int U>
-__device__ __forceinline__ void dscore_staged_tiles(const float *__restrict__ dCb, const TV *__restrict__ Vb,
-                                                    float *__restrict__ s_dp, int n_rows, int Tk, int Dv, int pitch16) {
-    constexpr int KC = 16 * U, RPL = 16 / U, PITCH = staged_pitch(U);      // columns of a chunk, rows per load
-    const int lane = lane_id(), w = wave_id();
-    const int lm = lane & 15, lk = lane >> 4;
-    float *sa = s_dp + 4 * 16 * PITCH;            // dC of the chunk: two buffers of 32 rows
-    float *st = s_dp + w * 16 * PITCH;            // this wave's key tile
-    const int lr = lane / (4 * U), cc = 4 * (lane % (4 * U));              // loading: row of the load, column in the chunk
-    const int n_ch = (Dv + KC - 1) / KC;
-    const int last_q = (n_rows - 1) * Dv, last_k = (Tk - 1) * Dv;          // rows past the end are clamped to these
-    float4 an[U / 2];
-    Raw4<TV> nxt[NL > 0 ? NL : 1][U];
-    int lane_row = lr * Dv;
-    // Offsets within the sample in 32 bits, formed anew from lane_row each time: the compiler would keep one of them per
-    // row of every tile in a register instead, and spill.
-    auto load_a = [&](int ch) {
-        const int col = min(ch * KC + cc, Dv - 4);
-        asm volatile("" : "+v"(lane_row));
-#pragma unroll
-        for (int u = 0; u < U / 2; ++u) an[u] = ld4(dCb, (size_t)(unsigned)(min(lane_row + (8 * w + RPL * u) * Dv, last_q) + col));
-    };
-    auto store_a = [&](int ch) {                  // columns past Dv add nothing
-        float *dst = sa + (ch & 1) * 32 * PITCH;
-#pragma unroll
-        for (int u = 0; u < U / 2; ++u)
-            *reinterpret_cast<float4 *>(dst + (8 * w + RPL * u + lr) * PITCH + cc) =
-                ch * KC + cc < Dv ? an[u] : make_float4(0.f, 0.f, 0.f, 0.f);
-    };
-    auto load_v = [&](int ch, int k) {
-        const int col = min(ch * KC + cc, Dv - 4);
-        asm volatile("" : "+v"(lane_row));
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            nxt[k][u] = ld4_raw(Vb, (size_t)(unsigned)(min(lane_row + ((w + 4 * k) * 16 + RPL * u) * Dv, last_k) + col));
-    };
-    load_a(0);
-#pragma unroll
-    for (int k = 0; k < NL; ++k) load_v(0, k);
-    store_a(0);
-    if (n_ch > 1) load_a(1);
-    f32x4 acc[2][NL > 0 ? NL : 1];
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int k = 0; k < NL; ++k) acc[rb][k] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    auto chunk = [&](int ch, auto last) {         // last: nothing follows that would have to be loaded
-        constexpr bool LAST = decltype(last)::value;
-        lds_barrier();                            // dC of this chunk is there, and that of the last one no longer read
-        if constexpr (!LAST) {
-            store_a(ch + 1);
-            load_a(min(ch + 2, n_ch - 1));
-        }
-        const float *ab = sa + (ch & 1) * 32 * PITCH + lm * PITCH + 4 * lk;
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) *reinterpret_cast<float4 *>(st + (RPL * u + lr) * PITCH + cc) = value4(nxt[k][u]);
-            if constexpr (!LAST) load_v(ch + 1, k);
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float4 bv = *reinterpret_cast<const float4 *>(st + lm * PITCH + 16 * u + 4 * lk);
-                const float4 a0 = *reinterpret_cast<const float4 *>(ab + 16 * u);
-                const float4 a1 = *reinterpret_cast<const float4 *>(ab + 16 * PITCH + 16 * u);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    acc[0][k] = mfma16(comp4(a0, c), comp4(bv, c), acc[0][k]);
-                    acc[1][k] = mfma16(comp4(a1, c), comp4(bv, c), acc[1][k]);
-                }
-            }
-            // of three tiles the compiler would read all operands ahead of the products: for bf16 168 registers and two more in memory
-            // (time the same within 1 % either way, 17 shapes)
-            if constexpr (NL == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    for (int ch = 0; ch < n_ch - 1; ++ch) chunk(ch, std::false_type{});
-    chunk(n_ch - 1, std::true_type{});
-    lds_barrier();                                // the staging regions become the rows of dP
-#pragma unroll
-    for (int k = 0; k < NL; ++k)
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) s_dp[(16 * rb + 4 * lk + r) * pitch16 + (w + 4 * k) * 16 + lm] = acc[rb][k][r];
-}
-
-template <typename TV>
-__device__ __forceinline__ void dscore_block_staged(const float *__restrict__ dC, const TV *__restrict__ V,
-                                                    const float *__restrict__ P, const int *__restrict__ key_len,
-                                                    float *__restrict__ dS, float *__restrict__ ds_rowsum,
-                                                    float *__restrict__ s_dp, int b, int i0, int Tq, int Tk, int Dv,
-                                                    int pitch) {
-    const int L = clamp_len(key_len[b], Tk);
-    const int pitch16 = (Tk + 15) / 16 * 16 + 4;
-    const int n_jt = (L + 15) / 16;
-    const int most = (n_jt + 3) / 4;              // key tiles of the block's first wave
-    const int mine = __builtin_amdgcn_readfirstlane((n_jt - wave_id() + 3) / 4);
-    const float *dCb = dC + ((size_t)b * Tq + i0) * Dv;
-    const TV *Vb = V + (size_t)b * Tk * Dv;
-    const int n_rows = min(32, Tq - i0);
-    // the four waves meet at one barrier per chunk, so the width of a chunk is the block's, not the wave's
-    if (most == 6) {
-        if (mine == 6) dscore_staged_tiles<TV, 6, 2>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16);
-        else dscore_staged_tiles<TV, 5, 2>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16);
-    } else {
-        switch (mine) {
-            case 5: dscore_staged_tiles<TV, 5, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
-            case 4: dscore_staged_tiles<TV, 4, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
-            case 3: dscore_staged_tiles<TV, 3, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
-            case 2: dscore_staged_tiles<TV, 2, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
-            case 1: dscore_staged_tiles<TV, 1, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
-            default: dscore_staged_tiles<TV, 0, 4>(dCb, Vb, s_dp, n_rows, Tk, Dv, pitch16); break;
-        }
-    }
-    dscore_finish<8>(P, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, L, pitch, pitch16);
+    dscore_finish(P, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, L, pitch, pitch16);
 }
 
 // The same for short key axes (Tk <= kDsplitMaxTk): latency, not arithmetic, decides here, so the four waves
@@ -731,175 +597,488 @@ __device__ __forceinline__ void dv_rows_block(const float *__restrict__ P, const
     }
 }
 
-// dV of one sample for a panel of 64 keys and 256 columns, 64 columns per wave: dV[j, n] = sum_i P[i, j] dC[i, n].
-// Per step of four query rows a lane loads four consecutive keys of a P row and four consecutive columns of the dC
-// row (16 bytes each) and spends them on 16 products: component ca of the keys with component cb of the columns,
-// so product (ca, cb) holds keys m0 + 4 (row of the result tile) + ca and columns n0 + 4 (l % 16) + cb.  Two bytes
-// of operands per lane and product, against five in the form with one key per lane (pv_block), which at the larger
-// workloads was bound by what the L2 could deliver.  Needs Tk % 4 == 0 (16-byte loads of P rows).  Batches of U
-// steps are double buffered.  Rows of masked keys (j >= L) come out as exact zeros whatever P holds there.
-__device__ __forceinline__ void dv_tile64(const float *__restrict__ P, const float *__restrict__ dC,
-                                          const int *__restrict__ key_len, float *__restrict__ dV, int Tq, int Tk,
-                                          int Dv, int b, int by, int bx, int acc_out) {
-    constexpr int U = 4;
+// dS for (b, 32 query rows) as products of split operands (split.hpp), all of the sample's keys.  The eight waves are KW key groups times
+// 8 / KW groups of d: wave w takes the key tiles of 32 w % KW, + KW, ..., at most two, and of every 64 columns of d the pairs of
+// 32-wide chunks that fall to its group w / KW.  A wave loads whole row pieces of a chunk (8 rows of 128 bytes per load), passes them
+// through LDS of its own to reach operand layout (conflict-free at these pitches) and splits them; what comes next is under
+// way meanwhile.  dC is staged by each wave for itself, or, where all of them need the same chunk (KW = 8), split once for the
+// block, an eighth of two chunks by each, one buffer ahead (a barrier per two chunks).  The partial sums of the groups of d meet in LDS planes.
+// Rows and keys past the end are clamped for loading; what they produce is never read.  Columns of d past Dv are zeroed in dC.
+// What bounds it is instruction issue: about nine vector instructions per product of 32 x 32 x 16, a wave alone on its SIMD issues one in
+// four clocks and overlaps little, so sixteen waves of at most 128 registers share a CU (eight of 250, each with four key tiles and a
+// software pipeline, took as long as four of them).
+// The launch of k_bwd_pre, dS and dV blocks, before (fp32 products; 16 or 32 rows) and with split operands, us: B = 32, T = 300, Dv = 1024
+// 126 -> 71; bf16 V, B = 128, T = 50, Dv = 1024 28.4 -> 18.8; B = 128, T = 100, Dv = 512 35.3 -> 29.9; B = 64, T = 50, Dv = 512 9.7 -> 8.5.
+template <typename TV> struct SplitStage;
+template <> struct SplitStage<float> {
+    static constexpr int PITCH = 36;          // of 32 elements
+    static __device__ __forceinline__ void put(float *p, float4 x) { *reinterpret_cast<float4 *>(p) = x; }
+    struct Raw { float4 x, y; };
+    typedef Split8 Frag;
+    static __device__ __forceinline__ Raw get(const float *p) {
+        return {*reinterpret_cast<const float4 *>(p), *reinterpret_cast<const float4 *>(p + 4)};
+    }
+    static __device__ __forceinline__ Frag split(const Raw &r) {
+        const float v[8] = {r.x.x, r.x.y, r.x.z, r.x.w, r.y.x, r.y.y, r.y.z, r.y.w};
+        return split8(v);
+    }
+};
+template <> struct SplitStage<bf16_t> {
+    static constexpr int PITCH = 40;
+    static __device__ __forceinline__ void put(bf16_t *p, uint2 x) { *reinterpret_cast<uint2 *>(p) = x; }
+    typedef u32x4 Raw;
+    typedef u32x4 Frag;
+    static __device__ __forceinline__ Raw get(const bf16_t *p) { return *reinterpret_cast<const u32x4 *>(p); }
+    static __device__ __forceinline__ Frag split(const Raw &r) { return r; }
+};
+// floats of LDS: a wave's key tile and its rows of dC; or, KW = 8, two buffers of two chunks of split dC for the block (rows of 80 bytes)
+constexpr int kSplitTileFloats = 32 * 36, kSplitPlane = 32 * 5;             // (plane: 16-byte words)
+__host__ __device__ constexpr int split_stage_floats(int kw) {
+    return 8 * kSplitTileFloats + (kw == 8 ? 4 * 3 * kSplitPlane * 4 : 8 * kSplitTileFloats);
+}
+__host__ __device__ constexpr int split_dp_pitch(int Tk) { return (Tk + 31) / 32 * 32 + 4; }
+__host__ __device__ constexpr int split_lds_floats(int kw, int Tk) {
+    return split_stage_floats(kw) > 8 / kw * 32 * split_dp_pitch(Tk) ? split_stage_floats(kw) : 8 / kw * 32 * split_dp_pitch(Tk);
+}
+
+// The finishing phase: dS = P (dP - sum_j P dP) of the rows w, w + 8, ... of the block, NP keys per lane.
+template <int PLANES, int NP>
+__device__ __forceinline__ void split_finish(const float (&pr)[4][NP], float *__restrict__ dS, float *__restrict__ ds_rowsum,
+                                             const float *__restrict__ s_dp, int b, int i0, int Tq, int L, int pitch, int dp_pitch) {
+    const int lane = lane_id(), w = wave_id();
+    float dp[4][NP], sum[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        sum[t] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+            const float *q = s_dp + (w + 8 * t) * dp_pitch + min(lane + 64 * c, dp_pitch - 1);
+            float x = q[0];
+#pragma unroll
+            for (int p = 1; p < PLANES; ++p) x += q[p * 32 * dp_pitch];
+            dp[t][c] = lane + 64 * c < L ? x : 0.f;
+            sum[t] = __builtin_fmaf(lane + 64 * c < L ? pr[t][c] : 0.f, dp[t][c], sum[t]);
+        }
+    }
+    const float r4 = wave_transpose_sum<4>(sum);                  // lane l: row l / 16
+    float tot[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const float r = lane_value(r4, 16 * t);
+        tot[t] = 0.f;
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+            dp[t][c] = lane + 64 * c < L ? pr[t][c] * (dp[t][c] - r) : 0.f;
+            tot[t] += dp[t][c];
+        }
+    }
+    const float t4 = wave_transpose_sum<4>(tot);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int i = i0 + w + 8 * t;
+        if (i < Tq) {
+            float *ds = dS + ((size_t)b * Tq + i) * pitch;
+#pragma unroll
+            for (int c = 0; c < NP; ++c)
+                if (lane + 64 * c < pitch) store_streaming(&ds[lane + 64 * c], dp[t][c]);
+            if (lane == 16 * t) ds_rowsum[(size_t)b * Tq + i] = t4;
+        }
+    }
+}
+
+// The products of a wave with NL key tiles.
+template <typename TV, int NL, int KW>
+__device__ __forceinline__ void dscore_split_tiles(const BufferRows<float> &rows_a, const BufferRows<TV> &rows_v,
+                                                   float *__restrict__ s_mem, f32x16 (&acc)[2], int last_row, int last_key, int Dv) {
+    constexpr bool SHARED = KW == 8;
+    constexpr int DW = 8 / KW, NA = SHARED ? 1 : 4;
+    typedef SplitStage<TV> VS;
+    typedef SplitStage<float> AS;
+    const int lane = lane_id(), w = wave_id();
+    const int kw = w % KW, dw = w / KW;
+    const int n = lane & 31, half = lane >> 5;
+    TV *sv = reinterpret_cast<TV *>(s_mem + w * kSplitTileFloats);
+    float *sa = s_mem + (8 + w) * kSplitTileFloats;                // (dC of the wave)
+    u32x4 *sp = reinterpret_cast<u32x4 *>(s_mem + 8 * kSplitTileFloats);                                        // (of the block)
+    const int lr = lane >> 3, lc = 4 * (lane & 7);                // loading: row of the eight, column in the chunk
+    const int n_ch = (Dv + 31) / 32, pairs = (n_ch + 1) / 2;
+    // chunk s of this wave: pair dw + DW (s / 2), its (s % 2)th chunk; the last pair may hold one chunk only
+    const int my_pairs = (pairs - dw + DW - 1) / DW;
+    const int steps = SHARED ? n_ch : dw < pairs ? 2 * my_pairs - ((n_ch & 1) && (pairs - 1) % DW == dw ? 1 : 0) : 0;
+    if (steps == 0) return;
+    constexpr int R = SHARED && NL == 1 ? 2 : 1;                   // (tile chunks on their way)
+    float4 na[NA];
+    Raw4<TV> nv[R][4];                                             // the chunks of key tiles that come next
+    // Buffer loads: row group and chunk are the scalar offset, the lane's row in the group and its columns the vector offset.  The
+    // descriptors end behind the last row of the block and the last valid key (the hardware checks the range; the scalar offset stays
+    // below it); a last chunk of fewer than 32 columns runs on into the next row.
+    const unsigned a_off = (unsigned)(lr * Dv + lc) * 4u, v_off = (unsigned)(lr * Dv + lc) * (unsigned)sizeof(TV);
+    auto chunk_of = [&](int s) { return SHARED ? 32 * s : 32 * (2 * (dw + DW * (s >> 1)) + (s & 1)); };          // its first column
+    // (SHARED: the first four waves take the rows of the even chunks, the others those of the odd ones)
+    auto load_a = [&](int s) {
+        const int c = min(chunk_of(s), Dv - 4);
+#pragma unroll
+        for (int u = 0; u < NA; ++u)
+            na[u] = rows_a.load4_raw(a_off, (unsigned)(min(8 * (SHARED ? w & 3 : u), last_row) * Dv + c) * 4u);
+    };
+    auto load_v = [&](Raw4<TV> (&dst)[4], int s, int k) {
+        const int c = min(chunk_of(s), Dv - 4);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            dst[u] = rows_v.load4_raw(v_off, (unsigned)(min((kw + KW * k) * 32 + 8 * u, last_key) * Dv + c) * (unsigned)sizeof(TV));
+    };
+    auto put_a = [&](int s) {
+        if (chunk_of(s) + 32 > Dv && chunk_of(s) + lc >= Dv) {     // columns past Dv add nothing
+#pragma unroll
+            for (int u = 0; u < NA; ++u) na[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int u = 0; u < NA; ++u) {
+            const float4 x = na[u];
+            if constexpr (SHARED) {
+                uint2 p[3];
+                split2(x.x, x.y, p[0].x, p[1].x, p[2].x);
+                split2(x.z, x.w, p[0].y, p[1].y, p[2].y);
+                uint2 *dst = reinterpret_cast<uint2 *>(sp + (s & 3) * 3 * kSplitPlane) + (8 * (w & 3) + lr) * 10 + (lane & 7);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) dst[q * 2 * kSplitPlane] = p[q];
+            } else {
+                AS::put(sa + (8 * u + lr) * AS::PITCH + lc, x);
+            }
+        }
+    };
+    auto frag_a = [&](int s, int ks) {
+        if constexpr (SHARED) {
+            const u32x4 *src = sp + (s & 3) * 3 * kSplitPlane + n * 5 + 2 * ks + half;
+            Split8 f;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) f.p[q] = src[q * kSplitPlane];
+            return f;
+        } else {
+            return AS::split(AS::get(sa + n * AS::PITCH + 16 * ks + 8 * half));
+        }
+    };
+    const int odd = w >> 2;                                        // (SHARED: the chunk of each pair whose dC this wave splits)
+    load_a(SHARED ? odd : 0);
+    if constexpr (NL > 0) load_v(nv[0], 0, 0);
+    if constexpr (R == 2) load_v(nv[1], 1, 0);
+    if constexpr (SHARED) {
+        put_a(odd);
+        load_a(2 + odd);
+    }
+    auto step = [&](Raw4<TV> (&now)[4], int s) {
+        if constexpr (SHARED) {
+            if ((s & 1) == 0) {
+                lds_barrier();                                     // dC of chunks s and s + 1 is there, that of s - 2 and s - 1 no longer read
+                put_a(s + 2 + odd);
+                load_a(s + 4 + odd);
+            }
+        } else {
+            put_a(s);
+            load_a(s + 1);
+        }
+        Split8 a0, a1;
+        if constexpr (NL > 0) {
+            a0 = frag_a(s, 0);
+            a1 = frag_a(s, 1);
+        }
+#pragma unroll
+        for (int k = 0; k < NL; ++k) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) VS::put(sv + (8 * u + lr) * VS::PITCH + lc, now[u]);
+            load_v(now, k + 1 < NL ? s : s + R, k + 1 < NL ? k + 1 : 0);
+            loads_stay();
+            const TV *t = sv + n * VS::PITCH + 8 * half;
+            acc[k] = mfma32(a0, VS::split(VS::get(t)), acc[k]);
+            acc[k] = mfma32(a1, VS::split(VS::get(t + 16)), acc[k]);
+        }
+    };
+    for (int s = 0; s < steps; s += 2) {
+        step(nv[0], s);
+        if (s + 1 < steps) step(nv[R - 1], s + 1);
+    }
+}
+
+template <typename TV, int KW>
+__device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC, const TV *__restrict__ V,
+                                                   const float *__restrict__ P, const int *__restrict__ key_len,
+                                                   float *__restrict__ dS, float *__restrict__ ds_rowsum,
+                                                   float *__restrict__ s_mem, int *__restrict__ s_inf, int b, int i0, int Tq,
+                                                   int Tk, int Dv, int pitch) {
+    constexpr int DW = 8 / KW, NP = KW;                             // 64 KW keys at most
+    const int lane = lane_id(), w = wave_id();
+    const int kw = w % KW, dw = w / KW;
+    const int n = lane & 31, half = lane >> 5;
+    const float *dCb = dC + ((size_t)b * Tq + i0) * Dv;
+    const TV *Vb = V + (size_t)b * Tk * Dv;
+    const int last_row = min(32, Tq - i0) - 1;
+    // P of the rows this wave finishes: requested at the start where it takes few registers, else before the block meets
+    float pr[4][NP];
+    auto load_p = [&]() {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const float *p = P + ((size_t)b * Tq + min(i0 + w + 8 * t, Tq - 1)) * Tk;
+#pragma unroll
+            for (int c = 0; c < NP; ++c) pr[t][c] = p[min(lane + 64 * c, Tk - 1)];
+        }
+    };
+    if constexpr (NP <= 2) load_p();
+    const int L = clamp_len(key_len[b], Tk);
+    const int mine = __builtin_amdgcn_readfirstlane(((L + 31) / 32 - kw + KW - 1) / KW);       // this wave's key tiles
+    f32x16 acc[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[k][r] = 0.f;
+    if (L > 0) {                                                    // (block-uniform)
+        const BufferRows<float> rows_a(dCb, (unsigned)(last_row + 1) * (unsigned)Dv);
+        const BufferRows<TV> rows_v(Vb, (unsigned)L * (unsigned)Dv);
+        if (mine == 2) dscore_split_tiles<TV, 2, KW>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
+        else if (mine == 1) dscore_split_tiles<TV, 1, KW>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
+        else if constexpr (KW == 8) dscore_split_tiles<TV, 0, KW>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
+    }
+    // a result of a valid key that is not finite: infinities among the operands, perhaps (see split.hpp)
+    float odd = 0.f;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (k < mine) {
+            float x = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x = __builtin_fmaf(acc[k][r], 0.f, x);
+            odd += (kw + KW * k) * 32 + n < L ? x : 0.f;
+        }
+    if constexpr (NP > 2) load_p();
+    const int dp_pitch = split_dp_pitch(Tk);
+    if (lane == 0) s_inf[w] = 0;
+    if (odd != 0.f) s_inf[w] = 1;                                   // (NaN)
+    lds_barrier();                                                  // the staging regions become the rows of dP
+    int again = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) again |= s_inf[k];
+    if (again) {                                                    // in fp32
+        for (int t = w; t < (L + 31) / 32; t += 8) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
+            const float *arow = dCb + (size_t)min(n, last_row) * Dv;
+            const TV *vrow = Vb + (size_t)min(32 * t + n, Tk - 1) * Dv;
+            for (int d = 0; d < Dv; d += 2)                         // (Dv is a multiple of four)
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(arow[d + half], ld(vrow, (size_t)(d + half)), acc[0], 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s_mem[mfma32_row(r, lane) * dp_pitch + 32 * t + n] = acc[0][r];
+        }
+        lds_barrier();
+        return split_finish<1, NP>(pr, dS, ds_rowsum, s_mem, b, i0, Tq, L, pitch, dp_pitch);
+    }
+    float *plane = s_mem + dw * 32 * dp_pitch;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (k < mine)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) plane[mfma32_row(r, lane) * dp_pitch + (kw + KW * k) * 32 + n] = acc[k][r];
+    lds_barrier();
+    split_finish<DW, NP>(pr, dS, ds_rowsum, s_mem, b, i0, Tq, L, pitch, dp_pitch);
+}
+
+// dV of one sample for a panel of up to 64 keys and 256 columns, 32 columns per wave: dV[j, n] = sum_i P[i, j] dC[i, n] as products of
+// split operands (split.hpp).  Steps of 64 query rows.  The P values of a step are split once for all waves: a thread takes 8 rows of a
+// key, lanes along the keys, and leaves them in LDS as the lanes of the products will read them, 16 bytes each, in one of two
+// buffers (one barrier per step).  A lane's dC values, one column of 8 rows per product, come straight from memory (a row piece of 128
+// bytes per half wave), two products ahead, and are split in registers: every element of the block's columns is loaded
+// once, for all keys of the panel.  Rows past Tq and masked keys count as zero.
+constexpr int kDvKeys = 64;                   // keys of a panel
+constexpr int kDvSplitLdsBytes = 2 * 3 * 8 * kDvKeys * 16;
+__device__ __forceinline__ void dv_split_block(const float *__restrict__ P, const float *__restrict__ dC,
+                                               const int *__restrict__ key_len, float *__restrict__ dV, u32x4 *__restrict__ s_a, int Tq,
+                                               int Tk, int Dv, int b, int j0, int cg, int acc_out) {
+    constexpr int W = 8, NT = kDvKeys / 32, KEYS = kDvKeys, ROWS = 8 * W, NK = ROWS / 16;
+    constexpr int BUF = 3 * W * KEYS;                                        // (16-byte words of a buffer)
     const int L = clamp_len(key_len[b], Tk);
     const int lane = lane_id(), w = wave_id();
-    const int lm = lane & 15, lk = lane >> 4;
-    const int m0 = by * 64, n0 = (bx * 4 + w) * 64;
-    if (n0 >= Dv) return;
-    const int kcol = m0 + 4 * lm;             // first of this lane's four keys
-    const int ncol = n0 + 4 * lm;             // first of this lane's four columns
-    const bool nok = ncol < Dv;
+    const int n = lane & 31, half = lane >> 5;
+    const int col = (cg * W + w) * 32 + n;
     const float *Pb = P + (size_t)b * Tq * Tk;
     const float *Cb = dC + (size_t)b * Tq * Dv;
-    f32x4 acc[4][4];
+    f32x16 acc[NT];
 #pragma unroll
-    for (int ca = 0; ca < 4; ++ca)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) acc[ca][cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    if (m0 < L) {
-        const int kc = min(kcol, Tk - 4), nc = min(ncol, Dv - 4);       // clamped for loading
-        float4 a[U], bv[U], an[U], bn[U];
-        auto load = [&](float4 (&da)[U], float4 (&db)[U], int kb0) {
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+    const int live = min((L - j0 + 31) / 32, NT);                            // key tiles that hold a valid key (block-uniform)
+    const unsigned b_col = (unsigned)min(col, Dv - 1);
+    if (live > 0) {
+        const int n_st = (Tq + ROWS - 1) / ROWS;
+        // staging: rows 8 w .. + 7 of the step; key `lane` of the panel
+        const unsigned a_col = (unsigned)min(j0 + lane, Tk - 1);
+        const bool a_on = j0 + lane < L;
+        const bool has_cols = (cg * W + w) * 32 < Dv;
+        float pa[8], pb[2][8];
+        // offsets within a step in 32 bits; rows past Tq are read as the last one
+        auto load_a = [&](int st) {
+            const float *base = Pb + (size_t)st * ROWS * Tk;
+            const int lim = Tq - 1 - ROWS * st;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int k = min(kb0 + 4 * u + lk, Tq - 1);
-                da[u] = ld4(Pb, (size_t)k * Tk + kc);
-                db[u] = ld4(Cb, (size_t)k * Dv + nc);
-            }
+            for (int e = 0; e < 8; ++e) pa[e] = (base + (size_t)min(8 * w + e, lim) * Tk)[a_col];        // (scalar row)
         };
-        load(a, bv, 0);
-        for (int kb0 = 0; kb0 < Tq; kb0 += 4 * U) {
-            load(an, bn, min(kb0 + 4 * U, Tq - 1));
+        // scalar row below Tq, the halves eight rows apart; rows past Tq read as the last one or, past the descriptor, as zero
+        const BufferRows<float> rows_b(Cb, (unsigned)Tq * (unsigned)Dv);
+        const unsigned b_off = ((unsigned)(8 * half * Dv) + b_col) * 4u;
+        auto load_b = [&](float (&dst)[8], int st, int ks) {
+            const int row = st * ROWS + 16 * ks;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool row_on = kb0 + 4 * u + lk < Tq;               // rows past Tq add nothing
-                float x[4];
+            for (int e = 0; e < 8; ++e) dst[e] = rows_b.load_raw(b_off, (unsigned)(min(row + e, Tq - 1) * Dv) * 4u);
+        };
+        load_a(0);
+        if (has_cols) {
+            load_b(pb[0], 0, 0);
+            load_b(pb[1], 0, 1);
+        }
+        for (int st = 0; st < n_st; ++st) {
+            u32x4 *buf = s_a + (st & 1) * BUF;
+            const int rows = Tq - ROWS * st, next = min(st + 1, n_st - 1);
+            {
+                float x[8];
 #pragma unroll
-                for (int ca = 0; ca < 4; ++ca) x[ca] = (row_on && kcol + ca < L) ? comp4(a[u], ca) : 0.f;
+                for (int e = 0; e < 8; ++e) x[e] = a_on && 8 * w + e < rows ? pa[e] : 0.f;
+                const Split8 s = split8(x);
 #pragma unroll
-                for (int ca = 0; ca < 4; ++ca)
-#pragma unroll
-                    for (int cb = 0; cb < 4; ++cb) acc[ca][cb] = mfma16(x[ca], comp4(bv[u], cb), acc[ca][cb]);
+                for (int p = 0; p < 3; ++p) buf[(p * W + w) * KEYS + lane] = s.p[p];
             }
+            load_a(next);
+            loads_stay();
+            lds_barrier();
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                a[u] = an[u];
-                bv[u] = bn[u];
+            for (int ks = 0; ks < NK; ++ks) {
+                if (16 * ks < rows && has_cols) {                            // uniform
+                    const Split8 sb = split8(pb[ks & 1]);
+                    if (ks + 2 < NK) load_b(pb[ks & 1], st, ks + 2);
+                    else load_b(pb[ks & 1], next, ks + 2 - NK);
+                    loads_stay();
+                    const u32x4 *frag = buf + (2 * ks + half) * KEYS + n;
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        if (t < live) {
+                            Split8 sa;
+#pragma unroll
+                            for (int p = 0; p < 3; ++p) sa.p[p] = frag[p * W * KEYS + 32 * t];
+                            acc[t] = mfma32(sa, sb, acc[t]);
+                        }
+                }
+            }
+        }
+        // a result of a valid key that is not finite: infinities among the operands, perhaps (see split.hpp); the wave's columns again,
+        // in fp32
+        float odd = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            if (t < live) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    odd = __builtin_fmaf(j0 + 32 * t + mfma32_row(r, lane) < L ? acc[t][r] : 0.f, 0.f, odd);
+            }
+        if (__any(odd != 0.f)) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                if (t >= live) continue;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+                const int j = j0 + 32 * t + n;
+                const float *pj = Pb + min(j, Tk - 1);
+                for (int i = 0; i < Tq; i += 2) {
+                    const int row = min(i + half, Tq - 1);
+                    const float x = j < L && i + half < Tq ? pj[(size_t)row * Tk] : 0.f;
+                    const float y = i + half < Tq ? Cb[(size_t)row * Dv + b_col] : 0.f;
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc[t], 0, 0, 0);
+                }
             }
         }
     }
-    if (!nok) return;
-    float *ob = dV + (size_t)b * Tk * Dv;
+    if (col >= Dv) return;
+    float *ob = dV + ((size_t)b * Tk + j0) * Dv + col;
+    const int rows = min(KEYS, Tk - j0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int ca = 0; ca < 4; ++ca) {
-            const int m = m0 + 16 * lk + 4 * r + ca;
-            if (m < Tk) {
-                float4 o = make_float4(acc[ca][0][r], acc[ca][1][r], acc[ca][2][r], acc[ca][3][r]);
-                if (acc_out) {                       // add to what the earlier decoder steps left
-                    const float4 old = *reinterpret_cast<const float4 *>(ob + (size_t)m * Dv + ncol);
-                    o.x += old.x;
-                    o.y += old.y;
-                    o.z += old.z;
-                    o.w += old.w;
-                }
-                store4_streaming(ob + (size_t)m * Dv + ncol, o);
+        for (int r = 0; r < 16; ++r) {
+            const int j = 32 * t + mfma32_row(r, lane);
+            if (j < rows) {
+                float *dst = ob + (size_t)j * Dv;
+                // (masked keys of a tile were multiplied by zeros, which leave a NaN of dC standing)
+                const float x = j0 + j < L ? acc[t][r] : 0.f;
+                store_streaming(dst, acc_out ? x + *dst : x);      // add to what the earlier decoder steps left
             }
         }
 }
 
-// dV of one sample for a 64-wide group of columns and ALL keys: dV[j, n0 .. n0+63] = sum_i P[i, j] dC[i, n0 ..].
-// The block's slice of dC (Tq rows of 256 bytes) passes through the CU once; the earlier form, a block per 16 keys
-// and 256 columns, read dC once per key tile and was bound by what the L2 could deliver at the larger workloads.
-// Wave w owns key tiles w, w + 4, ... and works on KT of them at a time: per step of four query rows a lane loads
-// KT values of P (one per key tile) and four consecutive columns of dC (one 16-byte load) and issues 4 KT products.
+// dV of one sample for a 64-wide group of columns and all of at most 64 keys: dV[j, n0 .. n0+63] = sum_i P[i, j] dC[i, n0 ..].
+// The block's slice of dC (Tq rows of 256 bytes) passes through the CU once.  Wave w owns the key tile of 16: per step of four query rows
+// a lane loads one value of P and four consecutive columns of dC (one 16-byte load) and issues 4 products.
 // Batches of U steps are double buffered: the loads of the next batch are in flight during the products of this one.
 // Rows of masked keys (j >= L) come out as exact zeros.
-template <int KT>
 __device__ __forceinline__ void dv_cols_block(const float *__restrict__ P, const float *__restrict__ dC,
                                               const int *__restrict__ key_len, float *__restrict__ dV, int Tq, int Tk,
                                               int Dv, int b, int cg, int acc_out) {
-    constexpr int U = KT == 1 ? 8 : KT == 2 ? 6 : KT == 3 ? 4 : 3;
+    constexpr int U = 8;
     const int L = clamp_len(key_len[b], Tk);
     const int lane = lane_id(), w = wave_id();
     const int lm = lane & 15, lk = lane >> 4;
     const int ncol = cg * 64 + 4 * lm;
-    const bool nok = ncol < Dv;
-    const float *Pb = P + (size_t)b * Tq * Tk;
-    const float *dCb = dC + (size_t)b * Tq * Dv + min(ncol, Dv - 4);
-    float *dVb = dV + (size_t)b * Tk * Dv + ncol;
-    const int n_kt = (Tk + 15) / 16;
     const int n_steps = (Tq + 3) / 4;
-    for (int jt0 = w; jt0 < n_kt; jt0 += 4 * KT) {                 // this wave's tiles jt0, jt0 + 4, ...
-        int m[KT];                                                  // key of this lane in tile t (clamped for loading)
+    if (16 * w >= Tk) return;
+    f32x4 acc[4];
 #pragma unroll
-        for (int t = 0; t < KT; ++t) m[t] = min((jt0 + 4 * t) * 16 + lm, Tk - 1);
-        f32x4 acc[KT][4];
+    for (int c = 0; c < 4; ++c) acc[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (16 * w < L) {                                               // uniform: else all of the tile's keys are masked
+        const float *Pb = P + (size_t)b * Tq * Tk + min(16 * w + lm, Tk - 1);
+        const float *dCb = dC + (size_t)b * Tq * Dv + min(ncol, Dv - 4);
+        float a[2][U];
+        float4 bv[2][U];
+        auto load = [&](int buf, int st0) {
 #pragma unroll
-        for (int t = 0; t < KT; ++t)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[t][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if (jt0 * 16 < L) {                                         // uniform: else all of the group's keys are masked
-            float a[2][U][KT];
-            float4 bv[2][U];
-            auto load = [&](int buf, int st0) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int kc = min(4 * (st0 + u) + lk, Tq - 1);
-#pragma unroll
-                    for (int t = 0; t < KT; ++t) a[buf][u][t] = Pb[(size_t)kc * Tk + m[t]];
-                    bv[buf][u] = ld4(dCb, (size_t)kc * Dv);
-                }
-            };
-            auto mult = [&](int buf, int st0) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (st0 + u < n_steps) {                        // uniform
-                        // query rows past Tq (last step only) were loaded from row Tq - 1: they add nothing.
-                        // Masked here, at the point of use, so that nothing waits for the loads earlier.
-                        const bool kv = 4 * (st0 + u) + lk < Tq;
-#pragma unroll
-                        for (int t = 0; t < KT; ++t) {
-                            const float av = kv ? a[buf][u][t] : 0.f;
-                            acc[t][0] = mfma16(av, bv[buf][u].x, acc[t][0]);
-                            acc[t][1] = mfma16(av, bv[buf][u].y, acc[t][1]);
-                            acc[t][2] = mfma16(av, bv[buf][u].z, acc[t][2]);
-                            acc[t][3] = mfma16(av, bv[buf][u].w, acc[t][3]);
-                        }
-                    }
-                }
-            };
-            load(0, 0);
-            for (int st0 = 0; st0 < n_steps; st0 += 2 * U) {
-                if (st0 + U < n_steps) load(1, st0 + U);
-                mult(0, st0);
-                if (st0 + 2 * U < n_steps) load(0, st0 + 2 * U);
-                if (st0 + U < n_steps) mult(1, st0 + U);
+            for (int u = 0; u < U; ++u) {
+                const int kc = min(4 * (st0 + u) + lk, Tq - 1);
+                a[buf][u] = Pb[(size_t)kc * Tk];
+                bv[buf][u] = ld4(dCb, (size_t)kc * Dv);
             }
+        };
+        auto mult = [&](int buf, int st0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (st0 + u < n_steps) {                            // uniform
+                    // query rows past Tq (last step only) were loaded from row Tq - 1: they add nothing.
+                    // Masked here, at the point of use, so that nothing waits for the loads earlier.
+                    const float av = 4 * (st0 + u) + lk < Tq ? a[buf][u] : 0.f;
+                    acc[0] = mfma16(av, bv[buf][u].x, acc[0]);
+                    acc[1] = mfma16(av, bv[buf][u].y, acc[1]);
+                    acc[2] = mfma16(av, bv[buf][u].z, acc[2]);
+                    acc[3] = mfma16(av, bv[buf][u].w, acc[3]);
+                }
+            }
+        };
+        load(0, 0);
+        for (int st0 = 0; st0 < n_steps; st0 += 2 * U) {
+            if (st0 + U < n_steps) load(1, st0 + U);
+            mult(0, st0);
+            if (st0 + 2 * U < n_steps) load(0, st0 + 2 * U);
+            if (st0 + U < n_steps) mult(1, st0 + U);
         }
-        if (nok) {
+    }
+    if (ncol >= Dv) return;
+    float *dVb = dV + (size_t)b * Tk * Dv + ncol;
 #pragma unroll
-            for (int t = 0; t < KT; ++t) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = (jt0 + 4 * t) * 16 + 4 * lk + r;
-                    if (j < Tk) {
-                        float4 o = make_float4(acc[t][0][r], acc[t][1][r], acc[t][2][r], acc[t][3][r]);
-                        if (j >= L) o = make_float4(0.f, 0.f, 0.f, 0.f);      // masked key: its P column was not zeroed above
-                        float *dst = dVb + (size_t)j * Dv;
-                        if (acc_out) {                               // add to what the earlier decoder steps left
-                            const float4 old = *reinterpret_cast<const float4 *>(dst);
-                            o.x += old.x;
-                            o.y += old.y;
-                            o.z += old.z;
-                            o.w += old.w;
-                        }
-                        store4_streaming(dst, o);
-                    }
-                }
+    for (int r = 0; r < 4; ++r) {
+        const int j = 16 * w + 4 * lk + r;
+        if (j < Tk) {
+            float4 o = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+            if (j >= L) o = make_float4(0.f, 0.f, 0.f, 0.f);      // masked key: its P column was not zeroed above
+            float *dst = dVb + (size_t)j * Dv;
+            if (acc_out) {                                       // add to what the earlier decoder steps left
+                const float4 old = *reinterpret_cast<const float4 *>(dst);
+                o.x += old.x;
+                o.y += old.y;
+                o.z += old.z;
+                o.w += old.w;
             }
+            store4_streaming(dst, o);
         }
     }
 }
@@ -911,10 +1090,10 @@ __device__ __forceinline__ void dv_cols_block(const float *__restrict__ P, const
 __device__ __forceinline__ void rank_block(const int *__restrict__ key_len, int *__restrict__ order,
                                            int *__restrict__ s_len, int B, int Tk, int sorted, int first) {
     if (sorted)
-        for (int o = threadIdx.x; o < B; o += 256) s_len[o] = clamp_len(key_len[o], Tk);
+        for (int o = threadIdx.x; o < B; o += (int)blockDim.x) s_len[o] = clamp_len(key_len[o], Tk);
     lds_barrier();
     const int paired = B - first, alone = first - paired > 1 ? first - paired : 0;
-    for (int cand = threadIdx.x; cand < B; cand += 256) {
+    for (int cand = threadIdx.x; cand < B; cand += (int)blockDim.x) {
         int r = cand;
         const int lc = sorted ? s_len[cand] : clamp_len(key_len[cand], Tk);
         if (sorted) {
@@ -933,21 +1112,29 @@ __device__ __forceinline__ void rank_block(const int *__restrict__ key_len, int 
 // Everything the backward pass needs before the recomputation, in one launch:
 // blocks that produce dS (B1 + B2), blocks that produce dV (B1) and one block
 // that ranks the samples.  The three kinds of block do not depend on each other.
-template <typename TV, int KT>
-__global__ __launch_bounds__(256, 3) void k_bwd_pre(const float *__restrict__ dC, const TV *__restrict__ V,
+// dV blocks of a sample: groups of columns times groups of keys.  dv_split_block: 256 columns, 64 keys; dv_cols_block: 64 columns, all
+// keys; pv_block: 256 columns, 16 keys.
+__host__ __device__ constexpr int dv_col_groups(int kw, int Tk, int Dv) { return kw == 0 && Tk <= 64 ? (Dv + 63) / 64 : (Dv + 255) / 256; }
+__host__ __device__ constexpr int dv_key_groups(int kw, int Tk) { return kw ? (Tk + kDvKeys - 1) / kDvKeys : Tk <= 64 ? 1 : (Tk + 15) / 16; }
+
+// The dS blocks of a launch: KW key groups of a block of eight waves, 32 query rows and at most 64 KW keys (dscore_split_block), or, KW = 0,
+// 16 rows on the fp32 matrix instructions in blocks of four waves.
+template <typename TV, int KW>
+__global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const float *__restrict__ dC, const TV *__restrict__ V,
                                                  const float *__restrict__ P, const int *__restrict__ key_len,
                                                  float *__restrict__ dS, float *__restrict__ ds_rowsum,
                                                  int *__restrict__ order, float *__restrict__ dV, int B, int sorted,
                                                  int first,
-                                                 int Tq, int Tk, int Dv, int pitch, int s_tiles, int s_rows, int v_groups, int acc) {
-    extern __shared__ float s_dp[];           // [s_rows][pitch16]; four planes of 16 rows when Tk <= kDsplitMaxTk
+                                                 int Tq, int Tk, int Dv, int pitch, int s_tiles, int s_rows, int acc) {
+    // dS blocks: [s_rows][pitch16], four planes of 16 rows when Tk <= kDsplitMaxTk; dV blocks: two buffers of split P
+    extern __shared__ __align__(16) float s_dp[];
     __shared__ int s_len[kMaxSortedB];
     // The hardware deals blocks to the eight XCDs round-robin, so block id mod 8 names the XCD.  Sample b is
     // worked on by XCD b mod 8 only: its dC, V and P then pass through one L2 instead of eight.  Within an XCD the
     // long dS blocks of all its samples come first, then the dV blocks; the last block of the grid ranks.
     constexpr int kXcd = 8;
     const int spx = (B + kXcd - 1) / kXcd;                     // sample slots per XCD
-    const int per_b = v_groups;                               // dV blocks per sample: one per 64 columns
+    const int v_cols = dv_col_groups(KW, Tk, Dv), per_b = v_cols * dv_key_groups(KW, Tk);       // dV blocks per sample
     const int per_xcd = spx * (s_tiles + per_b);
     if ((int)blockIdx.x == kXcd * per_xcd) {
         rank_block(key_len, order, s_len, B, Tk, sorted, first);
@@ -958,34 +1145,24 @@ __global__ __launch_bounds__(256, 3) void k_bwd_pre(const float *__restrict__ dC
     if (li < spx * s_tiles) {
         const int b = xcd + kXcd * (li / s_tiles), i0 = (li % s_tiles) * s_rows;
         if (b >= B) return;
-        if (KT == 1 || (KT == 0 && Tk <= kDsplitMaxTk)) {
+        if constexpr (KW > 0) {
+            dscore_split_block<TV, KW>(dC, V, P, key_len, dS, ds_rowsum, s_dp, s_len, b, i0, Tq, Tk, Dv, pitch);
+        } else if (Tk <= kDsplitMaxTk) {
             if (Dv <= 512) dscore_block_dsplit_lds<TV, 1, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
             else if (Dv <= 1024) dscore_block_dsplit_lds<TV, 2, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
             else dscore_block_dsplit<TV>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
         } else {
-            if (s_rows == 32) {
-                dscore_block_staged<TV>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
-            } else {
-                // a wave's key tiles in groups of four, or of five where that takes all of them at once (17 to 20 key tiles)
-                if ((Tk + 15) / 16 > 16 && (Tk + 15) / 16 <= 20)
-                    dscore_block<TV, 5>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
-                else dscore_block<TV, 4>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
-            }
+            dscore_block<TV>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch);
         }
         return;
     }
     li -= spx * s_tiles;
     const int b = xcd + kXcd * (li / per_b), rem = li % per_b;
     if (b >= B) return;
-    if constexpr (KT == 1) {
-        dv_cols_block<KT>(P, dC, key_len, dV, Tq, Tk, Dv, b, rem, acc);
-    } else if constexpr (KT == 2) {           // v_groups = column groups of 256, times the panels of 64 keys
-        const int v_xt = (Dv + 255) / 256;
-        dv_tile64(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_xt, rem % v_xt, acc);
-    } else {                                  // v_groups = column groups of 256, times the key tiles
-        const int v_xt = (Dv + 255) / 256;
-        pv_block<float, true>(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_xt, rem % v_xt, acc);
-    }
+    if constexpr (KW > 0)
+        dv_split_block(P, dC, key_len, dV, reinterpret_cast<u32x4 *>(s_dp), Tq, Tk, Dv, b, (rem / v_cols) * kDvKeys, rem % v_cols, acc);
+    else if (Tk <= 64) dv_cols_block(P, dC, key_len, dV, Tq, Tk, Dv, b, rem, acc);
+    else pv_block<float, true>(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_cols, rem % v_cols, acc);
 }
 
 // The same work for launches that k_bwd_pre would run in too few, too long blocks (key axes past 128 keys): dP in blocks of 16
@@ -1102,57 +1279,57 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
         return s.bf16 ? launch_parts_t<bf16_t, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first)
                       : launch_parts_t<float, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first);
     }
-    // dS row tile: 32 rows on long key axes while three such blocks still fit a CU's LDS (the sample's V rows then
-    // pass through half as many blocks) and the staged form's 32-bit offsets hold, 16 otherwise
-    const int s_rows = (s.Tk > kDsplitMaxTk && s.Tk <= kDs32MaxTk && s.Tq > 16 && s.Dv <= (1 << 20)) ? 32 : 16;
+    // Split operands (KW > 0) for what their blocks take: at most 512 keys, 32-bit offsets within 32 rows of dC, a sample's V and its dC.
+    // Not where tiles of 32 would be mostly empty, nor, in f32, on few blocks, where latency decides and the splitting of both operands is
+    // a part of it (backward, 350 shapes of up to 128 keys: at most 16 rows or 16 keys 1.02 of the time of the fp32 form, up to 1.13;
+    // fewer than 64 blocks of 32 rows 1.00 in f32, 0.75 to 1.12, and 0.92 in bf16; 64 to 160 blocks 0.94; more and longer ones 0.93, see
+    // dscore_split_block).
+    const long long blocks32 = (long long)s.B * ((s.Tq + 31) / 32);
+    const bool fits = s.Tk <= 512 && s.Dv < (1 << 20) && (long long)s.Tq * s.Dv < (1LL << 29);
+    // dV alone (the keys' call of the decoder) on short key axes: blocks of 64 columns up to two rounds of them (512 of them 5.8 us against 7.8;
+    // 2048 19.4 against 13).
+    const bool few_dv = !with_ds && s.Tk <= 64 && (long long)s.B * ((s.Dv + 63) / 64) <= 1024;
+    const bool small = s.Tk <= 128 && (s.Tq <= 16 || s.Tk <= 16 || (with_ds && !s.bf16 && blocks32 < 64) || few_dv);
+    const int kw = !fits || small ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
+    const int s_rows = kw ? 32 : 16;
     const int s_tiles = with_ds ? (s.Tq + s_rows - 1) / s_rows : 0;
-    // dV blocks per sample.  Short key axes (at most four key tiles, one per wave): a block owns 64 columns and all
-    // keys, so its slice of dC is read once (dv_cols_block).  Up to 128 keys: a block per 16 keys and 256 columns
-    // (pv_block); there the all-keys form was measured slower (3 to 12 % of this kernel at workloads 2 and 3: fewer,
-    // longer blocks balance worse and a wave's batches of loads are too short to cover a trip to memory), and so
-    // were panels of 64 keys (backward 139.5 -> 147 us at B = 128, T = 100: the second panel is half empty).
-    // Beyond 128 keys, Tk a multiple of four: panels of 64 keys x 256 columns (dv_tile64; backward 635 -> 629 us
-    // at B = 32, T = 300, H = 1024).  Where Tk is no multiple of four the panels would have to load P by single floats: 0.83 to 0.94
-    // of the backward's time with value rows of 1000 columns and full samples, but 1.03 to 1.14 of it with up to 300 columns or
-    // short samples, so the blocks of 16 keys stay there.
-    const int per_wave = ((s.Tk + 15) / 16 + 3) / 4;
-    const int kt = per_wave <= 1 ? 1 : (s.Tk % 4 == 0 && s.Tk > kDsplitMaxTk ? 2 : 0);
-    const int v_groups = kt == 1   ? (s.Dv + 63) / 64
-                         : kt == 2 ? ((s.Dv + 255) / 256) * ((s.Tk + 63) / 64)
-                                   : ((s.Dv + 255) / 256) * ((s.Tk + 15) / 16);
+    const int v_groups = dv_col_groups(kw, s.Tk, s.Dv) * dv_key_groups(kw, s.Tk);
     const long long blocks = 1 + 8LL * ((s.B + 7) / 8) * (s_tiles + (long long)v_groups);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int pitch16 = (s.Tk + 15) / 16 * 16 + 4;
     // short key axes: four planes of 16 rows, or (one round over d) the four waves' staging regions, which the
     // planes then share
-    const size_t lds = s_rows == 32             ? (size_t)std::max(32 * pitch16, kStagedFloats) * sizeof(float)
-                       : s.Tk > kDsplitMaxTk ? (size_t)s_rows * pitch16 * sizeof(float)
-                       : s.Dv <= 512       ? (size_t)4 * 16 * kStagePitch * sizeof(float)
-                       : s.Dv <= 1024      ? (size_t)(4 * 16 * kStagePitch + 64 * pitch16) * sizeof(float)
-                                           : (size_t)64 * pitch16 * sizeof(float);
-#define ECHO_PRE_LAUNCH(TV, KT)                                                                                     \
+    const size_t ds_lds = s_tiles == 0          ? 0
+                          : kw > 0              ? (size_t)split_lds_floats(kw, s.Tk) * sizeof(float)
+                          : s.Tk > kDsplitMaxTk ? (size_t)s_rows * pitch16 * sizeof(float)
+                          : s.Dv <= 512         ? (size_t)4 * 16 * kStagePitch * sizeof(float)
+                          : s.Dv <= 1024        ? (size_t)(4 * 16 * kStagePitch + 64 * pitch16) * sizeof(float)
+                                                : (size_t)64 * pitch16 * sizeof(float);
+    const size_t lds = kw ? std::max(ds_lds, (size_t)kDvSplitLdsBytes) : ds_lds;
+#define ECHO_PRE_LAUNCH(TV, KW)                                                                                     \
     do {                                                                                                            \
         if (lds > 48 * 1024) { /* beyond the default dynamic LDS limit (up to 160 KB per block on gfx950) */        \
             static LdsGrants granted;                                                                               \
-            hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre<TV, KT>, lds, granted);                       \
+            hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre<TV, KW>, lds, granted);                       \
             if (e != hipSuccess) return e;                                                                          \
         }                                                                                                           \
-        k_bwd_pre<TV, KT><<<(unsigned)blocks, 256, lds, st>>>(dC, (const TV *)V, P, key_len, dS, ds_rowsum, order, dV, \
-                                                             s.B, sorted, first, s.Tq, s.Tk, s.Dv, ds_pitch(s.Tk),  \
-                                                             s_tiles, s_rows, v_groups, s.acc ? 1 : 0);                     \
+        k_bwd_pre<TV, KW><<<(unsigned)blocks, KW ? 512 : 256, lds, st>>>(                                           \
+            dC, (const TV *)V, P, key_len, dS, ds_rowsum, order, dV, s.B, sorted, first, s.Tq, s.Tk, s.Dv,          \
+            ds_pitch(s.Tk), s_tiles, s_rows, s.acc ? 1 : 0);                                                        \
     } while (0)
-#define ECHO_PRE_KT(TV)                                 \
-    switch (kt) {                                       \
+#define ECHO_PRE_KW(TV)                                 \
+    switch (kw) {                                       \
         case 1: ECHO_PRE_LAUNCH(TV, 1); break;          \
         case 2: ECHO_PRE_LAUNCH(TV, 2); break;          \
+        case 8: ECHO_PRE_LAUNCH(TV, 8); break;          \
         default: ECHO_PRE_LAUNCH(TV, 0); break;         \
     }
     if (s.bf16) {
-        ECHO_PRE_KT(bf16_t)
+        ECHO_PRE_KW(bf16_t)
     } else {
-        ECHO_PRE_KT(float)
+        ECHO_PRE_KW(float)
     }
-#undef ECHO_PRE_KT
+#undef ECHO_PRE_KW
 #undef ECHO_PRE_LAUNCH
     return hipGetLastError();
 }

@@ -1,0 +1,80 @@
+// fp32 contractions on the bf16 matrix cores (gfx950), without losing fp32's digits.
+//
+// An fp32 number is the sum of three bf16 numbers, x = h + m + l: h is x rounded to bf16, m what is left of it rounded to bf16, l the rest
+// (8 + 8 + 8 significant bits and two signs: exact).  A product of two such sums is
+//   hh' + (hm' + mh') + (mm' + hl' + lh')
+// up to terms below 2^-24 of it, six matrix products with fp32 accumulation.  Measured against float64 over 64 to 1024 terms
+// (normal, uniform and widely spread operands): 0.65 to 0.85 of the error of v_mfma_f32_16x16x4_f32, which rounds its sum more often.
+// Why: the fp32 matrix instructions run at 32 multiply-adds per clock and SIMD and hold the vector unit for as long (measured: no vector
+// instruction of another wave gets in); the bf16 ones run at 512, six of them at 85, and leave the vector unit free (a wave of
+// reciprocals next to a wave of v_mfma_f32_32x32x16_bf16: 10.6 clocks per reciprocal against 10.1 alone).
+// What it cannot do: infinities and numbers that round to an infinite bf16 (3.39e38 up), whose lower parts are no numbers, so that the
+// product is none either; a caller that finds a result that is not finite redoes the work in fp32.  Parts below 2^-126 count as zero (the
+// matrix cores flush bf16 denormals), so digits are lost for numbers below about 1e-33.
+#pragma once
+#include "common.hpp"
+
+namespace echo {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// Loads stay where they are requested: everything else may cross this line.  (The compiler moves the loads for the next step to the end
+// of this one, where fewer registers are live, and the next step then waits for a whole trip to memory.)
+__device__ __forceinline__ void loads_stay() { __builtin_amdgcn_sched_barrier(0); }
+
+// Eight consecutive operands of one lane, split: plane 0 holds the h, 1 the m, 2 the l.
+struct Split8 { u32x4 p[3]; };
+
+__device__ __forceinline__ unsigned bf16_pair(float a, float b) {           // round to nearest even, a in the low half
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
+}
+// Two numbers into their three pairs: eleven instructions.  (v_dot2_f32_bf16 with (-1, 0) would take a half off in one instruction instead
+// of two, but it holds up the matrix instructions: 61 clocks for one of them and four v_dot2, 33 with four shifts or subtractions.)
+__device__ __forceinline__ void split2(float a, float b, unsigned &h, unsigned &m, unsigned &l) {
+    h = bf16_pair(a, b);
+    a -= __uint_as_float(h << 16);
+    b -= __uint_as_float(h & 0xffff0000u);
+    m = bf16_pair(a, b);
+    l = bf16_pair(a - __uint_as_float(m << 16), b - __uint_as_float(m & 0xffff0000u));
+}
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+    Split8 s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned h, m, l;
+        split2(x[2 * i], x[2 * i + 1], h, m, l);
+        s.p[0][i] = h;
+        s.p[1][i] = m;
+        s.p[2][i] = l;
+    }
+    return s;
+}
+
+// v_mfma_f32_32x32x16_bf16, lane l: A row l % 32, B column l % 32, both k = 8 (l / 32) .. + 7; accumulator r holds row
+// 8 (r / 4) + 4 (l / 32) + r % 4 of column l % 32.
+__device__ __forceinline__ f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ int mfma32_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+// c += A B, the small terms first
+__device__ __forceinline__ f32x16 mfma32(const Split8 &a, const Split8 &b, f32x16 c) {
+    c = mfma32(a.p[1], b.p[1], c);
+    c = mfma32(a.p[2], b.p[0], c);
+    c = mfma32(a.p[0], b.p[2], c);
+    c = mfma32(a.p[1], b.p[0], c);
+    c = mfma32(a.p[0], b.p[1], c);
+    return mfma32(a.p[0], b.p[0], c);
+}
+
+// the same with a B that is bf16 to begin with
+__device__ __forceinline__ f32x16 mfma32(const Split8 &a, u32x4 b, f32x16 c) {
+    c = mfma32(a.p[2], b, c);
+    c = mfma32(a.p[1], b, c);
+    return mfma32(a.p[0], b, c);
+}
+
+}  // namespace echo

@@ -109,9 +109,8 @@ CASES = [
     ("pre_parts_few_rows_bf16", 4, 3, 137, 24, 68, "bf16", False),
     ("pre_parts_two_rounds_bf16", 2, 70, 190, 24, 1024, "bf16", False),
     ("pre_parts_keys_past_384", 1, 90, 470, 24, 40, "f32", False),
-    # the same without parts: 32 query rows per block, operands through LDS, one to six key tiles per wave (and none, where a sample
-    # is short), value rows of less than a chunk, exactly one, one and a bit, two and a bit; with six tiles, whose chunks are half as
-    # wide, also two and a bit and three and a bit; 16 rows, tiles in groups of five; more than 384 keys
+    # the same without parts: full and short key tiles, value rows of less than a chunk, exactly one, one and a bit, two and a bit, three and a
+    # bit; at most 16 rows
     ("pre_staged_keys_129", 101, 32, 129, 8, 4, "f32", False),
     ("pre_staged_four_tiles", 51, 65, 255, 8, 68, "f32", False),
     ("pre_staged_five_tiles_bf16", 40, 97, 319, 8, 132, "bf16", False),
@@ -122,6 +121,23 @@ CASES = [
     ("pre_rows_of_16_five_tiles", 101, 16, 300, 8, 44, "f32", False),
     ("pre_rows_of_16_five_tiles_bf16", 105, 15, 317, 8, 132, "bf16", False),
     ("pre_rows_of_16_keys_past_384", 60, 50, 390, 8, 44, "f32", False),
+    # pre-kernel on split operands: 17 to 64, 65 to 128 and more keys (up to two key tiles of 32 per wave, and none); rows that are no multiple
+    # of 32 and of the 64 of a dV step, one step and several; value rows of less than a chunk of 32 columns, exactly one, part of a second
+    # one, an odd number of them, more chunks than waves, more columns than a dV block; key panels of 64 with one key in the last; and
+    # the fewest blocks that take it, next to one that does not
+    ("pre_split_17_keys", 130, 17, 17, 8, 4, "f32", False),
+    ("pre_split_64_keys_36_columns", 130, 33, 64, 8, 36, "f32", False),
+    ("pre_split_64_keys_260_columns_bf16", 130, 65, 64, 8, 260, "bf16", False),
+    ("pre_split_33_keys_544_columns", 64, 32, 33, 8, 544, "f32", False),
+    ("pre_not_split_63_blocks", 63, 32, 33, 8, 544, "f32", False),
+    ("pre_split_1060_columns_bf16", 40, 64, 40, 8, 1060, "bf16", False),
+    ("pre_split_65_keys_32_columns", 130, 64, 65, 8, 32, "f32", False),
+    ("pre_split_128_keys_100_columns", 70, 129, 128, 8, 100, "f32", False),
+    ("pre_split_97_keys_96_columns_bf16", 70, 31, 97, 8, 96, "bf16", False),
+    ("pre_split_129_keys_516_columns", 201, 17, 129, 8, 516, "f32", False),
+    ("pre_split_257_keys_36_columns", 50, 70, 257, 8, 36, "f32", False),
+    ("pre_split_512_keys_64_columns_bf16", 51, 64, 512, 8, 64, "bf16", False),
+    ("pre_not_split_513_keys", 51, 64, 513, 8, 64, "f32", False),
     # whole backward in one launch: one tile, remainders of the tiles, one row, one key, three tiles, all sixteen with two per wave,
     # slices of 16 to 64 columns, several pieces of columns of each width, entries that need the exponential of the sum
     ("small_one_tile", 4, 6, 7, 16, 16, "f32", True),

@@ -230,3 +230,94 @@ def test_large_entries_cost_little(case, what):
     withal = best()
     print(f"{1e3 * without:.1f} -> {1e3 * withal:.1f} us", flush=True)
     assert withal <= 2 * without, (without, withal)
+
+
+PRE = [
+    # name, B, Tq, Tk, Dv, dtype: up to 64, 128 and more keys on split operands
+    ("64_keys", 70, 60, 60, 516, "f32"),
+    ("64_keys_bf16", 70, 60, 60, 516, "bf16"),
+    ("128_keys", 40, 100, 100, 516, "f32"),
+    ("300_keys", 20, 300, 300, 260, "f32"),
+]
+
+
+def _backward(B, Tq, Tk, Dv, dt, change=None):
+    """P and the gradients of a batch of full samples; change(dC, V) edits them before the backward pass."""
+    import torch
+    from paper_1805_08899_amd import binding as eb
+    H = 32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17)
+    store = torch.bfloat16 if dt == "bf16" else torch.float32
+    rand = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    q, k, v, V = (x.to(store) for x in (rand(B, Tq, H), rand(B, Tk, H), rand(H), rand(B, Tk, Dv)))
+    dC = rand(B, Tq, Dv)
+    key_len = torch.full((B,), Tk, dtype=torch.int32, device="cuda")
+    out = {n: torch.empty(*s, device="cuda") for n, s in (("C", (B, Tq, Dv)), ("P", (B, Tq, Tk)), ("dQp", (B, Tq, H)), ("dKp", (B, Tk, H)),
+                                                          ("dV", (B, Tk, Dv)), ("dv", (H,)))}
+    desc = eb.make_desc(B, Tq, Tk, H, Dv, dt)
+    ws = torch.empty(max(16, eb.echo_attn_fwd_workspace_bytes(desc), eb.echo_attn_bwd_workspace_bytes(desc)), dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream()
+    eb.check(eb.echo_attn_fwd(desc, q, k, V, v, key_len, out["C"], out["P"], ws, stream=st))
+    if change:
+        change(dC, V)
+    eb.check(eb.echo_attn_bwd(desc, dC, out["P"], q, k, V, v, key_len, out["dQp"], out["dKp"], out["dV"], out["dv"], ws, stream=st))
+    torch.cuda.synchronize()
+    return {n: x.cpu() for n, x in out.items()}, dC.cpu(), V.cpu(), q.cpu(), k.cpu(), v.cpu()
+
+
+@pytest.mark.parametrize("case", PRE, ids=[c[0] for c in PRE])
+def test_error_of_products_of_split_operands(case):
+    """dV = P^T dC and, through dQp, dP = dC V^T as six products of bf16 parts.  dV, a sum of n terms: six roundings of the partial sum per 16
+    terms, each off by U / sqrt(3) of it (root mean square), the partial sums sqrt(1/2) of the result on average: U sqrt(n / 16), twice that
+    allowed; fp32 products without parts, 16 roundings per 16 terms, would be at 1.6.  dQp also has the roundings of the recomputation; 2e-6
+    is what its own tests allow."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    name, B, Tq, Tk, Dv, dt = case
+    print("split operands", case, flush=True)
+    out, dC, V, q, k, v = _backward(B, Tq, Tk, Dv, dt)
+    P, dC, V, q, k, v = (x[:4].double() if x.dim() > 1 else x.double() for x in (out["P"], dC, V, q, k, v))
+    rel = lambda got, ref: float((got.double() - ref).norm() / ref.norm())
+    e_dv = rel(out["dV"][:4], P.transpose(1, 2) @ dC)
+    dP = dC @ V.transpose(1, 2)
+    dS = P * (dP - (P * dP).sum(-1, keepdim=True))
+    dQ = torch.stack([(dS[b, :, :, None] * (1 - torch.tanh(q[b, :, None] + k[b, None]) ** 2)).sum(1) * v for b in range(4)])
+    e_dq = rel(out["dQp"][:4], dQ)
+    print(f"{name}: dV {e_dv:.2e}, dQp {e_dq:.2e}", flush=True)
+    assert e_dv <= 2 * U * (Tq / 16 + 1) ** 0.5, e_dv
+    assert e_dq <= 2e-6, e_dq
+
+
+@pytest.mark.parametrize("case", PRE, ids=[c[0] for c in PRE])
+def test_operands_that_do_not_split(case):
+    """Infinities and the largest finite numbers have no bf16 parts: an infinite dC makes its column of dV infinite, and its row of dQp and
+    the sample's dKp no numbers, as in fp32; the largest finite dC gives the fp32 products; everything else stays what it was."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    name, B, Tq, Tk, Dv, dt = case
+    print("operands that do not split", case, flush=True)
+    plain = _backward(B, Tq, Tk, Dv, dt)[0]
+    top = float(np.finfo(np.float32).max)
+    i, d = Tq - 1, Dv - 3
+
+    def change(dC, V):
+        dC[0, i, d] = float("inf")
+        V[0, :, d] = 1.0                                      # (after the forward pass: only the backward pass sees it)
+        dC[1, i, d] = top
+        V[1, :, d] = 0.0
+
+    out, dC = _backward(B, Tq, Tk, Dv, dt, change)[:2]
+    assert torch.isinf(out["dV"][0, :, d]).all()
+    rest = torch.ones(Dv, dtype=torch.bool)
+    rest[d] = False
+    for b in (0, 1):
+        assert torch.allclose(out["dV"][b][:, rest], plain["dV"][b][:, rest], rtol=0, atol=4e-5)
+    assert torch.isnan(out["dQp"][0, i]).all() and torch.isfinite(out["dQp"][0, :i]).all()
+    assert torch.isnan(out["dKp"][0]).all() and torch.isnan(out["dv"]).all()
+    want = out["P"][1].double().T @ dC[1, :, d].double()
+    assert float(((out["dV"][1, :, d].double() - want) / want).abs().max()) <= 1e-5
+    for n in ("dQp", "dKp"):
+        assert torch.isfinite(out[n][1]).all()
+    for n in ("dQp", "dKp", "dV"):
+        assert torch.equal(out[n][2:], plain[n][2:]), n
