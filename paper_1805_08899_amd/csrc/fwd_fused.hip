@@ -54,7 +54,12 @@ constexpr int FW_XCD = 8;        // blockIdx.x mod 8 selects the XCD
 constexpr int FW_CU_PER_XCD = 32;
 constexpr int FW_KB = 16;        // value rows per batch in the context phase (two batches in flight per wave)
 constexpr int FW_SPREAD_B = 32;        // batches below this may be spread over the XCDs tile by tile
-constexpr int FW_MAX_RANKED_B = 128;   // the in-kernel ranking keeps two lengths per lane
+constexpr int FW_MAX_RANKED_B = 256;   // the in-kernel ranking keeps two or four lengths per lane
+// Past 128 samples the ranking pays where there are more than one round of blocks, so that the last ones should be light ones, and a block is
+// long against what the ranking costs it (about a microsecond): 0.89 of the launch's time over 56 shapes of uneven lengths beyond this
+// line, 1.00 to 1.03 where all lengths are equal; B = 256, T = 60, H = 512 in bf16 63.8 -> 55.2 us.  Below it up to 1.28.
+__host__ constexpr bool fw_ranks_large_batch(long long blocks8, int Tk, int H) { return blocks8 > 700 && (long long)Tk * H >= 15000; }
+constexpr int FW_RANK_BITS = 4;        // leading bits of the lengths that order them
 constexpr int FW_ROW_REGS = 16;  // row mode: 16-byte registers a wave spends on its keys (keys x slices)
 
 // row mode: the longest key share a wave can hold with ns slices of h (1 stands in for streaming mode, ns = 0)
@@ -837,9 +842,58 @@ struct ContextAllRows {
     }
 };
 
+// The sample with r samples before it in the order of valid keys, the most first, ties to the lower index: radix selection over the
+// FW_RANK_BITS leading bits of the lengths, held G per lane, then the r-th of those left by index.  (Four bits balance as well as
+// all of them and the selection is shorter: 0.97 of the launch's time over 150 shapes of up to 128 samples.)  One wave; the sample and its valid
+// keys go to s_pick.
+template <int G>
+__device__ __forceinline__ void fw_rank_select(const int *__restrict__ key_len, int B, int Tk, int r, int *__restrict__ s_pick) {
+    const int lane = lane_id();
+    int len[G];
+    // all counts are requested before any is used (as guarded loads the second left only after the first had
+    // arrived: a second trip to memory for batches of more than 64)
+#pragma unroll
+    for (int g = 0; g < G; ++g) len[g] = key_len[min(lane + 64 * g, B - 1)];
+    unsigned long long act[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        len[g] = clamp_len(len[g], Tk);
+        act[g] = __ballot(lane + 64 * g < B);
+    }
+    const int top = 32 - __builtin_clz((unsigned)Tk), last = max(top - FW_RANK_BITS, 0);         // bits in use
+    bool differs = false;                                      // (all samples equally long: nothing to order)
+#pragma unroll
+    for (int g = 0; g < G; ++g) differs = differs || len[g] != __builtin_amdgcn_readfirstlane(len[0]);
+    for (int bit = __any(differs) ? top - 1 : -1; bit >= last; --bit) {
+        unsigned long long on[G];
+        int cnt = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            on[g] = __ballot(((unsigned)len[g] >> bit) & 1u) & act[g];
+            cnt += __popcll(on[g]);
+        }
+        if (cnt > r) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) act[g] = on[g];
+        } else {
+            r -= cnt;
+#pragma unroll
+            for (int g = 0; g < G; ++g) act[g] &= ~on[g];
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(act[g] >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)act[g], 0u));
+        if (((act[g] >> lane) & 1ull) && before == r) {
+            s_pick[0] = lane + 64 * g;
+            s_pick[1] = len[g];
+        }
+        r -= __popcll(act[g]);
+    }
+}
+
 // Which (sample, row tile) this block works on and the sample's valid keys; see "Placement" at the top.
-// Ranked mode: wave 0 finds the sample that holds a given rank by radix selection over composite keys
-// (valid keys, then index) held two per lane, and hands the answer to the other waves through s_pick.
+// Ranked mode: wave 0 finds the sample that holds a given rank (fw_rank_select) and hands the answer to the other waves through s_pick.
 // Returns false if the block has nothing to do (uniformly for the whole block).
 __device__ __forceinline__ bool fw_pick_item(const int *__restrict__ key_len, int B, int Tk, int tiles, int ranked,
                                              int *s_pick, int &b, int &tile, int &L) {
@@ -871,37 +925,10 @@ __device__ __forceinline__ bool fw_pick_item(const int *__restrict__ key_len, in
     const int m = rho / tiles;             // the tiles of a sample weigh the same
     tile = rho % tiles;
     if (wave_id() == 0) {
-        const int lane = lane_id();
-        const int c0 = lane, c1 = lane + 64;
-        // larger key = more valid keys, ties to the lower index; bits: length above 7 bits of (127 - index)
-        // both counts are requested before either is used (as two guarded loads the second left only after the
-        // first had arrived: a second trip to memory for batches of more than 64)
-        const int len0 = key_len[min(c0, B - 1)], len1 = key_len[min(c1, B - 1)];
-        const unsigned key0 = c0 < B ? ((unsigned)clamp_len(len0, Tk) << 7) | (unsigned)(127 - c0) : 0u;
-        const unsigned key1 = c1 < B ? ((unsigned)clamp_len(len1, Tk) << 7) | (unsigned)(127 - c1) : 0u;
-        unsigned long long act0 = __ballot(c0 < B), act1 = __ballot(c1 < B);
         // keys larger than the wanted one
-        int r = spread ? m : (m / 2) * (2 * FW_XCD) + ((m & 1) ? 2 * FW_XCD - 1 - xcd : xcd);
-        const int top = 7 + 32 - __builtin_clz((unsigned)Tk);                        // bits in use
-        for (int bit = top - 1; bit >= 0; --bit) {
-            const unsigned long long m0 = __ballot((key0 >> bit) & 1u) & act0;
-            const unsigned long long m1 = __ballot((key1 >> bit) & 1u) & act1;
-            const int cnt = __popcll(m0) + __popcll(m1);
-            if (cnt > r) {
-                act0 = m0;
-                act1 = m1;
-            } else {
-                r -= cnt;
-                act0 &= ~m0;
-                act1 &= ~m1;
-            }
-        }
-        // exactly one candidate is left
-        const bool mine = act0 ? ((act0 >> lane) & 1ull) != 0 : ((act1 >> lane) & 1ull) != 0;
-        if (mine) {
-            s_pick[0] = act0 ? c0 : c1;
-            s_pick[1] = (int)((act0 ? key0 : key1) >> 7);
-        }
+        const int r = spread ? m : (m / 2) * (2 * FW_XCD) + ((m & 1) ? 2 * FW_XCD - 1 - xcd : xcd);
+        if (B <= 128) fw_rank_select<2>(key_len, B, Tk, r, s_pick);
+        else fw_rank_select<4>(key_len, B, Tk, r, s_pick);
     }
     lds_barrier();
     b = s_pick[0];
@@ -1237,7 +1264,8 @@ static hipError_t launch_fwd_fused_k(const AttnShape &s, const void *Qp, const v
         const int most = min(s.Tq, 2 * tiles);
         while (tiles < most && (long long)FW_XCD * samples_per_xcd * (tiles + 1) <= 2 * FW_XCD * FW_CU_PER_XCD) ++tiles;
     }
-    const int ranked = s.B <= FW_MAX_RANKED_B ? 1 : 0;
+    const int ranked = s.B <= 128 || (s.B <= FW_MAX_RANKED_B &&
+                                      fw_ranks_large_batch((long long)s.B * ((s.Tq + 7) / 8), s.Tk, s.H)) ? 1 : 0;
     // A small batch spread over all XCDs, tile by tile, once an XCD would get more than a tile per CU: whole samples to XCDs
     // leave XCDs idle or unequal (B = 8 of 100 to 300 keys: 88 -> 66 us; B = 20: 26 -> 23).  The price, every XCD reading
     // every key and value row, grows with the batch; at B = 32 the two are level.

@@ -413,3 +413,27 @@ def test_accumulating_backward(case):
         assert (np.abs(got[k] - (base.astype(np.float64) + alone[k])) <= roundings * 2.0 ** -24 * size + 1e-30).all(), k
     for b, L in enumerate(np.clip(inputs["key_len"], 0, Tk)):
         assert np.array_equal(got["dKp"][b, L:], held["dKp"][b, L:]) and np.array_equal(got["dV"][b, L:], held["dV"][b, L:])
+
+
+@pytest.mark.parametrize("lengths", ["equal", "two", "top_bits_equal", "any"])
+@pytest.mark.parametrize("B", [65, 128, 129, 256])
+def test_forward_order_of_the_samples(B, lengths):
+    """Every sample has to come up once whatever the lengths tie in: all equal, two of them, all with the same leading bits, all different
+    ones; two lengths per lane (up to 128 samples) and four."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import harness
+    Tq, Tk, H = 8 * (705 // B) + 8, 66, 228                    # (more than 700 blocks of eight rows, 66 x 228 > 15000)
+    print("order of the samples", B, lengths, flush=True)
+    wl = Workload(f"order_{B}_{lengths}", B, Tq, Tk, H, 4, "f32", 0.5, 1, Tk, False)
+    inputs = make_inputs(wl, seed=B)
+    rng = np.random.default_rng(B)
+    inputs["key_len"][:] = {"equal": np.full(B, 7), "two": rng.choice([0, Tk], B), "top_bits_equal": rng.integers(64, 67, B),
+                            "any": rng.integers(0, Tk + 1, B)}[lengths]
+    db = harness.DeviceBatch(wl, inputs, guard_bytes=4096)
+    db.poison_outputs()
+    db.fwd()
+    db.bwd()
+    got = db.results()
+    assert db.check_guards() == []
+    assert_parity(got, oracle_outputs(inputs), inputs, "f32", wl.name)
