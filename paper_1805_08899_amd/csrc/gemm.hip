@@ -1234,13 +1234,12 @@ __global__ __launch_bounds__(256) void k_ds_finish(const float *__restrict__ P, 
     if (lane == 0) ds_rowsum[row] = tot;
 }
 
-// k_bwd_pre has one dS block per 32 query rows, which takes all keys and all of d; with at most 100 of them (200 if the rows are
-// wide, so that a block is long) the shorter blocks win what the extra launch costs (4 to 5 us).  Both launches together:
-// B = 1, T = 400, Dv = 512 70 -> 14 us; B = 4, T = 300, Dv = 1024 68 -> 30; B = 16, T = 300, Dv = 512 55 -> 44; B = 20, T = 150,
-// Dv = 300 25 -> 21; level at B = 40, T = 150, Dv = 256.
+// k_bwd_pre has one dS block per 32 query rows, which takes all keys and all of d; with at most 50 of them the shorter blocks win what
+// the extra launch costs (4 to 5 us; B = 1, T = 400, Dv = 512 70 -> 14 us for the pre-kernel as it was on fp32 products).  Backward on split operands
+// against parts, 150 shapes of more than 128 keys: up to 14 blocks 1.17 of the time, to 29 1.12, to 44 1.03, to 59 0.98, to 74 0.96, to 200
+// 0.75 to 0.97.
 bool bwd_pre_in_parts(const AttnShape &s) {
-    return s.Tk > kDsplitMaxTk && s.Dv <= 1024 && s.B <= kMaxSortedB &&
-           (long long)s.B * ((s.Tq + 31) / 32) <= (s.Dv >= 384 ? 200 : 100);
+    return s.Tk > kDsplitMaxTk && s.Dv <= 1024 && s.B <= kMaxSortedB && (long long)s.B * ((s.Tq + 31) / 32) <= 50;
 }
 
 template <typename TV, int ROUNDS>
