@@ -1294,17 +1294,27 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
     // B = 1, T = 53, H = 48: 7.2 against 7.6).
     // An H of three slices takes the form for four, idle lanes included, on grids up to a round of its blocks (B = 20, T = 5 / 4, H =
     // 712: 9.8 -> 7.4 us; 240 shapes of 18 to 32 keys up to 512 blocks: the fastest of all forms, or within 6 % of it, on all).
+    // Many blocks are done sooner in narrow slices and four waves, whose phases four blocks on a CU cover for one another: with two slices
+    // of h from 49 keys on in f32 (over 30 shapes 0.93 of the launch's time, 0.78 to 1.06; B = 134, T = 42 / 62, H = 512 45.4 -> 35.7
+    // us), in bf16, where the row mode has registers to spare, past three rounds of blocks (B = 256, T = 60, H = 512 55.5 -> 52.5; up
+    // to 1500 blocks 1.03); from 33 keys past four rounds, one slice among them (over 48 shapes 0.95; 0.75 to 1.05; with fewer
+    // blocks level, 1.05 to 1.13 where the value rows are wide).  With fewer keys the two are level.
     const int row_ns = fwd_row_mode_slices(s);
     const bool three = s.H > 2 * FW_ST && s.H <= 3 * FW_ST;
-    if (row_ns > 0 && (three ? n8 <= 512 : 5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
+    const bool many = (s.Tk > 32 && s.H > 128 && n8 > 2048) || (s.Tk > 48 && row_ns == 2 && n8 > (s.bf16 ? 1500 : 700));
+    if (row_ns > 0 && !many && (three ? n8 <= 512 : 5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
         switch (row_ns) {
             case 1: return launch_fwd_fused_t<T, 8, 64, 1, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
             case 2: return launch_fwd_fused_t<T, 8, 64, 2, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
             default: return launch_fwd_fused_t<T, 8, 64, 4, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
         }
     }
-    // Streaming mode.  At most two keys per wave leave the lane groups of a narrow slice without keys of their own (B = 74, T = 3 / 4,
-    // H = 660: 9.8 us in them, 9.1 in slices of 256).
+    // Streaming mode.  Few keys on more than a round of blocks: slices of 128 columns in four waves, also where lane groups have hardly a
+    // key each (up to 16 keys against slices of 256 in eight waves, over 66 shapes up to H = 153 0.54 to 0.75 of the time, over 15 of 513
+    // to 768 0.69 to 0.90; B = 277, T = 9 / 11, H = 56 16.1 -> 10.8 us; 17 to 32 keys at 513 to 768 0.94 over 46 shapes).
+    if (n8 >= 512 && (s.Tk <= 16 ? s.H <= 768 : s.Tk <= 32 && three))
+        return launch_fwd_fused_t<T, 8, 32, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+    // At most two keys per wave leave the lane groups of a narrow slice without keys of their own.
     if (s.Tk <= 16) return launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
     // A grid that blocks of eight rows do not fill: blocks of four rows, of eight waves (two blocks on a CU) while there is
     // hardly more than one for a CU, else of four waves (four blocks on a CU, 1024 at a time), up to about a round of them at H <= 512.
@@ -1335,14 +1345,15 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
     // Full grids: blocks of four waves, four of them on a CU (9 % faster than eight-wave blocks at B = 128, T = 100, H = 512).
     // Slices of 128 columns, two lane groups: a pass takes eight keys, and its reduction and addressing are shared by twice as
     // many (81 -> 77 us at that shape); slices of 64 where H fills them better (B = 23, T = 217 / 286, H = 40: 79 -> 35 us) and
-    // up to 128 columns in any case (B = 253, T = 197 / 260, H = 112: 240 -> 228; B = 66, T = 140, H = 124 in bf16: 59 -> 55).
+    // up to 128 columns from 33 keys on in any case (B = 253, T = 197 / 260, H = 112: 240 -> 228; B = 66, T = 140, H = 124 in bf16: 59 ->
+    // 55; with 17 to 32 keys 1.05 of the time over 16 shapes of 65 to 128 columns).
     // They hold beyond H = 512 as long as four row tiles fit a CU's LDS (H <= 768) or slices of 256 waste lanes (H = 516, B = 103, T =
     // 123 / 90: 105 -> 85; H = 884, B = 113, T = 106 in bf16: 162 -> 147; H = 760, B = 139, T = 82 / 128: 139 -> 130); where they
     // waste none, the eight-wave block, two per CU, keeps more waves resident (H = 1024, B = 32, T = 300: 301 against 307; in bf16
     // at B = 128, T = 50 42 against 45) and balances better on less than two rounds (B = 28, T = 134, H = 672: 47 against 58), in bf16 than three (B = 77, T = 94 / 81, H =
     // 752, 924 blocks: 52.6 against 54.0).
     if (s.H <= 512 || wide_wastes || (s.H <= 768 && n8 >= (s.bf16 ? 1600 : 850))) {
-        if (s.H <= 128 || 12 * p16 <= 11 * p32) return launch_fwd_fused_t<T, 8, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
+        if (s.H <= (s.Tk <= 32 ? 64 : 128) || 12 * p16 <= 11 * p32) return launch_fwd_fused_t<T, 8, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
         return launch_fwd_fused_t<T, 8, 32, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
     }
     return launch_fwd_fused_t<T, 8, 64, 0, 8>(s, Qp, Kp, V, v, key_len, C, P, st);

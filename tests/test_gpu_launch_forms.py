@@ -63,6 +63,16 @@ CASES = [
     ("forward_full_slices_of_128", 140, 29, 66, 243, 4, "f32", True),
     ("forward_full_slices_of_128_bf16", 140, 31, 70, 241, 4, "bf16", False),
     ("forward_full_slices_of_256", 50, 53, 40, 1001, 4, "f32", True),
+    # few keys on more than a round of blocks: one key, as many as lane groups, past 16 with three slices of h and with up to 128 columns;
+    # many blocks with the keys of the row mode
+    ("forward_few_keys_many_blocks", 300, 9, 1, 33, 4, "f32", False),
+    ("forward_few_keys_many_blocks_16", 256, 15, 16, 130, 68, "f32", True),
+    ("forward_few_keys_many_blocks_bf16", 180, 23, 9, 645, 8, "bf16", False),
+    ("forward_17_keys_many_blocks_wide_h", 256, 11, 17, 600, 36, "f32", True),
+    ("forward_32_keys_many_blocks", 200, 46, 32, 127, 4, "f32", True),
+    ("forward_33_keys_past_four_rounds", 230, 66, 33, 129, 12, "f32", True),
+    ("forward_49_keys_many_blocks", 120, 47, 49, 258, 132, "f32", True),
+    ("forward_49_keys_many_blocks_bf16", 190, 57, 64, 300, 260, "bf16", False),
     # beyond H = 512: four rows in eight waves at their last grid, four rows in four waves next to it on short key axes, then eight
     # rows in eight waves, and four rows in four waves again where slices of 256 columns waste lanes
     ("forward_wide_four_rows_eight_waves", 36, 61, 70, 530, 4, "f32", True),
