@@ -120,7 +120,7 @@ struct KeyStream {
     int H, lane4, grp, k_lo, npass, NS;
     int base, extra;                    // pass p has base + (p < extra) keys
     int p_f, s_f;                       // slice that the next fetch will load
-    float4 cur[FW_NJ];
+    RawKey<T> cur[FW_NJ];
 
     __device__ __forceinline__ void init(const T *kb_, int H_, int lane, int k_lo_, int nk, int NS_) {
         kb = kb_;
@@ -158,9 +158,9 @@ struct KeyStream {
             if constexpr (KG == 1) {
                 // row address from scalars, column from the lane: the load takes them as base and offset
                 const T *row = kb + (size_t)(unsigned)(min(j0 + c, j1 - 1) * H);
-                cur[c] = ld4_any(row, (size_t)hc);
+                cur[c].load(row, (size_t)hc);
             } else {
-                cur[c] = ld4_any(kb, (size_t)((unsigned)(min(j0 + c * KG + grp, j1 - 1) * H) + hc));
+                cur[c].load(kb, (size_t)((unsigned)(min(j0 + c * KG + grp, j1 - 1) * H) + hc));
             }
         }
         const bool wrap = s_f + 1 == NS;
@@ -213,8 +213,10 @@ __device__ __forceinline__ bool fw_pass(const float *__restrict__ s_e, const flo
         if constexpr (RT == 8) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int c = 0; c < NJ; ++c) {
+            ks.cur[c].pin();
+            const float4 kx = ks.cur[c].get();
 #pragma unroll
-            for (int q = 0; q < 4; ++q) fk[q][c] = fast_exp2(kTwoLog2e * comp(ks.cur[c], q));
+            for (int q = 0; q < 4; ++q) fk[q][c] = fast_exp2(kTwoLog2e * comp(kx, q));
             kmax = fmaxf(fmaxf(kmax, fk[0][c]), fmaxf(fk[1][c], fmaxf(fk[2][c], fk[3][c])));
         }
         ks.advance();
