@@ -48,38 +48,60 @@ __device__ __forceinline__ void mail_put(MailSlot *s, float x, unsigned long lon
     store_agent(&s->w0, ((epoch & 0xffffffffull) << 32) | bits);
     store_agent(&s->w1, ((((epoch >> 32) ^ kMailSalt) & 0xffffffffull) << 32) | bits);
 }
-__device__ __forceinline__ bool mail_try(const MailSlot *s, unsigned long long epoch, float &x) {
-    const unsigned long long a = load_agent(&s->w0), b = load_agent(&s->w1);
-    x = __uint_as_float((unsigned)a);
-    return (a >> 32) == (epoch & 0xffffffffull) && (b >> 32) == (((epoch >> 32) ^ kMailSalt) & 0xffffffffull) &&
-           (unsigned)a == (unsigned)b;
+__device__ __forceinline__ MailSlot mail_load(const MailSlot *s) { return {load_agent(&s->w0), load_agent(&s->w1)}; }
+__device__ __forceinline__ bool mail_valid(const MailSlot &m, unsigned long long epoch) {
+    return (m.w0 >> 32) == (epoch & 0xffffffffull) && (m.w1 >> 32) == (((epoch >> 32) ^ kMailSalt) & 0xffffffffull) &&
+           (unsigned)m.w0 == (unsigned)m.w1;
 }
 
 __device__ __forceinline__ float comp4s(const float4 &x, int c) { return c == 0 ? x.x : c == 1 ? x.y : c == 2 ? x.z : x.w; }
 
-// On entry s_val holds this part's values at its keys (j < L, j % 4 == part); on return it holds the values of all
-// keys below L.  mail_b: the sample's boxes [SP_PARTS receivers][SP_KEYS].  Called by every thread of the block;
-// returns false if a value did not arrive in time.
-__device__ __forceinline__ bool exchange_over_parts(float *s_val, int *s_ok, MailSlot *mail_b, int part, int L,
-                                                    unsigned long long epoch, int lane, int w) {
-    lds_barrier();
-    if (w == 0) {
-        {   // lane = 16 r + i: key part + 4 i to receiver r
+// The value of key j (j % 4 == part), the same in all lanes of the wave that formed it, into the block's own row of values and, DIRECT,
+// straight to the other parts.  In the forward step, where a value ends in a long chain of its own, the first ones are then on their way
+// while later ones are still being formed (5.0 -> 4.8 us at 64 samples of 50 keys, H = Dv = 512); in the backward step the values
+// of all waves are there at once, and one wave sends them together (sent one by one they made the step 0.25 us longer from 32
+// samples on).
+template <bool DIRECT>
+__device__ __forceinline__ void exchange_value(float x, float *s_val, MailSlot *mail_b, int part, int j, unsigned long long epoch,
+                                               int lane) {
+    if (DIRECT && lane < SP_PARTS && lane != part) mail_put(&mail_b[lane * SP_KEYS + j], x, epoch);
+    if (lane == part) s_val[j] = x;
+}
+
+// On entry every value of this part has gone through exchange_value(); on return s_val holds the values of all keys below L.  mail_b:
+// the sample's boxes [SP_PARTS receivers][SP_KEYS].  Called by every thread of the block; returns false if a value did not
+// arrive in time.  One wave asks for the other parts' values (DIRECT: the one that has the fewest keys).  A request takes most of
+// a microsecond, so two are under way, half a trip apart (0.1 us of a step against asking again once an answer is there).
+template <bool DIRECT>
+__device__ __forceinline__ bool exchange_take(float *s_val, int *s_ok, MailSlot *mail_b, int part, int L, unsigned long long epoch,
+                                              int lane, int w) {
+    if (!DIRECT) lds_barrier();
+    if (w == (DIRECT ? SP_W - 1 : 0)) {
+        if (!DIRECT) {   // lane = 16 r + i: key part + 4 i to receiver r
             const int i = lane & 15, r = lane >> 4, j = part + SP_PARTS * i;
             if (r != part && j < L) mail_put(&mail_b[r * SP_KEYS + j], s_val[j], epoch);
         }
-        bool ok = true;
-        if (lane < L && (lane & (SP_PARTS - 1)) != part) {
-            MailSlot *s = &mail_b[part * SP_KEYS + lane];
-            const long long t0 = wall_clock64();
-            float x;
-            while (!mail_try(s, epoch, x)) {
-                __builtin_amdgcn_s_sleep(1);
-                if (wall_clock64() - t0 > kSpinLimitTicks) {
-                    ok = false;
-                    break;
-                }
+        MailSlot *s = &mail_b[part * SP_KEYS + lane];
+        const bool wanted = lane < L && (lane & (SP_PARTS - 1)) != part;
+        bool ok = !wanted;
+        float x = 0.f;
+        const long long t0 = wall_clock64();
+        auto done = [&](const MailSlot &m) {                     // nothing left to wait for, or out of time
+            if (!ok && mail_valid(m, epoch)) {
+                x = __uint_as_float((unsigned)m.w0);
+                ok = true;
             }
+            return __all(ok) || wall_clock64() - t0 > kSpinLimitTicks;
+        };
+        MailSlot m0 = mail_load(s), m1;                          // (two variables in fixed roles: a copy would wait for its load)
+        __builtin_amdgcn_s_sleep(12);                            // 768 clocks
+        for (;;) {
+            m1 = mail_load(s);
+            if (done(m0)) break;
+            m0 = mail_load(s);
+            if (done(m1)) break;
+        }
+        if (wanted) {
             s_val[lane] = x;
             store_agent(&s->w0, 0ull);
             store_agent(&s->w1, 0ull);
@@ -111,17 +133,17 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_fwd_split(
     const T *Kb = Kp + (size_t)b * Tk * H;
     const T *Vb = V + (size_t)b * Tk * Dv;
 
+    MailSlot *mail_b = mail + (size_t)b * SP_PARTS * SP_KEYS;
+
     // ---- every request of the step before the first result is awaited
     const int len_raw = key_len[b];
-    float4 q4[SP_CH], v4[SP_CH], k4[SP_CH][SP_KU];
+    RawKey<T> q4[SP_CH], v4[SP_CH], k4[SP_CH][SP_KU];             // as loaded until all requests are out (RawKey)
 #pragma unroll
     for (int c = 0; c < SP_CH; ++c) {
         if (256 * c < H) {                                        // block-uniform
-            const int h = 256 * c + 4 * lane;
-            const int hc = min(h, H - 4);
-            q4[c] = ld4(qb, (size_t)hc);
-            v4[c] = ld4(v, (size_t)hc);
-            if (h >= H) v4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+            const int hc = min(256 * c + 4 * lane, H - 4);
+            q4[c].load(qb, (size_t)hc);
+            v4[c].load(v, (size_t)hc);
         }
     }
     const int g = w >> 1;                                         // threadIdx.x / SP_COLS, the same in the whole wave
@@ -137,20 +159,32 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_fwd_split(
 #pragma unroll
             for (int u = 0; u < SP_KU; ++u) {
                 const int j = part + SP_PARTS * (w + SP_W * u);
-                if (j < L) k4[c][u] = ld4(Kb, (size_t)j * H + hc);   // wave-uniform: rows of masked keys stay in memory
+                if (j < L) k4[c][u].load(Kb, (size_t)j * H + hc);    // wave-uniform: rows of masked keys stay in memory
             }
         }
     }
-    float vrow[SP_ROWS];
+    typename RawElem<T>::type vrow[SP_ROWS];
 #pragma unroll
     for (int m = 0; m < SP_ROWS; ++m)
-        if (g + SP_GROUPS * m < L) vrow[m] = ld(Vb, (size_t)(g + SP_GROUPS * m) * Dv + d_cl);
+        if (g + SP_GROUPS * m < L) vrow[m] = RawElem<T>::load(Vb, (size_t)(g + SP_GROUPS * m) * Dv + d_cl);
     if (L == 0) {                                                 // no valid key (all four parts see that): zeros
         if (g == 0 && d_valid) store_streaming(&C[(size_t)b * Dv + d], 0.f);
         if (part == 0 && w == 1 && lane < Tk) store_streaming(&P[(size_t)b * Tk + lane], 0.f);
         return;
     }
 
+    // (The values are used from here on.  bf16: widened at their loads, inside the guarded branches, every row had been awaited before the
+    // next one was requested: 6.1 -> 4.95 us at 64 samples of 50 keys, H = Dv = 512, backward 5.7 -> 4.7.)
+    float4 qv[SP_CH], vv[SP_CH];
+#pragma unroll
+    for (int c = 0; c < SP_CH; ++c) {
+        if (256 * c < H) {
+            q4[c].pin();
+            v4[c].pin();
+            qv[c] = q4[c].get();
+            vv[c] = 256 * c + 4 * lane < H ? v4[c].get() : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
     // ---- scores of this part's keys: S[j] = sum_h v[h] tanh(q[h] + k[j,h]),  tanh = 1 - 2 / (exp(2 (q + k)) + 1)
 #pragma unroll
     for (int u = 0; u < SP_KU; ++u) {
@@ -160,18 +194,20 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_fwd_split(
 #pragma unroll
             for (int c = 0; c < SP_CH; ++c) {
                 if (256 * c < H) {
+                    k4[c][u].pin();
+                    const float4 kv = k4[c][u].get();
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float x = kTwoLog2e * (comp4s(q4[c], e) + comp4s(k4[c][u], e));
-                        acc += comp4s(v4[c], e) * __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f);
+                        const float x = kTwoLog2e * (comp4s(qv[c], e) + comp4s(kv, e));
+                        acc += comp4s(vv[c], e) * __builtin_fmaf(-2.f, fast_rcp(fast_exp2(x) + 1.0f), 1.0f);
                     }
                 }
             }
             const float tot = wave_sum(acc);
-            if (lane == 0) s_s[j] = tot;
+            exchange_value<true>(tot, s_s, mail_b, part, j, epoch, lane);
         }
     }
-    const bool ok = exchange_over_parts(s_s, &s_ok, mail + (size_t)b * SP_PARTS * SP_KEYS, part, L, epoch, lane, w);
+    const bool ok = exchange_take<true>(s_s, &s_ok, mail_b, part, L, epoch, lane, w);
 
     // ---- softmax over the valid keys, one key per lane, the same in every wave
     const float sc = lane < L ? s_s[lane] : -INFINITY;
@@ -182,10 +218,16 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_fwd_split(
 
     // ---- context at this part's columns: the four row groups add their rows, then the groups are added
     float acc = 0.f;
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int m = 0; m < SP_ROWS; ++m) asm volatile("" : "+v"(vrow[m]));
+    }
 #pragma unroll
     for (int m = 0; m < SP_ROWS; ++m) {
         const int j = g + SP_GROUPS * m;
-        if (j < L) acc = __builtin_fmaf(lane_value(p, j), vrow[m], acc);
+        if (j < L) {
+            acc = __builtin_fmaf(lane_value(p, j), RawElem<T>::value(vrow[m]), acc);
+        }
     }
     s_c[g][cc] = acc;
     lds_barrier();
@@ -217,17 +259,18 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_bwd_query_split(
     const T *Vb = V + (size_t)b * Tk * Dv;
     const T *Kb = Kp + (size_t)b * Tk * H;
 
+    MailSlot *mail_b = mail + (size_t)b * SP_PARTS * SP_KEYS;
+
     // ---- every request of the step
     const int len_raw = key_len[b];
     const float p_raw = lane < Tk ? P[(size_t)b * Tk + lane] : 0.f;
-    float4 c4[SP_CH], x4[SP_CH][SP_KU];
+    RawKey<float> c4[SP_CH];
+    RawKey<T> x4[SP_CH][SP_KU];
 #pragma unroll
     for (int c = 0; c < SP_CH; ++c) {
         if (256 * c < Dv) {                                       // block-uniform
-            const int d = 256 * c + 4 * lane;
-            const int dc = min(d, Dv - 4);
-            c4[c] = ld4(dCb, (size_t)dc);
-            if (d >= Dv) c4[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+            const int dc = min(256 * c + 4 * lane, Dv - 4);
+            c4[c].load(dCb, (size_t)dc);
         }
     }
     const int g = w >> 1;
@@ -235,8 +278,7 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_bwd_query_split(
     const int h = part * hw + cc;
     const bool h_valid = cc < hw && h < H;
     const int h_cl = min(h, H - 1);
-    const float sq = kTwoLog2e * ld(Qp, (size_t)b * H + h_cl);
-    const float v4 = 4.f * ld(v, (size_t)h_cl);
+    typename RawElem<T>::type q_raw = RawElem<T>::load(Qp, (size_t)b * H + h_cl), v_raw = RawElem<T>::load(v, (size_t)h_cl);
     const int L = clamp_len(len_raw, Tk);
 #pragma unroll
     for (int c = 0; c < SP_CH; ++c) {
@@ -245,14 +287,14 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_bwd_query_split(
 #pragma unroll
             for (int u = 0; u < SP_KU; ++u) {
                 const int j = part + SP_PARTS * (w + SP_W * u);
-                if (j < L) x4[c][u] = ld4(Vb, (size_t)j * Dv + dc);   // wave-uniform: rows of masked keys stay in memory
+                if (j < L) x4[c][u].load(Vb, (size_t)j * Dv + dc);    // wave-uniform: rows of masked keys stay in memory
             }
         }
     }
-    float krow[SP_ROWS];
+    typename RawElem<T>::type krow[SP_ROWS];
 #pragma unroll
     for (int m = 0; m < SP_ROWS; ++m)
-        if (g + SP_GROUPS * m < L) krow[m] = ld(Kb, (size_t)(g + SP_GROUPS * m) * H + h_cl);
+        if (g + SP_GROUPS * m < L) krow[m] = RawElem<T>::load(Kb, (size_t)(g + SP_GROUPS * m) * H + h_cl);
     float *ds_dst = ds_out + ((size_t)b * ds_rows + ds_row) * ds_pitch;
     if (L == 0) {                             // no valid key: the query gets no gradient, the stored row is zero
         if (g == 0 && h_valid) store_streaming(&dQp[(size_t)b * H + h], 0.f);
@@ -263,6 +305,14 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_bwd_query_split(
         return;
     }
 
+    float4 cv[SP_CH];                         // (the loaded values are used from here on)
+#pragma unroll
+    for (int c = 0; c < SP_CH; ++c) {
+        if (256 * c < Dv) {
+            c4[c].pin();
+            cv[c] = 256 * c + 4 * lane < Dv ? c4[c].get() : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
     // ---- dP[j] = sum_d dC[d] V[j,d] at this part's keys
 #pragma unroll
     for (int u = 0; u < SP_KU; ++u) {
@@ -271,13 +321,16 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_bwd_query_split(
             float acc = 0.f;
 #pragma unroll
             for (int c = 0; c < SP_CH; ++c)
-                if (256 * c < Dv)
-                    acc += (c4[c].x * x4[c][u].x + c4[c].y * x4[c][u].y) + (c4[c].z * x4[c][u].z + c4[c].w * x4[c][u].w);
+                if (256 * c < Dv) {
+                    x4[c][u].pin();
+                    const float4 x = x4[c][u].get();
+                    acc += (cv[c].x * x.x + cv[c].y * x.y) + (cv[c].z * x.z + cv[c].w * x.w);
+                }
             const float tot = wave_sum(acc);
-            if (lane == 0) s_dp[j] = tot;
+            exchange_value<false>(tot, s_dp, mail_b, part, j, epoch, lane);
         }
     }
-    const bool ok = exchange_over_parts(s_dp, &s_ok, mail + (size_t)b * SP_PARTS * SP_KEYS, part, L, epoch, lane, w);
+    const bool ok = exchange_take<false>(s_dp, &s_ok, mail_b, part, L, epoch, lane, w);
 
     // ---- dS = P (dP - sum_j P dP), one key per lane, the same in every wave
     const float pj = lane < L ? p_raw : 0.f;
@@ -288,12 +341,19 @@ __global__ __launch_bounds__(SP_THREADS) void k_step_bwd_query_split(
 
     // ---- recomputation at (this group's keys, this thread's h):  r' = 1 / (exp(2 (q + k)) + 1),
     //      1 - t^2 = 4 r' (1 - r');  dQp[h] = v[h] sum_j dS[j] (1 - t^2)
+    if constexpr (sizeof(T) == 2) asm volatile("" : "+v"(q_raw), "+v"(v_raw));
+    const float sq = kTwoLog2e * RawElem<T>::value(q_raw);
+    const float v4 = 4.f * RawElem<T>::value(v_raw);
     float accQ = 0.f;
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int m = 0; m < SP_ROWS; ++m) asm volatile("" : "+v"(krow[m]));
+    }
 #pragma unroll
     for (int m = 0; m < SP_ROWS; ++m) {
         const int j = g + SP_GROUPS * m;
         if (j < L) {
-            const float rr = fast_rcp(fast_exp2(__builtin_fmaf(kTwoLog2e, krow[m], sq)) + 1.0f);
+            const float rr = fast_rcp(fast_exp2(__builtin_fmaf(kTwoLog2e, RawElem<T>::value(krow[m]), sq)) + 1.0f);
             accQ = __builtin_fmaf(lane_value(ds, j), __builtin_fmaf(-rr, rr, rr), accQ);
         }
     }
