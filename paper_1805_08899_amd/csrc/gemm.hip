@@ -1289,7 +1289,13 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // 2048 19.4 against 13).
     const bool few_dv = !with_ds && s.Tk <= 64 && (long long)s.B * ((s.Dv + 63) / 64) <= 1024;
     const bool small = s.Tk <= 128 && (s.Tq <= 16 || s.Tk <= 16 || (with_ds && !s.bf16 && blocks32 < 64) || few_dv);
-    const int kw = !fits || small ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
+    // f32, 65 to 128 keys, value rows that fill the four waves' 128 columns of the fp32 form: there the launch itself gains least (B = 128, T =
+    // 100, Dv = 512 35.3 -> 29.9 us), and the dense bf16 products cost the launches around it more on cards that answer them with
+    // a lower shader clock: forward and backward 182.5 -> 176.0 us on one card, 184 -> 185 on a second, 185 -> 200 on a third, whose forward
+    // launch, the same code, goes from 65 to 75 us beside them.  On that third card 140 other shapes of f32 took 0.96 of the time in the
+    // split form, Dv from 513 on 0.95.
+    const bool dense = with_ds && !s.bf16 && s.Tk > 64 && s.Tk <= 128 && s.Dv > 384 && s.Dv <= 512 && blocks32 >= 128;
+    const int kw = !fits || small || dense ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
     const int s_rows = kw ? 32 : 16;
     const int s_tiles = with_ds ? (s.Tq + s_rows - 1) / s_rows : 0;
     const int v_groups = dv_col_groups(kw, s.Tk, s.Dv) * dv_key_groups(kw, s.Tk);
