@@ -59,7 +59,10 @@ constexpr int FW_MAX_RANKED_B = 256;   // the in-kernel ranking keeps two or fou
 // long against what the ranking costs it (about a microsecond): 0.89 of the launch's time over 56 shapes of uneven lengths beyond this
 // line, 1.00 to 1.03 where all lengths are equal; B = 256, T = 60, H = 512 in bf16 63.8 -> 55.2 us.  Below it up to 1.28.
 __host__ constexpr bool fw_ranks_large_batch(long long blocks8, int Tk, int H) { return blocks8 > 700 && (long long)Tk * H >= 15000; }
-constexpr int FW_RANK_BITS = 4;        // leading bits of the lengths that order them
+// Leading bits of the lengths that order the samples.  The selection is in front of everything a block does: four bits took 0.97 of the
+// launch's time of all of them over 150 shapes of up to 128 samples, but up to 2 % more where a block is long, which five give back (B = 128,
+// T = 100, H = 512 62.3 -> 61.0 us, B = 32, T = 300, H = 1024 263.9 -> 260.1; in short blocks five take 0.3 % more than four).
+__device__ constexpr int fw_rank_bits(int Tk, int H) { return Tk * H >= 30000 ? 5 : 4; }
 constexpr int FW_ROW_REGS = 16;  // row mode: 16-byte registers a wave spends on its keys (keys x slices)
 
 // row mode: the longest key share a wave can hold with ns slices of h (1 stands in for streaming mode, ns = 0)
@@ -845,11 +848,10 @@ struct ContextAllRows {
 };
 
 // The sample with r samples before it in the order of valid keys, the most first, ties to the lower index: radix selection over the
-// FW_RANK_BITS leading bits of the lengths, held G per lane, then the r-th of those left by index.  (Four bits balance as well as
-// all of them and the selection is shorter: 0.97 of the launch's time over 150 shapes of up to 128 samples.)  One wave; the sample and its valid
-// keys go to s_pick.
+// `bits` leading bits of the lengths, held G per lane, then the r-th of those left by index.  One wave; the sample and its valid keys go to
+// s_pick.
 template <int G>
-__device__ __forceinline__ void fw_rank_select(const int *__restrict__ key_len, int B, int Tk, int r, int *__restrict__ s_pick) {
+__device__ __forceinline__ void fw_rank_select(const int *__restrict__ key_len, int B, int Tk, int bits, int r, int *__restrict__ s_pick) {
     const int lane = lane_id();
     int len[G];
     // all counts are requested before any is used (as guarded loads the second left only after the first had
@@ -862,7 +864,7 @@ __device__ __forceinline__ void fw_rank_select(const int *__restrict__ key_len, 
         len[g] = clamp_len(len[g], Tk);
         act[g] = __ballot(lane + 64 * g < B);
     }
-    const int top = 32 - __builtin_clz((unsigned)Tk), last = max(top - FW_RANK_BITS, 0);         // bits in use
+    const int top = 32 - __builtin_clz((unsigned)Tk), last = max(top - bits, 0);         // bits in use
     bool differs = false;                                      // (all samples equally long: nothing to order)
 #pragma unroll
     for (int g = 0; g < G; ++g) differs = differs || len[g] != __builtin_amdgcn_readfirstlane(len[0]);
@@ -897,7 +899,7 @@ __device__ __forceinline__ void fw_rank_select(const int *__restrict__ key_len, 
 // Which (sample, row tile) this block works on and the sample's valid keys; see "Placement" at the top.
 // Ranked mode: wave 0 finds the sample that holds a given rank (fw_rank_select) and hands the answer to the other waves through s_pick.
 // Returns false if the block has nothing to do (uniformly for the whole block).
-__device__ __forceinline__ bool fw_pick_item(const int *__restrict__ key_len, int B, int Tk, int tiles, int ranked,
+__device__ __forceinline__ bool fw_pick_item(const int *__restrict__ key_len, int B, int Tk, int H, int tiles, int ranked,
                                              int *s_pick, int &b, int &tile, int &L) {
     const int xcd = blockIdx.x % FW_XCD, li = blockIdx.x / FW_XCD;
     if (!ranked) {                         // samples x, x+8, ... on XCD x, in index order
@@ -929,8 +931,8 @@ __device__ __forceinline__ bool fw_pick_item(const int *__restrict__ key_len, in
     if (wave_id() == 0) {
         // keys larger than the wanted one
         const int r = spread ? m : (m / 2) * (2 * FW_XCD) + ((m & 1) ? 2 * FW_XCD - 1 - xcd : xcd);
-        if (B <= 128) fw_rank_select<2>(key_len, B, Tk, r, s_pick);
-        else fw_rank_select<4>(key_len, B, Tk, r, s_pick);
+        if (B <= 128) fw_rank_select<2>(key_len, B, Tk, fw_rank_bits(Tk, H), r, s_pick);
+        else fw_rank_select<4>(key_len, B, Tk, fw_rank_bits(Tk, H), r, s_pick);
     }
     lds_barrier();
     b = s_pick[0];
@@ -989,7 +991,7 @@ __global__ __launch_bounds__(64 * W, 4) void k_fwd_fused(
 
     __shared__ int s_pick[2];
     int b, tile, L;
-    if (!fw_pick_item(key_len, B, Tk, tiles, ranked, s_pick, b, tile, L)) return;
+    if (!fw_pick_item(key_len, B, Tk, H, tiles, ranked, s_pick, b, tile, L)) return;
     if (w == 0) load_v(st_col);
     b = __builtin_amdgcn_readfirstlane(b);
     tile = __builtin_amdgcn_readfirstlane(tile);
