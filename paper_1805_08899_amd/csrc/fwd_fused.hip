@@ -1299,13 +1299,13 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
     // An H of three slices takes the form for four, idle lanes included, on grids up to a round of its blocks (B = 20, T = 5 / 4, H =
     // 712: 9.8 -> 7.4 us; 240 shapes of 18 to 32 keys up to 512 blocks: the fastest of all forms, or within 6 % of it, on all).
     // Many blocks are done sooner in narrow slices and four waves, whose phases four blocks on a CU cover for one another: with two slices
-    // of h from 49 keys on in f32 (over 30 shapes 0.93 of the launch's time, 0.78 to 1.06; B = 134, T = 42 / 62, H = 512 45.4 -> 35.7
-    // us), in bf16, where the row mode has registers to spare, past three rounds of blocks (B = 256, T = 60, H = 512 55.5 -> 52.5; up
-    // to 1500 blocks 1.03); from 33 keys past four rounds, one slice among them (over 48 shapes 0.95; 0.75 to 1.05; with fewer
-    // blocks level, 1.05 to 1.13 where the value rows are wide).  With fewer keys the two are level.
+    // of h from 49 keys on (over 30 shapes in f32 0.93 of the launch's time, 0.78 to 1.06; over 70 in bf16 0.95, 0.83 to 1.04; B = 134, T =
+    // 42 / 62, H = 512 45.4 -> 35.7 us; B = 256, T = 60, H = 512 in bf16 55.5 -> 50.2); from 33 keys past four rounds, one slice among
+    // them (over 48 shapes 0.95; 0.75 to 1.05; with fewer blocks level, 1.05 to 1.13 where the value rows are wide).  With fewer
+    // keys the two are level.
     const int row_ns = fwd_row_mode_slices(s);
     const bool three = s.H > 2 * FW_ST && s.H <= 3 * FW_ST;
-    const bool many = (s.Tk > 32 && s.H > 128 && n8 > 2048) || (s.Tk > 48 && row_ns == 2 && n8 > (s.bf16 ? 1500 : 700));
+    const bool many = (s.Tk > 32 && s.H > 128 && n8 > 2048) || (s.Tk > 48 && row_ns == 2 && n8 > 700);
     if (row_ns > 0 && !many && (three ? n8 <= 512 : 5 * s.H >= 3 * FW_ST * row_ns || n8 < 512)) {
         switch (row_ns) {
             case 1: return launch_fwd_fused_t<T, 8, 64, 1, 8>(s, Qp, Kp, V, v, key_len, C, P, st);
@@ -1354,9 +1354,9 @@ static hipError_t launch_fwd_fused_mode(const AttnShape &s, const void *Qp, cons
     // They hold beyond H = 512 as long as four row tiles fit a CU's LDS (H <= 768) or slices of 256 waste lanes (H = 516, B = 103, T =
     // 123 / 90: 105 -> 85; H = 884, B = 113, T = 106 in bf16: 162 -> 147; H = 760, B = 139, T = 82 / 128: 139 -> 130); where they
     // waste none, the eight-wave block, two per CU, keeps more waves resident (H = 1024, B = 32, T = 300: 301 against 307; in bf16
-    // at B = 128, T = 50 42 against 45) and balances better on less than two rounds (B = 28, T = 134, H = 672: 47 against 58), in bf16 than three (B = 77, T = 94 / 81, H =
-    // 752, 924 blocks: 52.6 against 54.0).
-    if (s.H <= 512 || wide_wastes || (s.H <= 768 && n8 >= (s.bf16 ? 1600 : 850))) {
+    // at B = 128, T = 50 42 against 45) and balances better on less than two rounds (B = 28, T = 134, H = 672: 47 against 58), in bf16 up to 1000
+    // blocks (B = 64, T = 114 / 133, H = 656, 960 blocks: 72.7 against 77.8; B = 210, T = 35 / 38, H = 712, 1050 blocks: 38.1 against 32.5).
+    if (s.H <= 512 || wide_wastes || (s.H <= 768 && n8 >= (s.bf16 ? 1000 : 850))) {
         if (s.H <= (s.Tk <= 32 ? 64 : 128) || 12 * p16 <= 11 * p32) return launch_fwd_fused_t<T, 8, 16, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
         return launch_fwd_fused_t<T, 8, 32, 0, 4>(s, Qp, Kp, V, v, key_len, C, P, st);
     }
