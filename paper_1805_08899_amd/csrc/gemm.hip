@@ -874,7 +874,8 @@ __device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC,
     for (int k = 0; k < 2; ++k)
         if (k < mine)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) plane[mfma32_row(r, lane) * dp_pitch + (kw + KW * k) * 32 + n] = acc[k][r];
+            for (int r = 0; r < 16; ++r)
+                plane[mfma32_row(r, lane) * dp_pitch + (kw + KW * k) * 32 + n] = acc[k][r] * split_back<TV>;
     lds_barrier();
     split_finish<DW, NP>(pr, dS, ds_rowsum, s_mem, b, i0, Tq, L, pitch, dp_pitch);
 }
@@ -905,6 +906,7 @@ __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, cons
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
     const int live = min((L - j0 + 31) / 32, NT);                            // key tiles that hold a valid key (block-uniform)
     const unsigned b_col = (unsigned)min(col, Dv - 1);
+    float back = split_back<float>;
     if (live > 0) {
         const int n_st = (Tq + ROWS - 1) / ROWS;
         // staging: rows 8 w .. + 7 of the step; key `lane` of the panel
@@ -976,6 +978,7 @@ __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, cons
                     odd = __builtin_fmaf(j0 + 32 * t + mfma32_row(r, lane) < L ? acc[t][r] : 0.f, 0.f, odd);
             }
         if (__any(odd != 0.f)) {
+            back = 1.f;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 if (t >= live) continue;
@@ -1003,7 +1006,7 @@ __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, cons
             if (j < rows) {
                 float *dst = ob + (size_t)j * Dv;
                 // (masked keys of a tile were multiplied by zeros, which leave a NaN of dC standing)
-                const float x = j0 + j < L ? acc[t][r] : 0.f;
+                const float x = j0 + j < L ? acc[t][r] * back : 0.f;
                 store_streaming(dst, acc_out ? x + *dst : x);      // add to what the earlier decoder steps left
             }
         }

@@ -3,14 +3,18 @@
 // An fp32 number is the sum of three bf16 numbers, x = h + m + l: h is x rounded to bf16, m what is left of it rounded to bf16, l the rest
 // (8 + 8 + 8 significant bits and two signs: exact).  A product of two such sums is
 //   hh' + (hm' + mh') + (mm' + hl' + lh')
-// up to terms below 2^-24 of it, six matrix products with fp32 accumulation.  Measured against float64 over 64 to 1024 terms
+// up to terms below 2^-24 of it, six matrix products with fp32 accumulation (Henry, Tang, Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019).  Measured against float64 over 64 to 1024 terms
 // (normal, uniform and widely spread operands): 0.65 to 0.85 of the error of v_mfma_f32_16x16x4_f32, which rounds its sum more often.
 // Why: the fp32 matrix instructions run at 32 multiply-adds per clock and SIMD and hold the vector unit for as long (measured: no vector
 // instruction of another wave gets in); the bf16 ones run at 512, six of them at 85, and leave the vector unit free (a wave of
 // reciprocals next to a wave of v_mfma_f32_32x32x16_bf16: 10.6 clocks per reciprocal against 10.1 alone).
-// What it cannot do: infinities and numbers that round to an infinite bf16 (3.39e38 up), whose lower parts are no numbers, so that the
-// product is none either; a caller that finds a result that is not finite redoes the work in fp32.  Parts below 2^-126 count as zero (the
-// matrix cores flush bf16 denormals), so digits are lost for numbers below about 1e-33.
+// Small numbers: fp32 operands are multiplied by 2^24 before they are split, and the caller multiplies the sums by split_back.  A part is a
+// whole multiple of 2^-149, as the number is; scaled it is zero or at least 2^-125, which bf16 holds.  (As they are, bf16 keeps multiples of
+// 2^-133 of them, and operands of 1e-34, 1e-35 and 1e-36 gave errors of 2.9e-7, 2.7e-6 and 2.7e-5; scaled 1.1e-7 throughout, fp32 products
+// 1.4e-7.  It costs two of thirteen instructions per pair, and 0 to 0.6 % of forward and backward over 17 shapes.)
+// What it cannot do: infinities, operands past 2^104 (2e31) and sums past 2^80 (1.2e24, with a bf16 operand 2^104) are not finite; a caller that
+// finds such a result redoes the work in fp32.
 #pragma once
 #include "common.hpp"
 
@@ -32,9 +36,15 @@ struct Split8 { u32x4 p[3]; };
 __device__ __forceinline__ unsigned bf16_pair(float a, float b) {           // round to nearest even, a in the low half
     return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){a, b}, bf16x2));
 }
-// Two numbers into their three pairs: eleven instructions.  (v_dot2_f32_bf16 with (-1, 0) would take a half off in one instruction instead
+constexpr float kSplitScale = 0x1p24f;
+// what takes the scale off a sum of products of a split operand with one of type TB
+template <typename TB> __device__ constexpr float split_back = sizeof(TB) == 4 ? 0x1p-48f : 0x1p-24f;
+
+// Two numbers into their three pairs: thirteen instructions.  (v_dot2_f32_bf16 with (-1, 0) would take a half off in one instruction instead
 // of two, but it holds up the matrix instructions: 61 clocks for one of them and four v_dot2, 33 with four shifts or subtractions.)
 __device__ __forceinline__ void split2(float a, float b, unsigned &h, unsigned &m, unsigned &l) {
+    a *= kSplitScale;
+    b *= kSplitScale;
     h = bf16_pair(a, b);
     a -= __uint_as_float(h << 16);
     b -= __uint_as_float(h & 0xffff0000u);

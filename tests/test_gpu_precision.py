@@ -241,8 +241,8 @@ PRE = [
 ]
 
 
-def _backward(B, Tq, Tk, Dv, dt, change=None):
-    """P and the gradients of a batch of full samples; change(dC, V) edits them before the backward pass."""
+def _backward(B, Tq, Tk, Dv, dt, change=None, change_P=None):
+    """P and the gradients of a batch of full samples; change(dC, V) and change_P(P) edit them before the backward pass."""
     import torch
     from paper_1805_08899_amd import binding as eb
     H = 32
@@ -261,9 +261,23 @@ def _backward(B, Tq, Tk, Dv, dt, change=None):
     eb.check(eb.echo_attn_fwd(desc, q, k, V, v, key_len, out["C"], out["P"], ws, stream=st))
     if change:
         change(dC, V)
+    if change_P:
+        change_P(out["P"])
     eb.check(eb.echo_attn_bwd(desc, dC, out["P"], q, k, V, v, key_len, out["dQp"], out["dKp"], out["dV"], out["dv"], ws, stream=st))
     torch.cuda.synchronize()
     return {n: x.cpu() for n, x in out.items()}, dC.cpu(), V.cpu(), q.cpu(), k.cpu(), v.cpu()
+
+
+def _errors_of_products(out, dC, V, q, k, v):
+    """Relative errors of dV and dQp of the first four samples against float64."""
+    import torch
+    P, dC, V, q, k, v = (x[:4].double() if x.dim() > 1 else x.double() for x in (out["P"], dC, V, q, k, v))
+    rel = lambda got, ref: float((got.double() - ref).norm() / ref.norm())
+    e_dv = rel(out["dV"][:4], P.transpose(1, 2) @ dC)
+    dP = dC @ V.transpose(1, 2)
+    dS = P * (dP - (P * dP).sum(-1, keepdim=True))
+    dQ = torch.stack([(dS[b, :, :, None] * (1 - torch.tanh(q[b, :, None] + k[b, None]) ** 2)).sum(1) * v for b in range(4)])
+    return e_dv, rel(out["dQp"][:4], dQ)
 
 
 @pytest.mark.parametrize("case", PRE, ids=[c[0] for c in PRE])
@@ -277,16 +291,42 @@ def test_error_of_products_of_split_operands(case):
     name, B, Tq, Tk, Dv, dt = case
     print("split operands", case, flush=True)
     out, dC, V, q, k, v = _backward(B, Tq, Tk, Dv, dt)
-    P, dC, V, q, k, v = (x[:4].double() if x.dim() > 1 else x.double() for x in (out["P"], dC, V, q, k, v))
-    rel = lambda got, ref: float((got.double() - ref).norm() / ref.norm())
-    e_dv = rel(out["dV"][:4], P.transpose(1, 2) @ dC)
-    dP = dC @ V.transpose(1, 2)
-    dS = P * (dP - (P * dP).sum(-1, keepdim=True))
-    dQ = torch.stack([(dS[b, :, :, None] * (1 - torch.tanh(q[b, :, None] + k[b, None]) ** 2)).sum(1) * v for b in range(4)])
-    e_dq = rel(out["dQp"][:4], dQ)
+    e_dv, e_dq = _errors_of_products(out, dC, V, q, k, v)
     print(f"{name}: dV {e_dv:.2e}, dQp {e_dq:.2e}", flush=True)
     assert e_dv <= 2 * U * (Tq / 16 + 1) ** 0.5, e_dv
     assert e_dq <= 2e-6, e_dq
+
+
+@pytest.mark.parametrize("what", ["gradients", "values", "probabilities", "one_key"])
+@pytest.mark.parametrize("case", PRE, ids=[c[0] for c in PRE])
+def test_small_operands_lose_no_digits(case, what):
+    """Operands of 1e-35 and below: their bf16 parts are below what bf16 holds, unless they are scaled.  Bounds of
+    test_error_of_products_of_split_operands; all scales are powers of two, and the results stay normal numbers."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    name, B, Tq, Tk, Dv, dt = case
+    print("small operands", case, what, flush=True)
+    scales = {"gradients": (-119, 8, 0), "values": (90, -119, 0)}.get(what, (0, 0, -115))           # of dC, V, P
+
+    def change(dC, V):
+        dC.mul_(2.0 ** scales[0])
+        V.mul_(2.0 ** scales[1])
+
+    def change_P(P):
+        (P[:, :, 1] if what == "one_key" else P).mul_(2.0 ** scales[2])
+
+    out, dC, V, q, k, v = _backward(B, Tq, Tk, Dv, dt, change, change_P)
+    dv_bound = 2 * U * (Tq / 16 + 1) ** 0.5
+    if what == "one_key":
+        want = out["P"][:, :, 1:2].double().transpose(1, 2) @ dC.double()
+        e_dv = float((out["dV"][:, 1:2].double() - want).norm() / want.norm())
+    else:
+        e_dv, e_dq = _errors_of_products(out, dC, V, q, k, v)
+    print(f"{name} {what}: dV {e_dv:.2e}", flush=True)
+    assert e_dv <= dv_bound, e_dv
+    if what in ("gradients", "values"):
+        print(f"dQp {e_dq:.2e}", flush=True)
+        assert e_dq <= 2e-6, e_dq
 
 
 @pytest.mark.parametrize("case", PRE, ids=[c[0] for c in PRE])
