@@ -604,6 +604,9 @@ __device__ __forceinline__ void dv_rows_block(const float *__restrict__ P, const
 // way meanwhile.  dC is staged by each wave for itself, or, where all of them need the same chunk (KW = 8), split once for the
 // block, an eighth of two chunks by each, one buffer ahead (a barrier per two chunks).  The partial sums of the groups of d meet in LDS planes.
 // Rows and keys past the end are clamped for loading; what they produce is never read.  Columns of d past Dv are zeroed in dC.
+// Results that are not finite are formed again in fp32 by the same waves, several loads under way at a time (backward at B = 64, T = 50, H = Dv =
+// 512 27 -> 34 us with one infinity per sample, at B = 32, T = 300, H = Dv = 1024 461 -> 538, 564 with nothing but NaN; two columns per load: 62,
+// 740 and 876).
 // What bounds it is instruction issue: about nine vector instructions per product of 32 x 32 x 16, a wave alone on its SIMD issues one in
 // four clocks and overlaps little, so sixteen waves of at most 128 registers share a CU (eight of 250, each with four key tiles and a
 // software pipeline, took as long as four of them).
@@ -855,19 +858,34 @@ __device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC,
     int again = 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k) again |= s_inf[k];
-    if (again) {                                                    // in fp32
-        for (int t = w; t < (L + 31) / 32; t += 8) {
+    float back = split_back<TV>;
+    if (again) {                                                    // the wave's products again, in fp32
+        back = 1.f;
+        const float *arow = dCb + (size_t)min(n, last_row) * Dv;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[0][r] = 0.f;
-            const float *arow = dCb + (size_t)min(n, last_row) * Dv;
-            const TV *vrow = Vb + (size_t)min(32 * t + n, Tk - 1) * Dv;
-            for (int d = 0; d < Dv; d += 2)                         // (Dv is a multiple of four)
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(arow[d + half], ld(vrow, (size_t)(d + half)), acc[0], 0, 0, 0);
+        for (int k = 0; k < 2; ++k) {
+            if (k >= mine) continue;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s_mem[mfma32_row(r, lane) * dp_pitch + 32 * t + n] = acc[0][r];
+            for (int r = 0; r < 16; ++r) acc[k][r] = 0.f;
+            const TV *vrow = Vb + (size_t)min((kw + KW * k) * 32 + n, Tk - 1) * Dv;
+            // PC pieces of 8 columns of d at a time, all loads of them before the first product: step c of a piece is column 4 half + c
+            constexpr int PC = KW == 8 ? 2 : 4;
+            for (int d0 = 8 * PC * dw; d0 < Dv; d0 += 8 * PC * DW) {
+                float4 a[PC], x[PC];
+#pragma unroll
+                for (int u = 0; u < PC; ++u) {
+                    const int d = d0 + 8 * u + 4 * half;
+                    a[u] = ld4(arow, (size_t)min(d, Dv - 4));
+                    x[u] = ld4(vrow, (size_t)min(d, Dv - 4));
+                    if (d >= Dv) a[u] = x[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+#pragma unroll
+                for (int u = 0; u < PC; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp4(a[u], c), comp4(x[u], c), acc[k], 0, 0, 0);
+            }
         }
-        lds_barrier();
-        return split_finish<1, NP>(pr, dS, ds_rowsum, s_mem, b, i0, Tq, L, pitch, dp_pitch);
     }
     float *plane = s_mem + dw * 32 * dp_pitch;
 #pragma unroll
@@ -875,7 +893,7 @@ __device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC,
         if (k < mine)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                plane[mfma32_row(r, lane) * dp_pitch + (kw + KW * k) * 32 + n] = acc[k][r] * split_back<TV>;
+                plane[mfma32_row(r, lane) * dp_pitch + (kw + KW * k) * 32 + n] = acc[k][r] * back;
     lds_barrier();
     split_finish<DW, NP>(pr, dS, ds_rowsum, s_mem, b, i0, Tq, L, pitch, dp_pitch);
 }
@@ -980,17 +998,26 @@ __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, cons
         if (__any(odd != 0.f)) {
             back = 1.f;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                if (t >= live) continue;
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-                const int j = j0 + 32 * t + n;
-                const float *pj = Pb + min(j, Tk - 1);
-                for (int i = 0; i < Tq; i += 2) {
-                    const int row = min(i + half, Tq - 1);
-                    const float x = j < L && i + half < Tq ? pj[(size_t)row * Tk] : 0.f;
-                    const float y = i + half < Tq ? Cb[(size_t)row * Dv + b_col] : 0.f;
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc[t], 0, 0, 0);
+            for (int i = 0; i < Tq; i += 16) {                               // all loads of 16 rows before their first product
+                float x[NT][8], y[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int row = min(i + 2 * u + half, Tq - 1);
+                    y[u] = Cb[(size_t)row * Dv + b_col];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) x[t][u] = Pb[(size_t)row * Tk + min(j0 + 32 * t + n, Tk - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const bool on = i + 2 * u + half < Tq;
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        if (t < live)
+                            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(on && j0 + 32 * t + n < L ? x[t][u] : 0.f, on ? y[u] : 0.f,
+                                                                          acc[t], 0, 0, 0);
                 }
             }
         }
