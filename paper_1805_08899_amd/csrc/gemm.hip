@@ -639,6 +639,7 @@ constexpr int kSplitTileFloats = 32 * 36, kSplitPlane = 32 * 5;             // (
 __host__ __device__ constexpr int split_stage_floats(int kw) {
     return 8 * kSplitTileFloats + (kw == 8 ? 4 * 3 * kSplitPlane * 4 : 8 * kSplitTileFloats);
 }
+constexpr size_t kAloneLdsBytes = 84 * 1024;                                // (of 160 KB)
 __host__ __device__ constexpr int split_dp_pitch(int Tk) { return (Tk + 31) / 32 * 32 + 4; }
 __host__ __device__ constexpr int split_lds_floats(int kw, int Tk) {
     return split_stage_floats(kw) > 8 / kw * 32 * split_dp_pitch(Tk) ? split_stage_floats(kw) : 8 / kw * 32 * split_dp_pitch(Tk);
@@ -1340,7 +1341,14 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
                           : s.Dv <= 512         ? (size_t)4 * 16 * kStagePitch * sizeof(float)
                           : s.Dv <= 1024        ? (size_t)(4 * 16 * kStagePitch + 64 * pitch16) * sizeof(float)
                                                 : (size_t)64 * pitch16 * sizeof(float);
-    const size_t lds = kw ? std::max(ds_lds, (size_t)kDvSplitLdsBytes) : ds_lds;
+    // One block per CU, by asking for more than half of its LDS, for f32 on long key axes and wide value rows, once there is a dS block for every
+    // CU.  Two of them keep the matrix cores so busy with dense bf16 products that some cards lower the shader clock, by up to 10 %, for the
+    // launches around this one too; one does not, and loses less than that.  Forward and backward over fp32 products, two blocks and one: B =
+    // 32, T = 300, H = 1024 0.97 to 1.00 and 0.94 on a card that reacts, 0.92 and 0.93 on three that do not; twice the samples 1.05 and 0.97,
+    // 0.97 and 0.97; 24 shapes of 200 to 480 keys that take this line 1.01 (0.87 to 1.05) and 0.95 (0.89 to 1.00), 0.92 and 0.94; with 400
+    // columns 1.01 and 1.03 on the first.  From 129 to 192 keys, where waves have no key tile, 1.01 (up to 1.07) and 0.99, 0.93 and 0.96.
+    const bool alone = kw == 8 && with_ds && !s.bf16 && s.Tk > 192 && s.Dv >= 512 && blocks32 >= 256;
+    const size_t lds = std::max(ds_lds, alone ? kAloneLdsBytes : kw ? (size_t)kDvSplitLdsBytes : (size_t)0);
 #define ECHO_PRE_LAUNCH(TV, KW)                                                                                     \
     do {                                                                                                            \
         if (lds > 48 * 1024) { /* beyond the default dynamic LDS limit (up to 160 KB per block on gfx950) */        \

@@ -151,6 +151,12 @@ CASES = [
     ("pre_split_257_keys_36_columns", 50, 70, 257, 8, 36, "f32", False),
     ("pre_split_512_keys_64_columns_bf16", 51, 64, 512, 8, 64, "bf16", False),
     ("pre_not_split_513_keys", 51, 64, 513, 8, 64, "f32", False),
+    # one block per CU: the fewest keys, columns and rows that take it, and one key, four columns and one sample less; several key tiles per wave
+    ("pre_alone_193_keys_512_columns", 128, 33, 193, 8, 512, "f32", False),
+    ("pre_not_alone_192_keys", 128, 33, 192, 8, 512, "f32", False),
+    ("pre_not_alone_508_columns", 128, 33, 193, 8, 508, "f32", False),
+    ("pre_not_alone_255_blocks", 255, 17, 193, 8, 512, "f32", False),
+    ("pre_alone_512_keys_548_columns", 86, 65, 512, 8, 548, "f32", False),
     # whole backward in one launch: one tile, remainders of the tiles, one row, one key, three tiles, all sixteen with two per wave,
     # slices of 16 to 64 columns, several pieces of columns of each width, entries that need the exponential of the sum
     ("small_one_tile", 4, 6, 7, 16, 16, "f32", True),
