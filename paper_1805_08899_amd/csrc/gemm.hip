@@ -611,7 +611,7 @@ __device__ __forceinline__ void dv_rows_block(const float *__restrict__ P, const
 // four clocks and overlaps little, so sixteen waves of at most 128 registers share a CU (eight of 250, each with four key tiles and a
 // software pipeline, took as long as four of them).
 // The launch of k_bwd_pre, dS and dV blocks, before (fp32 products; 16 or 32 rows) and with split operands, us: B = 32, T = 300, Dv = 1024
-// 126 -> 71; bf16 V, B = 128, T = 50, Dv = 1024 28.4 -> 18.8; B = 128, T = 100, Dv = 512 35.3 -> 29.9; B = 64, T = 50, Dv = 512 9.7 -> 8.5.
+// 126 -> 71 (one block per CU, as it is launched now, 79); bf16 V, B = 128, T = 50, Dv = 1024 28.4 -> 18.8; B = 64, T = 50, Dv = 512 9.7 -> 8.5.
 template <typename TV> struct SplitStage;
 template <> struct SplitStage<float> {
     static constexpr int PITCH = 36;          // of 32 elements
@@ -1320,12 +1320,12 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // 2048 19.4 against 13).
     const bool few_dv = !with_ds && s.Tk <= 64 && (long long)s.B * ((s.Dv + 63) / 64) <= 1024;
     const bool small = s.Tk <= 128 && (s.Tq <= 16 || s.Tk <= 16 || (with_ds && !s.bf16 && blocks32 < 64) || few_dv);
-    // f32, 65 to 128 keys, value rows that fill the four waves' 128 columns of the fp32 form: there the launch itself gains least (B = 128, T =
-    // 100, Dv = 512 35.3 -> 29.9 us), and the dense bf16 products cost the launches around it more on cards that answer them with
-    // a lower shader clock: forward and backward 182.5 -> 176.0 us on one card, 184 -> 185 on a second, 185 -> 200 on a third, whose forward
-    // launch, the same code, goes from 65 to 75 us beside them.  On that third card 140 other shapes of f32 took 0.96 of the time in the
-    // split form, Dv from 513 on 0.95.
-    const bool dense = with_ds && !s.bf16 && s.Tk > 64 && s.Tk <= 128 && s.Dv > 384 && s.Dv <= 512 && blocks32 >= 128;
+    // f32, 65 to 128 keys, value rows that fill the four waves' 128 columns of the fp32 form to seven eighths and more, and a block for every CU:
+    // there the launch itself gains least from split operands (B = 128, T = 100, Dv = 512 39 -> 33 us), and on cards that answer dense bf16
+    // products with a lower shader clock the launches around it lose more, one block per CU or two.  Forward and backward over fp32 products on
+    // a card that reacts and on one that does not: ten shapes inside 1.03 (0.99 to 1.05) and 0.97 (0.93 to 1.03); 384 to 447 columns 0.98
+    // (0.92 to 1.01) and 0.95; more than 512 0.93 (0.90 to 0.98) and 0.91; 448 to 512 and fewer blocks 0.96 and 0.94.
+    const bool dense = with_ds && !s.bf16 && s.Tk > 64 && s.Tk <= 128 && s.Dv >= 448 && s.Dv <= 512 && blocks32 >= 256;
     const int kw = !fits || small || dense ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
     const int s_rows = kw ? 32 : 16;
     const int s_tiles = with_ds ? (s.Tq + s_rows - 1) / s_rows : 0;

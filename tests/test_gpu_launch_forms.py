@@ -145,8 +145,13 @@ CASES = [
     ("pre_split_128_keys_100_columns", 70, 129, 128, 8, 100, "f32", False),
     ("pre_split_97_keys_96_columns_bf16", 70, 31, 97, 8, 96, "bf16", False),
     ("pre_split_100_keys_384_columns", 64, 60, 100, 8, 384, "f32", False),
-    ("pre_not_split_100_keys_388_columns", 64, 60, 100, 8, 388, "f32", False),
-    ("pre_not_split_128_keys_512_columns", 64, 33, 128, 8, 512, "f32", False),
+    ("pre_split_100_keys_388_columns", 64, 60, 100, 8, 388, "f32", False),
+    ("pre_split_128_keys_512_columns", 64, 33, 128, 8, 512, "f32", False),
+    ("pre_split_444_columns", 128, 33, 100, 8, 444, "f32", False),
+    ("pre_not_split_448_columns", 128, 33, 100, 8, 448, "f32", False),
+    ("pre_not_split_512_columns", 128, 33, 65, 8, 512, "f32", False),
+    ("pre_split_516_columns", 128, 33, 65, 8, 516, "f32", False),
+    ("pre_split_255_blocks", 255, 17, 128, 8, 512, "f32", False),
     ("pre_split_129_keys_516_columns", 201, 17, 129, 8, 516, "f32", False),
     ("pre_split_257_keys_36_columns", 50, 70, 257, 8, 36, "f32", False),
     ("pre_split_512_keys_64_columns_bf16", 51, 64, 512, 8, 64, "bf16", False),
