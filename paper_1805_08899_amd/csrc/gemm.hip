@@ -1040,6 +1040,85 @@ __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, cons
         }
 }
 
+// dV of one sample for a panel of 64 keys and 256 columns, 64 columns per wave: dV[j, n] = sum_i P[i, j] dC[i, n].
+// Per step of four query rows a lane loads four consecutive keys of a P row and four consecutive columns of the dC
+// row (16 bytes each) and spends them on 16 products: component ca of the keys with component cb of the columns,
+// so product (ca, cb) holds keys m0 + 4 (row of the result tile) + ca and columns n0 + 4 (l % 16) + cb.  Two bytes
+// of operands per lane and product, against five in the form with one key per lane (pv_block), which at the larger
+// workloads was bound by what the L2 could deliver.  Needs Tk % 4 == 0 (16-byte loads of P rows).  Batches of U
+// steps are double buffered.  Rows of masked keys (j >= L) come out as exact zeros whatever P holds there.
+__device__ __forceinline__ void dv_tile64(const float *__restrict__ P, const float *__restrict__ dC,
+                                          const int *__restrict__ key_len, float *__restrict__ dV, int Tq, int Tk,
+                                          int Dv, int b, int by, int bx, int acc_out) {
+    constexpr int U = 4;
+    const int L = clamp_len(key_len[b], Tk);
+    const int lane = lane_id(), w = wave_id();
+    const int lm = lane & 15, lk = lane >> 4;
+    const int m0 = by * 64, n0 = (bx * 4 + w) * 64;
+    if (n0 >= Dv) return;
+    const int kcol = m0 + 4 * lm;             // first of this lane's four keys
+    const int ncol = n0 + 4 * lm;             // first of this lane's four columns
+    const bool nok = ncol < Dv;
+    const float *Pb = P + (size_t)b * Tq * Tk;
+    const float *Cb = dC + (size_t)b * Tq * Dv;
+    f32x4 acc[4][4];
+#pragma unroll
+    for (int ca = 0; ca < 4; ++ca)
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) acc[ca][cb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (m0 < L) {
+        const int kc = min(kcol, Tk - 4), nc = min(ncol, Dv - 4);       // clamped for loading
+        float4 a[U], bv[U], an[U], bn[U];
+        auto load = [&](float4 (&da)[U], float4 (&db)[U], int kb0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = min(kb0 + 4 * u + lk, Tq - 1);
+                da[u] = ld4(Pb, (size_t)k * Tk + kc);
+                db[u] = ld4(Cb, (size_t)k * Dv + nc);
+            }
+        };
+        load(a, bv, 0);
+        for (int kb0 = 0; kb0 < Tq; kb0 += 4 * U) {
+            load(an, bn, min(kb0 + 4 * U, Tq - 1));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool row_on = kb0 + 4 * u + lk < Tq;               // rows past Tq add nothing
+                float x[4];
+#pragma unroll
+                for (int ca = 0; ca < 4; ++ca) x[ca] = (row_on && kcol + ca < L) ? comp4(a[u], ca) : 0.f;
+#pragma unroll
+                for (int ca = 0; ca < 4; ++ca)
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb) acc[ca][cb] = mfma16(x[ca], comp4(bv[u], cb), acc[ca][cb]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a[u] = an[u];
+                bv[u] = bn[u];
+            }
+        }
+    }
+    if (!nok) return;
+    float *ob = dV + (size_t)b * Tk * Dv;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int ca = 0; ca < 4; ++ca) {
+            const int m = m0 + 16 * lk + 4 * r + ca;
+            if (m < Tk) {
+                float4 o = make_float4(acc[ca][0][r], acc[ca][1][r], acc[ca][2][r], acc[ca][3][r]);
+                if (acc_out) {                       // add to what the earlier decoder steps left
+                    const float4 old = *reinterpret_cast<const float4 *>(ob + (size_t)m * Dv + ncol);
+                    o.x += old.x;
+                    o.y += old.y;
+                    o.z += old.z;
+                    o.w += old.w;
+                }
+                store4_streaming(ob + (size_t)m * Dv + ncol, o);
+            }
+        }
+}
+
 // dV of one sample for a 64-wide group of columns and all of at most 64 keys: dV[j, n0 .. n0+63] = sum_i P[i, j] dC[i, n0 ..].
 // The block's slice of dC (Tq rows of 256 bytes) passes through the CU once.  Wave w owns the key tile of 16: per step of four query rows
 // a lane loads one value of P and four consecutive columns of dC (one 16-byte load) and issues 4 products.
@@ -1143,14 +1222,16 @@ __device__ __forceinline__ void rank_block(const int *__restrict__ key_len, int 
 // Everything the backward pass needs before the recomputation, in one launch:
 // blocks that produce dS (B1 + B2), blocks that produce dV (B1) and one block
 // that ranks the samples.  The three kinds of block do not depend on each other.
-// dV blocks of a sample: groups of columns times groups of keys.  dv_split_block: 256 columns, 64 keys; dv_cols_block: 64 columns, all
-// keys; pv_block: 256 columns, 16 keys.
+// dV blocks of a sample: groups of columns times groups of keys.  dv_split_block and dv_tile64: 256 columns, 64 keys; dv_cols_block:
+// 64 columns, all keys; pv_block: 256 columns, 16 keys.
 __host__ __device__ constexpr int dv_col_groups(int kw, int Tk, int Dv) { return kw == 0 && Tk <= 64 ? (Dv + 63) / 64 : (Dv + 255) / 256; }
-__host__ __device__ constexpr int dv_key_groups(int kw, int Tk) { return kw ? (Tk + kDvKeys - 1) / kDvKeys : Tk <= 64 ? 1 : (Tk + 15) / 16; }
+__host__ __device__ constexpr int dv_key_groups(int kw, bool panels, int Tk) {
+    return kw || panels ? (Tk + kDvKeys - 1) / kDvKeys : Tk <= 64 ? 1 : (Tk + 15) / 16;
+}
 
 // The dS blocks of a launch: KW key groups of a block of eight waves, 32 query rows and at most 64 KW keys (dscore_split_block), or, KW = 0,
-// 16 rows on the fp32 matrix instructions in blocks of four waves.
-template <typename TV, int KW>
+// 16 rows on the fp32 matrix instructions in blocks of four waves.  PANELS (KW = 0): dV in dv_tile64.
+template <typename TV, int KW, bool PANELS>
 __global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const float *__restrict__ dC, const TV *__restrict__ V,
                                                  const float *__restrict__ P, const int *__restrict__ key_len,
                                                  float *__restrict__ dS, float *__restrict__ ds_rowsum,
@@ -1165,7 +1246,7 @@ __global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const fl
     // long dS blocks of all its samples come first, then the dV blocks; the last block of the grid ranks.
     constexpr int kXcd = 8;
     const int spx = (B + kXcd - 1) / kXcd;                     // sample slots per XCD
-    const int v_cols = dv_col_groups(KW, Tk, Dv), per_b = v_cols * dv_key_groups(KW, Tk);       // dV blocks per sample
+    const int v_cols = dv_col_groups(KW, Tk, Dv), per_b = v_cols * dv_key_groups(KW, PANELS, Tk);       // dV blocks per sample
     const int per_xcd = spx * (s_tiles + per_b);
     if ((int)blockIdx.x == kXcd * per_xcd) {
         rank_block(key_len, order, s_len, B, Tk, sorted, first);
@@ -1192,6 +1273,7 @@ __global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const fl
     if (b >= B) return;
     if constexpr (KW > 0)
         dv_split_block(P, dC, key_len, dV, reinterpret_cast<u32x4 *>(s_dp), Tq, Tk, Dv, b, (rem / v_cols) * kDvKeys, rem % v_cols, acc);
+    else if constexpr (PANELS) dv_tile64(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_cols, rem % v_cols, acc);
     else if (Tk <= 64) dv_cols_block(P, dC, key_len, dV, Tq, Tk, Dv, b, rem, acc);
     else pv_block<float, true>(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_cols, rem % v_cols, acc);
 }
@@ -1265,12 +1347,17 @@ __global__ __launch_bounds__(256) void k_ds_finish(const float *__restrict__ P, 
     if (lane == 0) ds_rowsum[row] = tot;
 }
 
-// k_bwd_pre has one dS block per 32 query rows, which takes all keys and all of d; with at most 50 of them the shorter blocks win what
-// the extra launch costs (4 to 5 us; B = 1, T = 400, Dv = 512 70 -> 14 us for the pre-kernel as it was on fp32 products).  Backward on split operands
-// against parts, 150 shapes of more than 128 keys: up to 14 blocks 1.17 of the time, to 29 1.12, to 44 1.03, to 59 0.98, to 74 0.96, to 200
-// 0.75 to 0.97.
+// What the blocks of split operands take: at most 512 keys, 32-bit offsets within 32 rows of dC, a sample's V and its dC.
+static bool split_fits(const AttnShape &s) { return s.Tk <= 512 && s.Dv < (1 << 20) && (long long)s.Tq * s.Dv < (1LL << 29); }
+
+// k_bwd_pre's dS blocks take all keys and all of d; with few of them the shorter blocks win what the extra launch costs (4 to 5 us; B = 1, T = 400,
+// Dv = 512 70 -> 14 us for the pre-kernel as it was on fp32 products).  Where they would be blocks of split operands, up to 50 blocks of 32 rows:
+// backward on these against parts, 150 shapes of 129 to 512 keys, up to 14 blocks 1.17 of the time, to 29 1.12, to 44 1.03, to 59 0.98, to 74
+// 0.96, to 200 0.75 to 0.97.  Where they would be fp32 blocks of 16 rows, up to 100, 200 where the rows are wide: without parts B = 8, T = 600,
+// H = Dv = 512 468 -> 523 us, bf16 B = 5, T = 600, Dv = 512 91 -> 189; 22 shapes of more than 512 keys 1.28 (0.99 to 2.07).
 bool bwd_pre_in_parts(const AttnShape &s) {
-    return s.Tk > kDsplitMaxTk && s.Dv <= 1024 && s.B <= kMaxSortedB && (long long)s.B * ((s.Tq + 31) / 32) <= 50;
+    const int most = split_fits(s) ? 50 : s.Dv >= 384 ? 200 : 100;
+    return s.Tk > kDsplitMaxTk && s.Dv <= 1024 && s.B <= kMaxSortedB && (long long)s.B * ((s.Tq + 31) / 32) <= most;
 }
 
 template <typename TV, int ROUNDS>
@@ -1309,13 +1396,11 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
         return s.bf16 ? launch_parts_t<bf16_t, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first)
                       : launch_parts_t<float, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first);
     }
-    // Split operands (KW > 0) for what their blocks take: at most 512 keys, 32-bit offsets within 32 rows of dC, a sample's V and its dC.
-    // Not where tiles of 32 would be mostly empty, nor, in f32, on few blocks, where latency decides and the splitting of both operands is
+    // Split operands (KW > 0) for what their blocks take (split_fits).  Not where tiles of 32 would be mostly empty, nor, in f32, on few blocks, where latency decides and the splitting of both operands is
     // a part of it (backward, 350 shapes of up to 128 keys: at most 16 rows or 16 keys 1.02 of the time of the fp32 form, up to 1.13;
     // fewer than 64 blocks of 32 rows 1.00 in f32, 0.75 to 1.12, and 0.92 in bf16; 64 to 160 blocks 0.94; more and longer ones 0.93, see
     // dscore_split_block).
     const long long blocks32 = (long long)s.B * ((s.Tq + 31) / 32);
-    const bool fits = s.Tk <= 512 && s.Dv < (1 << 20) && (long long)s.Tq * s.Dv < (1LL << 29);
     // dV alone (the keys' call of the decoder) on short key axes: blocks of 64 columns up to two rounds of them (512 of them 5.8 us against 7.8;
     // 2048 19.4 against 13).
     const bool few_dv = !with_ds && s.Tk <= 64 && (long long)s.B * ((s.Dv + 63) / 64) <= 1024;
@@ -1326,10 +1411,15 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // a card that reacts and on one that does not: ten shapes inside 1.03 (0.99 to 1.05) and 0.97 (0.93 to 1.03); 384 to 447 columns 0.98
     // (0.92 to 1.01) and 0.95; more than 512 0.93 (0.90 to 0.98) and 0.91; 448 to 512 and fewer blocks 0.96 and 0.94.
     const bool dense = with_ds && !s.bf16 && s.Tk > 64 && s.Tk <= 128 && s.Dv >= 448 && s.Dv <= 512 && blocks32 >= 256;
-    const int kw = !fits || small || dense ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
+    const int kw = !split_fits(s) || small || dense ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
+    // fp32 products past 128 keys: dV in panels of 64 keys where P rows allow 16-byte loads and the panels still fill the chip, or there are
+    // few rows to share a block's start among (blocks of 16 keys over panels: 28 shapes of 516 to 1000 keys with 800 panels and more 1.02 of the
+    // backward's time, 0.98 to 1.07; ten of 96 to 793 panels 0.94, 0.86 to 0.99; up to 12 rows and 132 to 500 keys 1.03, 1.00 to 1.09).
+    const bool panels = kw == 0 && s.Tk > kDsplitMaxTk && s.Tk % 4 == 0 &&
+                        (s.Tq <= 16 || s.B * ((s.Dv + 255LL) / 256) * ((s.Tk + kDvKeys - 1) / kDvKeys) >= 800);
     const int s_rows = kw ? 32 : 16;
     const int s_tiles = with_ds ? (s.Tq + s_rows - 1) / s_rows : 0;
-    const int v_groups = dv_col_groups(kw, s.Tk, s.Dv) * dv_key_groups(kw, s.Tk);
+    const int v_groups = dv_col_groups(kw, s.Tk, s.Dv) * dv_key_groups(kw, panels, s.Tk);
     const long long blocks = 1 + 8LL * ((s.B + 7) / 8) * (s_tiles + (long long)v_groups);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int pitch16 = (s.Tk + 15) / 16 * 16 + 4;
@@ -1349,23 +1439,26 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // columns 1.01 and 1.03 on the first.  From 129 to 192 keys, where waves have no key tile, 1.01 (up to 1.07) and 0.99, 0.93 and 0.96.
     const bool alone = kw == 8 && with_ds && !s.bf16 && s.Tk > 192 && s.Dv >= 512 && blocks32 >= 256;
     const size_t lds = std::max(ds_lds, alone ? kAloneLdsBytes : kw ? (size_t)kDvSplitLdsBytes : (size_t)0);
-#define ECHO_PRE_LAUNCH(TV, KW)                                                                                     \
+#define ECHO_PRE_LAUNCH(TV, KW, PANELS)                                                                             \
     do {                                                                                                            \
         if (lds > 48 * 1024) { /* beyond the default dynamic LDS limit (up to 160 KB per block on gfx950) */        \
             static LdsGrants granted;                                                                               \
-            hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre<TV, KW>, lds, granted);                       \
+            hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre<TV, KW, PANELS>, lds, granted);               \
             if (e != hipSuccess) return e;                                                                          \
         }                                                                                                           \
-        k_bwd_pre<TV, KW><<<(unsigned)blocks, KW ? 512 : 256, lds, st>>>(                                           \
+        k_bwd_pre<TV, KW, PANELS><<<(unsigned)blocks, KW ? 512 : 256, lds, st>>>(                                   \
             dC, (const TV *)V, P, key_len, dS, ds_rowsum, order, dV, s.B, sorted, first, s.Tq, s.Tk, s.Dv,          \
             ds_pitch(s.Tk), s_tiles, s_rows, s.acc ? 1 : 0);                                                        \
     } while (0)
 #define ECHO_PRE_KW(TV)                                 \
     switch (kw) {                                       \
-        case 1: ECHO_PRE_LAUNCH(TV, 1); break;          \
-        case 2: ECHO_PRE_LAUNCH(TV, 2); break;          \
-        case 8: ECHO_PRE_LAUNCH(TV, 8); break;          \
-        default: ECHO_PRE_LAUNCH(TV, 0); break;         \
+        case 1: ECHO_PRE_LAUNCH(TV, 1, false); break;   \
+        case 2: ECHO_PRE_LAUNCH(TV, 2, false); break;   \
+        case 8: ECHO_PRE_LAUNCH(TV, 8, false); break;   \
+        default:                                        \
+            if (panels) ECHO_PRE_LAUNCH(TV, 0, true);   \
+            else ECHO_PRE_LAUNCH(TV, 0, false);         \
+            break;                                      \
     }
     if (s.bf16) {
         ECHO_PRE_KW(bf16_t)

@@ -156,6 +156,18 @@ CASES = [
     ("pre_split_257_keys_36_columns", 50, 70, 257, 8, 36, "f32", False),
     ("pre_split_512_keys_64_columns_bf16", 51, 64, 512, 8, 64, "bf16", False),
     ("pre_not_split_513_keys", 51, 64, 513, 8, 64, "f32", False),
+    # more than 512 keys, fp32 products in blocks of 16 rows: dV in panels of 64 keys (800 panels, or up to 16 rows) and in blocks of 16 keys
+    # (fewer panels, or P rows that are no whole 16 bytes), remainders of the rows, value rows that are no whole 32 columns and more than
+    # 1024; and in parts up to 100 blocks of 32 rows, 200 of wide rows
+    ("pre_long_panels_44_columns_bf16", 101, 18, 516, 8, 44, "bf16", False),
+    ("pre_long_panels_one_key_group_short", 134, 17, 580, 8, 4, "f32", False),
+    ("pre_long_panels_9_rows", 101, 9, 520, 8, 44, "f32", False),
+    ("pre_long_panels_1028_columns", 21, 17, 516, 8, 1028, "f32", False),
+    ("pre_long_16_keys_132_columns", 101, 33, 513, 8, 132, "f32", False),
+    ("pre_long_few_panels_132_columns_bf16", 51, 65, 516, 8, 132, "bf16", False),
+    ("pre_long_1028_columns_bf16", 3, 20, 515, 8, 1028, "bf16", False),
+    ("pre_long_parts_100_blocks", 50, 64, 516, 8, 40, "f32", False),
+    ("pre_long_parts_200_blocks_bf16", 100, 33, 513, 8, 388, "bf16", False),
     # one block per CU: the fewest keys, columns and rows that take it, and one key, four columns and one sample less; several key tiles per wave
     ("pre_alone_193_keys_512_columns", 128, 33, 193, 8, 512, "f32", False),
     ("pre_not_alone_192_keys", 128, 33, 192, 8, 512, "f32", False),
@@ -208,6 +220,38 @@ def test_launch_form(case):
     again = db.results()
     for k in first:
         assert np.array_equal(first[k], again[k]), (name, k, "not reproducible")
+
+
+PARTS = [
+    # B, Tq, Tk, Dv, dtype, whether the pre-kernel runs in parts: up to 50 blocks of 32 rows where the other form would be split operands, up to
+    # 100 or 200 where it would be fp32 products
+    (50, 32, 129, 8, "f32", True), (51, 32, 129, 8, "f32", False), (50, 1, 512, 1024, "bf16", True), (51, 1, 512, 1024, "bf16", False),
+    (100, 32, 513, 380, "f32", True), (101, 32, 513, 380, "f32", False), (200, 3, 516, 384, "bf16", True), (201, 3, 516, 384, "bf16", False),
+    (3, 40, 600, 1028, "f32", False), (40, 20, 128, 8, "f32", False),
+]
+
+
+@pytest.mark.parametrize("case", PARTS, ids=["_".join(map(str, c[:5])) for c in PARTS])
+def test_which_launches_run_in_parts(case):
+    """The launch that finishes the parts is there exactly where the rule says (a limit drawn for split operands had also held where there are
+    none: up to twice the time past 512 keys)."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import binding as eb, harness
+    B, Tq, Tk, Dv, dt, parts = case
+    print("parts", case, flush=True)
+    wl = Workload("parts", B, Tq, Tk, 100, Dv, dt, 0.5, 1, Tk, dt == "bf16")
+    db = harness.DeviceBatch(wl, make_inputs(wl, seed=3), guard_bytes=4096)
+    db.fwd()
+    eb.echo_attn_profile_enable(True)
+    try:
+        eb.echo_attn_profile_read()
+        db.bwd()
+        torch.cuda.synchronize()
+        names = eb.echo_attn_profile_read()
+    finally:
+        eb.echo_attn_profile_enable(False)
+    assert "bwd_pre" in names and ("ds_finish" in names) == parts, names
 
 
 LARGE_ROWS = [
