@@ -1404,6 +1404,11 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // dV alone (the keys' call of the decoder) on short key axes: blocks of 64 columns up to two rounds of them (512 of them 5.8 us against 7.8;
     // 2048 19.4 against 13).
     const bool few_dv = !with_ds && s.Tk <= 64 && (long long)s.B * ((s.Dv + 63) / 64) <= 1024;
+    // dV alone of few rows, any number of keys: a step of 64 rows and the splitting of all of dC for it are a waste there (fp32 blocks over split ones, 129 to
+    // 500 keys: 29 launches of up to 12 rows 0.95 of the time, 0.92 to 1.01; 16 rows and more level).  With dS, whose rows of V are split
+    // once for up to 32 rows of dC, split operands stay ahead past 128 keys at any number of rows: 51 shapes of 1 to 16 rows 0.87 of
+    // the time that the backward takes on the fp32 forms (0.47 to 1.25; at 64 value columns 0.99, 0.87 to 1.19).
+    const bool few_rows_dv = !with_ds && s.Tq <= 12;
     const bool small = s.Tk <= 128 && (s.Tq <= 16 || s.Tk <= 16 || (with_ds && !s.bf16 && blocks32 < 64) || few_dv);
     // f32, 65 to 128 keys, value rows that fill the four waves' 128 columns of the fp32 form to seven eighths and more, and a block for every CU:
     // there the launch itself gains least from split operands (B = 128, T = 100, Dv = 512 39 -> 33 us), and on cards that answer dense bf16
@@ -1411,7 +1416,7 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // a card that reacts and on one that does not: ten shapes inside 1.03 (0.99 to 1.05) and 0.97 (0.93 to 1.03); 384 to 447 columns 0.98
     // (0.92 to 1.01) and 0.95; more than 512 0.93 (0.90 to 0.98) and 0.91; 448 to 512 and fewer blocks 0.96 and 0.94.
     const bool dense = with_ds && !s.bf16 && s.Tk > 64 && s.Tk <= 128 && s.Dv >= 448 && s.Dv <= 512 && blocks32 >= 256;
-    const int kw = !split_fits(s) || small || dense ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
+    const int kw = !split_fits(s) || small || few_rows_dv || dense ? 0 : s.Tk <= 64 ? 1 : s.Tk <= 128 ? 2 : 8;
     // fp32 products past 128 keys: dV in panels of 64 keys where P rows allow 16-byte loads and the panels still fill the chip, or there are
     // few rows to share a block's start among (blocks of 16 keys over panels: 28 shapes of 516 to 1000 keys with 800 panels and more 1.02 of the
     // backward's time, 0.98 to 1.07; ten of 96 to 793 panels 0.94, 0.86 to 0.99; up to 12 rows and 132 to 500 keys 1.03, 1.00 to 1.09).

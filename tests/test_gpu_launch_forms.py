@@ -358,6 +358,42 @@ def test_step_of_one_query(case):
     assert_parity(got, oracle_outputs(inputs, workers=1), inputs, dt, name)
 
 
+KEYS_ALONE = [
+    # B, Tq, Tk, Dv, dtype: dV of the keys' call on more than 50 blocks and past 128 keys: up to 12 rows in fp32, in panels of 64 keys or, where
+    # P rows are no whole 16 bytes, in blocks of 16; more rows on split operands
+    (60, 12, 132, 260, "f32"), (60, 13, 132, 260, "f32"), (60, 12, 131, 36, "bf16"), (60, 13, 131, 36, "bf16"), (60, 1, 512, 1028, "f32"),
+    (60, 5, 129, 4, "f32"), (60, 7, 513, 68, "f32"),
+]
+
+
+@pytest.mark.parametrize("case", KEYS_ALONE, ids=["_".join(map(str, c)) for c in KEYS_ALONE])
+def test_values_gradient_of_few_rows(case):
+    """dV = P^T dC over Tq terms: a product and at most Tq additions of fp32, and the two roundings that split operands add, of the terms'
+    magnitudes."""
+    import torch
+    assert torch.cuda.is_available(), "needs the GPU"
+    from paper_1805_08899_amd import binding as eb, harness
+    B, Tq, Tk, Dv, dt = case
+    print("keys alone", case, flush=True)
+    wl = Workload("keys", B, Tq, Tk, 8, Dv, dt, 0.5, 1, Tk, dt == "bf16")
+    inputs = make_inputs(wl, seed=41)
+    inputs["key_len"][:3] = (0, Tk, 1)
+    db = harness.DeviceBatch(wl, inputs, guard_bytes=4096)
+    db.poison_outputs()
+    db.fwd()
+    ds = torch.zeros(eb.echo_attn_steps_ds_bytes(db.desc), dtype=torch.uint8, device=db.device)
+    eb.check(eb.echo_attn_steps_bwd_keys(db.desc, db.dC, db.P, db.Qp, db.Kp, db.v, db.key_len, ds, db.dKp, db.dV, db.dv, db.ws,
+                                         stream=torch.cuda.current_stream(db.device)))
+    torch.cuda.synchronize()
+    assert db.check_guards() == []
+    P, dC, dV = (x.cpu().numpy().astype(np.float64) for x in (db.P, db.dC, db.dV))
+    for b in range(B):
+        L = int(inputs["key_len"][b])
+        assert (dV[b, L:] == 0).all(), b
+        bound = (Tq + 3) * 2.0 ** -24 * (np.abs(P[b, :, :L]).T @ np.abs(dC[b])) + 1e-44
+        assert (np.abs(dV[b, :L] - P[b, :, :L].T @ dC[b]) <= bound).all(), b
+
+
 ORDERS = [
     # name, B, Tq, Tk, H, samples whose blocks are among the first 256 (0: more than 512 blocks): slices of 64 columns in one round; more
     # than a round of slices of 16 where slices of 64 would be one; every tanh twice in independent blocks; parts of a round; an odd
