@@ -119,18 +119,18 @@ CASES = [
     ("pre_parts_few_rows_bf16", 4, 3, 137, 24, 68, "bf16", False),
     ("pre_parts_two_rounds_bf16", 2, 70, 190, 24, 1024, "bf16", False),
     ("pre_parts_keys_past_384", 1, 90, 470, 24, 40, "f32", False),
-    # the same without parts: full and short key tiles, value rows of less than a chunk, exactly one, one and a bit, two and a bit, three and a
-    # bit; at most 16 rows
-    ("pre_staged_keys_129", 101, 32, 129, 8, 4, "f32", False),
-    ("pre_staged_four_tiles", 51, 65, 255, 8, 68, "f32", False),
-    ("pre_staged_five_tiles_bf16", 40, 97, 319, 8, 132, "bf16", False),
-    ("pre_staged_six_tiles", 60, 33, 384, 8, 60, "f32", False),
-    ("pre_staged_six_tiles_bf16", 102, 17, 333, 8, 64, "bf16", False),
-    ("pre_staged_six_tiles_three_chunks_bf16", 102, 17, 333, 8, 76, "bf16", False),
-    ("pre_staged_six_tiles_four_chunks", 60, 33, 384, 8, 100, "f32", False),
-    ("pre_rows_of_16_five_tiles", 101, 16, 300, 8, 44, "f32", False),
-    ("pre_rows_of_16_five_tiles_bf16", 105, 15, 317, 8, 132, "bf16", False),
-    ("pre_rows_of_16_keys_past_384", 60, 50, 390, 8, 44, "f32", False),
+    # without parts, on split operands: five to twelve key tiles of 32 for the eight waves, the last one full or short; value rows of less than a
+    # chunk of 32 columns, two and a bit, four and a bit; at most 16 rows
+    ("pre_split_129_keys", 101, 32, 129, 8, 4, "f32", False),
+    ("pre_split_255_keys", 51, 65, 255, 8, 68, "f32", False),
+    ("pre_split_319_keys_bf16", 40, 97, 319, 8, 132, "bf16", False),
+    ("pre_split_384_keys", 60, 33, 384, 8, 60, "f32", False),
+    ("pre_split_333_keys_bf16", 102, 17, 333, 8, 64, "bf16", False),
+    ("pre_split_333_keys_76_columns_bf16", 102, 17, 333, 8, 76, "bf16", False),
+    ("pre_split_384_keys_100_columns", 60, 33, 384, 8, 100, "f32", False),
+    ("pre_split_16_rows_300_keys", 101, 16, 300, 8, 44, "f32", False),
+    ("pre_split_15_rows_317_keys_bf16", 105, 15, 317, 8, 132, "bf16", False),
+    ("pre_split_390_keys", 60, 50, 390, 8, 44, "f32", False),
     # pre-kernel on split operands: 17 to 64, 65 to 128 and more keys (up to two key tiles of 32 per wave, and none); rows that are no multiple
     # of 32 and of the 64 of a dV step, one step and several; value rows of less than a chunk of 32 columns, exactly one, part of a second
     # one, an odd number of them, more chunks than waves, more columns than a dV block; key panels of 64 with one key in the last; and
