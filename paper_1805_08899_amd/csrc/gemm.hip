@@ -690,8 +690,8 @@ __device__ __forceinline__ void split_finish(const float (&pr)[4][NP], float *__
     }
 }
 
-// The products of a wave with NL key tiles.
-template <typename TV, int NL, int KW>
+// The products of a wave with NL key tiles.  APART: those of each chunk summed on their own (add16).
+template <typename TV, int NL, int KW, bool APART>
 __device__ __forceinline__ void dscore_split_tiles(const BufferRows<float> &rows_a, const BufferRows<TV> &rows_v,
                                                    float *__restrict__ s_mem, f32x16 (&acc)[2], int last_row, int last_key, int Dv) {
     constexpr bool SHARED = KW == 8;
@@ -793,8 +793,12 @@ __device__ __forceinline__ void dscore_split_tiles(const BufferRows<float> &rows
             load_v(now, k + 1 < NL ? s : s + R, k + 1 < NL ? k + 1 : 0);
             loads_stay();
             const TV *t = sv + n * VS::PITCH + 8 * half;
-            acc[k] = mfma32(a0, VS::split(VS::get(t)), acc[k]);
-            acc[k] = mfma32(a1, VS::split(VS::get(t + 16)), acc[k]);
+            if constexpr (APART) {
+                add16(acc[k], mfma32(a1, VS::split(VS::get(t + 16)), mfma32(a0, VS::split(VS::get(t)), zero16())));
+            } else {
+                acc[k] = mfma32(a0, VS::split(VS::get(t)), acc[k]);
+                acc[k] = mfma32(a1, VS::split(VS::get(t + 16)), acc[k]);
+            }
         }
     };
     for (int s = 0; s < steps; s += 2) {
@@ -803,7 +807,7 @@ __device__ __forceinline__ void dscore_split_tiles(const BufferRows<float> &rows
     }
 }
 
-template <typename TV, int KW>
+template <typename TV, int KW, bool APART>
 __device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC, const TV *__restrict__ V,
                                                    const float *__restrict__ P, const int *__restrict__ key_len,
                                                    float *__restrict__ dS, float *__restrict__ ds_rowsum,
@@ -837,9 +841,9 @@ __device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC,
     if (L > 0) {                                                    // (block-uniform)
         const BufferRows<float> rows_a(dCb, (unsigned)(last_row + 1) * (unsigned)Dv);
         const BufferRows<TV> rows_v(Vb, (unsigned)L * (unsigned)Dv);
-        if (mine == 2) dscore_split_tiles<TV, 2, KW>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
-        else if (mine == 1) dscore_split_tiles<TV, 1, KW>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
-        else if constexpr (KW == 8) dscore_split_tiles<TV, 0, KW>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
+        if (mine == 2) dscore_split_tiles<TV, 2, KW, APART>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
+        else if (mine == 1) dscore_split_tiles<TV, 1, KW, APART>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
+        else if constexpr (KW == 8) dscore_split_tiles<TV, 0, KW, APART>(rows_a, rows_v, s_mem, acc, last_row, L - 1, Dv);
     }
     // a result of a valid key that is not finite: infinities among the operands, perhaps (see split.hpp)
     float odd = 0.f;
@@ -907,6 +911,7 @@ __device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC,
 // once, for all keys of the panel.  Rows past Tq and masked keys count as zero.
 constexpr int kDvKeys = 64;                   // keys of a panel
 constexpr int kDvSplitLdsBytes = 2 * 3 * 8 * kDvKeys * 16;
+template <bool APART>
 __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, const float *__restrict__ dC,
                                                const int *__restrict__ key_len, float *__restrict__ dV, u32x4 *__restrict__ s_a, int Tq,
                                                int Tk, int Dv, int b, int j0, int cg, int acc_out) {
@@ -981,7 +986,8 @@ __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, cons
                             Split8 sa;
 #pragma unroll
                             for (int p = 0; p < 3; ++p) sa.p[p] = frag[p * W * KEYS + 32 * t];
-                            acc[t] = mfma32(sa, sb, acc[t]);
+                            if constexpr (APART) add16(acc[t], mfma32(sa, sb, zero16()));
+                            else acc[t] = mfma32(sa, sb, acc[t]);
                         }
                 }
             }
@@ -1230,8 +1236,9 @@ __host__ __device__ constexpr int dv_key_groups(int kw, bool panels, int Tk) {
 }
 
 // The dS blocks of a launch: KW key groups of a block of eight waves, 32 query rows and at most 64 KW keys (dscore_split_block), or, KW = 0,
-// 16 rows on the fp32 matrix instructions in blocks of four waves.  PANELS (KW = 0): dV in dv_tile64.
-template <typename TV, int KW, bool PANELS>
+// 16 rows on the fp32 matrix instructions in blocks of four waves.  ALT: with KW = 0 dV in panels (dv_tile64), with KW = 8 short
+// runs of products summed on their own.
+template <typename TV, int KW, bool ALT>
 __global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const float *__restrict__ dC, const TV *__restrict__ V,
                                                  const float *__restrict__ P, const int *__restrict__ key_len,
                                                  float *__restrict__ dS, float *__restrict__ ds_rowsum,
@@ -1246,7 +1253,7 @@ __global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const fl
     // long dS blocks of all its samples come first, then the dV blocks; the last block of the grid ranks.
     constexpr int kXcd = 8;
     const int spx = (B + kXcd - 1) / kXcd;                     // sample slots per XCD
-    const int v_cols = dv_col_groups(KW, Tk, Dv), per_b = v_cols * dv_key_groups(KW, PANELS, Tk);       // dV blocks per sample
+    const int v_cols = dv_col_groups(KW, Tk, Dv), per_b = v_cols * dv_key_groups(KW, KW == 0 && ALT, Tk);       // dV blocks per sample
     const int per_xcd = spx * (s_tiles + per_b);
     if ((int)blockIdx.x == kXcd * per_xcd) {
         rank_block(key_len, order, s_len, B, Tk, sorted, first);
@@ -1258,7 +1265,7 @@ __global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const fl
         const int b = xcd + kXcd * (li / s_tiles), i0 = (li % s_tiles) * s_rows;
         if (b >= B) return;
         if constexpr (KW > 0) {
-            dscore_split_block<TV, KW>(dC, V, P, key_len, dS, ds_rowsum, s_dp, s_len, b, i0, Tq, Tk, Dv, pitch);
+            dscore_split_block<TV, KW, ALT>(dC, V, P, key_len, dS, ds_rowsum, s_dp, s_len, b, i0, Tq, Tk, Dv, pitch);
         } else if (Tk <= kDsplitMaxTk) {
             if (Dv <= 512) dscore_block_dsplit_lds<TV, 1, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
             else if (Dv <= 1024) dscore_block_dsplit_lds<TV, 2, false>(dC, V, P, key_len, dS, ds_rowsum, s_dp, b, i0, Tq, Tk, Dv, pitch, 0);
@@ -1272,8 +1279,8 @@ __global__ __launch_bounds__(KW ? 512 : 256, KW ? 4 : 3) void k_bwd_pre(const fl
     const int b = xcd + kXcd * (li / per_b), rem = li % per_b;
     if (b >= B) return;
     if constexpr (KW > 0)
-        dv_split_block(P, dC, key_len, dV, reinterpret_cast<u32x4 *>(s_dp), Tq, Tk, Dv, b, (rem / v_cols) * kDvKeys, rem % v_cols, acc);
-    else if constexpr (PANELS) dv_tile64(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_cols, rem % v_cols, acc);
+        dv_split_block<ALT>(P, dC, key_len, dV, reinterpret_cast<u32x4 *>(s_dp), Tq, Tk, Dv, b, (rem / v_cols) * kDvKeys, rem % v_cols, acc);
+    else if constexpr (ALT) dv_tile64(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_cols, rem % v_cols, acc);
     else if (Tk <= 64) dv_cols_block(P, dC, key_len, dV, Tq, Tk, Dv, b, rem, acc);
     else pv_block<float, true>(P, dC, key_len, dV, Tq, Tk, Dv, b, rem / v_cols, rem % v_cols, acc);
 }
@@ -1355,8 +1362,9 @@ static bool split_fits(const AttnShape &s) { return s.Tk <= 512 && s.Dv < (1 << 
 // backward on these against parts, 150 shapes of 129 to 512 keys, up to 14 blocks 1.17 of the time, to 29 1.12, to 44 1.03, to 59 0.98, to 74
 // 0.96, to 200 0.75 to 0.97.  Where they would be fp32 blocks of 16 rows, up to 100, 200 where the rows are wide: without parts B = 8, T = 600,
 // H = Dv = 512 468 -> 523 us, bf16 B = 5, T = 600, Dv = 512 91 -> 189; 22 shapes of more than 512 keys 1.28 (0.99 to 2.07).
+static int most_parts_fp32(const AttnShape &s) { return s.Dv >= 384 ? 200 : 100; }
 bool bwd_pre_in_parts(const AttnShape &s) {
-    const int most = split_fits(s) ? 50 : s.Dv >= 384 ? 200 : 100;
+    const int most = split_fits(s) ? 50 : most_parts_fp32(s);
     return s.Tk > kDsplitMaxTk && s.Dv <= 1024 && s.B <= kMaxSortedB && (long long)s.B * ((s.Tq + 31) / 32) <= most;
 }
 
@@ -1422,6 +1430,11 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // backward's time, 0.98 to 1.07; ten of 96 to 793 panels 0.94, 0.86 to 0.99; up to 12 rows and 132 to 500 keys 1.03, 1.00 to 1.09).
     const bool panels = kw == 0 && s.Tk > kDsplitMaxTk && s.Tk % 4 == 0 &&
                         (s.Tq <= 16 || s.B * ((s.Dv + 255LL) / 256) * ((s.Tk + kDvKeys - 1) / kDvKeys) >= 800);
+    // Few blocks of split operands past 128 keys: short runs of products are summed on their own, as the parts, which these grids ran in on fp32
+    // products, sum in four shorter chains.  Error against float64 of dV and dP (300 keys, T = 300, Dv = 512): parts 1.6e-7 and 2.3e-7, one
+    // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 % of forward and backward.  On more blocks one chain of
+    // fp32 products, 3.1e-7 and 4.2e-7, came before.
+    const bool apart = kw == 8 && blocks32 <= most_parts_fp32(s);
     const int s_rows = kw ? 32 : 16;
     const int s_tiles = with_ds ? (s.Tq + s_rows - 1) / s_rows : 0;
     const int v_groups = dv_col_groups(kw, s.Tk, s.Dv) * dv_key_groups(kw, panels, s.Tk);
@@ -1444,14 +1457,14 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // columns 1.01 and 1.03 on the first.  From 129 to 192 keys, where waves have no key tile, 1.01 (up to 1.07) and 0.99, 0.93 and 0.96.
     const bool alone = kw == 8 && with_ds && !s.bf16 && s.Tk > 192 && s.Dv >= 512 && blocks32 >= 256;
     const size_t lds = std::max(ds_lds, alone ? kAloneLdsBytes : kw ? (size_t)kDvSplitLdsBytes : (size_t)0);
-#define ECHO_PRE_LAUNCH(TV, KW, PANELS)                                                                             \
+#define ECHO_PRE_LAUNCH(TV, KW, ALT)                                                                                \
     do {                                                                                                            \
         if (lds > 48 * 1024) { /* beyond the default dynamic LDS limit (up to 160 KB per block on gfx950) */        \
             static LdsGrants granted;                                                                               \
-            hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre<TV, KW, PANELS>, lds, granted);               \
+            hipError_t e = ensure_dynamic_lds((const void *)k_bwd_pre<TV, KW, ALT>, lds, granted);                  \
             if (e != hipSuccess) return e;                                                                          \
         }                                                                                                           \
-        k_bwd_pre<TV, KW, PANELS><<<(unsigned)blocks, KW ? 512 : 256, lds, st>>>(                                   \
+        k_bwd_pre<TV, KW, ALT><<<(unsigned)blocks, KW ? 512 : 256, lds, st>>>(                                      \
             dC, (const TV *)V, P, key_len, dS, ds_rowsum, order, dV, s.B, sorted, first, s.Tq, s.Tk, s.Dv,          \
             ds_pitch(s.Tk), s_tiles, s_rows, s.acc ? 1 : 0);                                                        \
     } while (0)
@@ -1459,7 +1472,10 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     switch (kw) {                                       \
         case 1: ECHO_PRE_LAUNCH(TV, 1, false); break;   \
         case 2: ECHO_PRE_LAUNCH(TV, 2, false); break;   \
-        case 8: ECHO_PRE_LAUNCH(TV, 8, false); break;   \
+        case 8:                                         \
+            if (apart) ECHO_PRE_LAUNCH(TV, 8, true);    \
+            else ECHO_PRE_LAUNCH(TV, 8, false);         \
+            break;                                      \
         default:                                        \
             if (panels) ECHO_PRE_LAUNCH(TV, 0, true);   \
             else ECHO_PRE_LAUNCH(TV, 0, false);         \

@@ -87,4 +87,17 @@ __device__ __forceinline__ f32x16 mfma32(const Split8 &a, u32x4 b, f32x16 c) {
     return mfma32(a.p[0], b, c);
 }
 
+// c += s: the sum of a short run of products, formed from zero, on its own.  A chain of products into one accumulator rounds the whole sum six
+// times per 16 terms, this once per run.
+__device__ __forceinline__ void add16(f32x16 &c, const f32x16 &s) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) c[r] += s[r];
+}
+__device__ __forceinline__ f32x16 zero16() {
+    f32x16 z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    return z;
+}
+
 }  // namespace echo

@@ -168,6 +168,11 @@ CASES = [
     ("pre_long_1028_columns_bf16", 3, 20, 515, 8, 1028, "bf16", False),
     ("pre_long_parts_100_blocks", 50, 64, 516, 8, 40, "f32", False),
     ("pre_long_parts_200_blocks_bf16", 100, 33, 513, 8, 388, "bf16", False),
+    # short runs of products summed on their own: the most blocks that do it, narrow and wide value rows, and one more
+    ("pre_apart_100_blocks", 50, 33, 129, 8, 380, "f32", False),
+    ("pre_apart_200_blocks_bf16", 100, 33, 257, 8, 388, "bf16", False),
+    ("pre_apart_one_row", 51, 1, 512, 8, 36, "f32", False),
+    ("pre_not_apart_101_blocks", 101, 17, 129, 8, 380, "f32", False),
     # one block per CU: the fewest keys, columns and rows that take it, and one key, four columns and one sample less; several key tiles per wave
     ("pre_alone_193_keys_512_columns", 128, 33, 193, 8, 512, "f32", False),
     ("pre_not_alone_192_keys", 128, 33, 192, 8, 512, "f32", False),
