@@ -30,7 +30,10 @@
  *     and must be 16-byte aligned.  The library never allocates, frees or
  *     keeps a pointer.
  *   - Qp, Kp, V, v have the element type desc->in_dtype (fp32, or bf16 stored
- *     as 16-bit patterns); all arithmetic and every output is fp32.
+ *     as 16-bit patterns); all arithmetic and every output is fp32.  (The
+ *     products behind dV and dS may be formed from three bf16 parts of every
+ *     fp32 operand, which add up to it exactly, over the whole range of fp32;
+ *     their errors are no larger than those of fp32 products.)
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*; NULL is the
  *     default stream) and the call returns without synchronising.  The return
  *     value reports argument validation and launch errors only.

@@ -607,7 +607,7 @@ __device__ __forceinline__ void dv_rows_block(const float *__restrict__ P, const
 // Results that are not finite are formed again in fp32 by the same waves, several loads under way at a time (backward at B = 64, T = 50, H = Dv =
 // 512 27 -> 34 us with one infinity per sample, at B = 32, T = 300, H = Dv = 1024 461 -> 538, 564 with nothing but NaN; two columns per load: 62,
 // 740 and 876).
-// What bounds it is instruction issue: about nine vector instructions per product of 32 x 32 x 16, a wave alone on its SIMD issues one in
+// What bounds it is instruction issue: about ten vector instructions per product of 32 x 32 x 16, a wave alone on its SIMD issues one in
 // four clocks and overlaps little, so sixteen waves of at most 128 registers share a CU (eight of 250, each with four key tiles and a
 // software pipeline, took as long as four of them).
 // The launch of k_bwd_pre, dS and dV blocks, before (fp32 products; 16 or 32 rows) and with split operands, us: B = 32, T = 300, Dv = 1024
