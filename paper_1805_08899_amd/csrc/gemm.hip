@@ -607,9 +607,10 @@ __device__ __forceinline__ void dv_rows_block(const float *__restrict__ P, const
 // Results that are not finite are formed again in fp32 by the same waves, several loads under way at a time (backward at B = 64, T = 50, H = Dv =
 // 512 27 -> 34 us with one infinity per sample, at B = 32, T = 300, H = Dv = 1024 461 -> 538, 564 with nothing but NaN; two columns per load: 62,
 // 740 and 876).
-// What bounds it is instruction issue: about ten vector instructions per product of 32 x 32 x 16, a wave alone on its SIMD issues one in
-// four clocks and overlaps little, so sixteen waves of at most 128 registers share a CU (eight of 250, each with four key tiles and a
-// software pipeline, took as long as four of them).
+// What bounds it: a wave alone on its SIMD issues a vector instruction in four clocks and overlaps little of that with its products, about ten
+// instructions per product of 32 x 32 x 16, so sixteen waves of at most 128 registers share a CU (eight of 250, each with four key tiles and a
+// software pipeline, took as long as four of them).  Counters of the launch at B = 32, T = 300, Dv = 1024, one block per CU: vector issue 23 % of the
+// SIMDs' clocks, matrix cores 27 %; bf16, B = 128, T = 50, Dv = 1024 24 and 13 %.
 // The launch of k_bwd_pre, dS and dV blocks, before (fp32 products; 16 or 32 rows) and with split operands, us: B = 32, T = 300, Dv = 1024
 // 126 -> 71 (one block per CU, as it is launched now, 79); bf16 V, B = 128, T = 50, Dv = 1024 28.4 -> 18.8; B = 64, T = 50, Dv = 512 9.7 -> 8.5.
 template <typename TV> struct SplitStage;
@@ -1432,7 +1433,8 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
                         (s.Tq <= 16 || s.B * ((s.Dv + 255LL) / 256) * ((s.Tk + kDvKeys - 1) / kDvKeys) >= 800);
     // Few blocks of split operands past 128 keys: short runs of products are summed on their own, as the parts, which these grids ran in on fp32
     // products, sum in four shorter chains.  Error against float64 of dV and dP (300 keys, T = 300, Dv = 512): parts 1.6e-7 and 2.3e-7, one
-    // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 % of forward and backward.  On more blocks one chain of
+    // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 % of forward and backward, 2 to 8 % of the
+    // backward where there are few rows.  On more blocks one chain of
     // fp32 products, 3.1e-7 and 4.2e-7, came before.
     const bool apart = kw == 8 && blocks32 <= most_parts_fp32(s);
     const int s_rows = kw ? 32 : 16;
@@ -1450,12 +1452,15 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
                           : s.Dv <= 1024        ? (size_t)(4 * 16 * kStagePitch + 64 * pitch16) * sizeof(float)
                                                 : (size_t)64 * pitch16 * sizeof(float);
     // One block per CU, by asking for more than half of its LDS, for f32 on long key axes and wide value rows, once there is a dS block for every
-    // CU.  Two of them keep the matrix cores so busy with dense bf16 products that some cards lower the shader clock, by up to 10 %, for the
+    // CU and they are full to three quarters.  Two of them keep the matrix cores so busy with dense bf16 products that some cards lower the shader clock, by up to 10 %, for the
     // launches around this one too; one does not, and loses less than that.  Forward and backward over fp32 products, two blocks and one: B =
     // 32, T = 300, H = 1024 0.97 to 1.00 and 0.94 on a card that reacts, 0.92 and 0.93 on three that do not; twice the samples 1.05 and 0.97,
     // 0.97 and 0.97; 24 shapes of 200 to 480 keys that take this line 1.01 (0.87 to 1.05) and 0.95 (0.89 to 1.00), 0.92 and 0.94; with 400
     // columns 1.01 and 1.03 on the first.  From 129 to 192 keys, where waves have no key tile, 1.01 (up to 1.07) and 0.99, 0.93 and 0.96.
-    const bool alone = kw == 8 && with_ds && !s.bf16 && s.Tk > 192 && s.Dv >= 512 && blocks32 >= 256;
+    // Blocks of few rows do not make them busy (256 samples of 4 and 16 rows, 300 and 200 keys, 1024 columns: two blocks 152 and 111 us for the
+    // backward, one 176 and 135).
+    const bool alone = kw == 8 && with_ds && !s.bf16 && s.Tk > 192 && s.Dv >= 512 && blocks32 >= 256 &&
+                       4LL * s.B * s.Tq >= 3 * 32 * blocks32;
     const size_t lds = std::max(ds_lds, alone ? kAloneLdsBytes : kw ? (size_t)kDvSplitLdsBytes : (size_t)0);
 #define ECHO_PRE_LAUNCH(TV, KW, ALT)                                                                                \
     do {                                                                                                            \

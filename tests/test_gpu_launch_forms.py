@@ -173,12 +173,14 @@ CASES = [
     ("pre_apart_200_blocks_bf16", 100, 33, 257, 8, 388, "bf16", False),
     ("pre_apart_one_row", 51, 1, 512, 8, 36, "f32", False),
     ("pre_not_apart_101_blocks", 101, 17, 129, 8, 380, "f32", False),
-    # one block per CU: the fewest keys, columns and rows that take it, and one key, four columns and one sample less; several key tiles per wave
-    ("pre_alone_193_keys_512_columns", 128, 33, 193, 8, 512, "f32", False),
-    ("pre_not_alone_192_keys", 128, 33, 192, 8, 512, "f32", False),
-    ("pre_not_alone_508_columns", 128, 33, 193, 8, 508, "f32", False),
-    ("pre_not_alone_255_blocks", 255, 17, 193, 8, 512, "f32", False),
-    ("pre_alone_512_keys_548_columns", 86, 65, 512, 8, 548, "f32", False),
+    # one block per CU: the fewest keys, columns, blocks and rows per block that take it, and one key, four columns, one sample and one row less;
+    # several key tiles per wave
+    ("pre_alone_193_keys_512_columns", 128, 48, 193, 4, 512, "f32", False),
+    ("pre_not_alone_192_keys", 128, 48, 192, 4, 512, "f32", False),
+    ("pre_not_alone_508_columns", 128, 48, 193, 4, 508, "f32", False),
+    ("pre_not_alone_254_blocks", 127, 48, 193, 4, 512, "f32", False),
+    ("pre_not_alone_47_rows", 128, 47, 193, 4, 512, "f32", False),
+    ("pre_alone_512_keys_548_columns", 65, 125, 512, 4, 548, "f32", False),
     # whole backward in one launch: one tile, remainders of the tiles, one row, one key, three tiles, all sixteen with two per wave,
     # slices of 16 to 64 columns, several pieces of columns of each width, entries that need the exponential of the sum
     ("small_one_tile", 4, 6, 7, 16, 16, "f32", True),
