@@ -865,7 +865,7 @@ __device__ __forceinline__ void dscore_split_block(const float *__restrict__ dC,
 #pragma unroll
     for (int k = 0; k < 8; ++k) again |= s_inf[k];
     float back = split_back<TV>;
-    if (again) {                                                    // the wave's products again, in fp32
+    if (KW == 8 ? again : __builtin_expect(again, 0)) {             // the wave's products again, in fp32 (KW = 8: the hint costs registers)
         back = 1.f;
         const float *arow = dCb + (size_t)min(n, last_row) * Dv;
 #pragma unroll
@@ -1003,7 +1003,7 @@ __device__ __forceinline__ void dv_split_block(const float *__restrict__ P, cons
                 for (int r = 0; r < 16; ++r)
                     odd = __builtin_fmaf(j0 + 32 * t + mfma32_row(r, lane) < L ? acc[t][r] : 0.f, 0.f, odd);
             }
-        if (__any(odd != 0.f)) {
+        if (__builtin_expect(__any(odd != 0.f), 0)) {
             back = 1.f;
 #pragma unroll
             for (int t = 0; t < NT; ++t)
@@ -1433,7 +1433,7 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
                         (s.Tq <= 16 || s.B * ((s.Dv + 255LL) / 256) * ((s.Tk + kDvKeys - 1) / kDvKeys) >= 800);
     // Few blocks of split operands past 128 keys: short runs of products are summed on their own, as the parts, which these grids ran in on fp32
     // products, sum in four shorter chains.  Error against float64 of dV and dP (300 keys, T = 300, Dv = 512): parts 1.6e-7 and 2.3e-7, one
-    // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 % of forward and backward, 2 to 8 % of the
+    // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 % of forward and backward, 2 to 12 % (once 19) of the
     // backward where there are few rows.  On more blocks one chain of
     // fp32 products, 3.1e-7 and 4.2e-7, came before.
     const bool apart = kw == 8 && blocks32 <= most_parts_fp32(s);
