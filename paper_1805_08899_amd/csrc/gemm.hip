@@ -1405,18 +1405,18 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
         return s.bf16 ? launch_parts_t<bf16_t, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first)
                       : launch_parts_t<float, 2>(s, dC, V, P, key_len, dS, order, dV, st, with_ds, first);
     }
-    // Split operands (KW > 0) for what their blocks take (split_fits).  Not where tiles of 32 would be mostly empty, nor, in f32, on few blocks, where latency decides and the splitting of both operands is
-    // a part of it (backward, 350 shapes of up to 128 keys: at most 16 rows or 16 keys 1.02 of the time of the fp32 form, up to 1.13;
-    // fewer than 64 blocks of 32 rows 1.00 in f32, 0.75 to 1.12, and 0.92 in bf16; 64 to 160 blocks 0.94; more and longer ones 0.93, see
-    // dscore_split_block).
+    // Split operands (KW > 0) for what their blocks take (split_fits).  Not where tiles of 32 would be mostly empty, nor, in f32, on few
+    // blocks, where latency decides and the splitting of both operands is a part of it (backward, 350 shapes of up to 128 keys: at most 16
+    // rows or 16 keys 1.02 of the time of the fp32 form, up to 1.13; fewer than 64 blocks of 32 rows 1.00 in f32, 0.75 to 1.12, and 0.92 in
+    // bf16; 64 to 160 blocks 0.94; more and longer ones 0.93, see dscore_split_block).
     const long long blocks32 = (long long)s.B * ((s.Tq + 31) / 32);
     // dV alone (the keys' call of the decoder) on short key axes: blocks of 64 columns up to two rounds of them (512 of them 5.8 us against 7.8;
     // 2048 19.4 against 13).
     const bool few_dv = !with_ds && s.Tk <= 64 && (long long)s.B * ((s.Dv + 63) / 64) <= 1024;
-    // dV alone of few rows, any number of keys: a step of 64 rows and the splitting of all of dC for it are a waste there (fp32 blocks over split ones, 129 to
-    // 500 keys: 29 launches of up to 12 rows 0.95 of the time, 0.92 to 1.01; 16 rows and more level).  With dS, whose rows of V are split
-    // once for up to 32 rows of dC, split operands stay ahead past 128 keys at any number of rows: 51 shapes of 1 to 16 rows 0.87 of
-    // the time that the backward takes on the fp32 forms (0.47 to 1.25; at 64 value columns 0.99, 0.87 to 1.19).
+    // dV alone of few rows, any number of keys: a step of 64 rows and the splitting of all of dC for it are a waste there (fp32 blocks over
+    // split ones, 129 to 500 keys: 29 launches of up to 12 rows 0.95 of the time, 0.92 to 1.01; 16 rows and more level).  With dS, whose rows
+    // of V are split once for up to 32 rows of dC, split operands stay ahead past 128 keys at any number of rows: 51 shapes of 1 to 16
+    // rows 0.87 of the time that the backward takes on the fp32 forms (0.47 to 1.25; at 64 value columns 0.99, 0.87 to 1.19).
     const bool few_rows_dv = !with_ds && s.Tq <= 12;
     const bool small = s.Tk <= 128 && (s.Tq <= 16 || s.Tk <= 16 || (with_ds && !s.bf16 && blocks32 < 64) || few_dv);
     // f32, 65 to 128 keys, value rows that fill the four waves' 128 columns of the fp32 form to seven eighths and more, and a block for every CU:
@@ -1434,8 +1434,7 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
     // Few blocks of split operands past 128 keys: short runs of products are summed on their own, as the parts, which these grids ran in on fp32
     // products, sum in four shorter chains.  Error against float64 of dV and dP (300 keys, T = 300, Dv = 512): parts 1.6e-7 and 2.3e-7, one
     // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 % of forward and backward, 2 to 12 % (once 19) of the
-    // backward where there are few rows.  On more blocks one chain of
-    // fp32 products, 3.1e-7 and 4.2e-7, came before.
+    // backward where there are few rows.  On more blocks one chain of fp32 products, 3.1e-7 and 4.2e-7, came before.
     const bool apart = kw == 8 && blocks32 <= most_parts_fp32(s);
     const int s_rows = kw ? 32 : 16;
     const int s_tiles = with_ds ? (s.Tq + s_rows - 1) / s_rows : 0;
@@ -1452,9 +1451,9 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
                           : s.Dv <= 1024        ? (size_t)(4 * 16 * kStagePitch + 64 * pitch16) * sizeof(float)
                                                 : (size_t)64 * pitch16 * sizeof(float);
     // One block per CU, by asking for more than half of its LDS, for f32 on long key axes and wide value rows, once there is a dS block for every
-    // CU and they are full to three quarters.  Two of them keep the matrix cores so busy with dense bf16 products that some cards lower the shader clock, by up to 10 %, for the
-    // launches around this one too; one does not, and loses less than that.  Forward and backward over fp32 products, two blocks and one: B =
-    // 32, T = 300, H = 1024 0.97 to 1.00 and 0.94 on a card that reacts, 0.92 and 0.93 on three that do not; twice the samples 1.05 and 0.97,
+    // CU and they are full to three quarters.  Two of them keep the matrix cores so busy with dense bf16 products that some cards lower the
+    // shader clock, by up to 10 %, for the launches around this one too; one does not, and loses less than that.  Forward and backward
+    // over fp32 products, two blocks and one: B = 32, T = 300, H = 1024 0.97 to 1.00 and 0.94 on a card that reacts, 0.92 and 0.93 on three that do not; twice the samples 1.05 and 0.97,
     // 0.97 and 0.97; 24 shapes of 200 to 480 keys that take this line 1.01 (0.87 to 1.05) and 0.95 (0.89 to 1.00), 0.92 and 0.94; with 400
     // columns 1.01 and 1.03 on the first.  From 129 to 192 keys, where waves have no key tile, 1.01 (up to 1.07) and 0.99, 0.93 and 0.96.
     // Blocks of few rows do not make them busy (256 samples of 4 and 16 rows, 300 and 200 keys, 1024 columns: two blocks 152 and 111 us for the
