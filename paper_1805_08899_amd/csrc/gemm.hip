@@ -771,6 +771,7 @@ __device__ __forceinline__ void dscore_split_tiles(const BufferRows<float> &rows
         put_a(odd);
         load_a(2 + odd);
     }
+    f32x16 run = zero16();                                         // (APART)
     auto step = [&](Raw4<TV> (&now)[4], int s) {
         if constexpr (SHARED) {
             if ((s & 1) == 0) {
@@ -794,8 +795,10 @@ __device__ __forceinline__ void dscore_split_tiles(const BufferRows<float> &rows
             load_v(now, k + 1 < NL ? s : s + R, k + 1 < NL ? k + 1 : 0);
             loads_stay();
             const TV *t = sv + n * VS::PITCH + 8 * half;
-            if constexpr (APART) {
-                add16(acc[k], mfma32(a1, VS::split(VS::get(t + 16)), mfma32(a0, VS::split(VS::get(t)), zero16())));
+            if constexpr (APART) {                                  // (the run before this one is done by now, where an add behind its own waits)
+                const auto b0 = VS::split(VS::get(t));
+                add16(acc[k > 0 ? k - 1 : NL - 1], run);
+                run = mfma32(a1, VS::split(VS::get(t + 16)), mfma32(a0, b0, zero16()));
             } else {
                 acc[k] = mfma32(a0, VS::split(VS::get(t)), acc[k]);
                 acc[k] = mfma32(a1, VS::split(VS::get(t + 16)), acc[k]);
@@ -806,6 +809,7 @@ __device__ __forceinline__ void dscore_split_tiles(const BufferRows<float> &rows
         step(nv[0], s);
         if (s + 1 < steps) step(nv[R - 1], s + 1);
     }
+    if constexpr (APART && NL > 0) add16(acc[NL - 1], run);
 }
 
 template <typename TV, int KW, bool APART>
@@ -1433,7 +1437,7 @@ hipError_t launch_bwd_pre(const AttnShape &s, const float *dC, const void *V, co
                         (s.Tq <= 16 || s.B * ((s.Dv + 255LL) / 256) * ((s.Tk + kDvKeys - 1) / kDvKeys) >= 800);
     // Few blocks of split operands past 128 keys: short runs of products are summed on their own, as the parts, which these grids ran in on fp32
     // products, sum in four shorter chains.  Error against float64 of dV and dP (300 keys, T = 300, Dv = 512): parts 1.6e-7 and 2.3e-7, one
-    // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 % of forward and backward, 2 to 12 % (once 19) of the
+    // chain of split products 2.6e-7 and 3.5e-7, this 1.0e-7 and 1.4e-7, for 0.5 to 1.5 % of forward and backward, 1 to 5 % (once 9) of the
     // backward where there are few rows.  On more blocks one chain of fp32 products, 3.1e-7 and 4.2e-7, came before.
     const bool apart = kw == 8 && blocks32 <= most_parts_fp32(s);
     const int s_rows = kw ? 32 : 16;
