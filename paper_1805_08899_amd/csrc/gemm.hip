@@ -612,7 +612,7 @@ __device__ __forceinline__ void dv_rows_block(const float *__restrict__ P, const
 // software pipeline, took as long as four of them).  Counters of the launch at B = 32, T = 300, Dv = 1024, one block per CU: vector issue 23 % of the
 // SIMDs' clocks, matrix cores 27 %; bf16, B = 128, T = 50, Dv = 1024 24 and 13 %.
 // The launch of k_bwd_pre, dS and dV blocks, before (fp32 products; 16 or 32 rows) and with split operands, us: B = 32, T = 300, Dv = 1024
-// 126 -> 73, 83 with one block per CU, as it is launched now; bf16 V, B = 128, T = 50, Dv = 1024 28.4 -> 18.8; B = 64, T = 50, Dv = 512 9.7 -> 8.5.
+// 126 -> 73, 83 with one block per CU, as it is launched now; bf16 V, B = 128, T = 50, Dv = 1024 28.4 -> 18.6; B = 64, T = 50, Dv = 512 9.7 -> 9.0.
 template <typename TV> struct SplitStage;
 template <> struct SplitStage<float> {
     static constexpr int PITCH = 36;          // of 32 elements
